@@ -343,10 +343,12 @@ ST3_EXPORT st3_status st3_decode_layer_step(const st3_attn_shape* shape, const s
  * loop over l).  `layers` is a HOST array; entry i carries exactly the arguments
  * st3_decode_layer_step takes for that layer.  The result is the same as calling
  * st3_decode_layer_step for i = 0 .. n_layers-1 in order.  Step (2) of a layer depends on that
- * layer's attention only, so all layers attend first (one launch each) and their steps (2) then
- * run side by side in one launch (up to 64 layers; each attention launch leaves its layer's
- * step-(2) arguments in the layer's workspace, where that launch reads them).  Every layer needs
- * buffers and a workspace of its own.
+ * layer's attention only, so all layers attend first (up to 21 layers per launch; lazy layers
+ * behind the ordinary ones) and their steps (2) then run side by side in one launch (up to 64
+ * layers; the attention launch leaves each layer's step-(2) arguments in the layer's workspace,
+ * where that launch reads them).  Every layer needs buffers and a workspace of its own; a layer
+ * whose `out` shares memory with another layer's out, q, k_new or v_new makes the step run layer
+ * by layer, one launch each.
  * Lazy layers (inherit_from >= 0) are available through this call only: a group's evictions must
  * wait until its last lazy layer has attended, which the per-layer call cannot arrange.
  * ------------------------------------------------------------------------------------------- */
@@ -458,8 +460,8 @@ ST3_EXPORT st3_status st3_cosine_similarity(const float* va, const int32_t* ids_
  *   attached that receives the kernel's own start and end on the caller's stream; this stops
  *   silently once n launches are used.
  * st3_profile_read waits for the recorded events, returns the summed / min / max kernel time in
- *   milliseconds and the number of launches timed, and switches recording off.  HOST pointers, any
- *   may be NULL.
+ *   milliseconds and the number of layer attentions timed (a launch that serves n layers counts as
+ *   n, each with an n-th of its time), and switches recording off.  HOST pointers, any may be NULL.
  * st3_debug_set_prefill_path: which kernel st3_prefill_attention uses for bf16 inputs.  0 =
  *   automatic (MFMA kernel), 1 = the float32 row kernel, 2 = MFMA or fail.  Lets the two be
  *   compared on one input.

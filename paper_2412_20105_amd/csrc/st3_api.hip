@@ -30,19 +30,21 @@ struct DecodeProfiler {
     std::mutex mu;
     std::vector<hipEvent_t> ev;     // 2 per launch
     size_t used = 0;                // launches recorded
+    std::vector<int> layers;        // of each: how many layers' attention it did
     bool on = false;
 };
 static DecodeProfiler g_prof;
 
 // Hands out the next event pair; the caller passes it to hipExtLaunchKernelGGL, which stamps the
 // two events with the kernel's own start and end.
-bool profile_take(hipEvent_t* start, hipEvent_t* stop) {
+bool profile_take(hipEvent_t* start, hipEvent_t* stop, int layers) {
     if (!g_prof.on) return false;                   // (never set unless the debug block is enabled)
     std::lock_guard<std::mutex> lock(g_prof.mu);
     if (!g_prof.on) return false;
     if ((g_prof.used + 1) * 2 > g_prof.ev.size()) { g_prof.on = false; return false; }      // pool exhausted
     *start = g_prof.ev[g_prof.used * 2];
     *stop = g_prof.ev[g_prof.used * 2 + 1];
+    g_prof.layers[g_prof.used] = layers;
     g_prof.used += 1;
     return true;
 }
@@ -52,13 +54,14 @@ st3_status validate_kv_value_only(const st3_attn_shape* s, const st3_kv_layer* k
 st3_status enqueue_inherit(const st3_attn_shape* shape, const st3_kv_layer* kv, const st3_segments* seg,
                            int32_t max_kv_len, const void* v_new, const void* src_workspace,
                            size_t src_workspace_bytes, int32_t src_capacity, void* out, void* workspace,
-                           size_t workspace_bytes, hipStream_t st, const PlanStash* stash = nullptr);
+                           size_t workspace_bytes, hipStream_t st);
 st3_status enqueue_decode(const st3_attn_shape* shape, const void* q, const st3_kv_layer* kv,
                           const st3_segments* seg, int32_t max_kv_len, const void* k_new, const void* v_new,
                           void* out, float* vis_mass, int64_t mass_stride, bool want_mass, bool defer_mass,
-                          bool keep_all_logits, void* workspace, size_t workspace_bytes, hipStream_t st,
-                          bool defer_merge = false, const PlanStash* stash = nullptr);
-bool decode_is_split(const st3_attn_shape* shape, const st3_kv_layer* kv, int32_t max_kv_len);
+                          bool keep_all_logits, void* workspace, size_t workspace_bytes, hipStream_t st);
+st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const st3_layer_step* layers, int mode,
+                               const char* has_heirs, const EvictArgs* plan, StepCommon& common, const StepLayer** entry,
+                               bool& split, hipStream_t st);
 
 }  // namespace st3
 
@@ -229,40 +232,50 @@ static st3_status check_step(const st3_attn_shape* shape, int32_t n_layers, cons
     return ST3_OK;
 }
 
-// Append + attention of layer i of a checked step; the mass stays pending for the layer's plan.
-// merge_in_plan: strips cut into chunks leave their partials for the layer's plan to merge (the
-// whole-step call); else a merge launch follows the attention and `out` is complete right after it.
-// stash (may be null): words the launch leaves in the layer's workspace for the launch that plans the layer.
+// Append + attention of layer i of a checked step; the mass stays pending for the layer's plan, `out` is complete when
+// the launch (and, for strips cut into chunks, the merge launch behind it) has run.
 static st3_status enqueue_layer_attend(const st3_attn_shape* shape, const st3_layer_step* layers, int i, bool has_heirs,
-                                       hipStream_t st, bool merge_in_plan, const PlanStash* stash = nullptr) {
+                                       hipStream_t st) {
     const st3_layer_step& L = layers[i];
     if (L.inherit_from >= 0) {
         const st3_layer_step& S = layers[L.inherit_from];
         return enqueue_inherit(shape, &L.kv, &L.seg, L.seg.max_kv_len + 1, L.v_new, S.workspace, S.workspace_bytes,
-                               S.kv.capacity, L.out, L.workspace, L.workspace_bytes, st, stash);
+                               S.kv.capacity, L.out, L.workspace, L.workspace_bytes, st);
     }
     return enqueue_decode(shape, L.q, &L.kv, &L.seg, L.seg.max_kv_len + 1, L.k_new, L.v_new, L.out, L.vis_mass,
-                          L.mass_stride, L.vis_mass != nullptr, true, has_heirs, L.workspace, L.workspace_bytes, st,
-                          merge_in_plan, stash);
+                          L.mass_stride, L.vis_mass != nullptr, true, has_heirs, L.workspace, L.workspace_bytes, st);
 }
 
-// The plans of layers [i0, i1) (finish the mass, count the new row, rank, evict): a plan workgroup is
-// latency bound, so the layers' plans are best run side by side.  Their arguments travel by value,
-// 16 layers per launch, unless `stashed` tells where the layers' attention launches have left a copy
-// of each plan in device memory: then one launch reads them there (up to 64 layers).
-static void enqueue_plan_range(const std::vector<EvictArgs>& plan, const std::vector<char>& needs_apply, int i0, int i1,
-                               int B, hipStream_t st, const std::vector<const EvictArgs*>* stashed = nullptr) {
-    if (i1 <= i0) return;
-    if (stashed != nullptr) launch_evict_plan_table(stashed->data() + i0, plan.data() + i0, i1 - i0, B, st);
-    else launch_evict_plan_batch(plan.data() + i0, i1 - i0, B, st);
-    for (int i = i0; i < i1; ++i)
-        if (needs_apply[(size_t)i]) launch_evict_apply(plan[(size_t)i], B, st);
+static void enqueue_applies(const std::vector<EvictArgs>& plan, const std::vector<char>& needs_apply, int B, hipStream_t st) {
+    for (size_t i = 0; i < plan.size(); ++i)
+        if (needs_apply[i]) launch_evict_apply(plan[i], B, st);
 }
 
+// The plans of all layers (finish the mass, count the new row, rank, evict): a plan workgroup is latency bound, so the
+// layers' plans are best run side by side.  Their arguments travel by value, 16 layers per launch.
 static st3_status enqueue_plans(const std::vector<EvictArgs>& plan, const std::vector<char>& needs_apply, int B,
                                 hipStream_t st) {
-    enqueue_plan_range(plan, needs_apply, 0, (int)plan.size(), B, st);
+    launch_evict_plan_batch(plan.data(), (int)plan.size(), B, st);
+    enqueue_applies(plan, needs_apply, B, st);
     return check_launch();
+}
+
+// Whether some layer's output shares memory with another layer's output or with what another layer reads as its token:
+// such a step means what its layers mean one after the other, so they cannot share a launch.
+static bool layers_share_rows(const st3_attn_shape* shape, int n_layers, const st3_layer_step* layers) {
+    const uintptr_t bytes = (uintptr_t)shape->batch * shape->heads * shape->head_dim * elem_bytes(shape->dtype);
+    auto meet = [bytes](const void* x, const void* y) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(x), b = reinterpret_cast<uintptr_t>(y);
+        return (a < b ? b - a : a - b) < bytes;
+    };
+    for (int i = 0; i < n_layers; ++i)
+        for (int j = 0; j < n_layers; ++j) {
+            if (i == j) continue;
+            const st3_layer_step& L = layers[j];
+            if (meet(layers[i].out, L.out) || meet(layers[i].out, L.v_new)) return true;
+            if (L.inherit_from < 0 && (meet(layers[i].out, L.q) || meet(layers[i].out, L.k_new))) return true;
+        }
+    return false;
 }
 
 }  // namespace st3
@@ -285,7 +298,7 @@ extern "C" st3_status st3_decode_layer_attend(const st3_attn_shape* shape, int32
     if (s != ST3_OK) return s;
     bool has_heirs = false;
     for (int i = layer + 1; i < n_layers; ++i) has_heirs = has_heirs || layers[i].inherit_from == layer;
-    return enqueue_layer_attend(shape, layers, layer, has_heirs, reinterpret_cast<hipStream_t>(stream), false);
+    return enqueue_layer_attend(shape, layers, layer, has_heirs, reinterpret_cast<hipStream_t>(stream));
 }
 
 extern "C" st3_status st3_decode_plans(const st3_attn_shape* shape, int32_t n_layers, const st3_layer_step* layers,
@@ -306,37 +319,25 @@ extern "C" st3_status st3_decode_step(const st3_attn_shape* shape, int32_t n_lay
     st3_status s = check_step(shape, n_layers, layers, mode, plan, needs_apply, has_heirs);
     if (s != ST3_OK) return s;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    // All of a step's inputs are here, so nothing needs a layer's output before the step ends: where
-    // the strips are cut into chunks (B*H alone does not fill the chip) the chunk partials are merged
-    // by the layer's plan instead of by a launch of their own behind every attention.
-    std::vector<const EvictArgs*> stashed((size_t)n_layers, nullptr);
+    // All of a step's inputs are here, so nothing needs a layer's output before the step ends: many layers attend in one
+    // launch, and where strips are cut into chunks the chunk partials are merged beside the plans.
+    if (!layers_share_rows(shape, n_layers, layers)) {
+        StepCommon common{};
+        std::vector<const StepLayer*> entry((size_t)n_layers, nullptr);
+        bool split = false;
+        s = enqueue_step_attend(shape, n_layers, layers, mode, has_heirs.data(), plan.data(), common, entry.data(), split, st);
+        if (s == ST3_OK) {
+            launch_evict_plan_table(common, entry.data(), n_layers, split, st);
+            enqueue_applies(plan, needs_apply, shape->batch, st);
+            return check_launch();
+        }
+        if (s != ST3_ERR_UNSUPPORTED) return s;
+    }
     for (int i = 0; i < n_layers; ++i) {
-        const st3_layer_step& L = layers[i];
-        const bool in_plan = L.inherit_from < 0 && decode_is_split(shape, &L.kv, L.seg.max_kv_len + 1);
-        if (in_plan) {
-            const DecodeWs wl = decode_ws(shape->batch, shape->heads, shape->head_dim, L.kv.capacity);
-            char* ws = reinterpret_cast<char*>(L.workspace);
-            plan[i].merge_part_o = reinterpret_cast<const float*>(ws + wl.part_o);
-            plan[i].merge_out = L.out;
-            plan[i].merge_D = shape->head_dim;
-            plan[i].merge_bf16 = shape->dtype == ST3_BF16 ? 1 : 0;
-            plan[i].part_ml = reinterpret_cast<const float*>(ws + wl.part_ml);
-            plan[i].pending = reinterpret_cast<const int32_t*>(ws + wl.pending);
-            plan[i].nsplit_cap = wl.nsplit_cap;
-        }
-        // the layer's plan travels with its attention launch into the layer's workspace; the plan launches read it there
-        PlanStash stash{};
-        std::memcpy(stash.w, &plan[i], sizeof(EvictArgs));
-        {
-            const DecodeWs wl = decode_ws(shape->batch, shape->heads, shape->head_dim, L.kv.capacity);
-            stash.dst = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(L.workspace) + wl.plan_args);
-            stashed[i] = reinterpret_cast<const EvictArgs*>(stash.dst);
-        }
-        s = enqueue_layer_attend(shape, layers, i, has_heirs[i] != 0, st, in_plan, &stash);
+        s = enqueue_layer_attend(shape, layers, i, has_heirs[i] != 0, st);
         if (s != ST3_OK) return s;
     }
-    enqueue_plan_range(plan, needs_apply, 0, n_layers, shape->batch, st, &stashed);
-    return check_launch();
+    return enqueue_plans(plan, needs_apply, shape->batch, st);
 }
 
 extern "C" st3_status st3_profile_enable(int32_t max_launches) {
@@ -350,6 +351,7 @@ extern "C" st3_status st3_profile_enable(int32_t max_launches) {
         if (err != hipSuccess) { set_last_hip_error(err); return ST3_ERR_HIP; }
         g_prof.ev.push_back(e);
     }
+    g_prof.layers.assign(g_prof.ev.size() / 2, 0);
     g_prof.used = 0;
     g_prof.on = true;
     return ST3_OK;
@@ -361,15 +363,20 @@ extern "C" st3_status st3_profile_read(double* total_ms, int64_t* launches, doub
     std::lock_guard<std::mutex> lock(g_prof.mu);
     g_prof.on = false;
     double tot = 0.0, mn = 1e30, mx = 0.0;
+    int64_t count = 0;
     for (size_t i = 0; i < g_prof.used; ++i) {
         hipError_t err = hipEventSynchronize(g_prof.ev[2 * i + 1]);
         float ms = 0.f;
         if (err == hipSuccess) err = hipEventElapsedTime(&ms, g_prof.ev[2 * i], g_prof.ev[2 * i + 1]);
         if (err != hipSuccess) { set_last_hip_error(err); return ST3_ERR_HIP; }
-        tot += ms; mn = ms < mn ? ms : mn; mx = ms > mx ? ms : mx;
+        tot += ms;
+        const int n = g_prof.layers[i];             // a launch over n layers counts as n of equal share
+        ms /= (float)n;
+        count += n;
+        mn = ms < mn ? ms : mn; mx = ms > mx ? ms : mx;
     }
     if (total_ms) *total_ms = tot;
-    if (launches) *launches = (int64_t)g_prof.used;
+    if (launches) *launches = count;
     if (min_ms) *min_ms = g_prof.used ? mn : 0.0;
     if (max_ms) *max_ms = mx;
     g_prof.used = 0;

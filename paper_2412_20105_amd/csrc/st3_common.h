@@ -36,7 +36,7 @@ inline st3_status check_launch() {
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+__host__ __device__ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int elem_bytes(int dtype) { return dtype == ST3_BF16 ? 2 : dtype == ST3_E4M3 ? 1 : 4; }
 // bytes of one cache element of a layer
 inline int kv_elem_bytes(const st3_attn_shape* s, const st3_kv_layer* kv) {
@@ -109,6 +109,26 @@ inline int decode_nsplit(int B, int H, int max_kv, int target_wgs = kDecodeTarge
     if (ns > kDecodeMaxSplit) ns = kDecodeMaxSplit;
     return ns < 1 ? 1 : (int)ns;
 }
+// Chunks of a strip of `len` rows in the whole-step call, where `rows` is the sum of the lengths of all layers that are
+// launched together and the chunk partials are merged inside the step's plan launch: chunks of equal LENGTH over all
+// layers, as long as about kStepTargetWgs workgroups allow.  Measured at targets of 1024 / 2048 / 3072 / 4096 / 8192, us per step:
+// 7B batch 1 72.1 / 72.6 / 73.4 / 78.2 / 93.1, 13B batch 8 with lazy layers 563 / 563 / 571 / 565 / 611, high resolution batch 8
+// E4M3 699 / 699 / 698 / 699 / 711; 13B batch 32 is not cut by any of them.
+#ifndef ST3_STEP_TARGET_WGS
+#define ST3_STEP_TARGET_WGS 2048
+#endif
+#ifndef ST3_STEP_MIN_CHUNK
+#define ST3_STEP_MIN_CHUNK 64
+#endif
+constexpr int kStepTargetWgs = ST3_STEP_TARGET_WGS;
+constexpr int kStepMinChunk = ST3_STEP_MIN_CHUNK;
+inline int step_nsplit(int B, int H, int len, int64_t rows) {
+    int64_t chunk = (int64_t)B * H * rows / kStepTargetWgs;
+    if (chunk < kStepMinChunk) chunk = kStepMinChunk;
+    if (chunk > kLogitStageMaxRows) chunk = kLogitStageMaxRows;
+    const int64_t ns = (len + chunk - 1) / chunk;
+    return ns < 1 ? 1 : ns > kDecodeMaxSplit ? kDecodeMaxSplit : (int)ns;
+}
 // Chunk length for that split count: a multiple of 32 rows.
 inline int decode_chunk(int max_kv, int nsplit) {
     int c = (max_kv + nsplit - 1) / nsplit;
@@ -116,25 +136,64 @@ inline int decode_chunk(int max_kv, int nsplit) {
     return c < 32 ? 32 : c;
 }
 
-// A layer's attention launch can leave up to 256 bytes of the host's choosing in the layer's workspace (one workgroup stores
-// them): the whole-step call passes each layer's eviction-plan arguments this way, so that ONE plan launch can serve every
-// layer of the step - by value, 16 layers' arguments fill the kernel-argument block.
-constexpr int kPlanStashWords = 64;
-struct PlanStash {
-    uint32_t w[kPlanStashWords];
-    uint32_t* dst;              // DEVICE, in the layer's workspace; null: nothing to leave
+// ---------------------------------------------------------------------------------------------
+// The whole-step call serves many layers with one attention launch.  What differs from layer to layer travels by value:
+// 192 bytes a layer, kStepLayersMax layers in the 4 KB argument block.  The launch leaves each entry in its layer's
+// workspace, where the step's one plan launch (which covers more layers than fit one argument block) reads it.
+// ---------------------------------------------------------------------------------------------
+struct StepCommon {
+    int32_t B, H, D, mode;      // mode: st3_compact_mode
+    int32_t cache_eb, out_bf16; // bytes of a cache element; outputs are bf16 (else float32)
+    float scale_l2;
+    int32_t layers;             // entries of the table
 };
+struct StepLayer {
+    const void* q;              // lazy layer: the source layer's workspace
+    void* k;                    // lazy layer: null
+    void* v;
+    const void* k_new;          // lazy layer: unused
+    const void* v_new;
+    void* out;
+    int32_t* kv_len;
+    int32_t* vis_len;
+    const int32_t* tail_start;
+    float* score_col;
+    int32_t* id_col;
+    float* mass;                // null: no mass
+    char* ws;
+    const float* k_scale;
+    const float* v_scale;
+    int64_t stride_b, stride_h; // cache elements
+    int32_t stride_t, col_stride, mass_stride;
+    int32_t sys_len, max_vis, max_kv;       // bounds BEFORE the step (max_kv does not count the appended row)
+    int32_t keep_count;         // < 0: no eviction
+    int32_t chunk;              // rows per chunk of a strip
+    int32_t hint_base, hint_gap;            // lazy layer: hint_base is the source cache's capacity
+    int32_t capacity;
+    uint8_t nsplit, nsplit_cap; // chunks per strip of this launch / that the workspace has room for (at most 64)
+    uint8_t src_nsplit_cap;     // lazy layer: of the source's workspace
+    uint8_t flags;
+};
+static_assert(sizeof(StepLayer) == 184, "kStepLayersMax entries must fit the kernel-argument block");
+constexpr uint8_t kStepInlineApply = 1, kStepKeepAll = 2, kStepLazy = 4, kStepWantMass = 8;
+constexpr int kStepLayersMax = 21;
+constexpr int kStepLayerWords = sizeof(StepLayer) / 4;
+struct StepTable {
+    StepCommon c;
+    StepLayer layer[kStepLayersMax];
+};
+static_assert(sizeof(StepTable) <= 4000, "the table travels by value");
 
 struct DecodeWs {
-    size_t part_o, part_ml, logits, pending, plan_args, moves_cnt, moves, total;
+    size_t part_o, part_ml, logits, pending, step_entry, moves_cnt, moves, total;
     int nsplit_cap;
     int max_moves;
 };
 
-inline DecodeWs decode_ws(int B, int H, int D, int capacity) {
+// (products and sums only, so that kernels can rebuild the offsets from nsplit_cap)
+__host__ __device__ inline DecodeWs decode_ws_sized(int B, int H, int D, int capacity, int nsplit_cap) {
     DecodeWs w{};
-    if (capacity < 1) capacity = 1;
-    w.nsplit_cap = decode_nsplit(B, H, capacity, kDecodeTargetWgsMax);
+    w.nsplit_cap = nsplit_cap;
     w.max_moves = capacity;                 // a stable shift moves every row at most once
     size_t off = 0;
     const size_t BH = (size_t)B * H;
@@ -142,11 +201,16 @@ inline DecodeWs decode_ws(int B, int H, int D, int capacity) {
     w.part_ml = off;    off = align_up(off + BH * w.nsplit_cap * 2 * sizeof(float), 256);
     w.logits = off;     off = align_up(off + BH * (size_t)capacity * sizeof(float), 256);   // [B,H,capacity]
     w.pending = off;    off = align_up(off + (size_t)B * 4 * sizeof(int32_t), 256);         // [B][4]
-    w.plan_args = off;  off = align_up(off + kPlanStashWords * sizeof(uint32_t), 256);       // what a PlanStash leaves
+    w.step_entry = off; off = align_up(off + sizeof(StepLayer), 256);                        // what a whole-step launch leaves
     w.moves_cnt = off;  off = align_up(off + (size_t)B * sizeof(int32_t), 256);
     w.moves = off;      off = align_up(off + (size_t)B * w.max_moves * 2 * sizeof(int32_t), 256);
     w.total = off;
     return w;
+}
+
+inline DecodeWs decode_ws(int B, int H, int D, int capacity) {
+    if (capacity < 1) capacity = 1;
+    return decode_ws_sized(B, H, D, capacity, decode_nsplit(B, H, capacity, kDecodeTargetWgsMax));
 }
 
 struct PrefillWs {

@@ -23,11 +23,14 @@
 
 #include <atomic>
 #include <cmath>
+#include <cstring>
+#include <type_traits>
 #include <utility>
+#include <vector>
 
 #include "st3_common.h"
 #include "st3_attend.h"
-#include "st3_decode.h"
+#include "st3_evict.h"
 
 #ifndef ST3_DECODE_THREADS
 #define ST3_DECODE_THREADS 256      // threads per workgroup of the attend kernel
@@ -38,7 +41,7 @@
 
 namespace st3 {
 
-bool profile_take(hipEvent_t* start, hipEvent_t* stop);     // st3_api.hip
+bool profile_take(hipEvent_t* start, hipEvent_t* stop, int layers);     // st3_api.hip
 
 namespace {
 
@@ -70,17 +73,18 @@ struct DecodeArgs {
     void* out;              // [B,H,D]
 };
 
-// Workgroup (0,0,0) of a launch leaves the stash words in the workspace (plain vector stores).  The stash is a kernel
-// parameter of its own, behind the argument struct, so that the struct's fields keep their places in the argument block.
-__device__ __forceinline__ void leave_stash(const PlanStash& st) {
-    if (st.dst != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x < kPlanStashWords)
-        st.dst[threadIdx.x] = st.w[threadIdx.x];
+// A store that leaves the line in L2 (NT = false) or goes past the caches.  (A template parameter and not a flag: the
+// compiler folds the two arms of a run-time choice into one ordinary store.)
+template <bool NT, typename V>
+__device__ __forceinline__ void store_hint(V* p, V v) {
+    if (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
 }
 
-template <typename T>
+template <typename T, bool NT = false>
 __device__ __forceinline__ void store_out(void* out, int64_t idx, float o) {
-    if (sizeof(T) == 4) reinterpret_cast<float*>(out)[idx] = o;
-    else reinterpret_cast<uint16_t*>(out)[idx] = (uint16_t)f32_to_bf16_bits(o);
+    if (sizeof(T) == 4) store_hint<NT>(reinterpret_cast<float*>(out) + idx, o);
+    else store_hint<NT>(reinterpret_cast<uint16_t*>(out) + idx, (uint16_t)f32_to_bf16_bits(o));
 }
 
 // This lane's 16-byte slice of a new token's row, in the format of the cache it is going into
@@ -107,14 +111,12 @@ struct NewRow<T, e4m3_t, D> {
     }
 };
 
-// grid (nsplit, H, B).  T: element type of q, k_new, v_new and out; KT: element type of the cache.
-template <typename T, typename KT, int D, int U>
-__global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS)
-__attribute__((amdgpu_waves_per_eu(ST3_DECODE_MIN_BLOCKS, ST3_DECODE_MIN_BLOCKS)))    // do not spill to reach a third wave
-void decode_attend_kernel(DecodeArgs a, PlanStash stash) {
+// One workgroup: chunk `split` of strip (b, h).  T: element type of q, k_new, v_new and out; KT: element type of the cache.
+// NTS: what the workgroup writes (output row, appended row, logits) goes past the caches.
+template <typename T, typename KT, int D, int U, bool NTS>
+__device__ __forceinline__ void attend_chunk(const DecodeArgs& a, const int split, const int h, const int b) {
     using M = RowMap<KT, D>;
     constexpr int EPL = M::EPL, LPR = M::LPR, TILE = U * M::RPL;
-    const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int c0 = split * a.chunk;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int64_t bh = (int64_t)b * a.H + h;
@@ -142,7 +144,6 @@ void decode_attend_kernel(DecodeArgs a, PlanStash stash) {
     const SeqLayout lay = seq_layout(a.sys_len, a.vis_len[b], a.max_vis, len_phys, a.tail_start, b);
     const int len = lay.vlen;
     const RowShift sh = lay.shift();
-    leave_stash(stash);
     if (split == 0 && h == 0 && tid == 0 && a.pending != nullptr) {
         // bit 0: the mass of this launch is still to be finished; above it: the rows this launch attends over
         a.pending[b * 4 + 0] = ((a.logits != nullptr && len > 0 && a.defer) ? 1 : 0) | (max(len, 0) << 1);
@@ -210,7 +211,7 @@ void decode_attend_kernel(DecodeArgs a, PlanStash stash) {
                                vis_hi);
         if (lane < 2 * LPR) {                       // store the row into the cache: lanes [0,LPR) K, [LPR,2*LPR) V
             KT* dst = (lane < LPR ? kbase : vbase) + (int64_t)(len_phys - 1) * a.stride_t + (lane % LPR) * EPL;
-            *reinterpret_cast<u32x4_t*>(dst) = lane < LPR ? kn_raw : vn_raw;
+            store_hint<NTS>(reinterpret_cast<u32x4_t*>(dst), lane < LPR ? kn_raw : vn_raw);
         }
     }
     finish_wave<KT, D>(st);
@@ -224,7 +225,8 @@ void decode_attend_kernel(DecodeArgs a, PlanStash stash) {
     if (lane == 0) { sm_m[wave] = st.m; sm_l[wave] = st.l; }
     __syncthreads();
     if (lg != nullptr) {
-        for (int i = tid; i < lg_hi - lg_lo; i += kDecodeThreads) lg[lg_lo - vis_lo + i] = sm_lg[i];
+        for (int i = tid; i < lg_hi - lg_lo; i += kDecodeThreads)
+            store_hint<NTS>(lg + (lg_lo - vis_lo + i), sm_lg[i]);
     }
     if (tid < D) {
         float m = sm_m[0];
@@ -238,10 +240,61 @@ void decode_attend_kernel(DecodeArgs a, PlanStash stash) {
             l = fmaf(sm_l[w], f, l);
         }
         const int64_t slot = bh * a.nsplit_cap + split;
-        if (a.nsplit == 1) store_out<T>(a.out, bh * D + tid, o / l * v_unit);
+        if (a.nsplit == 1) store_out<T, NTS>(a.out, bh * D + tid, o / l * v_unit);
         else a.part_o[slot * D + tid] = o * v_unit;
         if (tid == 0) { a.part_ml[slot * 2] = m; a.part_ml[slot * 2 + 1] = l; }
     }
+}
+
+// grid (nsplit, H, B)
+template <typename T, typename KT, int D, int U>
+__global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS)
+__attribute__((amdgpu_waves_per_eu(ST3_DECODE_MIN_BLOCKS, ST3_DECODE_MIN_BLOCKS)))    // do not spill to reach a third wave
+void decode_attend_kernel(DecodeArgs a) {
+    attend_chunk<T, KT, D, U, false>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
+// Workgroup (split, h, b) = (0, 0, 0) of a layer leaves the layer's table entry in its workspace (plain vector
+// stores): the step's plan launch reads it there.
+__device__ __forceinline__ void leave_entry(const StepCommon& c, const StepLayer& e, const DecodeWs& wl) {
+    if (threadIdx.x < kStepLayerWords)
+        reinterpret_cast<uint32_t*>(e.ws + wl.step_entry)[threadIdx.x] = reinterpret_cast<const uint32_t*>(&e)[threadIdx.x];
+}
+
+// The attention of several layers of a step that do not depend on each other; grid (most chunks of any of them, H,
+// B * layers), layers in order, so the longest strips (early layers keep the most rows) start first.  Bound by HBM; as a
+// launch per layer it was bound by the ramp and the tail of each launch and the gap behind it (about 9 us a layer, whatever
+// its bytes).  Whole step, us, one launch per layer -> up to 21 layers per launch: 7B batch 1 191 -> 75 (209 MB), 13B batch 8
+// with lazy layers 707 -> 557 (2.9 GB), high resolution batch 8 E4M3 830 -> 700 (3.6 GB), 13B batch 32 2514 -> 2437 (15.4 GB,
+// 6.3 TB/s; a kernel that only reads the same rows takes 2155).
+template <typename T, typename KT, int D, int U, bool NTS>
+__global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS)
+__attribute__((amdgpu_waves_per_eu(ST3_DECODE_MIN_BLOCKS, ST3_DECODE_MIN_BLOCKS)))
+void decode_attend_layers_kernel(StepTable t) {
+    const StepCommon& c = t.c;
+    const int li = __builtin_amdgcn_readfirstlane((int)blockIdx.z / c.B), b = (int)blockIdx.z - li * c.B;
+    const int split = blockIdx.x, h = blockIdx.y;
+    const StepLayer& e = t.layer[li];
+    if (split >= e.nsplit) return;
+    const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
+    const bool want = (e.flags & kStepWantMass) != 0, all = (e.flags & kStepKeepAll) != 0;
+    DecodeArgs a;
+    a.q = e.q; a.k = e.k; a.v = e.v;
+    a.stride_b = e.stride_b; a.stride_h = e.stride_h; a.stride_t = e.stride_t;
+    a.kv_len = e.kv_len; a.vis_len = e.vis_len; a.tail_start = e.tail_start;
+    a.B = c.B; a.sys_len = e.sys_len; a.max_vis = e.max_vis; a.max_kv = e.max_kv + 1; a.H = c.H;
+    a.nsplit = e.nsplit; a.nsplit_cap = e.nsplit_cap; a.chunk = e.chunk; a.capacity = e.capacity;
+    a.hint_base = e.hint_base; a.hint_gap = e.hint_gap;
+    a.defer = want; a.keep_all_logits = all;
+    a.scale_l2 = c.scale_l2; a.k_scale = e.k_scale; a.v_scale = e.v_scale;
+    a.part_o = reinterpret_cast<float*>(e.ws + wl.part_o);
+    a.part_ml = reinterpret_cast<float*>(e.ws + wl.part_ml);
+    a.logits = (want || all) ? reinterpret_cast<float*>(e.ws + wl.logits) : nullptr;
+    a.stage_rows = 0;           // (the launcher's)
+    a.pending = reinterpret_cast<int32_t*>(e.ws + wl.pending);
+    a.k_new = e.k_new; a.v_new = e.v_new; a.out = e.out;
+    if (split == 0 && h == 0 && b == 0) leave_entry(c, e, wl);
+    attend_chunk<T, KT, D, U, NTS>(a, split, h, b);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -313,13 +366,11 @@ __device__ __forceinline__ void wave_inherit(const T* vbase, int64_t stride_t, i
     }
 }
 
-// grid (nsplit, H, B)
+// One workgroup: chunk `split` of strip (b, h) of a lazy layer.
 template <typename T, typename KT, int D, int U>
-__global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_inherit_kernel(InheritArgs a, PlanStash stash) {
+__device__ __forceinline__ void inherit_chunk(const InheritArgs& a, const int split, const int h, const int b) {
     using M = RowMap<KT, D>;
     constexpr int EPL = M::EPL, LPR = M::LPR, TILE = U * M::RPL;
-    const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    leave_stash(stash);
     const int len_phys = min(a.kv_len[b] + (a.v_new != nullptr ? 1 : 0), a.max_kv);
     // rows are numbered without the gap a fixed-tail cache keeps behind its visual segment, as in the
     // source layer's attend launch (same lengths, same layout): its logits are indexed the same way
@@ -384,6 +435,38 @@ __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_
         if (a.nsplit == 1) store_out<T>(a.out, bh * D + tid, o * v_unit);
         else a.part_o[(bh * a.nsplit_cap + split) * D + tid] = o * v_unit;
     }
+}
+
+// grid (nsplit, H, B)
+template <typename T, typename KT, int D, int U>
+__global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_inherit_kernel(InheritArgs a) {
+    inherit_chunk<T, KT, D, U>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
+// Several lazy layers of a step (their sources have all attended); grid as in decode_attend_layers_kernel.
+template <typename T, typename KT, int D, int U>
+__global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_inherit_layers_kernel(StepTable t) {
+    const StepCommon& c = t.c;
+    const int li = __builtin_amdgcn_readfirstlane((int)blockIdx.z / c.B), b = (int)blockIdx.z - li * c.B;
+    const int split = blockIdx.x, h = blockIdx.y;
+    const StepLayer& e = t.layer[li];
+    if (split >= e.nsplit) return;
+    const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
+    const DecodeWs sl = decode_ws_sized(c.B, c.H, D, e.hint_base, e.src_nsplit_cap);
+    const char* sws = reinterpret_cast<const char*>(e.q);
+    InheritArgs a;
+    a.v = e.v; a.stride_b = e.stride_b; a.stride_h = e.stride_h; a.stride_t = e.stride_t;
+    a.kv_len = e.kv_len; a.vis_len = e.vis_len; a.tail_start = e.tail_start;
+    a.B = c.B; a.max_kv = e.max_kv + 1; a.H = c.H; a.nsplit = e.nsplit; a.nsplit_cap = e.nsplit_cap; a.chunk = e.chunk;
+    a.sys_len = e.sys_len; a.max_vis = e.max_vis;
+    a.src_logits = reinterpret_cast<const float*>(sws + sl.logits);
+    a.src_part_ml = reinterpret_cast<const float*>(sws + sl.part_ml);
+    a.src_pending = reinterpret_cast<const int32_t*>(sws + sl.pending);
+    a.src_capacity = e.hint_base; a.src_nsplit_cap = e.src_nsplit_cap;
+    a.part_o = reinterpret_cast<float*>(e.ws + wl.part_o);
+    a.v_new = e.v_new; a.v_scale = e.v_scale; a.out = e.out;
+    if (split == 0 && h == 0 && b == 0) leave_entry(c, e, wl);
+    inherit_chunk<T, KT, D, U>(a, split, h, b);
 }
 
 struct FinishArgs {
@@ -558,48 +641,74 @@ inline int cheapest(const double* cost, int n) {
     return best;
 }
 
-template <typename T, typename KT, int D, int U>
-void launch_attend_u(const DecodeArgs& da, const PlanStash& ps, int B, hipStream_t st) {
-    const dim3 grid(da.nsplit, da.H, B);
-    const size_t lds = (size_t)da.stage_rows * sizeof(float);       // dynamic LDS: the logit staging area
+// Launches `kernel` with the profiler's event pair attached when one is to be had; `layers` is how many layers'
+// attention the launch does.
+template <typename K, typename A>
+void launch_timed(K kernel, dim3 grid, size_t lds, hipStream_t st, int layers, const A& args) {
     hipEvent_t e0, e1;
-    if (profile_take(&e0, &e1))     // timed launch: the events receive the kernel's own start and end
-        hipExtLaunchKernelGGL((decode_attend_kernel<T, KT, D, U>), grid, dim3(kDecodeThreads), lds, st, e0, e1, 0, da, ps);
+    if (profile_take(&e0, &e1, layers))     // timed launch: the events receive the kernel's own start and end
+        hipExtLaunchKernelGGL(kernel, grid, dim3(kDecodeThreads), lds, st, e0, e1, 0, args);
     else
-        decode_attend_kernel<T, KT, D, U><<<grid, kDecodeThreads, lds, st>>>(da, ps);
+        kernel<<<grid, kDecodeThreads, lds, st>>>(args);
 }
 
-// Takes the cheapest of the builds Us... (in order of preference) for this launch.
+// go(U) with the forced tile size when one is set and built, else with build number `pick` of Us...
+template <int... Us, typename Go>
+void with_tile(std::integer_sequence<int, Us...>, int pick, Go go) {
+    const int us[] = {Us...};
+    int u = debug_state().attend_tile;          // 0 unless the debug block is enabled
+    if (!((u == Us) || ...)) u = us[pick];
+    ((u == Us ? (go(std::integral_constant<int, Us>{}), 0) : 0), ...);
+}
+
+// The cheapest of the builds Us... (in order of preference) for a launch of `items` workgroups.
 template <typename T, typename KT, int D, int... Us>
-void launch_attend_best(const DecodeArgs& da, const PlanStash& ps, int B, hipStream_t st, std::integer_sequence<int, Us...>) {
+int best_tile(int64_t items, std::integer_sequence<int, Us...>) {
     constexpr int N = sizeof...(Us);
     static std::atomic<int> slots[N][kMaxDevices];  // resident workgroups of each build, per device
-    const int us[N] = {Us...};
-    const int g_forced_tile = debug_state().attend_tile;    // 0 unless the debug block is enabled
-    if (g_forced_tile != 0 && ((g_forced_tile == Us) || ...)) {
-        ((g_forced_tile == Us ? (launch_attend_u<T, KT, D, Us>(da, ps, B, st), 0) : 0), ...);
-        return;
-    }
-    const int64_t items = (int64_t)da.nsplit * da.H * B;
     double cost[N];
     int i = 0;
     ((cost[i] = last_round_cost(items, resident_workgroups(decode_attend_kernel<T, KT, D, Us>, slots[i])), ++i), ...);
-    const int pick = us[cheapest(cost, N)];
-    ((pick == Us ? (launch_attend_u<T, KT, D, Us>(da, ps, B, st), 0) : 0), ...);
+    return cheapest(cost, N);
+}
+
+template <typename KT>
+using AttendTiles = std::conditional_t<sizeof(KT) == 1, std::integer_sequence<int, 3, 4, 1>, std::integer_sequence<int, 4, 6, 8, 1>>;
+
+template <typename T, typename KT, int D>
+void launch_attend(const DecodeArgs& da, int B, hipStream_t st) {
+    const dim3 grid(da.nsplit, da.H, B);
+    const size_t lds = (size_t)da.stage_rows * sizeof(float);       // dynamic LDS: the logit staging area
+    with_tile(AttendTiles<KT>{}, best_tile<T, KT, D>((int64_t)da.nsplit * da.H * B, AttendTiles<KT>{}), [&](auto u) {
+        launch_timed(decode_attend_kernel<T, KT, D, decltype(u)::value>, grid, lds, st, 1, da);
+    });
+}
+
+// `most`: the largest chunk count of any layer of the table.  One build: a launch over many layers runs many rounds of
+// workgroups of unequal length, there is no last round to fill.  Measured at U = 4 / 1 / 6 / 8 (E4M3: 3 / 4 / 1), us per step:
+// 7B batch 1 72.6 / 71.8 / 75.6 / 78.9, 13B batch 8 with lazy layers 563 / 571 / 560 / 565, 13B batch 32 2441 / 2457 / 2433 /
+// 2421, 13B batch 32 E4M3 1327 / 1404 / 1423, high resolution batch 8 E4M3 700 / 696 / 721.
+template <typename T, typename KT, int D>
+void launch_attend_layers(const StepTable& t, int most, int stage_rows, bool stream, hipStream_t st) {
+    const dim3 grid(most, t.c.H, t.c.B * t.c.layers);
+    const size_t lds = (size_t)stage_rows * sizeof(float);
+    with_tile(AttendTiles<KT>{}, 0, [&](auto u) {
+        if (stream) launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, true>, grid, lds, st, t.c.layers, t);
+        else launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, false>, grid, lds, st, t.c.layers, t);
+    });
 }
 
 template <typename T, typename KT, int D>
-void launch_attend(const DecodeArgs& da, const PlanStash& ps, int B, hipStream_t st) {
-    if constexpr (sizeof(KT) == 1) launch_attend_best<T, KT, D>(da, ps, B, st, std::integer_sequence<int, 3, 4, 1>{});
-    else launch_attend_best<T, KT, D>(da, ps, B, st, std::integer_sequence<int, 4, 6, 8, 1>{});
+void launch_inherit_layers(const StepTable& t, int most, hipStream_t st) {
+    decode_inherit_layers_kernel<T, KT, D, 4><<<dim3(most, t.c.H, t.c.B * t.c.layers), kDecodeThreads, 0, st>>>(t);
 }
 
 // The V-only kernel of lazy layers: 4 loads per lane and tile (4 KB per wave) were the fastest or
 // within 2 % of it at every batch size and for both cache formats (8, 12 and 16 loads lose up to
 // 17 % where the launch has more workgroups than fit at once; 2 loads lose at small batches).
 template <typename T, typename KT, int D>
-void launch_inherit(const InheritArgs& ia, const PlanStash& ps, int B, hipStream_t st) {
-    decode_inherit_kernel<T, KT, D, 4><<<dim3(ia.nsplit, ia.H, B), kDecodeThreads, 0, st>>>(ia, ps);
+void launch_inherit(const InheritArgs& ia, int B, hipStream_t st) {
+    decode_inherit_kernel<T, KT, D, 4><<<dim3(ia.nsplit, ia.H, B), kDecodeThreads, 0, st>>>(ia);
 }
 
 template <typename T, int D>
@@ -667,13 +776,14 @@ st3_status check_kv(const st3_attn_shape* s, const st3_kv_layer* kv, const st3_s
 
 }  // namespace
 
-// Whether a launch over kv_len <= max_kv_len rows cuts its strips into chunks (partials to merge).
-bool decode_is_split(const st3_attn_shape* shape, const st3_kv_layer* kv, int32_t max_kv_len) {
-    const DecodeWs wl = decode_ws(shape->batch, shape->heads, shape->head_dim, kv->capacity);
-    int nsplit = decode_nsplit(shape->batch, shape->heads, max_kv_len, kDecodeTargetWgsMerged);
-    if (nsplit > wl.nsplit_cap) nsplit = wl.nsplit_cap;
-    const int chunk = decode_chunk(max_kv_len, nsplit);
-    return (max_kv_len + chunk - 1) / chunk > 1;
+// The caller's guess at the layout of a fixed-tail cache, as the attend kernel takes it (none: INT_MAX, 0).
+static void layout_hint(const st3_segments* seg, int capacity, int32_t& hint_base, int32_t& hint_gap) {
+    hint_base = 0x7fffffff; hint_gap = 0;
+    if (seg->tail_start == nullptr || seg->tail_start_hint <= 0) return;
+    const int nv = std::max(0, std::min(seg->vis_len_hint, seg->max_vis_len));
+    const int base = seg->sys_len + nv;
+    const int ts = std::min(seg->tail_start_hint, capacity);        // (keeps row + gap far from overflow)
+    if (ts > base) { hint_base = base; hint_gap = ts - base; }
 }
 
 // Enqueues attention (+ the finish kernel when it is needed).  max_kv_len bounds the length the
@@ -682,8 +792,7 @@ bool decode_is_split(const st3_attn_shape* shape, const st3_kv_layer* kv, int32_
 st3_status enqueue_decode(const st3_attn_shape* shape, const void* q, const st3_kv_layer* kv,
                           const st3_segments* seg, int32_t max_kv_len, const void* k_new, const void* v_new,
                           void* out, float* vis_mass, int64_t mass_stride, bool want_mass, bool defer_mass,
-                          bool keep_all_logits, void* workspace, size_t workspace_bytes, hipStream_t st,
-                          bool defer_merge, const PlanStash* stash) {
+                          bool keep_all_logits, void* workspace, size_t workspace_bytes, hipStream_t st) {
     const int B = shape->batch, H = shape->heads, D = shape->head_dim;
     const DecodeWs wl = decode_ws(B, H, D, kv->capacity);
     if (workspace_bytes < wl.total) return ST3_ERR_WORKSPACE_TOO_SMALL;
@@ -694,14 +803,8 @@ st3_status enqueue_decode(const st3_attn_shape* shape, const void* q, const st3_
     da.stride_b = kv->stride_b; da.stride_h = kv->stride_h; da.stride_t = kv->stride_t;
     da.kv_len = seg->kv_len; da.vis_len = seg->vis_len; da.tail_start = seg->tail_start;
     da.B = B; da.sys_len = seg->sys_len; da.max_vis = seg->max_vis_len; da.max_kv = max_kv_len; da.H = H;
-    da.hint_base = 0x7fffffff; da.hint_gap = 0;
-    if (seg->tail_start != nullptr && seg->tail_start_hint > 0) {
-        const int nv = std::max(0, std::min(seg->vis_len_hint, seg->max_vis_len));
-        const int base = seg->sys_len + nv;
-        const int ts = std::min(seg->tail_start_hint, kv->capacity);    // (keeps row + gap far from overflow)
-        if (ts > base) { da.hint_base = base; da.hint_gap = ts - base; }
-    }
-    da.nsplit = decode_nsplit(B, H, max_kv_len, defer_merge ? kDecodeTargetWgsMerged : kDecodeTargetWgs);
+    layout_hint(seg, kv->capacity, da.hint_base, da.hint_gap);
+    da.nsplit = decode_nsplit(B, H, max_kv_len);
     if (da.nsplit > wl.nsplit_cap) da.nsplit = wl.nsplit_cap;
     da.nsplit_cap = wl.nsplit_cap;
     da.chunk = decode_chunk(max_kv_len, da.nsplit);
@@ -721,18 +824,16 @@ st3_status enqueue_decode(const st3_attn_shape* shape, const void* q, const st3_
     da.k_new = k_new; da.v_new = v_new;
     da.out = out;
     da.defer = (want_mass && defer_mass) ? 1 : 0;
-    const PlanStash ps = stash != nullptr ? *stash : PlanStash{};
-    ST3_DISPATCH_KV(launch_attend, shape, kv, da, ps, B, st);
+    ST3_DISPATCH_KV(launch_attend, shape, kv, da, B, st);
     const bool mass_now = want_mass && !defer_mass;
-    // defer_merge: the caller's eviction plan merges the chunk partials (whole-step call)
-    if ((da.nsplit > 1 && !defer_merge) || mass_now) {
+    if (da.nsplit > 1 || mass_now) {
         FinishArgs fa{};
         fa.part_o = da.part_o; fa.part_ml = da.part_ml; fa.logits = da.logits;
         fa.kv_len = seg->kv_len; fa.vis_len = seg->vis_len; fa.tail_start = seg->tail_start;
         fa.H = H; fa.nsplit = da.nsplit; fa.nsplit_cap = wl.nsplit_cap; fa.chunk = da.chunk;
         fa.capacity = kv->capacity; fa.max_vis = seg->max_vis_len; fa.max_kv = max_kv_len; fa.sys_len = seg->sys_len;
         fa.appended = k_new != nullptr ? 1 : 0;
-        fa.out = (da.nsplit > 1 && !defer_merge) ? out : nullptr;
+        fa.out = da.nsplit > 1 ? out : nullptr;
         fa.mass = mass_now ? vis_mass : nullptr; fa.mass_stride = mass_stride;
         ST3_DISPATCH(launch_finish, shape, fa, B, st);
     }
@@ -765,7 +866,7 @@ st3_status validate_kv_value_only(const st3_attn_shape* s, const st3_kv_layer* k
 st3_status enqueue_inherit(const st3_attn_shape* shape, const st3_kv_layer* kv, const st3_segments* seg,
                            int32_t max_kv_len, const void* v_new, const void* src_workspace,
                            size_t src_workspace_bytes, int32_t src_capacity, void* out, void* workspace,
-                           size_t workspace_bytes, hipStream_t st, const PlanStash* stash) {
+                           size_t workspace_bytes, hipStream_t st) {
     const int B = shape->batch, H = shape->heads, D = shape->head_dim;
     const DecodeWs wl = decode_ws(B, H, D, kv->capacity);
     const DecodeWs sl = decode_ws(B, H, D, src_capacity);
@@ -791,8 +892,7 @@ st3_status enqueue_inherit(const st3_attn_shape* shape, const st3_kv_layer* kv, 
     ia.part_o = reinterpret_cast<float*>(ws + wl.part_o);
     ia.v_new = v_new; ia.out = out;
     if (kv->format == ST3_KV_E4M3) ia.v_scale = kv->v_scale;
-    const PlanStash ps = stash != nullptr ? *stash : PlanStash{};
-    ST3_DISPATCH_KV(launch_inherit, shape, kv, ia, ps, B, st);
+    ST3_DISPATCH_KV(launch_inherit, shape, kv, ia, B, st);
     if (ia.nsplit > 1) {
         FinishArgs fa{};
         fa.part_o = ia.part_o; fa.kv_len = seg->kv_len; fa.vis_len = seg->vis_len; fa.tail_start = seg->tail_start;
@@ -802,6 +902,109 @@ st3_status enqueue_inherit(const st3_attn_shape* shape, const st3_kv_layer* kv, 
         fa.appended = v_new != nullptr ? 1 : 0;
         fa.out = out;
         ST3_DISPATCH(launch_finish, shape, fa, B, st);
+    }
+    return check_launch();
+}
+
+// ---------------------------------------------------------------------------------------------
+// All layers of a step, several per launch (the caller has checked them and knows that they share no buffers).
+// ---------------------------------------------------------------------------------------------
+// A launch writes one output row and two cache rows per strip, and the logits.  Left to the caches, those lines are evicted
+// between the reads of K and V, and every turn of the memory from reading to writing costs: with ordinary stores a plain
+// strip-reading kernel that writes as little (0.4 % of what it reads) falls from 7.04 to 6.18 TB/s, with non-temporal ones
+// to 6.61.  But what stays in the caches is found there by the plan launch that follows.  Measured, us per step, ordinary ->
+// non-temporal, by the bytes of the rows a launch writes: 7B batch 1 (0.4 MB) 74.3 -> 76.6, batch 4 (1.6 MB) 173 -> 184, high
+// resolution batch 8 E4M3 (2 MB) 700 -> 713, 13B batch 8 with lazy layers (4 MB) 563 -> 574, 13B batch 8 (4.9 MB) 659 -> 657,
+// batch 12 (7.4 MB) 975 -> 963, batch 16 (9.8 MB) 1290 -> 1270, batch 32 E4M3 (13 MB) 1352 -> 1327, batch 32 (20 MB) 2569 -> 2437.
+constexpr int64_t kStreamStoreBytes = (int64_t)7 << 20;
+
+// Attention of every layer of a checked step: the ordinary layers, up to kStepLayersMax per launch, then the lazy ones.
+// entry[i] receives where layer i's table entry will lie once the launches have run; split: some strip was cut, its
+// partials are left for the plan to merge.  Returns ST3_ERR_UNSUPPORTED, with nothing enqueued, for a step that a table
+// cannot describe.
+st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const st3_layer_step* layers, int mode,
+                               const char* has_heirs, const EvictArgs* plan, StepCommon& common, const StepLayer** entry,
+                               bool& split, hipStream_t st) {
+    const int B = shape->batch, H = shape->heads, D = shape->head_dim;
+    const int fmt = layers[0].kv.format;
+    common = StepCommon{B, H, D, mode, kv_elem_bytes(shape, &layers[0].kv), shape->dtype == ST3_BF16 ? 1 : 0, scale_log2(shape), 0};
+    int64_t rows[2] = {0, 0};           // of the ordinary and of the lazy layers
+    for (int i = 0; i < n_layers; ++i) {
+        const st3_layer_step& L = layers[i];
+        const int64_t most32 = 0x7fffffff;
+        if (L.kv.format != fmt || L.kv.stride_t > most32 || L.col_stride < 0 || L.col_stride > most32 || L.mass_stride < 0 ||
+            L.mass_stride > most32)
+            return ST3_ERR_UNSUPPORTED;
+        rows[L.inherit_from >= 0] += L.seg.max_kv_len + 1;
+    }
+    const int per = std::min(kStepLayersMax, 65535 / B);        // grid z is B * layers
+    if (per < 1) return ST3_ERR_UNSUPPORTED;
+    std::vector<StepLayer> e((size_t)n_layers);
+    std::vector<int> stage((size_t)n_layers, 0), members[2];
+    split = false;
+    for (int i = 0; i < n_layers; ++i) {
+        const st3_layer_step& L = layers[i];
+        const bool lazy = L.inherit_from >= 0;
+        const int len = L.seg.max_kv_len + 1;
+        const DecodeWs wl = decode_ws(B, H, D, L.kv.capacity);
+        StepLayer& s = e[(size_t)i];
+        memset(&s, 0, sizeof(s));
+        s.v = L.kv.v; s.v_new = L.v_new; s.out = L.out;
+        s.kv_len = L.seg.kv_len; s.vis_len = L.seg.vis_len; s.tail_start = L.seg.tail_start;
+        s.score_col = L.score_col; s.id_col = L.id_col; s.mass = plan[i].mass_dst; s.ws = reinterpret_cast<char*>(L.workspace);
+        if (fmt == ST3_KV_E4M3) { s.k_scale = L.kv.k_scale; s.v_scale = L.kv.v_scale; }
+        s.stride_b = L.kv.stride_b; s.stride_h = L.kv.stride_h; s.stride_t = (int32_t)L.kv.stride_t;
+        s.col_stride = (int32_t)L.col_stride; s.mass_stride = (int32_t)L.mass_stride;
+        s.sys_len = L.seg.sys_len; s.max_vis = L.seg.max_vis_len; s.max_kv = L.seg.max_kv_len;
+        s.keep_count = plan[i].keep_count; s.capacity = L.kv.capacity;
+        int nsplit = step_nsplit(B, H, len, rows[lazy]);
+        if (nsplit > wl.nsplit_cap) nsplit = wl.nsplit_cap;
+        s.chunk = decode_chunk(len, nsplit);
+        nsplit = (len + s.chunk - 1) / s.chunk;
+        s.nsplit = (uint8_t)nsplit; s.nsplit_cap = (uint8_t)wl.nsplit_cap;
+        split = split || nsplit > 1;
+        s.flags = (uint8_t)(plan[i].inline_apply ? kStepInlineApply : 0);
+        if (lazy) {
+            const st3_layer_step& S = layers[L.inherit_from];
+            const DecodeWs sl = decode_ws(B, H, D, S.kv.capacity);
+            if (L.workspace_bytes < wl.total || S.workspace_bytes < sl.total) return ST3_ERR_WORKSPACE_TOO_SMALL;
+            if (len > S.kv.capacity) return ST3_ERR_INVALID_ARG;        // the source kept a logit per cached key
+            s.q = S.workspace; s.hint_base = S.kv.capacity; s.src_nsplit_cap = (uint8_t)sl.nsplit_cap;
+            s.k = L.kv.k;               // its rows move with an eviction when the layer caches keys after all
+            s.flags |= kStepLazy;
+        } else {
+            s.q = L.q; s.k = L.kv.k; s.k_new = L.k_new;
+            layout_hint(&L.seg, L.kv.capacity, s.hint_base, s.hint_gap);
+            const bool want = L.vis_mass != nullptr && L.seg.max_vis_len > 0;
+            if (want) s.flags |= kStepWantMass;
+            if (has_heirs[i]) s.flags |= kStepKeepAll;
+            if (has_heirs[i]) stage[(size_t)i] = s.chunk;
+            else if (want) stage[(size_t)i] = std::min(s.chunk, L.seg.max_vis_len);
+            if (stage[(size_t)i] > 3 * kLogitStageMaxRows) return ST3_ERR_UNSUPPORTED;
+        }
+        entry[i] = reinterpret_cast<const StepLayer*>(s.ws + wl.step_entry);
+        members[lazy].push_back(i);
+    }
+    for (int lazy = 0; lazy < 2; ++lazy) {
+        const int n = (int)members[lazy].size();
+        const int launches = (n + per - 1) / per;
+        for (int g = 0, i0 = 0; g < launches; ++g) {
+            const int cnt = (n - i0 + launches - g - 1) / (launches - g);       // as equal as can be
+            StepTable t{};
+            t.c = common; t.c.layers = cnt;
+            int most = 1, stage_rows = 0;
+            int64_t row_bytes = 0;
+            for (int j = 0; j < cnt; ++j) {
+                const int i = members[lazy][(size_t)(i0 + j)];
+                t.layer[j] = e[(size_t)i];
+                most = std::max(most, (int)e[(size_t)i].nsplit);
+                stage_rows = std::max(stage_rows, stage[(size_t)i]);
+                row_bytes += (int64_t)B * H * D * (2 * common.cache_eb + elem_bytes(shape->dtype));
+            }
+            if (lazy) ST3_DISPATCH_KV(launch_inherit_layers, shape, &layers[0].kv, t, most, st);
+            else ST3_DISPATCH_KV(launch_attend_layers, shape, &layers[0].kv, t, most, stage_rows, row_bytes > kStreamStoreBytes, st);
+            i0 += cnt;
+        }
     }
     return check_launch();
 }
@@ -820,7 +1023,7 @@ extern "C" st3_status st3_decode_attention(const st3_attn_shape* shape, const vo
     if (vis_mass && mass_stride < seg->max_vis_len) return ST3_ERR_INVALID_ARG;
     return st3::enqueue_decode(shape, q, kv, seg, seg->max_kv_len, nullptr, nullptr, out, vis_mass, mass_stride,
                                vis_mass != nullptr, false, true, workspace, workspace_bytes,
-                               reinterpret_cast<hipStream_t>(stream), false, nullptr);
+                               reinterpret_cast<hipStream_t>(stream));
 }
 
 extern "C" st3_status st3_decode_attention_inherit(const st3_attn_shape* shape, const st3_kv_layer* kv,
@@ -835,7 +1038,7 @@ extern "C" st3_status st3_decode_attention_inherit(const st3_attn_shape* shape, 
     if (!st3::aligned16(workspace) || !st3::aligned16(src_workspace)) return ST3_ERR_INVALID_ARG;
     return st3::enqueue_inherit(shape, kv, seg, seg->max_kv_len, nullptr, src_workspace, src_workspace_bytes,
                                 src_kv_capacity, out, workspace, workspace_bytes,
-                                reinterpret_cast<hipStream_t>(stream), nullptr);
+                                reinterpret_cast<hipStream_t>(stream));
 }
 
 extern "C" st3_status st3_quantize_rows(const st3_attn_shape* shape, const st3_tensor4* src, const st3_kv_layer* kv,

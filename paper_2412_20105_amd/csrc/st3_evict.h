@@ -129,12 +129,35 @@ struct EvictArgs {
     int32_t nsplit_cap;
     float* mass_dst;
     int64_t mass_stride;
-    // chunk partials of the attention output that the attend launch left for this plan to merge
-    // (whole-step call with strips cut into chunks; null: the output is complete already)
-    const float* merge_part_o;  // [B,H,nsplit_cap,D]
-    void* merge_out;            // [B,H,D]
-    int32_t merge_D, merge_bf16;
 };
+
+// The plan of a layer whose table entry a whole-step attention launch has left in the layer's workspace.
+__device__ __forceinline__ EvictArgs plan_from_entry(const StepCommon& c, const StepLayer& e) {
+    const DecodeWs wl = decode_ws_sized(c.B, c.H, c.D, e.capacity, e.nsplit_cap);
+    EvictArgs a;
+    a.score_col = e.score_col; a.id_col = e.id_col; a.col_stride = e.col_stride;
+    a.vis_len = e.vis_len; a.kv_len = e.kv_len; a.tail_start = e.tail_start;
+    a.sys_len = e.sys_len; a.max_vis = e.max_vis; a.max_kv = e.max_kv;
+    a.keep_count = e.keep_count; a.mode = c.mode;
+    a.move_cnt = reinterpret_cast<int32_t*>(e.ws + wl.moves_cnt);
+    a.moves = reinterpret_cast<int32_t*>(e.ws + wl.moves);
+    a.max_moves = wl.max_moves;
+    a.appended = 1;
+    a.inline_apply = (e.flags & kStepInlineApply) != 0;
+    a.k = reinterpret_cast<char*>(e.k); a.v = reinterpret_cast<char*>(e.v);
+    a.stride_b = e.stride_b * c.cache_eb; a.stride_h = e.stride_h * c.cache_eb; a.stride_t = (int64_t)e.stride_t * c.cache_eb;
+    a.H = c.H; a.vecs_per_row = c.D * c.cache_eb / 16;
+    // a lazy layer's mass is finished from what its source's launch left
+    const bool lazy = (e.flags & kStepLazy) != 0;
+    const DecodeWs ml = lazy ? decode_ws_sized(c.B, c.H, c.D, e.hint_base, e.src_nsplit_cap) : wl;
+    const char* mws = lazy ? reinterpret_cast<const char*>(e.q) : e.ws;
+    a.part_ml = reinterpret_cast<const float*>(mws + ml.part_ml);
+    a.logits = reinterpret_cast<const float*>(mws + ml.logits);
+    a.pending = reinterpret_cast<const int32_t*>(mws + ml.pending);
+    a.nsplit_cap = ml.nsplit_cap; a.capacity = lazy ? e.hint_base : e.capacity;
+    a.mass_dst = e.mass; a.mass_stride = e.mass_stride;
+    return a;
+}
 
 __device__ __forceinline__ bool flag_at(const SelShared& sm, int p) { return (sm.flags[p >> 5] >> (p & 31)) & 1u; }
 
@@ -175,30 +198,40 @@ __device__ __forceinline__ void copy_rows_all_strips(const EvictArgs& a, int b, 
 // Merges the chunk partials of the output rows of heads [h0, h1) of sequence b in chunk order (what
 // decode_finish_kernel does when the attention is called on its own).  Runs beside the plan
 // workgroup of the same sequence, which rewrites the lengths: the number of rows the attend launch
-// saw therefore comes from the descriptor that launch left, not from the lengths.
-__device__ __forceinline__ void merge_chunks(const EvictArgs& a, int b, int h0, int h1) {
-    const int nsplit = min(a.pending[b * 4 + 1], a.nsplit_cap);
-    const int chunk = max(a.pending[b * 4 + 2], 32);
-    const int seen = a.pending[b * 4] >> 1;
-    const int ns = seen > 0 ? min((seen + chunk - 1) / chunk, nsplit) : 0;
+// saw therefore comes from the descriptor that launch left (a lazy layer: its source's launch, which
+// saw as many), not from the lengths.
+__device__ __forceinline__ void merge_chunks(const StepCommon& c, const StepLayer& e, int b, int h0, int h1) {
+    const bool lazy = (e.flags & kStepLazy) != 0;
+    const DecodeWs wl = decode_ws_sized(c.B, c.H, c.D, e.capacity, e.nsplit_cap);
+    const DecodeWs sl = lazy ? decode_ws_sized(c.B, c.H, c.D, e.hint_base, e.src_nsplit_cap) : wl;
+    const int seen = reinterpret_cast<const int32_t*>((lazy ? reinterpret_cast<const char*>(e.q) : e.ws) + sl.pending)[b * 4] >> 1;
+    const int ns = seen > 0 ? min((seen + e.chunk - 1) / e.chunk, (int)e.nsplit) : 0;
     if (ns <= 0) return;                                // an empty sequence had its zeros written by the attend launch
-    const int D = a.merge_D;
-    h1 = min(h1, a.H);
+    const int D = c.D;
+    h1 = min(h1, c.H);
+    const float* part_o = reinterpret_cast<const float*>(e.ws + wl.part_o);
+    const float* part_ml = reinterpret_cast<const float*>(e.ws + wl.part_ml);
     for (int idx = threadIdx.x; idx < (h1 - h0) * D; idx += blockDim.x) {
         const int h = h0 + idx / D, d = idx % D;
-        const int64_t bh = (int64_t)b * a.H + h;
-        const float* ml = a.part_ml + bh * a.nsplit_cap * 2;
-        float m = ml[0];
-        for (int s = 1; s < ns; ++s) m = fmaxf(m, ml[2 * s]);
-        float l = 0.f, o = 0.f;
-        for (int s = 0; s < ns; ++s) {
-            const float f = exp2_fast(ml[2 * s] - m);
-            l = fmaf(ml[2 * s + 1], f, l);
-            o = fmaf(a.merge_part_o[(bh * a.nsplit_cap + s) * D + d], f, o);
+        const int64_t bh = (int64_t)b * c.H + h;
+        const float* po = part_o + bh * wl.nsplit_cap * D + d;
+        float o = 0.f;
+        if (lazy) {                                     // partials of a lazy layer are normalised already
+            for (int s = 0; s < ns; ++s) o += po[(int64_t)s * D];
+        } else {
+            const float* ml = part_ml + bh * wl.nsplit_cap * 2;
+            float m = ml[0];
+            for (int s = 1; s < ns; ++s) m = fmaxf(m, ml[2 * s]);
+            float l = 0.f;
+            for (int s = 0; s < ns; ++s) {
+                const float f = exp2_fast(ml[2 * s] - m);
+                l = fmaf(ml[2 * s + 1], f, l);
+                o = fmaf(po[(int64_t)s * D], f, o);
+            }
+            o /= l;
         }
-        const float r = o / l;
-        if (a.merge_bf16) reinterpret_cast<uint16_t*>(a.merge_out)[bh * D + d] = (uint16_t)f32_to_bf16_bits(r);
-        else reinterpret_cast<float*>(a.merge_out)[bh * D + d] = r;
+        if (c.out_bf16) reinterpret_cast<uint16_t*>(e.out)[bh * D + d] = (uint16_t)f32_to_bf16_bits(o);
+        else reinterpret_cast<float*>(e.out)[bh * D + d] = o;
     }
 }
 
@@ -353,11 +386,10 @@ void launch_evict_plan(const EvictArgs& ea, int B, hipStream_t st);
 constexpr int kPlanBatch = 16;     // plans that fit the kernel-argument block by value
 // Plans of n layers (device work of one decode step) with one launch per kPlanBatch layers.
 void launch_evict_plan_batch(const EvictArgs* plans, int n, int B, hipStream_t st);
-// The same for plans that the layers' attention launches have left in device memory (PlanStash):
-// stashed[i] is where layer i's copy of plans[i] lies; one launch per kPlanTableMax layers.
+// The plans of n layers from the table entries that whole-step attention launches have left in the layers' workspaces;
+// merge: some strips were cut into chunks, whose partials are merged here too.  One launch per kPlanTableMax layers.
 constexpr int kPlanTableMax = 64;
-static_assert(sizeof(EvictArgs) <= kPlanStashWords * sizeof(uint32_t), "a layer's plan must fit the stash");
-void launch_evict_plan_table(const EvictArgs* const* stashed, const EvictArgs* plans, int n, int B, hipStream_t st);
+void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry, int n, bool merge, hipStream_t st);
 void launch_evict_apply(const EvictArgs& ea, int B, hipStream_t st);
 
 }  // namespace st3

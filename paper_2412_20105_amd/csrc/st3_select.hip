@@ -315,67 +315,53 @@ struct EvictBatch {
 };
 static_assert(sizeof(EvictBatch) <= 4000, "plans of one batch must fit the kernel argument segment");
 
-constexpr int kMergeHeads = 8;      // heads whose chunk partials one merge workgroup combines
-
-// grid (B, layers of the batch, 1 + merge workgroups): z = 0 runs the plan of (sequence x, layer y);
-// z >= 1 merges the chunk partials of that layer's attention output for kMergeHeads heads (only
-// launched when some layer of the batch left partials to merge).
+// grid (B, layers of the batch)
 __global__ __launch_bounds__(kSelThreads) void evict_plan_batch_kernel(EvictBatch batch) {
     __shared__ SelShared sm;
-    const EvictArgs& a = batch.layer[blockIdx.y];
-    if (blockIdx.z == 0) {
-        evict_plan_body(a, blockIdx.x, sm);
-    } else if (a.merge_out != nullptr && a.pending != nullptr) {
-        const int h0 = ((int)blockIdx.z - 1) * kMergeHeads;
-        if (h0 < a.H) merge_chunks(a, blockIdx.x, h0, h0 + kMergeHeads);
-    }
+    evict_plan_body(batch.layer[blockIdx.y], blockIdx.x, sm);
 }
 
 void launch_evict_plan_batch(const EvictArgs* plans, int n, int B, hipStream_t st) {
     for (int i0 = 0; i0 < n; i0 += kPlanBatch) {
         const int cnt = n - i0 < kPlanBatch ? n - i0 : kPlanBatch;
         EvictBatch batch;
-        int merge_heads = 0;
-        for (int i = 0; i < cnt; ++i) {
-            batch.layer[i] = plans[i0 + i];
-            if (plans[i0 + i].merge_out != nullptr && plans[i0 + i].H > merge_heads) merge_heads = plans[i0 + i].H;
-        }
+        for (int i = 0; i < cnt; ++i) batch.layer[i] = plans[i0 + i];
         for (int i = cnt; i < kPlanBatch; ++i) batch.layer[i] = EvictArgs{};
-        const int merge_wgs = (merge_heads + kMergeHeads - 1) / kMergeHeads;
-        evict_plan_batch_kernel<<<dim3(B, cnt, 1 + merge_wgs), kSelThreads, 0, st>>>(batch);
+        evict_plan_batch_kernel<<<dim3(B, cnt), kSelThreads, 0, st>>>(batch);
     }
 }
 
-// The same with the plans read from device memory, where the layers' attention launches left them
-// (PlanStash): up to kPlanTableMax layers per launch.  grid as above.
+constexpr int kMergeHeads = 8;      // heads whose chunk partials one merge workgroup combines
+
 struct PlanTable {
-    const EvictArgs* layer[kPlanTableMax];
+    StepCommon c;
+    const StepLayer* layer[kPlanTableMax];
 };
 
+// grid (B, layers, 1 + merge workgroups): z = 0 runs the plan of (sequence x, layer y); z >= 1 merges the chunk partials
+// of that layer's attention output for kMergeHeads heads (only launched when some layer left partials to merge).
 __global__ __launch_bounds__(kSelThreads) void evict_plan_table_kernel(PlanTable table) {
     __shared__ SelShared sm;
     // read once, ahead of every store of this kernel: uniform address, so the fields arrive in scalar registers
-    const EvictArgs a = *table.layer[blockIdx.y];
+    const StepLayer e = *table.layer[blockIdx.y];
     if (blockIdx.z == 0) {
+        const EvictArgs a = plan_from_entry(table.c, e);
         evict_plan_body(a, blockIdx.x, sm);
-    } else if (a.merge_out != nullptr && a.pending != nullptr) {
+    } else if (e.nsplit > 1) {
         const int h0 = ((int)blockIdx.z - 1) * kMergeHeads;
-        if (h0 < a.H) merge_chunks(a, blockIdx.x, h0, h0 + kMergeHeads);
+        if (h0 < table.c.H) merge_chunks(table.c, e, blockIdx.x, h0, h0 + kMergeHeads);
     }
 }
 
-void launch_evict_plan_table(const EvictArgs* const* stashed, const EvictArgs* plans, int n, int B, hipStream_t st) {
+void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry, int n, bool merge, hipStream_t st) {
     for (int i0 = 0; i0 < n; i0 += kPlanTableMax) {
         const int cnt = n - i0 < kPlanTableMax ? n - i0 : kPlanTableMax;
         PlanTable table;
-        int merge_heads = 0;
-        for (int i = 0; i < cnt; ++i) {
-            table.layer[i] = stashed[i0 + i];
-            if (plans[i0 + i].merge_out != nullptr && plans[i0 + i].H > merge_heads) merge_heads = plans[i0 + i].H;
-        }
+        table.c = c; table.c.layers = cnt;
+        for (int i = 0; i < cnt; ++i) table.layer[i] = entry[i0 + i];
         for (int i = cnt; i < kPlanTableMax; ++i) table.layer[i] = nullptr;
-        const int merge_wgs = (merge_heads + kMergeHeads - 1) / kMergeHeads;
-        evict_plan_table_kernel<<<dim3(B, cnt, 1 + merge_wgs), kSelThreads, 0, st>>>(table);
+        const int merge_wgs = merge ? (c.H + kMergeHeads - 1) / kMergeHeads : 0;
+        evict_plan_table_kernel<<<dim3(c.B, cnt, 1 + merge_wgs), kSelThreads, 0, st>>>(table);
     }
 }
 

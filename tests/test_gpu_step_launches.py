@@ -1,0 +1,126 @@
+"""The whole-step call serves many layers per launch: it must do what the same layers do one call at a time
+(st3_decode_layer_attend for each, then st3_decode_plans), at the edges of what a launch holds and of the rules that
+choose chunks and stores, and fall back to one launch per layer where layers share rows."""
+import pytest
+import torch
+
+from paper_2412_20105_amd import binding as st3
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+MODE = st3.ST3_HOLE_FILL
+
+
+class Step:
+    """One step's buffers; two objects of equal arguments hold equal values."""
+
+    def __init__(self, L, B, H, d, dtype, vis, tail, lazy=None, fixed_tail=True, e4m3=False, drop=2):
+        g = torch.Generator(device=DEV).manual_seed(L * 1009 + B * 31 + H)
+        rnd = lambda *s: torch.randn(s, generator=g, device=DEV)  # noqa: E731
+        self.shape = st3.make_shape(B, H, d, st3.ST3_F32 if dtype == torch.float32 else st3.ST3_BF16)
+        self.L, self.lazy = L, dict(lazy or {})
+        self.out = torch.zeros((L, B, H, d), dtype=dtype, device=DEV)
+        self.qkv = rnd(L, 3, B, H, d).to(dtype)
+        self.arr = (st3.LayerStep * L)()
+        self.state, self.refs = [], []
+        one = B * H * d * self.out.element_size()
+        for l in range(L):
+            src = self.lazy.get(l)
+            n = vis[l % len(vis)] if src is None else self.state[src]["n"]
+            rows = 3 + n + tail
+            cap = rows + 5 + l % 3
+            scale = torch.full((B, H), 0.01, dtype=torch.float32, device=DEV) if e4m3 else None
+
+            def cache():
+                x = rnd(B, H, cap, d)
+                return (x * 50).to(torch.float8_e4m3fn).view(torch.uint8) if e4m3 else x.to(dtype)
+
+            k, v = None if src is not None else cache(), cache()
+            s = {"n": n, "k": k, "v": v, "kv_len": torch.full((B,), rows, dtype=torch.int32, device=DEV),
+                 "vis_len": torch.full((B,), n, dtype=torch.int32, device=DEV),
+                 "tail": torch.full((B,), 3 + n, dtype=torch.int32, device=DEV) if fixed_tail else None,
+                 "mass": torch.zeros((B, max(n, 1)), dtype=torch.float32, device=DEV)}
+            if src is None:
+                s["score"] = torch.rand((B, max(n, 1)), generator=g, device=DEV)
+                s["ids"] = torch.rand((B, max(n, 1)), generator=g, device=DEV).argsort(dim=1).to(torch.int32)
+            else:
+                s["score"], s["ids"] = self.state[src]["score"].clone(), self.state[src]["ids"].clone()
+            s["ws"] = torch.empty((st3.st3_workspace_bytes(self.shape, cap, n, 1),), dtype=torch.uint8, device=DEV)
+            st3.st3_workspace_init(self.shape, cap, s["ws"])
+            kv = st3.kv_layer(k, v, None if k is None else scale, scale)
+            seg = st3.segments(3, n, rows, s["vis_len"], s["kv_len"], s["tail"], n, 3 + n if fixed_tail else 0)
+            self.refs += [kv, seg, scale]
+            e = self.arr[l]
+            e.kv, e.seg = kv, seg
+            e.score_col, e.id_col, e.col_stride = s["score"].data_ptr(), s["ids"].data_ptr(), s["score"].stride(0)
+            e.keep_after = n - drop if n > drop else -1
+            e.inherit_from = -1 if src is None else src
+            e.q, e.k_new, e.v_new = (self.qkv.data_ptr() + (3 * l + i) * one for i in range(3))
+            e.out, e.vis_mass, e.mass_stride = self.out[l].data_ptr(), s["mass"].data_ptr(), s["mass"].stride(0)
+            e.workspace, e.workspace_bytes = s["ws"].data_ptr(), s["ws"].numel()
+            self.state.append(s)
+
+    def whole(self):
+        st3.st3_decode_step(self.shape, self.arr, self.L, MODE)
+        torch.cuda.synchronize()
+        return self
+
+    def layer_by_layer(self):
+        for l in range(self.L):
+            st3.st3_decode_layer_attend(self.shape, self.arr, self.L, l, MODE)
+        st3.st3_decode_plans(self.shape, self.arr, self.L, MODE)
+        torch.cuda.synchronize()
+        return self
+
+
+def _same(a, b):
+    # Both add the same float32 products, cut into other chunks: an output differs by a few roundings of a sum whose
+    # terms are at most max|v| <= 6 in all (weights add to 1), i.e. 1e-5; a bf16 output then by one step (2^-8) more.
+    x, y = a.out.double(), b.out.double()
+    step = 2.0 ** -8 if a.out.dtype == torch.bfloat16 else 0.0
+    assert bool(((x - y).abs() <= 1e-5 + step * y.abs()).all()), float((x - y).abs().max())
+    for l, (s, t) in enumerate(zip(a.state, b.state)):
+        # masses: probabilities, relative error of a float32 exponent and normaliser
+        assert torch.allclose(s["mass"], t["mass"], rtol=5e-5, atol=1e-9), l
+        for name in ("ids", "score", "kv_len", "vis_len", "k", "v"):
+            if s[name] is not None:
+                assert torch.equal(s[name], t[name]), (l, name)
+
+
+BF, F32 = torch.bfloat16, torch.float32
+
+
+@pytest.mark.parametrize("args", [
+    dict(L=1, B=1, H=1, d=64, dtype=F32, vis=[5], tail=0),
+    dict(L=2, B=3, H=5, d=64, dtype=BF, vis=[0, 300], tail=1),                  # a layer without visual rows
+    dict(L=21, B=1, H=3, d=128, dtype=BF, vis=[130, 65, 64], tail=33),          # one full launch
+    dict(L=22, B=2, H=2, d=128, dtype=BF, vis=[700, 31, 1], tail=7),            # two launches, strips cut unevenly
+    dict(L=65, B=1, H=2, d=64, dtype=F32, vis=[40, 39], tail=2),                # two plan launches
+    dict(L=9, B=16, H=40, d=128, dtype=F32, vis=[20], tail=3),                  # rows written past the caches (8.8 MB)
+    dict(L=24, B=1, H=4, d=128, dtype=BF, vis=[500], tail=40, lazy={5: 4, 6: 4, 7: 4, 23: 22}),     # lazy strips cut too
+    dict(L=4, B=2, H=4, d=128, dtype=BF, vis=[260, 90], tail=40, lazy={1: 0}, fixed_tail=False),
+    dict(L=5, B=2, H=6, d=128, dtype=BF, vis=[200, 33], tail=9, e4m3=True, lazy={3: 2}),
+    dict(L=3, B=2, H=4, d=128, dtype=BF, vis=[300], tail=9, drop=80),           # evictions that a launch of their own moves
+    dict(L=2, B=1, H=2, d=64, dtype=F32, vis=[8190], tail=3000),                # strips longer than the logit staging area
+], ids=lambda a: "-".join(f"{k}{v}" for k, v in a.items() if k in ("L", "B", "H", "d", "drop")))
+def test_whole_step_is_the_layers_one_by_one(args):
+    _same(Step(**args).whole(), Step(**args).layer_by_layer())
+
+
+@pytest.mark.parametrize("field", ["q", "k_new", "v_new"])
+def test_layers_that_read_an_earlier_layers_output(field):
+    """Layer 2's token comes from layer 0's output buffer: in order, it is what layer 0 has just written (B * H = 600: no
+    strip is cut in either form, so layer by layer the output is there)."""
+    args = dict(L=3, B=20, H=30, d=64, dtype=BF, vis=[40], tail=5)
+    a, b = Step(**args), Step(**args)
+    for s in (a, b):
+        setattr(s.arr[2], field, s.out[0].data_ptr())
+    _same(a.whole(), b.layer_by_layer())
+
+
+def test_layers_that_share_an_output_buffer():
+    args = dict(L=3, B=20, H=30, d=64, dtype=BF, vis=[40], tail=5)
+    a, b = Step(**args), Step(**args)
+    for s in (a, b):
+        s.arr[2].out = s.arr[0].out
+    _same(a.whole(), b.layer_by_layer())
