@@ -327,7 +327,9 @@ extern "C" st3_status st3_decode_step(const st3_attn_shape* shape, int32_t n_lay
         bool split = false;
         s = enqueue_step_attend(shape, n_layers, layers, mode, has_heirs.data(), plan.data(), common, entry.data(), split, st);
         if (s == ST3_OK) {
-            launch_evict_plan_table(common, entry.data(), n_layers, split, st);
+            int most_vis = 0;
+            for (const EvictArgs& p : plan) most_vis = p.max_vis > most_vis ? p.max_vis : most_vis;
+            launch_evict_plan_table(common, entry.data(), n_layers, most_vis, split, st);
             enqueue_applies(plan, needs_apply, shape->batch, st);
             return check_launch();
         }

@@ -159,39 +159,136 @@ __device__ __forceinline__ EvictArgs plan_from_entry(const StepCommon& c, const 
     return a;
 }
 
-__device__ __forceinline__ bool flag_at(const SelShared& sm, int p) { return (sm.flags[p >> 5] >> (p & 31)) & 1u; }
-
 typedef uint32_t u32x4_v __attribute__((ext_vector_type(4)));
 
-// Address of 16-byte vector `idx` of a batch of row moves: idx enumerates (move, strip, vector).
-__device__ __forceinline__ char* move_addr(const EvictArgs& a, int b, const int32_t* mv, int first, int idx, int which) {
-    const int strips = (a.k ? 2 : 1) * a.H;             // K may be absent (layers that keep V only)
-    const int per_move = strips * a.vecs_per_row;
-    const int i = first + idx / per_move;
-    const int rem = idx % per_move;
-    const int strip = rem / a.vecs_per_row, vec = rem % a.vecs_per_row;
-    char* base = ((a.k && strip < a.H) ? a.k : a.v) + b * a.stride_b + (int64_t)(strip % a.H) * a.stride_h +
-                 (int64_t)vec * 16;
-    return base + mv[2 * i + which] * a.stride_t;
+// ---------------------------------------------------------------------------------------------
+// The plan workgroup.  Latency bound: a chain of dependent steps over a few kilobytes per (layer, sequence), and at small
+// batches there are fewer plans than compute units, so it takes as many threads as a workgroup may have.  Its parts before
+// -> after the 256-thread form, which kept eight head-strided loads in flight, ran six barriers per radix digit and went
+// through a move list in global memory (us a launch: high resolution batch 8 77 -> 30, 13B batch 8 with fast annealing 66 ->
+// 33, 7B batch 1 21 -> 13):
+//   mass      heads are dealt to thread groups, 12 loads in flight per thread
+//   select    two barriers per digit (one wave scans the histogram), and no further digit once the k-th key is apart
+//   lists     ranks from ballots, the list of a small eviction in LDS
+//   rows      moved past the caches: lines left dirty in L2 are written back between the reads of the next attention
+//             (whole step, ordinary -> non-temporal: 13B batch 8 with fast annealing 541 -> 506 us, 7B batch 16 layer by layer
+//             733 -> 704)
+// ---------------------------------------------------------------------------------------------
+constexpr int kPlanThreadsFew = 1024;       // one plan per compute unit at a time
+constexpr int kPlanThreadsMany = 512;       // three
+// Half the threads when the plans are several per compute unit, or so small that starting and stopping the waves is what
+// takes time.  Whole step, us, 1024 -> 512 threads: 32 plans (7B batch 1) 60 -> 62, 256 (high resolution) 648 -> 653, 320 (13B
+// batch 8) 506 -> 524, 640 (batch 16) 1248 -> 1244, 1280 (batch 32) 2423 -> 2410; 2 plans over 64 rows 16.8 -> 15.0.
+inline int plan_threads(int64_t plans, int most_vis) {
+    return plans > 512 || most_vis <= 128 ? kPlanThreadsMany : kPlanThreadsFew;
+}
+constexpr int kPlanMaxInline = 64;          // moves of an eviction that the plan workgroup applies itself (at most 48 evicted rows)
+
+struct PlanShared {
+    uint32_t keys[kSelLdsKeys];
+    int hist[4][256];
+    float hm[1024], hrl[1024];
+    int wave_tot[2][kPlanThreadsFew / kWave];
+    int mv[kPlanMaxInline][2];
+    int sel_bin, sel_want, sel_cnt, red;
+};
+
+// Ranks of two flags over the workgroup in thread order: r1 / r2 = how many threads before this one have the flag,
+// t1 / t2 = how many in all.  One barrier; calls in a row alternate `parity`.
+template <int NT>
+__device__ __forceinline__ void plan_ranks(bool f1, bool f2, int parity, PlanShared& sm, int& r1, int& r2, int& t1, int& t2) {
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const unsigned long long b1 = __ballot(f1), b2 = __ballot(f2), below = (1ull << lane) - 1;
+    if (lane == 0) sm.wave_tot[parity][wave] = __popcll(b1) | (__popcll(b2) << 16);
+    __syncthreads();
+    int base = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < NT / kWave; ++w) {
+        const int v = sm.wave_tot[parity][w];
+        base += w < wave ? v : 0;
+        tot += v;
+    }
+    r1 = (base & 0xffff) + __popcll(b1 & below);
+    r2 = (base >> 16) + __popcll(b2 & below);
+    t1 = tot & 0xffff; t2 = tot >> 16;
 }
 
-// Copies `count` rows (dst_i <- src_i, from the move list starting at entry `first`) on all
-// strips of sequence b.  Callers guarantee that no destination of the batch is a source of it.
-__device__ __forceinline__ void copy_rows_all_strips(const EvictArgs& a, int b, const int32_t* mv, int first, int count) {
-    constexpr int UR = 16;                              // independent 16-byte loads in flight per thread
-    const int total = count * (a.k ? 2 : 1) * a.H * a.vecs_per_row;
-    for (int base = 0; base < total; base += UR * kSelThreads) {
-        u32x4_v tmp[UR];
+// Finds the key of rank `want` (1-based, descending) among the elements for which f(i, key) is true, 8 bits at a time.
+// Returns its leading digits, zeros behind them: the search ends as soon as exactly the wanted elements share them.
+// `want` becomes how many of the elements equal to the returned digits belong to the top set, `ties` how many there are.
+// Ends with a barrier behind every use of sm.hist.
+template <int NT, class F>
+__device__ __forceinline__ uint32_t plan_select(F f, int n, int& want, int& ties, PlanShared& sm) {
+    const int tid = threadIdx.x;
+    for (int i = tid; i < 4 * 256; i += NT) (&sm.hist[0][0])[i] = 0;
+    __syncthreads();
+    uint32_t prefix = 0, pmask = 0;
+    for (int r = 0; r < 4; ++r) {
+        const int shift = 24 - 8 * r;
+        for (int i = tid; i < n; i += NT) {
+            uint32_t key;
+            if (f(i, key) && (key & pmask) == prefix) atomicAdd(&sm.hist[r][(key >> shift) & 255u], 1);
+        }
+        __syncthreads();
+        if (tid < kWave) {                              // lane l: bins 255 - 4 l ... 252 - 4 l
+            const int4 c = *reinterpret_cast<const int4*>(&sm.hist[r][252 - 4 * tid]);
+            const int sum = c.x + c.y + c.z + c.w;
+            int incl = sum;
 #pragma unroll
-        for (int u = 0; u < UR; ++u) {
-            const int idx = base + u * kSelThreads + (int)threadIdx.x;
-            if (idx < total) tmp[u] = *reinterpret_cast<const u32x4_v*>(move_addr(a, b, mv, first, idx, 1));
+            for (int off = 1; off < kWave; off <<= 1) {
+                const int t = __shfl_up(incl, off);
+                if (tid >= off) incl += t;
+            }
+            int before = incl - sum;
+            if (incl >= want && before < want) {
+                int bin = 255 - 4 * tid, cnt = c.w;
+                if (want > before + cnt) { before += cnt; cnt = c.z; --bin; }
+                if (want > before + cnt) { before += cnt; cnt = c.y; --bin; }
+                if (want > before + cnt) { before += cnt; cnt = c.x; --bin; }
+                sm.sel_bin = bin; sm.sel_want = want - before; sm.sel_cnt = cnt;
+            }
+        }
+        __syncthreads();
+        prefix |= (uint32_t)sm.sel_bin << shift;
+        pmask |= 255u << shift;
+        want = sm.sel_want;
+        ties = sm.sel_cnt;
+        if (want == ties) break;                        // uniform: sel_* are the workgroup's
+    }
+    __syncthreads();
+    return prefix;
+}
+
+// Copies rows dst(i) <- src(i), i < count, on all strips of sequence b.  Callers guarantee that no destination of the batch
+// is a source of it.  A wave moves one row of as many strips as 64 lanes of 16 bytes cover, kUR such pieces in flight.
+template <int NT, class Dst, class Src>
+__device__ __forceinline__ void copy_rows_all_strips(const EvictArgs& a, int b, int count, Dst dst, Src src) {
+    constexpr int kUR = 8;
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int strips = (a.k ? 2 : 1) * a.H;             // K may be absent (layers that keep V only)
+    const int vpr = a.vecs_per_row, spw = kWave / vpr;  // 4 ... 32, a power of two
+    const int groups = (strips + spw - 1) / spw;        // pieces per row
+    const int total = count * groups;
+    for (int q0 = wave; q0 < total; q0 += kUR * (NT / kWave)) {
+        u32x4_v tmp[kUR];
+        char* to[kUR];
+#pragma unroll
+        for (int u = 0; u < kUR; ++u) {
+            const int q = q0 + u * (NT / kWave);
+            to[u] = nullptr;
+            if (q >= total) continue;
+            const int i = q / groups;
+            const int strip = (q - i * groups) * spw + lane / vpr;
+            if (strip >= strips) continue;
+            const bool in_k = a.k && strip < a.H;
+            char* base = (in_k ? a.k : a.v) + b * a.stride_b + (int64_t)(strip >= a.H ? strip - a.H : strip) * a.stride_h +
+                         (lane % vpr) * 16;
+            tmp[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_v*>(base + src(i) * a.stride_t));
+            to[u] = base + dst(i) * a.stride_t;
         }
 #pragma unroll
-        for (int u = 0; u < UR; ++u) {
-            const int idx = base + u * kSelThreads + (int)threadIdx.x;
-            if (idx < total) *reinterpret_cast<u32x4_v*>(move_addr(a, b, mv, first, idx, 0)) = tmp[u];
-        }
+        for (int u = 0; u < kUR; ++u)
+            if (to[u] != nullptr) __builtin_nontemporal_store(tmp[u], reinterpret_cast<u32x4_v*>(to[u]));
     }
 }
 
@@ -235,29 +332,83 @@ __device__ __forceinline__ void merge_chunks(const StepCommon& c, const StepLaye
     }
 }
 
-// The whole per-sequence plan, run by one workgroup of kSelThreads threads for sequence b:
-//   1. finish the visual mass the attention kernel left pending (head reduction in head order),
+// The visual mass that the attention launch left pending: mass_row[j] = (1/H) sum_h exp2(logit[h][j] - m_h) / l_h for
+// j < n.  Heads are dealt to NT / keys groups of threads whose sums are added in group order: the result does not depend
+// on scheduling.  The row maxima and sums come from ns (max, sum) pairs per head, 1 << log_ns lanes per head.
+template <int NT>
+__device__ __forceinline__ void plan_mass(const EvictArgs& a, int b, int n, int ns, PlanShared& sm) {
+    const int tid = threadIdx.x, H = a.H;
+    int nsp = 1;
+    while (nsp < ns) nsp *= 2;                          // at most 64: a group lies in one wave
+    for (int base = 0; base < H * nsp; base += NT) {
+        const int x = base + tid, h = x / nsp, c = x & (nsp - 1);
+        float m = -INFINITY, l = 0.f;
+        if (h < H && c < ns) {
+            const float2 ml = *reinterpret_cast<const float2*>(a.part_ml + (((int64_t)b * H + h) * a.nsplit_cap + c) * 2);
+            m = ml.x; l = ml.y;
+        }
+        const float own = m;
+        for (int off = 1; off < nsp; off <<= 1) m = fmaxf(m, __shfl_xor(m, off));
+        l = c < ns ? l * exp2_fast(own - m) : 0.f;
+        for (int off = 1; off < nsp; off <<= 1) l += __shfl_xor(l, off);
+        if (h < H && c == 0) { sm.hm[h] = m; sm.hrl[h] = 1.0f / l; }
+    }
+    __syncthreads();
+    constexpr int kUH = 12;                             // loads in flight per thread
+    const int keys = n <= 256 ? 256 : n <= 512 ? 512 : NT;
+    const int groups = NT / keys, per = (H + groups - 1) / groups;
+    const int g = __builtin_amdgcn_readfirstlane(tid / keys);     // (a wave lies in one group)
+    const int h0 = g * per, h1 = min(H, h0 + per);
+    const float* lg = a.logits + a.sys_len + (int64_t)b * H * a.capacity;
+    float* row = a.mass_dst + b * a.mass_stride;
+    float* part = reinterpret_cast<float*>(sm.keys);    // (the keys are staged later)
+    for (int j = tid & (keys - 1); j < n; j += keys) {  // (one round unless n > NT, and then there is one group)
+        float acc = 0.f;
+        for (int h = h0; h < h1; h += kUH) {
+            float v[kUH];
+#pragma unroll
+            for (int u = 0; u < kUH; ++u) v[u] = lg[(int64_t)min(h + u, h1 - 1) * a.capacity + j];
+#pragma unroll
+            for (int u = 0; u < kUH; ++u) {
+                const int hh = min(h + u, h1 - 1);
+                const float p = exp2_fast(v[u] - sm.hm[hh]) * sm.hrl[hh];
+                acc += h + u < h1 ? p : 0.f;
+            }
+        }
+        if (groups == 1) row[j] = acc * (1.0f / (float)H);
+        else part[tid] = acc;
+    }
+    __syncthreads();                                    // the ranking may read these scores, or reuse sm.keys
+    if (groups > 1) {
+        if (tid < n && tid < keys) {
+            float acc = part[tid];
+            for (int i = 1; i < groups; ++i) acc += part[i * keys + tid];
+            row[tid] = acc * (1.0f / (float)H);
+        }
+        __syncthreads();
+    }
+}
+
+// The whole per-sequence plan, run by one workgroup of NT threads for sequence b:
+//   1. finish the visual mass the attention kernel left pending,
 //   2. rank the visual rows by score_col and evict down to keep_count (columns, and - when
 //      inline_apply - the K/V rows themselves),
 //   3. publish the new lengths (including the row the attention kernel appended).
-__device__ __forceinline__ void evict_plan_body(const EvictArgs& a, int b, SelShared& sm) {
+template <int NT>
+__device__ __forceinline__ void evict_plan_body(const EvictArgs& a, int b, PlanShared& sm) {
     const int tid = threadIdx.x;
     const int n = max(0, min(a.vis_len[b], a.max_vis));
     const int len = max(0, min(a.kv_len[b] + (a.appended ? 1 : 0), a.max_kv + (a.appended ? 1 : 0)));
     const int k = a.keep_count < 0 ? n : min(a.keep_count, n);
     int new_len = len, moves_left = 0;
     if (a.pending != nullptr && a.mass_dst != nullptr) {
-        // finish the mass the attention call left pending: `len` and `n` are the lengths it saw
-        __shared__ float sm_hm[1024], sm_hrl[1024];
-        const int valid = a.pending[b * 4] & 1;
-        if (valid) {
-            const int nsplit = min(a.pending[b * 4 + 1], a.nsplit_cap);
-            const int chunk = max(a.pending[b * 4 + 2], 32);
+        // `len` and `n` are the lengths the attention call saw
+        const int4 d = *reinterpret_cast<const int4*>(a.pending + b * 4);
+        if (d.x & 1) {
+            const int chunk = max(d.z, 32);
             const int seen = seq_layout(a.sys_len, n, a.max_vis, len, a.tail_start, b).vlen;    // rows the attend launch saw
-            const int ns = seen > 0 ? min((seen + chunk - 1) / chunk, nsplit) : 0;
-            head_norms(a.part_ml, b, a.H, ns, a.nsplit_cap, sm_hm, sm_hrl);
-            finish_mass(a.logits + a.sys_len, b, a.H, a.capacity, sm_hm, sm_hrl, 0, n, a.mass_dst + b * a.mass_stride);
-            __syncthreads();                            // the ranking below may read these scores
+            const int ns = seen > 0 ? min((seen + chunk - 1) / chunk, min(d.y, a.nsplit_cap)) : 0;
+            if (ns > 0) plan_mass<NT>(a, b, n, ns, sm);
         }
     }
     if (k < n && a.sys_len + n <= len) {                // something to evict, lengths consistent
@@ -266,45 +417,53 @@ __device__ __forceinline__ void evict_plan_body(const EvictArgs& a, int b, SelSh
         int32_t* mv = a.moves + (int64_t)b * a.max_moves * 2;
         uint32_t thr = 0, thr_id = 0;
         bool all_ties = true;
-        if (k > 0) mark_topk(scores, ids, n, k, true, sm, thr, thr_id, all_ties);
-        // flags -> LDS bitmap (one 32-bit word per 32 positions, built from wave ballots)
-        const int n_pad = (n + kSelThreads - 1) / kSelThreads * kSelThreads;
-        for (int p0 = 0; p0 < n_pad; p0 += kSelThreads) {
-            const int p = p0 + tid;
-            bool keep = false;
-            if (p < n && k > 0) keep = is_kept(sm.keys[p], ~(uint32_t)ids[p], thr, thr_id, all_ties);
-            unsigned long long bal = __ballot(keep);
-            if (tid % kWave == 0) {
-                sm.flags[(p >> 5)] = (uint32_t)bal;
-                sm.flags[(p >> 5) + 1] = (uint32_t)(bal >> 32);
+        if (k > 0) {
+            for (int i = tid; i < n; i += NT) sm.keys[i] = score_key(scores[i]);      // (read back behind a barrier)
+            int want = k, ties = 0;
+            thr = plan_select<NT>([&](int i, uint32_t& key) { key = sm.keys[i]; return true; }, n, want, ties, sm);
+            all_ties = want == ties;
+            if (!all_ties) {                            // the k-th score is shared: the lowest ids of its holders
+                int want2 = want, ties2 = 0;
+                thr_id = plan_select<NT>([&](int i, uint32_t& key) { key = ~(uint32_t)ids[i]; return sm.keys[i] == thr; }, n, want2,
+                                     ties2, sm);
             }
         }
-        __syncthreads();
+        auto kept_at = [&](int p) -> bool {
+            if (p >= n || k == 0) return false;
+            const uint32_t key = sm.keys[p];
+            return key > thr || (key == thr && (all_ties || ~(uint32_t)ids[p] >= thr_id));
+        };
+        // all_ties: thr may be the leading digits of the kept keys only; every key with larger or the same digits is kept
+        const int n_pad = (n + NT - 1) / NT * NT;
         const int g = n - k;                            // rows evicted
         // rows behind the visual segment that have to close up; none when the tail keeps its place
         const int r = a.tail_start ? 0 : len - (a.sys_len + n);
-        int m = 0;                                      // moves inside the visual segment
+        int parity = 0, r1, r2, t1, t2;
         if (a.mode == ST3_HOLE_FILL) {
+            const bool inl = a.inline_apply && g <= kPlanMaxInline;
             int base_h = 0, base_f = 0;
-            for (int p0 = 0; p0 < n_pad; p0 += kSelThreads) {
+            for (int p0 = 0; p0 < n_pad; p0 += NT, parity ^= 1) {
                 const int p = p0 + tid;
-                const bool kept = p < n && flag_at(sm, p);
+                const bool kept = kept_at(p);
                 const bool hole = p < k && !kept;
                 const bool fill = p >= k && kept;
-                int packed = (hole ? 1 : 0) | (fill ? (1 << 16) : 0);
-                int incl = block_incl_scan(packed, sm);
-                if (hole) mv[2 * (base_h + (incl & 0xffff) - 1)] = a.sys_len + p;
-                if (fill) mv[2 * (base_f + (incl >> 16) - 1) + 1] = a.sys_len + p;
-                __syncthreads();
-                if (tid == kSelThreads - 1) sm.red = incl;
-                __syncthreads();
-                base_h += sm.red & 0xffff;
-                base_f += sm.red >> 16;
+                plan_ranks<NT>(hole, fill, parity, sm, r1, r2, t1, t2);
+                if (inl) {                              // (ids that repeat could keep more rows than the list holds)
+                    if (hole && base_h + r1 < kPlanMaxInline) sm.mv[base_h + r1][0] = a.sys_len + p;
+                    if (fill && base_f + r2 < kPlanMaxInline) sm.mv[base_f + r2][1] = a.sys_len + p;
+                } else {
+                    if (hole) mv[2 * (base_h + r1)] = a.sys_len + p;
+                    if (fill) mv[2 * (base_f + r2) + 1] = a.sys_len + p;
+                }
+                base_h += t1; base_f += t2;
             }
-            m = min(base_h, base_f);                    // equal when the ids are distinct
+            const int m = min(min(base_h, base_f), inl ? kPlanMaxInline : n);      // all equal when the ids are distinct
             __syncthreads();                            // move list visible to the whole block
-            for (int i = tid; i < m; i += kSelThreads) {    // sources >= k, destinations < k: disjoint
-                int dst = mv[2 * i] - a.sys_len, src = mv[2 * i + 1] - a.sys_len;
+            for (int i = tid; i < m; i += NT) {   // sources >= k, destinations < k: disjoint
+                int dst, src;
+                if (inl) { dst = sm.mv[i][0]; src = sm.mv[i][1]; }
+                else { dst = mv[2 * i]; src = mv[2 * i + 1]; }
+                dst -= a.sys_len; src -= a.sys_len;
                 scores[dst] = scores[src];
                 ids[dst] = ids[src];
             }
@@ -313,49 +472,45 @@ __device__ __forceinline__ void evict_plan_body(const EvictArgs& a, int b, SelSh
             // and destinations are disjoint: r >= g -> src >= len-g >= sys+n; r < g -> dst < sys+k+r < sys+n.
             const int cnt = min(g, r);
             const int src0 = (r >= g) ? len - g : a.sys_len + n;
-            for (int j = tid; j < cnt; j += kSelThreads) {
-                mv[2 * (m + j)] = a.sys_len + k + j;
-                mv[2 * (m + j) + 1] = src0 + j;
-            }
-            moves_left = m + cnt;
-            if (a.inline_apply) {
-                __syncthreads();
-                copy_rows_all_strips(a, b, mv, 0, m);       // holes <- surviving tail of the segment
-                __syncthreads();                            // those reads are done before [k, n) is overwritten
-                copy_rows_all_strips(a, b, mv, m, cnt);
-                moves_left = 0;
+            if (inl) {
+                copy_rows_all_strips<NT>(a, b, m, [&](int i) { return (int64_t)sm.mv[i][0]; }, [&](int i) { return (int64_t)sm.mv[i][1]; });
+                if (cnt > 0) {
+                    __syncthreads();                    // those reads are done before [k, n) is overwritten
+                    copy_rows_all_strips<NT>(a, b, cnt, [&](int i) { return (int64_t)(a.sys_len + k + i); },
+                                         [&](int i) { return (int64_t)(src0 + i); });
+                }
+            } else {
+                for (int j = tid; j < cnt; j += NT) {
+                    mv[2 * (m + j)] = a.sys_len + k + j;
+                    mv[2 * (m + j) + 1] = src0 + j;
+                }
+                moves_left = m + cnt;
             }
         } else {
             // first hole = number of leading kept positions
-            int fh = n;
-            for (int p = tid; p < n; p += kSelThreads)
-                if (!flag_at(sm, p)) { fh = p; break; }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) fh = min(fh, __shfl_xor(fh, off));
-            if (tid % kWave == 0) sm.wave_tot[tid / kWave] = fh;
+            if (tid == 0) sm.red = n;
             __syncthreads();
-            fh = min(min(sm.wave_tot[0], sm.wave_tot[1]), min(sm.wave_tot[2], sm.wave_tot[3]));
+            for (int p = tid; p < n; p += NT)
+                if (!kept_at(p)) { atomicMin(&sm.red, p); break; }
             __syncthreads();
+            const int fh = sm.red;
             int base = 0;
-            for (int p0 = 0; p0 < n_pad; p0 += kSelThreads) {
+            for (int p0 = 0; p0 < n_pad; p0 += NT, parity ^= 1) {
                 const int p = p0 + tid;
-                const bool kept = p < n && flag_at(sm, p);
+                const bool kept = kept_at(p);
                 float sv = 0.f; int32_t iv = 0;
                 if (kept) { sv = scores[p]; iv = ids[p]; }
-                int incl = block_incl_scan(kept ? 1 : 0, sm);       // contains barriers: loads precede stores
-                const int rank = base + incl - 1;
+                plan_ranks<NT>(kept, false, parity, sm, r1, r2, t1, t2);    // contains a barrier: loads precede stores
+                const int rank = base + r1;
                 if (kept && p > fh) {
                     scores[rank] = sv; ids[rank] = iv;
                     mv[2 * (rank - fh)] = a.sys_len + rank;
                     mv[2 * (rank - fh) + 1] = a.sys_len + p;
                 }
-                __syncthreads();
-                if (tid == kSelThreads - 1) sm.red = incl;
-                __syncthreads();
-                base += sm.red;
+                base += t1;
             }
-            m = k - fh;
-            for (int j = tid; j < r; j += kSelThreads) {
+            const int m = k - fh;
+            for (int j = tid; j < r; j += NT) {
                 mv[2 * (m + j)] = a.sys_len + k + j;
                 mv[2 * (m + j) + 1] = a.sys_len + n + j;
             }
@@ -389,7 +544,8 @@ void launch_evict_plan_batch(const EvictArgs* plans, int n, int B, hipStream_t s
 // The plans of n layers from the table entries that whole-step attention launches have left in the layers' workspaces;
 // merge: some strips were cut into chunks, whose partials are merged here too.  One launch per kPlanTableMax layers.
 constexpr int kPlanTableMax = 64;
-void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry, int n, bool merge, hipStream_t st);
+// most_vis: the largest bound of any layer's visual rows.
+void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry, int n, int most_vis, bool merge, hipStream_t st);
 void launch_evict_apply(const EvictArgs& ea, int B, hipStream_t st);
 
 }  // namespace st3

@@ -6,6 +6,8 @@
 // (4 passes of 8 bits, histogram in LDS), followed - only when the k-th score is shared - by a
 // second radix select on the tie ids, so that the result is the unique top-k set under the total
 // order (score descending, id ascending).  One workgroup per sequence.
+#include <algorithm>
+
 #include "st3_evict.h"
 
 namespace st3 {
@@ -132,9 +134,9 @@ __global__ __launch_bounds__(256) void compact_rows_kernel(CompactArgs a) {
 // Decode-time eviction: ranking + move list + column update (one workgroup per sequence), then
 // a second kernel that applies the move list to every (b,h) strip of K and V.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kSelThreads) void evict_plan_kernel(EvictArgs a) {
-    __shared__ SelShared sm;
-    evict_plan_body(a, blockIdx.x, sm);
+__global__ __launch_bounds__(kPlanThreadsFew) void evict_plan_kernel(EvictArgs a) {
+    __shared__ PlanShared sm;
+    evict_plan_body<kPlanThreadsFew>(a, blockIdx.x, sm);
 }
 
 // ---- st3_gather_rows: out-of-place gather of kept rows, several tensors per launch -------------
@@ -306,7 +308,7 @@ st3_status build_evict_args(const st3_attn_shape* shape, const st3_kv_layer* kv,
 }
 
 void launch_evict_plan(const EvictArgs& ea, int B, hipStream_t st) {
-    evict_plan_kernel<<<B, kSelThreads, 0, st>>>(ea);
+    evict_plan_kernel<<<B, kPlanThreadsFew, 0, st>>>(ea);
 }
 
 // Up to kPlanBatch plans travel by value in the kernel arguments; grid (B, layers of the batch).
@@ -316,18 +318,26 @@ struct EvictBatch {
 static_assert(sizeof(EvictBatch) <= 4000, "plans of one batch must fit the kernel argument segment");
 
 // grid (B, layers of the batch)
-__global__ __launch_bounds__(kSelThreads) void evict_plan_batch_kernel(EvictBatch batch) {
-    __shared__ SelShared sm;
-    evict_plan_body(batch.layer[blockIdx.y], blockIdx.x, sm);
+template <int NT>
+__global__ __launch_bounds__(NT) void evict_plan_batch_kernel(EvictBatch batch) {
+    __shared__ PlanShared sm;
+    evict_plan_body<NT>(batch.layer[blockIdx.y], blockIdx.x, sm);
 }
 
 void launch_evict_plan_batch(const EvictArgs* plans, int n, int B, hipStream_t st) {
     for (int i0 = 0; i0 < n; i0 += kPlanBatch) {
         const int cnt = n - i0 < kPlanBatch ? n - i0 : kPlanBatch;
         EvictBatch batch;
-        for (int i = 0; i < cnt; ++i) batch.layer[i] = plans[i0 + i];
+        int most_vis = 0;
+        for (int i = 0; i < cnt; ++i) {
+            batch.layer[i] = plans[i0 + i];
+            most_vis = std::max(most_vis, plans[i0 + i].max_vis);
+        }
         for (int i = cnt; i < kPlanBatch; ++i) batch.layer[i] = EvictArgs{};
-        evict_plan_batch_kernel<<<dim3(B, cnt), kSelThreads, 0, st>>>(batch);
+        if (plan_threads((int64_t)B * cnt, most_vis) == kPlanThreadsFew)
+            evict_plan_batch_kernel<kPlanThreadsFew><<<dim3(B, cnt), kPlanThreadsFew, 0, st>>>(batch);
+        else
+            evict_plan_batch_kernel<kPlanThreadsMany><<<dim3(B, cnt), kPlanThreadsMany, 0, st>>>(batch);
     }
 }
 
@@ -340,20 +350,21 @@ struct PlanTable {
 
 // grid (B, layers, 1 + merge workgroups): z = 0 runs the plan of (sequence x, layer y); z >= 1 merges the chunk partials
 // of that layer's attention output for kMergeHeads heads (only launched when some layer left partials to merge).
-__global__ __launch_bounds__(kSelThreads) void evict_plan_table_kernel(PlanTable table) {
-    __shared__ SelShared sm;
+template <int NT>
+__global__ __launch_bounds__(NT) void evict_plan_table_kernel(PlanTable table) {
+    __shared__ PlanShared sm;
     // read once, ahead of every store of this kernel: uniform address, so the fields arrive in scalar registers
     const StepLayer e = *table.layer[blockIdx.y];
     if (blockIdx.z == 0) {
         const EvictArgs a = plan_from_entry(table.c, e);
-        evict_plan_body(a, blockIdx.x, sm);
+        evict_plan_body<NT>(a, blockIdx.x, sm);
     } else if (e.nsplit > 1) {
         const int h0 = ((int)blockIdx.z - 1) * kMergeHeads;
         if (h0 < table.c.H) merge_chunks(table.c, e, blockIdx.x, h0, h0 + kMergeHeads);
     }
 }
 
-void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry, int n, bool merge, hipStream_t st) {
+void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry, int n, int most_vis, bool merge, hipStream_t st) {
     for (int i0 = 0; i0 < n; i0 += kPlanTableMax) {
         const int cnt = n - i0 < kPlanTableMax ? n - i0 : kPlanTableMax;
         PlanTable table;
@@ -361,7 +372,11 @@ void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry,
         for (int i = 0; i < cnt; ++i) table.layer[i] = entry[i0 + i];
         for (int i = cnt; i < kPlanTableMax; ++i) table.layer[i] = nullptr;
         const int merge_wgs = merge ? (c.H + kMergeHeads - 1) / kMergeHeads : 0;
-        evict_plan_table_kernel<<<dim3(c.B, cnt, 1 + merge_wgs), kSelThreads, 0, st>>>(table);
+        const dim3 grid(c.B, cnt, 1 + merge_wgs);
+        if (plan_threads((int64_t)c.B * cnt, most_vis) == kPlanThreadsFew)
+            evict_plan_table_kernel<kPlanThreadsFew><<<grid, kPlanThreadsFew, 0, st>>>(table);
+        else
+            evict_plan_table_kernel<kPlanThreadsMany><<<grid, kPlanThreadsMany, 0, st>>>(table);
     }
 }
 

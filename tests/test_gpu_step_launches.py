@@ -124,3 +124,46 @@ def test_layers_that_share_an_output_buffer():
     for s in (a, b):
         s.arr[2].out = s.arr[0].out
     _same(a.whole(), b.layer_by_layer())
+
+
+@pytest.mark.parametrize("L,B,H,n,drop,ties,fixed_tail", [
+    (1, 1, 1, 1, 1, False, True),               # the last visual row goes
+    (2, 2, 5, 128, 3, True, True),              # the smaller workgroup's bound, heads that fill no group
+    (2, 2, 33, 129, 48, False, True),
+    (3, 1, 4, 256, 40, True, False),            # thread groups of the mass: 256, 257, 512, 513, 1024, 1025 rows
+    (3, 1, 3, 257, 2, False, True),
+    (2, 1, 7, 512, 49, False, True),            # one row more than the plan moves by itself
+    (2, 3, 6, 513, 5, True, True),
+    (2, 1, 9, 1024, 30, False, False),
+    (2, 1, 2, 1025, 1024, True, True),
+    (1, 2, 2, 8192, 20, False, True),           # the most rows a plan ranks
+    (8, 65, 2, 40, 7, True, True),              # more plans than 512
+])
+def test_plan_keeps_the_best_rows_and_finishes_the_mass(L, B, H, n, drop, ties, fixed_tail):
+    s = Step(L=L, B=B, H=H, d=64, dtype=F32, vis=[n], tail=6, fixed_tail=fixed_tail, drop=0)
+    k = n - drop
+    before = []
+    for l, st in enumerate(s.state):
+        s.arr[l].keep_after = k
+        if ties:        # a few values only: the k-th score is shared
+            st["score"].copy_((st["score"] * 4).floor() / 4)
+        before.append({x: st[x].clone() for x in ("k", "v", "score", "ids")})
+    s.whole()
+    for l, (st, was) in enumerate(zip(s.state, before)):
+        rows = 3 + n + 6
+        q, kn, _ = s.qkv[l].double()
+        keys = torch.cat([was["k"][:, :, :rows].double(), kn[:, :, None]], dim=2)
+        p = torch.softmax(torch.matmul(keys, q[..., None])[..., 0] / 8.0, dim=-1)
+        # float32 exponent of a logit good to 1e-6, normaliser and a sum over heads (as for every mass)
+        assert torch.allclose(st["mass"].double(), p[:, :, 3:3 + n].mean(dim=1), rtol=5e-5, atol=1e-9), l
+        assert st["vis_len"].tolist() == [k] * B and st["kv_len"].tolist() == [rows + 1 - (0 if fixed_tail else drop)] * B
+        for b in range(B):
+            sc, ids = was["score"][b].tolist(), was["ids"][b].tolist()
+            best = sorted(range(n), key=lambda i: (-sc[i], ids[i]))[:k]
+            got = st["ids"][b, :k].tolist()
+            assert sorted(got) == sorted(ids[i] for i in best), (l, b)
+            at = {ids[i]: i for i in range(n)}
+            src = torch.tensor([at[i] for i in got], dtype=torch.long, device=DEV)
+            assert torch.equal(st["score"][b, :k], was["score"][b][src]), (l, b)
+            for x in ("k", "v"):
+                assert torch.equal(st[x][b, :, 3:3 + k], was[x][b][:, 3 + src]), (l, b, x)
