@@ -9,35 +9,46 @@ namespace st3 {
 
 #if defined(__HIPCC__)
 
-// Row maximum and reciprocal row sum of every head of sequence b, rebuilt from the per-chunk
-// (max, sum) pairs in chunk order, into two LDS arrays of H entries.  Ends with a barrier.
+// Row maximum and reciprocal row sum of every head of sequence b, rebuilt from the per-chunk (max, sum) pairs (ns > 0 of
+// them, at most 64; a power of two of lanes per head), into two LDS arrays of H entries.  Ends with a barrier.
+template <int NT>
 __device__ __forceinline__ void head_norms(const float* part_ml, int b, int H, int ns, int nsplit_cap, float* sm_m,
                                            float* sm_rl) {
-    for (int h = threadIdx.x; h < H; h += blockDim.x) {
-        const float* ml = part_ml + ((int64_t)b * H + h) * nsplit_cap * 2;
+    int nsp = 1;
+    while (nsp < ns) nsp *= 2;                          // a head's lanes lie in one wave
+    for (int base = 0; base < H * nsp; base += NT) {
+        const int x = base + (int)threadIdx.x, h = x / nsp, c = x & (nsp - 1);
         float m = -INFINITY, l = 0.f;
-        if (ns > 0) {
-            m = ml[0];
-            for (int s = 1; s < ns; ++s) m = fmaxf(m, ml[2 * s]);
-            for (int s = 0; s < ns; ++s) l = fmaf(ml[2 * s + 1], exp2_fast(ml[2 * s] - m), l);
+        if (h < H && c < ns) {
+            const float2 ml = *reinterpret_cast<const float2*>(part_ml + (((int64_t)b * H + h) * nsplit_cap + c) * 2);
+            m = ml.x; l = ml.y;
         }
-        sm_m[h] = m;
-        sm_rl[h] = ns > 0 ? 1.0f / l : 0.f;
+        const float own = m;
+        for (int off = 1; off < nsp; off <<= 1) m = fmaxf(m, __shfl_xor(m, off));
+        l = c < ns ? l * exp2_fast(own - m) : 0.f;
+        for (int off = 1; off < nsp; off <<= 1) l += __shfl_xor(l, off);
+        if (h < H && c == 0) { sm_m[h] = m; sm_rl[h] = 1.0f / l; }
     }
     __syncthreads();
 }
 
-// mass_row[j] = (1/H) sum_h exp2(logit[b,h,j] - m_h) / l_h for j in [j0, j1); heads are added in
-// index order so the result does not depend on scheduling.
-__device__ __forceinline__ void finish_mass(const float* logits, int b, int H, int capacity, const float* sm_m,
-                                            const float* sm_rl, int j0, int j1, float* mass_row) {
-    const float* lgb = logits + (int64_t)b * H * capacity;
-    const float inv_h = 1.0f / (float)H;
-    for (int j = j0 + threadIdx.x; j < j1; j += blockDim.x) {
-        float acc = 0.f;
-        for (int h = 0; h < H; ++h) acc += exp2_fast(lgb[(int64_t)h * capacity + j] - sm_m[h]) * sm_rl[h];
-        mass_row[j] = acc * inv_h;
+// sum over rows [r0, r1) of exp2(x[r * stride] - m[r]) * rl[r], in row order, with kUH loads in flight.  r0 and r1 are the
+// same for the lanes of a wave.
+__device__ __forceinline__ float prob_sum(const float* x, int64_t stride, const float* m, const float* rl, int r0, int r1) {
+    constexpr int kUH = 12;
+    float acc = 0.f;
+    for (int r = r0; r < r1; r += kUH) {
+        float v[kUH];
+#pragma unroll
+        for (int u = 0; u < kUH; ++u) v[u] = x[(int64_t)min(r + u, r1 - 1) * stride];
+#pragma unroll
+        for (int u = 0; u < kUH; ++u) {
+            const int rr = min(r + u, r1 - 1);
+            const float p = exp2_fast(v[u] - m[rr]) * rl[rr];
+            acc += r + u < r1 ? p : 0.f;
+        }
     }
+    return acc;
 }
 
 #endif  // __HIPCC__

@@ -485,7 +485,8 @@ struct FinishArgs {
 };
 
 // grid (out_blocks + mass_blocks, B), 256 threads.  Blocks x < H (when out != null) merge the
-// chunk partials of head x; the rest produce 256 mass entries each.
+// chunk partials of head x; the rest produce kFinishKeys mass entries each.
+constexpr int kFinishKeys = kWave;
 template <typename T, int D>
 __global__ __launch_bounds__(256) void decode_finish_kernel(FinishArgs a) {
     const int b = blockIdx.y, tid = threadIdx.x;
@@ -517,12 +518,22 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(FinishArgs a) {
         return;
     }
     if (a.mass == nullptr) return;
-    __shared__ float sm_m[1024], sm_rl[1024];
+    // kFinishKeys mass entries: a wave takes a quarter of the heads, the quarters are added in order
+    __shared__ float sm_m[1024], sm_rl[1024], sm_part[4][kFinishKeys];
     const int nv = lay.nv;
-    head_norms(a.part_ml, b, a.H, ns, a.nsplit_cap, sm_m, sm_rl);
-    const int j0 = ((int)blockIdx.x - out_blocks) * 256;
-    finish_mass(a.logits + a.sys_len, b, a.H, a.capacity, sm_m, sm_rl, j0, min(j0 + 256, nv),
-                a.mass + (int64_t)b * a.mass_stride);
+    const int j = ((int)blockIdx.x - out_blocks) * kFinishKeys + tid % kWave;
+    if (ns == 0) {                                      // an empty sequence: no probabilities
+        if (j < nv && tid < kWave) a.mass[(int64_t)b * a.mass_stride + j] = 0.f;
+        return;
+    }
+    head_norms<256>(a.part_ml, b, a.H, ns, a.nsplit_cap, sm_m, sm_rl);
+    const int g = __builtin_amdgcn_readfirstlane(tid / kWave), per = (a.H + 3) / 4, h0 = g * per, h1 = min(a.H, h0 + per);
+    if (j < nv)
+        sm_part[g][tid % kWave] = prob_sum(a.logits + a.sys_len + (int64_t)b * a.H * a.capacity + j, a.capacity, sm_m, sm_rl, h0, h1);
+    __syncthreads();
+    if (j < nv && tid < kWave)
+        a.mass[(int64_t)b * a.mass_stride + j] = ((sm_part[0][tid] + sm_part[1][tid]) + (sm_part[2][tid] + sm_part[3][tid])) *
+                                                 (1.0f / (float)a.H);
 }
 
 struct AppendArgs {
@@ -713,7 +724,7 @@ void launch_inherit(const InheritArgs& ia, int B, hipStream_t st) {
 
 template <typename T, int D>
 void launch_finish(const FinishArgs& fa, int B, hipStream_t st) {
-    const int blocks = (fa.out ? fa.H : 0) + (fa.mass ? (fa.max_vis + 255) / 256 : 0);
+    const int blocks = (fa.out ? fa.H : 0) + (fa.mass ? (fa.max_vis + kFinishKeys - 1) / kFinishKeys : 0);
     if (blocks > 0) decode_finish_kernel<T, D><<<dim3(blocks, B), 256, 0, st>>>(fa);
 }
 
@@ -804,7 +815,10 @@ st3_status enqueue_decode(const st3_attn_shape* shape, const void* q, const st3_
     da.kv_len = seg->kv_len; da.vis_len = seg->vis_len; da.tail_start = seg->tail_start;
     da.B = B; da.sys_len = seg->sys_len; da.max_vis = seg->max_vis_len; da.max_kv = max_kv_len; da.H = H;
     layout_hint(seg, kv->capacity, da.hint_base, da.hint_gap);
-    da.nsplit = decode_nsplit(B, H, max_kv_len);
+    const bool mass_now = want_mass && !defer_mass;
+    // a call that finishes its mass has a second launch anyway, so that a cut costs it no launch (13B shape, five sequences
+    // of 173 to 1111 rows, attention + finish: 26 us in 200 workgroups, 20.5 us in 1000)
+    da.nsplit = decode_nsplit(B, H, max_kv_len, mass_now ? kDecodeTargetWgsMerged : kDecodeTargetWgs);
     if (da.nsplit > wl.nsplit_cap) da.nsplit = wl.nsplit_cap;
     da.nsplit_cap = wl.nsplit_cap;
     da.chunk = decode_chunk(max_kv_len, da.nsplit);
@@ -825,7 +839,6 @@ st3_status enqueue_decode(const st3_attn_shape* shape, const void* q, const st3_
     da.out = out;
     da.defer = (want_mass && defer_mass) ? 1 : 0;
     ST3_DISPATCH_KV(launch_attend, shape, kv, da, B, st);
-    const bool mass_now = want_mass && !defer_mass;
     if (da.nsplit > 1 || mass_now) {
         FinishArgs fa{};
         fa.part_o = da.part_o; fa.part_ml = da.part_ml; fa.logits = da.logits;

@@ -334,27 +334,11 @@ __device__ __forceinline__ void merge_chunks(const StepCommon& c, const StepLaye
 
 // The visual mass that the attention launch left pending: mass_row[j] = (1/H) sum_h exp2(logit[h][j] - m_h) / l_h for
 // j < n.  Heads are dealt to NT / keys groups of threads whose sums are added in group order: the result does not depend
-// on scheduling.  The row maxima and sums come from ns (max, sum) pairs per head, 1 << log_ns lanes per head.
+// on scheduling.  ns: chunks per head of the attention launch.
 template <int NT>
 __device__ __forceinline__ void plan_mass(const EvictArgs& a, int b, int n, int ns, PlanShared& sm) {
     const int tid = threadIdx.x, H = a.H;
-    int nsp = 1;
-    while (nsp < ns) nsp *= 2;                          // at most 64: a group lies in one wave
-    for (int base = 0; base < H * nsp; base += NT) {
-        const int x = base + tid, h = x / nsp, c = x & (nsp - 1);
-        float m = -INFINITY, l = 0.f;
-        if (h < H && c < ns) {
-            const float2 ml = *reinterpret_cast<const float2*>(a.part_ml + (((int64_t)b * H + h) * a.nsplit_cap + c) * 2);
-            m = ml.x; l = ml.y;
-        }
-        const float own = m;
-        for (int off = 1; off < nsp; off <<= 1) m = fmaxf(m, __shfl_xor(m, off));
-        l = c < ns ? l * exp2_fast(own - m) : 0.f;
-        for (int off = 1; off < nsp; off <<= 1) l += __shfl_xor(l, off);
-        if (h < H && c == 0) { sm.hm[h] = m; sm.hrl[h] = 1.0f / l; }
-    }
-    __syncthreads();
-    constexpr int kUH = 12;                             // loads in flight per thread
+    head_norms<NT>(a.part_ml, b, H, ns, a.nsplit_cap, sm.hm, sm.hrl);
     const int keys = n <= 256 ? 256 : n <= 512 ? 512 : NT;
     const int groups = NT / keys, per = (H + groups - 1) / groups;
     const int g = __builtin_amdgcn_readfirstlane(tid / keys);     // (a wave lies in one group)
@@ -363,18 +347,7 @@ __device__ __forceinline__ void plan_mass(const EvictArgs& a, int b, int n, int 
     float* row = a.mass_dst + b * a.mass_stride;
     float* part = reinterpret_cast<float*>(sm.keys);    // (the keys are staged later)
     for (int j = tid & (keys - 1); j < n; j += keys) {  // (one round unless n > NT, and then there is one group)
-        float acc = 0.f;
-        for (int h = h0; h < h1; h += kUH) {
-            float v[kUH];
-#pragma unroll
-            for (int u = 0; u < kUH; ++u) v[u] = lg[(int64_t)min(h + u, h1 - 1) * a.capacity + j];
-#pragma unroll
-            for (int u = 0; u < kUH; ++u) {
-                const int hh = min(h + u, h1 - 1);
-                const float p = exp2_fast(v[u] - sm.hm[hh]) * sm.hrl[hh];
-                acc += h + u < h1 ? p : 0.f;
-            }
-        }
+        const float acc = prob_sum(lg + j, a.capacity, sm.hm, sm.hrl, h0, h1);
         if (groups == 1) row[j] = acc * (1.0f / (float)H);
         else part[tid] = acc;
     }
