@@ -39,6 +39,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
@@ -210,7 +211,23 @@ __device__ __forceinline__ void tile_step(const uint16_t* Kt, const uint16_t* Vt
         for (int r = 0; r < 16; ++r)
             if (8 * (r / 4) + 4 * g + (r % 4) > c) sacc[NSUB - 1][r] = -INFINITY;
     }
-    if (lg_row != nullptr) {            // a row of the score window: keep the scaled logits of its visual keys
+    // A row of the score window keeps the scaled logits of its visual keys.  The wave that holds it sets the pace of the
+    // strip's heaviest workgroup, so the usual case - every key of the tile visible and visual - is eight 16-byte stores.
+    // (With a comparison and a store per key such a tile took 7200 cycles instead of 4250; 13B layer, batch 32: 396 -> 380 us a
+    // call, high resolution, batch 8: 1010 -> 940.)
+    if (!DIAG && k0 >= vis_lo && k0 + 32 * NSUB <= vis_hi) {
+        if (lg_row != nullptr) {
+            float* p = lg_row + (k0 - vis_lo) + 4 * g;      // (4-byte aligned, which is all a global store asks for)
+#pragma unroll
+            for (int sub = 0; sub < NSUB; ++sub)
+#pragma unroll
+                for (int rq = 0; rq < 4; ++rq) {
+                    const f32x4_a4 v = {sacc[sub][4 * rq] * scale_l2, sacc[sub][4 * rq + 1] * scale_l2,
+                                        sacc[sub][4 * rq + 2] * scale_l2, sacc[sub][4 * rq + 3] * scale_l2};
+                    *reinterpret_cast<f32x4_a4*>(p + 32 * sub + 8 * rq) = v;
+                }
+        }
+    } else if (lg_row != nullptr) {
 #pragma unroll
         for (int sub = 0; sub < NSUB; ++sub)
 #pragma unroll
