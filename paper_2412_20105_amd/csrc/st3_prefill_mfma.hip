@@ -314,34 +314,51 @@ __device__ __forceinline__ void consume_tile(const uint16_t* buf, int k0, int q0
         tile_step<D, 1, true>(Kt, Vt, qf, oacc, m_i, l_i, scale_l2, lm, c, g, k0, myq, lg_row, vis_lo, vis_hi);
 }
 
-// One-dimensional grid of ceil(n/128) * H * B workgroups (the mapping to query tile and strip is in the kernel).
-// Register budget: two waves per SIMD (256 registers each; the kernel takes 214), i.e. two workgroups
-// per compute unit: while one waits for a tile, a barrier or its first loads, the other one runs.
-// (MFMA and VALU work of the two waves of a SIMD add up rather than overlap on this part: measured.)
+// Normalises and stores a wave's 32 x D block of outputs.
+// The accumulator holds O transposed (a lane owns one query and, per register quad, 4 consecutive
+// columns): stored straight from there, a wave-wide store would touch 32 rows with 8 bytes each.
+// So the wave's 32 x D block goes through LDS (obuf: 32 rows of D + 8 elements, this wave's own)
+// and leaves as whole rows, 16 bytes per lane.
 template <int D>
-__global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(PrefillArgs a) {
-    using L = TileLayout<D>;
-    constexpr int KS = D / 16;          // contraction steps of S^T
-    constexpr int DT = D / 32;          // 32-row tiles of O^T
-    // two buffers as two objects, so that the compiler can tell a direct load into one from the reads of the other
-    __shared__ __attribute__((aligned(1024))) uint16_t buf0[2 * L::TILE];
-    __shared__ __attribute__((aligned(1024))) uint16_t buf1[2 * L::TILE];
+__device__ __forceinline__ void store_block(const PrefillArgs& a, int b, int h, uint16_t* obuf, const f32x16* oacc, float rl,
+                                            int q0, int n, bool wave_live, int lane, int g, int c) {
+    constexpr int DT = D / 32;
+    constexpr int OSTR = D + 8;                     // padded row, 16-byte aligned
+    constexpr int VPR = D / 8;                      // 16-byte vectors (lanes) per row
+    constexpr int RPI = 64 / VPR;                   // rows per wave-wide store
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+            const int dd = 32 * dt + 8 * rq + 4 * g;
+            const f32x2 o01 = {oacc[dt][4 * rq] * rl, oacc[dt][4 * rq + 1] * rl};
+            const f32x2 o23 = {oacc[dt][4 * rq + 2] * rl, oacc[dt][4 * rq + 3] * rl};
+            uint2 pk;                               // packed conversion, round to nearest even
+            pk.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(o01, bf16x2));
+            pk.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(o23, bf16x2));
+            *reinterpret_cast<uint2*>(obuf + c * OSTR + dd) = pk;
+        }
+    uint16_t* obase = reinterpret_cast<uint16_t*>(a.out) + b * a.o_sb + h * a.o_sh;
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+        const int r = i * RPI + lane / VPR;
+        const u32x4 val = *reinterpret_cast<const u32x4*>(obuf + r * OSTR + (lane % VPR) * 8);
+        if (wave_live && q0 + r < n) *reinterpret_cast<u32x4*>(obase + (int64_t)(q0 + r) * a.o_st + (lane % VPR) * 8) = val;
+    }
+}
 
-    // Workgroup -> (query tile, strip).  Workgroups go round-robin by linear id to the 8 XCDs (checked
-    // with a probe: XCC id == id % 8) and, within an XCD, in turn to its 4 shader engines; each XCD
-    // has an L2 of its own; a causal query tile costs in proportion to its index.  With the query
-    // tile as the fastest index, a tile count of 2 or 4 hands all heavy tiles to the same engines
-    // (measured: 4 tiles per strip ran slower than 5).  So each of the 32 dispatch lanes
-    // (id % 32) owns the strips congruent to it and receives the tiles of one strip back to back,
-    // heaviest first: all lanes see the same cost sequence and a strip's K and V stay in one L2.
-#ifndef ST3_PREFILL_LANES
-#define ST3_PREFILL_LANES 32
-#endif
-    constexpr int kLanes = ST3_PREFILL_LANES;
+// Workgroup -> (query tile, strip).  Workgroups go round-robin by linear id to the 8 XCDs (checked
+// with a probe: XCC id == id % 8) and, within an XCD, in turn to its 4 shader engines; each XCD
+// has an L2 of its own; a causal query tile costs in proportion to its index.  With the query
+// tile as the fastest index, a tile count of 2 or 4 hands all heavy tiles to the same engines
+// (measured: 4 tiles per strip ran slower than 5).  So each of the 32 dispatch lanes
+// (id % 32) owns the strips congruent to it and receives the tiles of one strip back to back,
+// heaviest first: all lanes see the same cost sequence and a strip's K and V stay in one L2.
+__device__ __forceinline__ void place_workgroup(const PrefillArgs& a, int& strip, int& qt) {
+    constexpr int kLanes = 32;
     const int n_qt = a.n_qt, strips = a.H * a.B;
     const int full = strips / kLanes * kLanes;
     const int lin = blockIdx.x;
-    int strip, qt;
     if (lin < full * n_qt) {
         const int dl = lin % kLanes, m = lin / kLanes;
         strip = (m / n_qt) * kLanes + dl;
@@ -351,6 +368,28 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(PrefillArgs a) {
         strip = full + r / n_qt;
         qt = n_qt - 1 - r % n_qt;
     }
+}
+
+// One-dimensional grid of ceil(n/128) * H * B workgroups (the mapping to query tile and strip is in the kernel).
+// Register budget: two waves per SIMD (256 registers each; the kernel takes 214), i.e. two workgroups
+// per compute unit: while one waits for a tile, a barrier or its first loads, the other one runs.
+// Cycles of a tile (64 keys below the diagonal, stamps inside the kernel): 630 issue of the next tile's loads, 760 S^T, 1250
+// softmax, 1110 O^T, 140 wait and barrier - about the same for a wave that has its SIMD to itself and for two that share it,
+// whose parts overlap, so a wave's chain is what bounds the kernel (2 x 1536 of its 4250 cycles are MFMAs).  Shortening the chain
+// inside a wave was measured slower: the softmax of one sub-tile between the MFMAs of the other (13B 385 -> 505 us: its VALU
+// work then waits, in order, behind MFMAs that queue for the matrix core its partner holds), the direct loads spread between
+// the MFMAs (378 -> 450 ... 520).
+template <int D>
+__global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(PrefillArgs a) {
+    using L = TileLayout<D>;
+    constexpr int KS = D / 16;          // contraction steps of S^T
+    constexpr int DT = D / 32;          // 32-row tiles of O^T
+    // two buffers as two objects, so that the compiler can tell a direct load into one from the reads of the other
+    __shared__ __attribute__((aligned(1024))) uint16_t buf0[2 * L::TILE];
+    __shared__ __attribute__((aligned(1024))) uint16_t buf1[2 * L::TILE];
+
+    int strip, qt;
+    place_workgroup(a, strip, qt);
     const int h = strip % a.H, b = strip / a.H;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 5, c = lane & 31;
@@ -428,36 +467,9 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(PrefillArgs a) {
     both_halves(l_i, l_lo, l_hi);
     const float l_tot = l_lo + l_hi;
     const float rl = 1.0f / l_tot;
-    // The accumulator holds O transposed (a lane owns one query and, per register quad, 4 consecutive
-    // columns): stored straight from there, a wave-wide store would touch 32 rows with 8 bytes each.
-    // So the wave's 32 x D block goes through LDS (both tile buffers are free after the last barrier;
-    // each wave uses a region of its own) and leaves as whole rows, 16 bytes per lane.
-    {
-        constexpr int OSTR = D + 8;                     // padded row, 16-byte aligned
-        constexpr int VPR = D / 8;                      // 16-byte vectors (lanes) per row
-        constexpr int RPI = 64 / VPR;                   // rows per wave-wide store
-        uint16_t* obuf = (wave < 2 ? buf0 : buf1) + (wave & 1) * (32 * OSTR);
-        static_assert(2 * 32 * OSTR <= 2 * L::TILE, "two waves' output blocks fit one tile buffer");
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                const int dd = 32 * dt + 8 * rq + 4 * g;
-                const f32x2 o01 = {oacc[dt][4 * rq] * rl, oacc[dt][4 * rq + 1] * rl};
-                const f32x2 o23 = {oacc[dt][4 * rq + 2] * rl, oacc[dt][4 * rq + 3] * rl};
-                uint2 pk;                               // packed conversion, round to nearest even
-                pk.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(o01, bf16x2));
-                pk.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(o23, bf16x2));
-                *reinterpret_cast<uint2*>(obuf + c * OSTR + dd) = pk;
-            }
-        uint16_t* obase = reinterpret_cast<uint16_t*>(a.out) + b * a.o_sb + h * a.o_sh;
-#pragma unroll
-        for (int i = 0; i < 32 / RPI; ++i) {
-            const int r = i * RPI + lane / VPR;
-            const u32x4 val = *reinterpret_cast<const u32x4*>(obuf + r * OSTR + (lane % VPR) * 8);
-            if (wave_live && q0 + r < n) *reinterpret_cast<u32x4*>(obase + (int64_t)(q0 + r) * a.o_st + (lane % VPR) * 8) = val;
-        }
-    }
+    uint16_t* obuf = (wave < 2 ? buf0 : buf1) + (wave & 1) * (32 * (D + 8));      // (both tile buffers are free after the last barrier)
+    static_assert(2 * 32 * (D + 8) <= 2 * L::TILE, "two waves' output blocks fit one tile buffer");
+    store_block<D>(a, b, h, obuf, oacc, rl, q0, n, wave_live, lane, g, c);
     if (myq < n) {
         if (lane_in_window && g == 0) {
             a.pre_ml[(bh * a.window + w_idx) * 2] = m_i;
@@ -466,22 +478,175 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(PrefillArgs a) {
     }
 }
 
+// The same attention for launches that leave compute units idle (a short prompt, a single sequence).  128 / KS queries per
+// workgroup: its four waves are KS groups that own the same query blocks and take the key tiles in turn, tile i to group
+// i % KS, KS tiles at a time in LDS.  There are KS times the workgroups and each walks its tiles in a KS-th of the steps; at
+// the end group 0 merges the groups' (maximum, sum, accumulator) through LDS.  One workgroup per compute unit (128 KB of LDS:
+// KS = 2 keeps the next two tiles in flight, KS = 4 has room for the current four only).
+template <int D, int KS>
+__global__ __launch_bounds__(256, 1) void prefill_mfma_split_kernel(PrefillArgs a) {
+    using L = TileLayout<D>;
+    constexpr int KSTEPS = D / 16, DT = D / 32;
+    constexpr int NB = 4 / KS;                          // 32-query blocks per workgroup
+    constexpr int NBUF = KS == 2 ? 2 : 1;
+    constexpr int TILE2 = 2 * L::TILE;                  // elements of a K tile and its V tile
+    __shared__ __attribute__((aligned(1024))) uint16_t buf[NBUF * KS * TILE2];
+    __shared__ float sm_m[KS][NB][64], sm_l[KS][NB][64];
+
+    int strip, qt;
+    place_workgroup(a, strip, qt);
+    const int h = strip % a.H, b = strip / a.H;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int g = lane >> 5, c = lane & 31;
+    const int blk = wave % NB, kg = wave / NB;
+    const int n = a.n;
+    const int q0 = qt * (32 * NB) + blk * 32 - a.q_shift;
+    const int myq = q0 + c;
+    const int64_t bh = (int64_t)b * a.H + h;
+    const uint16_t* Qp = reinterpret_cast<const uint16_t*>(a.q) + b * a.q_sb + h * a.q_sh;
+    const uint16_t* Kp = reinterpret_cast<const uint16_t*>(a.k) + b * a.k_sb + h * a.k_sh;
+    const uint16_t* Vp = reinterpret_cast<const uint16_t*>(a.v) + b * a.v_sb + h * a.v_sh;
+    uint32_t k_lane, v_lane;
+    {
+        const int row0 = wave * L::RPI + lane / L::UPR, u = lane % L::UPR;
+        const int rowc = min(row0, n - 1);
+        k_lane = (uint32_t)(2 * (rowc * a.k_st + (u ^ L::k_swz(row0)) * 8));
+        v_lane = (uint32_t)(2 * (rowc * a.v_st + (u ^ L::v_swz(row0)) * 8));
+    }
+    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+    const uint32_t lds0 = lds_addr(buf);
+    const int k_end = min(n, qt * (32 * NB) + 32 * NB - a.q_shift);     // keys this workgroup can see
+    const int nt = (k_end + kBN - 1) / kBN;
+    // the tiles of step s into buffer half s % NBUF (a tile past the last one is not loaded and not consumed)
+    auto load_step = [&](int s) {
+#pragma unroll
+        for (int i = 0; i < KS; ++i)
+            if (s * KS + i < nt)
+                issue_tile<D>(lds0 + (uint32_t)(((s % NBUF) * KS + i) * TILE2 * 2), Kp, Vp, k_lane, v_lane, a.k_st, a.v_st,
+                              (s * KS + i) * kBN, n, lane, wave, wave_s);
+    };
+    load_step(0);
+    Frag qf[KSTEPS];
+    {
+        const uint16_t* qrow = Qp + (int64_t)max(0, min(myq, n - 1)) * a.q_st;
+#pragma unroll
+        for (int s = 0; s < KSTEPS; ++s) qf[s].u4 = *reinterpret_cast<const u32x4*>(qrow + 16 * s + 8 * g);
+    }
+    LaneMap<D> lm;
+    lm.init(c, g);
+    f32x16 oacc[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
+    float m_i = -INFINITY, l_i = 0.f;
+    const bool wave_has_window = a.pre_logits != nullptr && q0 + 31 >= n - a.window && q0 < n && q0 >= 0;
+    const int w_idx = myq - (n - a.window);
+    const bool lane_in_window = wave_has_window && w_idx >= 0 && myq < n;
+    float* lg_row = lane_in_window ? a.pre_logits + (bh * a.window + w_idx) * a.vis_len : nullptr;
+    const int vis_lo = a.sys_len, vis_hi = a.sys_len + a.vis_len;
+    const bool wave_live = q0 >= 0 && q0 < n;
+
+    const int steps = (nt + KS - 1) / KS;
+    for (int s = 0; s < steps; ++s) {
+        wait_direct_loads();
+        __syncthreads();
+        if (NBUF == 2 && s + 1 < steps) load_step(s + 1);
+        const int t = s * KS + kg;
+        if (wave_live && t < nt && t * kBN <= q0)       // else the tile lies entirely above this wave's diagonal
+            consume_tile<D>(buf + ((s % NBUF) * KS + kg) * TILE2, t * kBN, q0, qf, oacc, m_i, l_i, a.scale_l2, lm, c, g, myq,
+                            lg_row, vis_lo, vis_hi);
+        if (NBUF == 1 && s + 1 < steps) {
+            __syncthreads();                            // every wave is done with the buffer
+            load_step(s + 1);
+        }
+    }
+    // ---- merge the key groups ----------------------------------------------------------------
+    // (a lane of every group holds the same query and the same columns; a group without tiles has sum 0 at maximum -inf)
+    __syncthreads();
+    float* merge = reinterpret_cast<float*>(buf);       // [KS - 1][NB][16 * DT][64]
+    sm_m[kg][blk][lane] = m_i;
+    sm_l[kg][blk][lane] = l_i;
+    if (kg > 0) {
+        float* dst = merge + ((kg - 1) * NB + blk) * (16 * DT * 64) + lane;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) dst[(dt * 16 + r) * 64] = oacc[dt][r];
+    }
+    __syncthreads();
+    if (kg > 0 || !wave_live) return;                   // (no barrier below)
+    float m = m_i;                                      // group 0 has tile 0, which every live query sees: finite
+#pragma unroll
+    for (int k = 1; k < KS; ++k) m = fmaxf(m, sm_m[k][blk][lane]);
+    const float f0 = exp2_fast(m_i - m);
+    float l = l_i * f0;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[dt][r] *= f0;
+#pragma unroll
+    for (int k = 1; k < KS; ++k) {
+        const float f = exp2_fast(sm_m[k][blk][lane] - m);
+        l = fmaf(sm_l[k][blk][lane], f, l);
+        const float* src = merge + ((k - 1) * NB + blk) * (16 * DT * 64) + lane;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[dt][r] = fmaf(src[(dt * 16 + r) * 64], f, oacc[dt][r]);
+    }
+    float l_lo, l_hi;
+    both_halves(l, l_lo, l_hi);
+    const float l_tot = l_lo + l_hi;
+    constexpr int kMergeElems = (KS - 1) * NB * 16 * DT * 64 * 2;       // of the merge area, in 16-bit elements
+    static_assert(kMergeElems + NB * 32 * (D + 8) <= NBUF * KS * TILE2, "merge area and output blocks fit the tile buffers");
+    store_block<D>(a, b, h, buf + kMergeElems + blk * (32 * (D + 8)), oacc, 1.0f / l_tot, q0, n, true, lane, g, c);
+    if (lane_in_window && g == 0) {
+        a.pre_ml[(bh * a.window + w_idx) * 2] = m;
+        a.pre_ml[(bh * a.window + w_idx) * 2 + 1] = l_tot;
+    }
+}
+
+// Key groups for a launch (1: the kernel without groups): as many as leave every workgroup a place of its own at once.  The
+// device holds 256 workgroups of the split kernel at D = 128 (LDS), 512 at D = 64.  With one or two strips per dispatch lane
+// the lanes stay balanced a little beyond that.  Measured, us a call, 1 / 2 / 4 groups, D = 128 (strips x tokens): 8 x 739
+// 29.4 / 23.0 / 18.7, 16 x 420 22.1 / 20.0 / 15.9, 32 x 310 18.1 / 16.8 / 17.3, 32 x 739 30.6 / 24.2 / 32.6, 64 x 420 23.6 /
+// 20.8 / 33.3, but 24 x 739 30.5 / 32.6, 40 x 420 22.7 / 25.3, 64 x 560 26.9 / 29.9, 96 x 224 17.3 / 19.8; D = 64: 32 x 420
+// 18.5 / 16.7 / 14.3, 64 x 739 26.3 / 21.7 / 26.7, 96 x 560 22.9 / 23.5 / 27.1.
+int key_groups(int D, int n, int64_t strips) {
+    const int64_t places = D == 128 ? 256 : 512;
+    if ((n + 31) / 32 * strips <= places) return 4;
+    const int64_t two = (n + 63) / 64 * strips;
+    if (two <= places || (strips % 32 == 0 && strips <= 64 && 4 * two <= 7 * places)) return 2;
+    return 1;
+}
+
 }  // namespace
 
 st3_status launch_prefill_mfma(const PrefillArgs& a, int B, int D, hipStream_t st) {
     // 8-byte output stores and 16-byte input loads need these alignments (rows are 16-byte aligned already)
     PrefillArgs pa = a;
-    pa.n_qt = (a.n + kBM - 1) / kBM;
-    pa.q_shift = (pa.n_qt * kBM - a.n) / 32 * 32;       // whole empty 32-row blocks, moved to the front
+    const int ks = key_groups(D, a.n, (int64_t)a.H * B);
+    const int bm = kBM / ks;
+    pa.n_qt = (a.n + bm - 1) / bm;
+    pa.q_shift = (pa.n_qt * bm - a.n) / 32 * 32;        // whole empty 32-row blocks, moved to the front
     pa.B = B;
     const int64_t wgs = (int64_t)pa.n_qt * a.H * B;
     if (wgs > 0x7fffffff) return ST3_ERR_UNSUPPORTED;
     // the direct loads address a strip as a scalar base plus a 32-bit byte offset
     if ((int64_t)a.n * a.k_st * 2 >= (int64_t)1 << 31 || (int64_t)a.n * a.v_st * 2 >= (int64_t)1 << 31) return ST3_ERR_UNSUPPORTED;
     dim3 grid((unsigned)wgs);
-    if (D == 128) prefill_mfma_kernel<128><<<grid, 256, 0, st>>>(pa);
-    else if (D == 64) prefill_mfma_kernel<64><<<grid, 256, 0, st>>>(pa);
-    else return ST3_ERR_UNSUPPORTED;
+    if (D != 128 && D != 64) return ST3_ERR_UNSUPPORTED;
+    if (ks == 1) {
+        if (D == 128) prefill_mfma_kernel<128><<<grid, 256, 0, st>>>(pa);
+        else prefill_mfma_kernel<64><<<grid, 256, 0, st>>>(pa);
+    } else if (ks == 2) {
+        if (D == 128) prefill_mfma_split_kernel<128, 2><<<grid, 256, 0, st>>>(pa);
+        else prefill_mfma_split_kernel<64, 2><<<grid, 256, 0, st>>>(pa);
+    } else {
+        if (D == 128) prefill_mfma_split_kernel<128, 4><<<grid, 256, 0, st>>>(pa);
+        else prefill_mfma_split_kernel<64, 4><<<grid, 256, 0, st>>>(pa);
+    }
     return ST3_OK;
 }
 
