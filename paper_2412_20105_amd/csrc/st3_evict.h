@@ -18,11 +18,9 @@ __device__ __forceinline__ uint32_t score_key(float f) {
 
 struct SelShared {
     uint32_t keys[kSelLdsKeys];
-    uint32_t flags[kSelLdsKeys / 32];
     int hist[256];
     int wave_tot[kSelWaves];
     int sel_bin, sel_want, sel_cnt;
-    int red;
 };
 
 // Inclusive scan of one int per thread over the 256 threads of the block, in thread order.
@@ -73,7 +71,7 @@ __device__ __forceinline__ uint32_t radix_select_desc(F f, int n, int& want, int
     return prefix;
 }
 
-// Marks the top-k entries of one row in sm.flags (bit p of word p/32).  Requires n <= kSelLdsKeys
+// The threshold of the top-k entries of one row (is_kept tells which they are).  Requires n <= kSelLdsKeys
 // when `staged`; otherwise keys are recomputed from global memory on every pass.
 // ids == nullptr: the position is the id.
 __device__ __forceinline__ void mark_topk(const float* scores, const int32_t* ids, int n, int k, bool staged, SelShared& sm,

@@ -374,11 +374,10 @@ __device__ __forceinline__ void place_workgroup(const PrefillArgs& a, int& strip
 // Register budget: two waves per SIMD (256 registers each; the kernel takes 214), i.e. two workgroups
 // per compute unit: while one waits for a tile, a barrier or its first loads, the other one runs.
 // Cycles of a tile (64 keys below the diagonal, stamps inside the kernel): 630 issue of the next tile's loads, 760 S^T, 1250
-// softmax, 1110 O^T, 140 wait and barrier - about the same for a wave that has its SIMD to itself and for two that share it,
-// whose parts overlap, so a wave's chain is what bounds the kernel (2 x 1536 of its 4250 cycles are MFMAs).  Shortening the chain
-// inside a wave was measured slower: the softmax of one sub-tile between the MFMAs of the other (13B 385 -> 505 us: its VALU
-// work then waits, in order, behind MFMAs that queue for the matrix core its partner holds), the direct loads spread between
-// the MFMAs (378 -> 450 ... 520).
+// softmax, 1110 O^T, 140 wait and barrier - for a wave that has its SIMD to itself, at a shader clock of 2.35 GHz, and for two
+// that share it alike, at 1.83 GHz: under full load the clock falls, and rearranging the tile moves nothing (us a call, 13B layer
+// batch 32 / high resolution batch 8: as it is 369 / 902; softmax of one sub-tile between the MFMAs of the other 368 / 905;
+// half of the waves loading after S^T 378 / 940, all of them 376 / 920).
 template <int D>
 __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(PrefillArgs a) {
     using L = TileLayout<D>;
