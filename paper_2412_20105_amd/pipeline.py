@@ -50,9 +50,9 @@ class LayerCache:
         self.score = torch.zeros((B, max(cap_v, 1)), dtype=torch.float32, device=device)
         self.ids = torch.zeros((B, max(cap_v, 1)), dtype=torch.int32, device=device)
         self.mass = torch.zeros((B, max(cap_v, 1)), dtype=torch.float32, device=device)
-        self.vis_len = torch.zeros((B,), dtype=torch.int32, device=device)
-        self.kv_len = torch.zeros((B,), dtype=torch.int32, device=device)
-        self.tail_start = None      # set at prefill when the tail keeps its place (Generation(fixed_tail=True))
+        self.lens = torch.zeros((3, B), dtype=torch.int32, device=device)
+        self.vis_len, self.kv_len = self.lens[0], self.lens[1]
+        self.tail_start = None      # lens[2] from the prefill on when the tail keeps its place (Generation(fixed_tail=True))
         self.h_tail = 0             # host copy of it
         self.kv = st3.kv_layer(self.k, self.v, self.k_scale, self.v_scale)
         # a workspace of its own: the attention leaves its logits here for the mass and for lazy layers
@@ -121,13 +121,32 @@ class Generation:
         self.keep_idx = torch.empty((batch, max(n_vis, 1)), dtype=torch.int32, device=device)
         self._alive = n_vis                 # visual tokens alive in the layer being prefetched
         self._inherit: Optional[torch.Tensor] = None
+        # (visual rows, device image [3, B] of [vis_len, kv_len, tail_start]) of each layer as its prefill leaves them
+        counts, alive = [], n_vis
+        for l in range(layers):
+            alive = min(alive, self.keep[l][0]) if l else alive
+            counts.append(alive)
+        images = self._length_images(counts)
+        self._lens0: List[tuple] = [(counts[l], images[l]) for l in range(layers)]
         self.t = 0
         eb = 2 if dtype == torch.bfloat16 else 4
         self._eb = eb
 
     # ------------------------------------------------------------------------------------
-    def _compact_column(self, col: torch.Tensor, idx: torch.Tensor, k: int, n: int):
-        st3.st3_compact_rows(col.data_ptr(), self.B, 1, col.stride(0) * 4, 0, 4, 4, idx, k, n, 0)
+    def _lens_after_prefill(self, l: int, alive: int) -> torch.Tensor:
+        """Device image [3, B] of layer l's lengths behind its prefill, with `alive` visual rows."""
+        if self._lens0[l][0] != alive:
+            self._lens0[l] = (alive, self._length_images([alive])[0])
+        return self._lens0[l][1]
+
+    def _length_images(self, counts: Sequence[int]) -> torch.Tensor:
+        ns, nx = self.n_sys, self.n_txt
+        rows = [[[n] * self.B, [ns + n + nx] * self.B, [ns + n] * self.B] for n in counts]
+        # (a copy from ordinary host memory: finished, on whatever stream, when it returns)
+        return torch.tensor(rows, dtype=torch.int32).to(self.device)
+
+    def _compact_column(self, col: torch.Tensor, idx: torch.Tensor, k: int, n: int, stream=None):
+        st3.st3_compact_rows(col.data_ptr(), self.B, 1, col.stride(0) * 4, 0, 4, 4, idx, k, n, 0, stream)
 
     def prefill_layer(self, l: int, Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor):
         """Q, K, V: device tensors [B,H,N0,d] over the unpruned prompt (Alg. 3, PVTP branch).
@@ -137,8 +156,9 @@ class Generation:
         """
         lc = self.layers[l]
         src = self.lazy.get(l)
-        B, ns, nv, nx = self.B, self.n_sys, self.n_vis, self.n_txt
+        ns, nv, nx = self.n_sys, self.n_vis, self.n_txt
         k_l = self.keep[l][0]
+        stream = torch.cuda.current_stream().cuda_stream        # looked up once, not once per call
         if l == 0:                  # a new job: nothing is inherited from the previous one
             self._alive = nv
             self._inherit = None
@@ -149,12 +169,12 @@ class Generation:
             lc.ids.copy_(prev.ids)
             if k_l < self._alive:
                 # Eq. 3: keep the k_l visual tokens the PREVIOUS layer's last row attended to most
-                st3.st3_select_topk(prev.mass, prev.ids, None, self._alive, k_l, None, self.keep_idx)
-                self._compact_column(lc.ids, self.keep_idx, k_l, self._alive)
-                if self._inherit is None:
-                    self._inherit = torch.empty_like(prev.mass)
-                self._inherit.copy_(prev.mass)
-                self._compact_column(self._inherit, self.keep_idx, k_l, self._alive)
+                st3.st3_select_topk(prev.mass, prev.ids, None, self._alive, k_l, None, self.keep_idx, stream)
+                self._compact_column(lc.ids, self.keep_idx, k_l, self._alive, stream)
+                # ... and their scores, which rank this layer and the ones behind it up to the next prune event
+                lc.score.copy_(prev.mass)
+                self._compact_column(lc.score, self.keep_idx, k_l, self._alive, stream)
+                self._inherit = lc.score
                 self._alive = k_l
         alive = self._alive
         n_l = ns + alive + nx
@@ -171,26 +191,23 @@ class Generation:
             # key staging buffer when the caches are E4M3)
             pairs = [(V, v_dst)]
             k_rows = self.k_stage if fp8 else self.layers[src].k
-        st3.st3_gather_rows(pairs, ns, lc.ids if alive < nv else None, alive, nv, nx)
-        out = self.out_stage[:, :, :n_l]
-        st3.st3_prefill_attention(self.shape, self.q_stage[:, :, :n_l], k_rows[:, :, :n_l], v_dst[:, :, :n_l],
-                                  n_l, ns, alive, self.window, out, lc.mass, lc.ws)
+        st3.st3_gather_rows(pairs, ns, lc.ids if alive < nv else None, alive, nv, nx, stream)
+        st3.st3_prefill_attention(self.shape, self.q_stage, k_rows, v_dst, n_l, ns, alive, self.window, self.out_stage,
+                                  lc.mass, lc.ws, stream)       # (rows [0, n_l) of each)
         if fp8:
             if src is None:
-                st3.st3_quantize_rows(self.shape, self.k_stage, lc.kv, 0, n_l)
-            st3.st3_quantize_rows(self.shape, self.v_stage, lc.kv, 1, n_l)
+                st3.st3_quantize_rows(self.shape, self.k_stage, lc.kv, 0, n_l, stream)
+            st3.st3_quantize_rows(self.shape, self.v_stage, lc.kv, 1, n_l, stream)
         # ranking column: scores of the most recent prune event, else the layer's own mass
-        lc.score.copy_(lc.mass if self._inherit is None else self._inherit)
-        lc.vis_len.fill_(alive)
-        lc.kv_len.fill_(n_l)
+        if self._inherit is not lc.score:
+            lc.score.copy_(lc.mass if self._inherit is None else self._inherit)
+        lc.lens.copy_(self._lens_after_prefill(l, alive))
         lc.h_vis, lc.h_kv = alive, n_l
         if self.fixed_tail:         # [system | kept visual | instruction] is contiguous now: the tail starts here for good
-            if lc.tail_start is None:
-                lc.tail_start = torch.empty((self.B,), dtype=torch.int32, device=self.device)
+            lc.tail_start = lc.lens[2]
             lc.h_tail = ns + alive
-            lc.tail_start.fill_(lc.h_tail)
         self._decoding = False
-        return out, lc.mass[:, :alive]
+        return self.out_stage[:, :, :n_l], lc.mass[:, :alive]
 
     # ------------------------------------------------------------------------------------
     def begin_decode(self):
