@@ -583,7 +583,7 @@ def main():
             "value": tokens / (ms_lc * 1e-3), "unit": "tokens/s", "ms_per_step": ms_lc,
             "decode_ms_per_token_step": (ms_lc - ms_prefill) / T,
             "calls": "st3_decode_layer_attend per layer + st3_decode_plans per step (the headline uses st3_decode_step: "
-                     "the same launches from one host call per step)"}
+                     "many layers per launch)"}
 
     # -- roofline of the dominant kernel (split-KV decode), from a second, instrumented pass ---------
     note(f"job {ms_job:.1f} ms, prefill {ms_prefill:.1f} ms")
@@ -599,7 +599,7 @@ def main():
         traffic, traffic_source = committed_traffic(w.name, B, a.kv_format, alg / max(cnt, 1))
         result["roofline"] = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                               "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": traffic_source,
-                              "kernel": "decode_attend_kernel", "launches": cnt,
+                              "kernel": "decode_attend_layers_kernel", "launches": cnt,     # layers served (up to 21 per launch)
                               "avg_launch_us": tot_ms * 1e3 / max(cnt, 1), "min_us": mn * 1e3, "max_us": mx * 1e3,
                               "alg_bytes_per_launch": alg / max(cnt, 1),
                               "kernel_time_share_of_job": tot_ms / ms_job}

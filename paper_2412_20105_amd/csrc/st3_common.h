@@ -74,8 +74,8 @@ constexpr int kDecodeTargetWgs = ST3_DECODE_TARGET_WGS;     // split the KV rang
 #ifndef ST3_DECODE_TARGET_WGS_MERGED
 #define ST3_DECODE_TARGET_WGS_MERGED 1024
 #endif
-// ... and this many when the chunk partials are merged inside the step's plan launch, where a split costs no launch of
-// its own (13B shape, attend launch: B = 4 14.1 -> 11.7 us, B = 8 21.7 -> 20.2 us; 256, 512, 1024, 1536, 2048 measured),
+// ... and this many for a call that finishes its mass in a second launch, where merging the chunk partials costs no launch
+// of its own (13B shape, attend launch: B = 4 14.1 -> 11.7 us, B = 8 21.7 -> 20.2 us; 256, 512, 1024, 1536, 2048 measured),
 // unless B*H alone reaches half of it (B*H >= 512 ran the same or slower when cut)
 constexpr int kDecodeTargetWgsMerged = ST3_DECODE_TARGET_WGS_MERGED;
 constexpr int kDecodeTargetWgsMax = kDecodeTargetWgs > kDecodeTargetWgsMerged ? kDecodeTargetWgs : kDecodeTargetWgsMerged;
@@ -96,7 +96,7 @@ inline int decode_nsplit(int B, int H, int max_kv, int target_wgs = kDecodeTarge
     if (target_wgs > kDecodeTargetWgs && 2 * bh >= target_wgs) want = 1;
     int64_t by_len = ((int64_t)max_kv + kDecodeMinChunk - 1) / kDecodeMinChunk;
     int64_t ns = want < by_len ? want : by_len;
-    // A small even number of chunks runs slower than the odd number below it (attend launch, whole-step call, 1 / 2 / 3 /
+    // A small even number of chunks runs slower than the odd number below it (attend launch of one layer, 1 / 2 / 3 /
     // 4 / 5 / 6 / 8 chunks: high-resolution prompt at batch 8, B*H = 256, 31.8 / 33.9 / 31.4 / 35.7 / 32.6 / 34.2 / 38.5 us;
     // 13B shape at batch 8, B*H = 320, 21.5 / 21.2 / 19.3 / 19.9 / 19.8 / 20.1 / 23.0 us): workgroup ids go round-robin to
     // the 8 XCDs, so with an even count a chunk index always meets the same XCDs (rotating the chunk index over the strips

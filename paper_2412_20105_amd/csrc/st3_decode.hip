@@ -7,9 +7,11 @@
 // un-normalised partials that decode_finish_kernel merges in chunk order.  For the visual mass the
 // attend kernel saves the scaled logits of the visual keys (collected in LDS, written out as whole
 // lines at the end of the workgroup) and every chunk's (max, sum); turning
-// them into probabilities and adding them over heads - in head order, so the sum is the same on
-// every run - is done by finish_mass(): in decode_finish_kernel for the stand-alone call, and by
+// them into probabilities and adding them over heads - in a fixed order, so the sum is the same on
+// every run - is done by prob_sum(): in decode_finish_kernel for the stand-alone call, and by
 // the layer's eviction-plan workgroup in the fused step (it needs the scores only then).
+// The whole-step call runs the same workgroups for many layers in one launch
+// (decode_attend_layers_kernel, decode_inherit_layers_kernel).
 // The token being appended is read from k_new/v_new as cache row kv_len[b] by the workgroup that
 // owns the end of the strip, which also stores it into the cache; kv_len itself is bumped by the
 // eviction plan that follows the attention.
