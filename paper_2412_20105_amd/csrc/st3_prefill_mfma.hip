@@ -255,7 +255,9 @@ __device__ __forceinline__ void tile_step(const uint16_t* Kt, const uint16_t* Vt
     const float m_cand = fmaxf(m_i, mx * scale_l2);
     const bool moved = m_cand - m_i > kLazy;            // m_i = -inf before the first key: moved
     const float m_new = moved ? m_cand : m_i;
-    const float alpha = exp2_fast(m_i - m_new);         // 1 when not moved; 0 before the first key
+    // (a group of waves can meet keys of logit -inf only; they weigh nothing, whatever the reference)
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = exp2_fast(m_i - m_ref);         // 1 when not moved; 0 before the first key
     m_i = m_new;
     float psum = 0.f;
     Frag pb[NSUB][2], pl[NSUB][2];
@@ -265,8 +267,8 @@ __device__ __forceinline__ void tile_step(const uint16_t* Kt, const uint16_t* Vt
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float p0 = exp2_fast(fmaf(sacc[sub][8 * kk + 2 * j], scale_l2, -m_new));      // masked: exp2(-inf) = 0
-                const float p1 = exp2_fast(fmaf(sacc[sub][8 * kk + 2 * j + 1], scale_l2, -m_new));
+                const float p0 = exp2_fast(fmaf(sacc[sub][8 * kk + 2 * j], scale_l2, -m_ref));      // masked: exp2(-inf) = 0
+                const float p1 = exp2_fast(fmaf(sacc[sub][8 * kk + 2 * j + 1], scale_l2, -m_ref));
                 psum += p0 + p1;
                 const uint32_t b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
                 pb[sub][kk].w[j] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);      // upper halves of (p0, p1)

@@ -11,9 +11,12 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def _run(B, H, d, n, sys_len, vis, window, extra_rows=0):
+def _run(B, H, d, n, sys_len, vis, window, extra_rows=0, dead=()):
     g = torch.Generator(device=DEV).manual_seed(n * 13 + H + d)
     q, k, v = (torch.randn((B, H, n + (extra_rows if i else 0), d), generator=g, device=DEV).to(torch.bfloat16) for i in range(3))
+    q[..., 0] = 1.0
+    for j in dead:
+        k[:, :, j, 0] = -math.inf       # keys of logit -inf for every query
     shape = st3.make_shape(B, H, d, st3.ST3_BF16)
     ws = torch.empty((st3.st3_workspace_bytes(shape, n, vis, window),), dtype=torch.uint8, device=DEV)
     ws.fill_(0xFF)                      # logits that no row has left are NaN
@@ -55,3 +58,10 @@ def test_one_group_every_offset_of_the_query_tiles(n):
 def test_window_rows_and_visual_edges(B, H, d, n, window, sys_len, short):
     """Visual segments that start and end inside tiles, up to the last key; window rows that do not see them all."""
     _run(B, H, d, n, sys_len, n - sys_len - short, window)
+
+
+@pytest.mark.parametrize("B,H,d,n", [(1, 2, 128, 250), (1, 32, 128, 300), (3, 33, 128, 200), (1, 2, 64, 250)])
+@pytest.mark.parametrize("tile", [1, 2])
+def test_a_tile_of_keys_that_weigh_nothing(B, H, d, n, tile):
+    """The first keys that a group of waves meets have logit -inf: they add nothing, and nothing turns into NaN."""
+    _run(B, H, d, n, 4, n - 20, 1, dead=range(64 * tile, 64 * tile + 64))
