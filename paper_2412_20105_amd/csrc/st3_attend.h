@@ -59,11 +59,15 @@ __device__ __forceinline__ void load_row_slice(const T* row, int lane, float* f)
 
 // Online-softmax state of one wave.  `l` holds, per lane, the sum of probabilities over the rows
 // of that lane's row-group only; `acc` likewise.  finish_wave() folds the row-groups together.
+// The maximum starts at the lowest finite value and not at -inf: while a wave, a chunk or a strip has met keys of logit -inf
+// only, differences against it stay defined and those keys weigh exp2(-inf) = 0 (against -inf they would be NaN, wherever such
+// keys fill a wave's first tile).  Every finite logit is at least that large, so it is a maximum like any other, and one that
+// belongs to no key drops out of a merge with exp2(lowest - m) = 0, or with a sum of 0 when it is the larger.
 template <int EPL>
 struct WaveState {
-    float m;            // running maximum (log2 domain), wave-uniform
-    float l;
-    float acc[EPL];
+    float m = -3.402823466e38f;     // running maximum (log2 domain), wave-uniform
+    float l = 0.f;
+    float acc[EPL] = {};
 };
 
 // Streams the tiles of U*RPL rows that start at r0, r0+step, r0+2*step, ... below r1; within a
@@ -114,7 +118,7 @@ __device__ __forceinline__ void wave_attend(const float* qf, const T* kbase, con
         }
         mt = wave_max_from<LPR>(mt);
         float m_new = fmaxf(st.m, mt);
-        float alpha = exp2_fast(st.m - m_new);       // first tile: exp2(-inf) = 0
+        float alpha = exp2_fast(st.m - m_new);       // first tile: 0, or 1 on sums of 0
         st.m = m_new;
         st.l *= alpha;
 #pragma unroll

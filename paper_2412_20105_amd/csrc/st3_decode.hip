@@ -161,9 +161,6 @@ __device__ __forceinline__ void attend_chunk(const DecodeArgs& a, const int spli
     const int c1 = min(c0 + a.chunk, len);
 
     WaveState<EPL> st;
-    st.m = -INFINITY; st.l = 0.f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) st.acc[e] = 0.f;
 
     // Scaled logits kept for later: those of the visual keys become the mass; a layer with lazy
     // followers (QK heredity, Eq. 6) keeps the logit of EVERY key for them.  Keeping all of them
@@ -233,11 +230,11 @@ __device__ __forceinline__ void attend_chunk(const DecodeArgs& a, const int spli
     if (tid < D) {
         float m = sm_m[0];
 #pragma unroll
-        for (int w = 1; w < kDecodeWaves; ++w) m = fmaxf(m, sm_m[w]);   // finite: the chunk is not empty
+        for (int w = 1; w < kDecodeWaves; ++w) m = fmaxf(m, sm_m[w]);   // finite (WaveState)
         float o = 0.f, l = 0.f;
 #pragma unroll
         for (int w = 0; w < kDecodeWaves; ++w) {
-            float f = exp2_fast(sm_m[w] - m);           // wave without rows: exp2(-inf) = 0
+            float f = exp2_fast(sm_m[w] - m);           // wave without rows: its sums are 0
             o = fmaf(sm_acc[w][tid], f, o);
             l = fmaf(sm_l[w], f, l);
         }

@@ -31,9 +31,6 @@ __global__ __launch_bounds__(256) void prefill_rows_kernel(PrefillArgs a) {
     float qf[EPL];
     load_q_slice<T, D>(qrow, lane, qf);
     WaveState<EPL> st;
-    st.m = -INFINITY; st.l = 0.f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) st.acc[e] = 0.f;
     const int64_t bh = (int64_t)b * a.H + h;
     const int w_idx = i - (a.n - a.window);
     float* lg = nullptr;
