@@ -138,18 +138,18 @@ inline int decode_chunk(int max_kv, int nsplit) {
 
 // ---------------------------------------------------------------------------------------------
 // The whole-step call serves many layers with one attention launch.  What differs from layer to layer travels by value:
-// 192 bytes a layer, kStepLayersMax layers in the 4 KB argument block.  The launch leaves each entry in its layer's
+// 184 bytes a layer, kStepLayersMax layers in the 4 KB argument block.  The launch leaves each entry in its layer's
 // workspace, where the step's one plan launch (which covers more layers than fit one argument block) reads it.
 // ---------------------------------------------------------------------------------------------
 struct StepCommon {
     int32_t B, H, D, mode;      // mode: st3_compact_mode
-    int32_t cache_eb, out_bf16; // bytes of a cache element; outputs are bf16 (else float32)
+    int32_t elem_bytes;         // of q, the new rows, the outputs and plain caches: 2 (bf16) or 4 (float32)
     float scale_l2;
     int32_t layers;             // entries of the table
 };
 struct StepLayer {
     const void* q;              // lazy layer: the source layer's workspace
-    void* k;                    // lazy layer: null
+    void* k;                    // lazy layer: null unless it caches keys all the same (they move with an eviction)
     void* v;
     const void* k_new;          // lazy layer: unused
     const void* v_new;
@@ -175,7 +175,7 @@ struct StepLayer {
     uint8_t flags;
 };
 static_assert(sizeof(StepLayer) == 184, "kStepLayersMax entries must fit the kernel-argument block");
-constexpr uint8_t kStepInlineApply = 1, kStepKeepAll = 2, kStepLazy = 4, kStepWantMass = 8;
+constexpr uint8_t kStepInlineApply = 1, kStepKeepAll = 2, kStepLazy = 4, kStepWantMass = 8, kStepE4M3 = 16;
 constexpr int kStepLayersMax = 21;
 constexpr int kStepLayerWords = sizeof(StepLayer) / 4;
 struct StepTable {

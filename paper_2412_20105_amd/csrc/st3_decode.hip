@@ -930,33 +930,33 @@ st3_status enqueue_inherit(const st3_attn_shape* shape, const st3_kv_layer* kv, 
 // batch 12 (7.4 MB) 975 -> 963, batch 16 (9.8 MB) 1290 -> 1270, batch 32 E4M3 (13 MB) 1352 -> 1327, batch 32 (20 MB) 2569 -> 2437.
 constexpr int64_t kStreamStoreBytes = (int64_t)7 << 20;
 
-// Attention of every layer of a checked step: the ordinary layers, up to kStepLayersMax per launch, then the lazy ones.
-// entry[i] receives where layer i's table entry will lie once the launches have run; split: some strip was cut, its
+// Attention of every layer of a checked step: the ordinary layers, up to kStepLayersMax per launch, then the lazy ones, caches of
+// either format in launches of their own (32 layers of the 7B shape, every other cache E4M3, us a step, layer by layer -> so:
+// batch 1 377 -> 60, batch 8 482 -> 290).
+// entry[i] receives where layer i's table entry will lie once the launches have run; split: some strip was cut and its
 // partials are left for the plan to merge.  Returns ST3_ERR_UNSUPPORTED, with nothing enqueued, for a step that a table
 // cannot describe.
 st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const st3_layer_step* layers, int mode,
                                const char* has_heirs, const EvictArgs* plan, StepCommon& common, const StepLayer** entry,
                                bool& split, hipStream_t st) {
     const int B = shape->batch, H = shape->heads, D = shape->head_dim;
-    const int fmt = layers[0].kv.format;
-    common = StepCommon{B, H, D, mode, kv_elem_bytes(shape, &layers[0].kv), shape->dtype == ST3_BF16 ? 1 : 0, scale_log2(shape), 0};
+    common = StepCommon{B, H, D, mode, elem_bytes(shape->dtype), scale_log2(shape), 0};
     int64_t rows[2] = {0, 0};           // of the ordinary and of the lazy layers
     for (int i = 0; i < n_layers; ++i) {
         const st3_layer_step& L = layers[i];
         const int64_t most32 = 0x7fffffff;
-        if (L.kv.format != fmt || L.kv.stride_t > most32 || L.col_stride < 0 || L.col_stride > most32 || L.mass_stride < 0 ||
-            L.mass_stride > most32)
+        if (L.kv.stride_t > most32 || L.col_stride < 0 || L.col_stride > most32 || L.mass_stride < 0 || L.mass_stride > most32)
             return ST3_ERR_UNSUPPORTED;
         rows[L.inherit_from >= 0] += L.seg.max_kv_len + 1;
     }
     const int per = std::min(kStepLayersMax, 65535 / B);        // grid z is B * layers
     if (per < 1) return ST3_ERR_UNSUPPORTED;
     std::vector<StepLayer> e((size_t)n_layers);
-    std::vector<int> stage((size_t)n_layers, 0), members[2];
+    std::vector<int> stage((size_t)n_layers, 0), groups[4];     // layers that may share launches, in launch order
     split = false;
     for (int i = 0; i < n_layers; ++i) {
         const st3_layer_step& L = layers[i];
-        const bool lazy = L.inherit_from >= 0;
+        const bool lazy = L.inherit_from >= 0, coded = L.kv.format == ST3_KV_E4M3;
         const int len = L.seg.max_kv_len + 1;
         const DecodeWs wl = decode_ws(B, H, D, L.kv.capacity);
         StepLayer& s = e[(size_t)i];
@@ -964,7 +964,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
         s.v = L.kv.v; s.v_new = L.v_new; s.out = L.out;
         s.kv_len = L.seg.kv_len; s.vis_len = L.seg.vis_len; s.tail_start = L.seg.tail_start;
         s.score_col = L.score_col; s.id_col = L.id_col; s.mass = plan[i].mass_dst; s.ws = reinterpret_cast<char*>(L.workspace);
-        if (fmt == ST3_KV_E4M3) { s.k_scale = L.kv.k_scale; s.v_scale = L.kv.v_scale; }
+        if (coded) { s.k_scale = L.kv.k_scale; s.v_scale = L.kv.v_scale; }
         s.stride_b = L.kv.stride_b; s.stride_h = L.kv.stride_h; s.stride_t = (int32_t)L.kv.stride_t;
         s.col_stride = (int32_t)L.col_stride; s.mass_stride = (int32_t)L.mass_stride;
         s.sys_len = L.seg.sys_len; s.max_vis = L.seg.max_vis_len; s.max_kv = L.seg.max_kv_len;
@@ -975,7 +975,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
         nsplit = (len + s.chunk - 1) / s.chunk;
         s.nsplit = (uint8_t)nsplit; s.nsplit_cap = (uint8_t)wl.nsplit_cap;
         split = split || nsplit > 1;
-        s.flags = (uint8_t)(plan[i].inline_apply ? kStepInlineApply : 0);
+        s.flags = (uint8_t)((plan[i].inline_apply ? kStepInlineApply : 0) | (coded ? kStepE4M3 : 0));
         if (lazy) {
             const st3_layer_step& S = layers[L.inherit_from];
             const DecodeWs sl = decode_ws(B, H, D, S.kv.capacity);
@@ -995,26 +995,28 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
             if (stage[(size_t)i] > 3 * kLogitStageMaxRows) return ST3_ERR_UNSUPPORTED;
         }
         entry[i] = reinterpret_cast<const StepLayer*>(s.ws + wl.step_entry);
-        members[lazy].push_back(i);
+        groups[2 * lazy + coded].push_back(i);
     }
-    for (int lazy = 0; lazy < 2; ++lazy) {
-        const int n = (int)members[lazy].size();
+    for (const std::vector<int>& members : groups) {
+        const int n = (int)members.size();
         const int launches = (n + per - 1) / per;
         for (int g = 0, i0 = 0; g < launches; ++g) {
             const int cnt = (n - i0 + launches - g - 1) / (launches - g);       // as equal as can be
+            const int first = members[(size_t)i0];
+            const bool lazy = layers[first].inherit_from >= 0;
+            const st3_kv_layer* kv = &layers[first].kv;
             StepTable t{};
             t.c = common; t.c.layers = cnt;
             int most = 1, stage_rows = 0;
-            int64_t row_bytes = 0;
             for (int j = 0; j < cnt; ++j) {
-                const int i = members[lazy][(size_t)(i0 + j)];
+                const int i = members[(size_t)(i0 + j)];
                 t.layer[j] = e[(size_t)i];
                 most = std::max(most, (int)e[(size_t)i].nsplit);
                 stage_rows = std::max(stage_rows, stage[(size_t)i]);
-                row_bytes += (int64_t)B * H * D * (2 * common.cache_eb + elem_bytes(shape->dtype));
             }
-            if (lazy) ST3_DISPATCH_KV(launch_inherit_layers, shape, &layers[0].kv, t, most, st);
-            else ST3_DISPATCH_KV(launch_attend_layers, shape, &layers[0].kv, t, most, stage_rows, row_bytes > kStreamStoreBytes, st);
+            const int64_t row_bytes = (int64_t)cnt * B * H * D * (2 * kv_elem_bytes(shape, kv) + elem_bytes(shape->dtype));
+            if (lazy) ST3_DISPATCH_KV(launch_inherit_layers, shape, kv, t, most, st);
+            else ST3_DISPATCH_KV(launch_attend_layers, shape, kv, t, most, stage_rows, row_bytes > kStreamStoreBytes, st);
             i0 += cnt;
         }
     }

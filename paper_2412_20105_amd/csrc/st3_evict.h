@@ -143,8 +143,9 @@ __device__ __forceinline__ EvictArgs plan_from_entry(const StepCommon& c, const 
     a.appended = 1;
     a.inline_apply = (e.flags & kStepInlineApply) != 0;
     a.k = reinterpret_cast<char*>(e.k); a.v = reinterpret_cast<char*>(e.v);
-    a.stride_b = e.stride_b * c.cache_eb; a.stride_h = e.stride_h * c.cache_eb; a.stride_t = (int64_t)e.stride_t * c.cache_eb;
-    a.H = c.H; a.vecs_per_row = c.D * c.cache_eb / 16;
+    const int eb = (e.flags & kStepE4M3) ? 1 : c.elem_bytes;
+    a.stride_b = e.stride_b * eb; a.stride_h = e.stride_h * eb; a.stride_t = (int64_t)e.stride_t * eb;
+    a.H = c.H; a.vecs_per_row = c.D * eb / 16;
     // a lazy layer's mass is finished from what its source's launch left
     const bool lazy = (e.flags & kStepLazy) != 0;
     const DecodeWs ml = lazy ? decode_ws_sized(c.B, c.H, c.D, e.hint_base, e.src_nsplit_cap) : wl;
@@ -325,7 +326,7 @@ __device__ __forceinline__ void merge_chunks(const StepCommon& c, const StepLaye
             }
             o /= l;
         }
-        if (c.out_bf16) reinterpret_cast<uint16_t*>(e.out)[bh * D + d] = (uint16_t)f32_to_bf16_bits(o);
+        if (c.elem_bytes == 2) reinterpret_cast<uint16_t*>(e.out)[bh * D + d] = (uint16_t)f32_to_bf16_bits(o);
         else reinterpret_cast<float*>(e.out)[bh * D + d] = o;
     }
 }

@@ -12,7 +12,7 @@ MODE = st3.ST3_HOLE_FILL
 
 
 class Step:
-    """One step's buffers; two objects of equal arguments hold equal values."""
+    """One step's buffers; two objects of equal arguments hold equal values.  e4m3: True, or the layers whose caches are E4M3."""
 
     def __init__(self, L, B, H, d, dtype, vis, tail, lazy=None, fixed_tail=True, e4m3=False, drop=2):
         g = torch.Generator(device=DEV).manual_seed(L * 1009 + B * 31 + H)
@@ -29,11 +29,12 @@ class Step:
             n = vis[l % len(vis)] if src is None else self.state[src]["n"]
             rows = 3 + n + tail
             cap = rows + 5 + l % 3
-            scale = torch.full((B, H), 0.01, dtype=torch.float32, device=DEV) if e4m3 else None
+            coded = e4m3 if isinstance(e4m3, bool) else l in e4m3
+            scale = torch.full((B, H), 0.01, dtype=torch.float32, device=DEV) if coded else None
 
             def cache():
                 x = rnd(B, H, cap, d)
-                return (x * 50).to(torch.float8_e4m3fn).view(torch.uint8) if e4m3 else x.to(dtype)
+                return (x * 50).to(torch.float8_e4m3fn).view(torch.uint8) if coded else x.to(dtype)
 
             k, v = None if src is not None else cache(), cache()
             s = {"n": n, "k": k, "v": v, "kv_len": torch.full((B,), rows, dtype=torch.int32, device=DEV),
