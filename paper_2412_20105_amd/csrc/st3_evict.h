@@ -3,6 +3,8 @@
 // device code of the selection and eviction kernels.
 #pragma once
 
+#include <cstddef>
+
 #include "st3_decode.h"
 
 namespace st3 {
@@ -184,13 +186,14 @@ inline int plan_threads(int64_t plans, int most_vis) {
 constexpr int kPlanMaxInline = 64;          // moves of an eviction that the plan workgroup applies itself (at most 48 evicted rows)
 
 struct PlanShared {
-    uint32_t keys[kSelLdsKeys];
-    int hist[4][256];
+    alignas(16) uint32_t keys[kSelLdsKeys];
+    alignas(16) int hist[4][256];       // scanned as int4
     float hm[1024], hrl[1024];
     int wave_tot[2][kPlanThreadsFew / kWave];
     int mv[kPlanMaxInline][2];
     int sel_bin, sel_want, sel_cnt, red;
 };
+static_assert(alignof(PlanShared) == 16 && offsetof(PlanShared, hist) % 16 == 0, "plan_select reads four bins at once");
 
 // Ranks of two flags over the workgroup in thread order: r1 / r2 = how many threads before this one have the flag,
 // t1 / t2 = how many in all.  One barrier; calls in a row alternate `parity`.
