@@ -32,22 +32,28 @@ __device__ __forceinline__ void head_norms(const float* part_ml, int b, int H, i
     __syncthreads();
 }
 
-// sum over rows [r0, r1) of exp2(x[r * stride] - m[r]) * rl[r], in row order, with kUH loads in flight.  r0 and r1 are the
-// same for the lanes of a wave.
-__device__ __forceinline__ float prob_sum(const float* x, int64_t stride, const float* m, const float* rl, int r0, int r1) {
-    constexpr int kUH = 12;
-    float acc = 0.f;
-    for (int r = r0; r < r1; r += kUH) {
-        float v[kUH];
+// acc + the sum over rows [r, r1) of exp2(x[r * stride] - m[r]) * rl[r], in row order, at most U of them and U loads in flight.
+template <int U>
+__device__ __forceinline__ float prob_sum_some(float acc, const float* x, int64_t stride, const float* m, const float* rl, int r, int r1) {
+    float v[U];
 #pragma unroll
-        for (int u = 0; u < kUH; ++u) v[u] = x[(int64_t)min(r + u, r1 - 1) * stride];
+    for (int u = 0; u < U; ++u) v[u] = x[(int64_t)min(r + u, r1 - 1) * stride];
 #pragma unroll
-        for (int u = 0; u < kUH; ++u) {
-            const int rr = min(r + u, r1 - 1);
-            const float p = exp2_fast(v[u] - m[rr]) * rl[rr];
-            acc += r + u < r1 ? p : 0.f;
-        }
+    for (int u = 0; u < U; ++u) {
+        const int rr = min(r + u, r1 - 1);
+        const float p = exp2_fast(v[u] - m[rr]) * rl[rr];
+        acc += r + u < r1 ? p : 0.f;
     }
+    return acc;
+}
+
+// The same over rows [r0, r1), eight loads in flight (twelve: 7B batch 1 58.7 us a step instead of 57.9); up to four rows do not
+// take the work of eight.  r0 and r1 are the same for the lanes of a wave.
+__device__ __forceinline__ float prob_sum(const float* x, int64_t stride, const float* m, const float* rl, int r0, int r1) {
+    if (r0 >= r1) return 0.f;
+    if (r1 - r0 <= 4) return prob_sum_some<4>(0.f, x, stride, m, rl, r0, r1);
+    float acc = 0.f;
+    for (int r = r0; r < r1; r += 8) acc = prob_sum_some<8>(acc, x, stride, m, rl, r, r1);
     return acc;
 }
 

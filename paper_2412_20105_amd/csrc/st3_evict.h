@@ -4,6 +4,7 @@
 #pragma once
 
 #include <cstddef>
+#include <type_traits>
 
 #include "st3_decode.h"
 
@@ -164,41 +165,61 @@ typedef uint32_t u32x4_v __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------------------------
 // The plan workgroup.  Latency bound: a chain of dependent steps over a few kilobytes per (layer, sequence), and at small
-// batches there are fewer plans than compute units, so it takes as many threads as a workgroup may have.  Its parts before
+// batches there are fewer plans than compute units, so it takes as many threads as there is work for (plan_threads).  Its parts before
 // -> after the 256-thread form, which kept eight head-strided loads in flight, ran six barriers per radix digit and went
 // through a move list in global memory (us a launch: high resolution batch 8 77 -> 30, 13B batch 8 with fast annealing 66 ->
 // 33, 7B batch 1 21 -> 13):
-//   mass      heads are dealt to thread groups, 12 loads in flight per thread
+//   mass      heads are dealt to thread groups, 8 loads in flight per thread
 //   select    two barriers per digit (one wave scans the histogram), and no further digit once the k-th key is apart
 //   lists     ranks from ballots, the list of a small eviction in LDS
 //   rows      moved past the caches: lines left dirty in L2 are written back between the reads of the next attention
 //             (whole step, ordinary -> non-temporal: 13B batch 8 with fast annealing 541 -> 506 us, 7B batch 16 layer by layer
 //             733 -> 704)
 // ---------------------------------------------------------------------------------------------
-constexpr int kPlanThreadsFew = 1024;       // one plan per compute unit at a time
-constexpr int kPlanThreadsMany = 512;       // three
-// Half the threads when the plans are several per compute unit, or so small that starting and stopping the waves is what
-// takes time.  Whole step, us, 1024 -> 512 threads: 32 plans (7B batch 1) 60 -> 62, 256 (high resolution) 648 -> 653, 320 (13B
-// batch 8) 506 -> 524, 640 (batch 16) 1248 -> 1244, 1280 (batch 32) 2423 -> 2410; 2 plans over 64 rows 16.8 -> 15.0.
-inline int plan_threads(int64_t plans, int most_vis) {
-    return plans > 512 || most_vis <= 128 ? kPlanThreadsMany : kPlanThreadsFew;
+constexpr int kPlanThreadsMost = 1024;
+// Threads of a plan workgroup: what its chain of steps is spread over (mass: rows times heads; ranking: rows), against waves that
+// start, meet at barriers and stop for nothing, and against plans that wait for each other when there are several per compute
+// unit (46 KB of LDS: three with 256 or 512 threads, two with 1024).  us a call with 256 / 512 / 1024 threads, and with the
+// 256-thread form of before: layer step of 2 heads, 16 rows, evicting 8 14.1 / 14.2 / 14.5 (14.3), 40 heads, 64 rows 15.8 / 16.4 /
+// 17.9 (17.7), 32 heads, 128 rows 19.5 / 19.1 / 20.4 (20.6); select-and-compact of 300 rows, batch 1 10.3 / 9.4 / 10.1 (10.8), batch 512
+// 12.6 / 12.1 / 19.1 (13.2), 576 rows, batch 256 13.2 / 12.4 / 12.2 (13.8), 16 rows, batch 2048 25 (256 threads) against 64 (1024);
+// whole steps, 512 -> 1024: 7B batch 1 (32 plans of up to 288 rows) 59.5 -> 58.9, 13B batch 8 (320 plans, up to 497 rows) 515 ->
+// 509, high resolution batch 8 645 -> 638; 40 layers, batch 12, 8 heads, 576 rows (480 plans) 127 -> 135, which the rule takes.
+inline int plan_threads(int64_t plans, int most_vis, int heads) {       // heads: 1 when no mass is to be finished
+    const int64_t mass = (int64_t)most_vis * heads;
+    if ((plans <= 512 && mass > 8192) || (plans <= 256 && most_vis > 512)) return 1024;
+    return most_vis > 256 || mass >= 3072 ? 512 : 256;
+}
+// Threads of a workgroup that ranks one row of n scores.  us a call, 256 / 512 / 1024 threads (256-thread form of before): 256
+// scores, batch 8 4.3 / 4.2 / 4.8 (5.3), batch 8192 27.9 / 30.6 / 64.0 (39.9), 365 scores 4.9 / 4.5 / 4.9 (6.3) and 35.4 / 34.3 / 68.4
+// (53.9), 2880 scores, batch 8 14.4 / 10.1 / 9.0 (18.3), batch 1024 21.1 / 18.3 / 23.1 (27.0).
+inline int topk_threads(int64_t rows, int n) { return n <= 256 ? 256 : n > 1024 && rows <= 512 ? 1024 : 512; }
+// Runs go(NT) with that many threads as a constant.
+template <typename Go>
+void with_threads(int threads, Go go) {
+    if (threads == 1024) go(std::integral_constant<int, 1024>{});
+    else if (threads == 512) go(std::integral_constant<int, 512>{});
+    else go(std::integral_constant<int, 256>{});
 }
 constexpr int kPlanMaxInline = 64;          // moves of an eviction that the plan workgroup applies itself (at most 48 evicted rows)
 
-struct PlanShared {
+// What ranking a row of scores needs, and what a plan needs besides.
+struct SelectShared {
     alignas(16) uint32_t keys[kSelLdsKeys];
     alignas(16) int hist[4][256];       // scanned as int4
-    float hm[1024], hrl[1024];
-    int wave_tot[2][kPlanThreadsFew / kWave];
-    int mv[kPlanMaxInline][2];
+    int wave_tot[2][kPlanThreadsMost / kWave];
     int sel_bin, sel_want, sel_cnt, red;
 };
-static_assert(alignof(PlanShared) == 16 && offsetof(PlanShared, hist) % 16 == 0, "plan_select reads four bins at once");
+static_assert(alignof(SelectShared) == 16 && offsetof(SelectShared, hist) % 16 == 0, "plan_select reads four bins at once");
+struct PlanShared : SelectShared {
+    float hm[1024], hrl[1024];
+    int mv[kPlanMaxInline][2];
+};
 
 // Ranks of two flags over the workgroup in thread order: r1 / r2 = how many threads before this one have the flag,
 // t1 / t2 = how many in all.  One barrier; calls in a row alternate `parity`.
 template <int NT>
-__device__ __forceinline__ void plan_ranks(bool f1, bool f2, int parity, PlanShared& sm, int& r1, int& r2, int& t1, int& t2) {
+__device__ __forceinline__ void plan_ranks(bool f1, bool f2, int parity, SelectShared& sm, int& r1, int& r2, int& t1, int& t2) {
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const unsigned long long b1 = __ballot(f1), b2 = __ballot(f2), below = (1ull << lane) - 1;
     if (lane == 0) sm.wave_tot[parity][wave] = __popcll(b1) | (__popcll(b2) << 16);
@@ -220,7 +241,7 @@ __device__ __forceinline__ void plan_ranks(bool f1, bool f2, int parity, PlanSha
 // `want` becomes how many of the elements equal to the returned digits belong to the top set, `ties` how many there are.
 // Ends with a barrier behind every use of sm.hist.
 template <int NT, class F>
-__device__ __forceinline__ uint32_t plan_select(F f, int n, int& want, int& ties, PlanShared& sm) {
+__device__ __forceinline__ uint32_t plan_select(F f, int n, int& want, int& ties, SelectShared& sm) {
     const int tid = threadIdx.x;
     for (int i = tid; i < 4 * 256; i += NT) (&sm.hist[0][0])[i] = 0;
     __syncthreads();
@@ -341,7 +362,8 @@ template <int NT>
 __device__ __forceinline__ void plan_mass(const EvictArgs& a, int b, int n, int ns, PlanShared& sm) {
     const int tid = threadIdx.x, H = a.H;
     head_norms<NT>(a.part_ml, b, H, ns, a.nsplit_cap, sm.hm, sm.hrl);
-    const int keys = n <= 256 ? 256 : n <= 512 ? 512 : NT;
+    // (few heads: one group, whose sums need not meet)
+    const int keys = H <= 8 ? NT : NT == 256 && n <= 64 ? 64 : NT == 256 && n <= 128 ? 128 : min(NT, n <= 256 ? 256 : n <= 512 ? 512 : NT);
     const int groups = NT / keys, per = (H + groups - 1) / groups;
     const int g = __builtin_amdgcn_readfirstlane(tid / keys);     // (a wave lies in one group)
     const int h0 = g * per, h1 = min(H, h0 + per);

@@ -30,11 +30,10 @@ struct TopkArgs {
     int64_t idx_stride;
 };
 
-// One workgroup per row: latency bound, so it has as many threads as there are (365 candidates, batch 8: 7.2 us with 256
-// threads, 4.9 with 1024).
-__global__ __launch_bounds__(kPlanThreadsFew) void select_topk_kernel(TopkArgs a) {
-    constexpr int NT = kPlanThreadsFew;
-    __shared__ PlanShared sm;
+// One workgroup per row, latency bound (topk_threads).
+template <int NT>
+__global__ __launch_bounds__(NT) void select_topk_kernel(TopkArgs a) {
+    __shared__ SelectShared sm;
     const int b = blockIdx.x, tid = threadIdx.x;
     int n = a.n_dev ? a.n_dev[b] : a.n;
     n = max(0, min(n, a.n));
@@ -146,9 +145,10 @@ __global__ __launch_bounds__(256) void compact_rows_kernel(CompactArgs a) {
 // Decode-time eviction: ranking + move list + column update (one workgroup per sequence), then
 // a second kernel that applies the move list to every (b,h) strip of K and V.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kPlanThreadsFew) void evict_plan_kernel(EvictArgs a) {
+template <int NT>
+__global__ __launch_bounds__(NT) void evict_plan_kernel(EvictArgs a) {
     __shared__ PlanShared sm;
-    evict_plan_body<kPlanThreadsFew>(a, blockIdx.x, sm);
+    evict_plan_body<NT>(a, blockIdx.x, sm);
 }
 
 // ---- st3_gather_rows: out-of-place gather of kept rows, several tensors per launch -------------
@@ -329,7 +329,9 @@ st3_status build_evict_args(const st3_attn_shape* shape, const st3_kv_layer* kv,
 }
 
 void launch_evict_plan(const EvictArgs& ea, int B, hipStream_t st) {
-    evict_plan_kernel<<<B, kPlanThreadsFew, 0, st>>>(ea);
+    with_threads(plan_threads(B, ea.max_vis, ea.mass_dst != nullptr ? ea.H : 1), [&](auto nt) {
+        evict_plan_kernel<decltype(nt)::value><<<B, decltype(nt)::value, 0, st>>>(ea);
+    });
 }
 
 // Up to kPlanBatch plans travel by value in the kernel arguments; grid (B, layers of the batch).
@@ -355,10 +357,9 @@ void launch_evict_plan_batch(const EvictArgs* plans, int n, int B, hipStream_t s
             most_vis = std::max(most_vis, plans[i0 + i].max_vis);
         }
         for (int i = cnt; i < kPlanBatch; ++i) batch.layer[i] = EvictArgs{};
-        if (plan_threads((int64_t)B * cnt, most_vis) == kPlanThreadsFew)
-            evict_plan_batch_kernel<kPlanThreadsFew><<<dim3(B, cnt), kPlanThreadsFew, 0, st>>>(batch);
-        else
-            evict_plan_batch_kernel<kPlanThreadsMany><<<dim3(B, cnt), kPlanThreadsMany, 0, st>>>(batch);
+        with_threads(plan_threads((int64_t)B * cnt, most_vis, plans[i0].H), [&](auto nt) {
+            evict_plan_batch_kernel<decltype(nt)::value><<<dim3(B, cnt), decltype(nt)::value, 0, st>>>(batch);
+        });
     }
 }
 
@@ -394,10 +395,9 @@ void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry,
         for (int i = cnt; i < kPlanTableMax; ++i) table.layer[i] = nullptr;
         const int merge_wgs = merge ? (c.H + kMergeHeads - 1) / kMergeHeads : 0;
         const dim3 grid(c.B, cnt, 1 + merge_wgs);
-        if (plan_threads((int64_t)c.B * cnt, most_vis) == kPlanThreadsFew)
-            evict_plan_table_kernel<kPlanThreadsFew><<<grid, kPlanThreadsFew, 0, st>>>(table);
-        else
-            evict_plan_table_kernel<kPlanThreadsMany><<<grid, kPlanThreadsMany, 0, st>>>(table);
+        with_threads(plan_threads((int64_t)c.B * cnt, most_vis, c.H), [&](auto nt) {
+            evict_plan_table_kernel<decltype(nt)::value><<<grid, decltype(nt)::value, 0, st>>>(table);
+        });
     }
 }
 
@@ -576,7 +576,9 @@ extern "C" st3_status st3_select_topk(const float* scores, int64_t score_stride,
     st3::TopkArgs a{};
     a.scores = scores; a.score_stride = score_stride; a.ids = tie_ids; a.id_stride = id_stride;
     a.n_dev = n_dev; a.n = n; a.k = k; a.mask = keep_mask; a.idx = keep_idx; a.idx_stride = idx_stride;
-    st3::select_topk_kernel<<<batch, st3::kPlanThreadsFew, 0, reinterpret_cast<hipStream_t>(stream)>>>(a);
+    st3::with_threads(st3::topk_threads(batch, n), [&](auto nt) {
+        st3::select_topk_kernel<decltype(nt)::value><<<batch, decltype(nt)::value, 0, reinterpret_cast<hipStream_t>(stream)>>>(a);
+    });
     return st3::check_launch();
 }
 
