@@ -47,13 +47,11 @@ __device__ __forceinline__ float prob_sum_some(float acc, const float* x, int64_
     return acc;
 }
 
-// The same over rows [r0, r1), eight loads in flight (twelve: 7B batch 1 58.7 us a step instead of 57.9); up to four rows do not
-// take the work of eight.  r0 and r1 are the same for the lanes of a wave.
+// The same over rows [r0, r1), U loads in flight.  r0 and r1 are the same for the lanes of a wave.
+template <int U>
 __device__ __forceinline__ float prob_sum(const float* x, int64_t stride, const float* m, const float* rl, int r0, int r1) {
-    if (r0 >= r1) return 0.f;
-    if (r1 - r0 <= 4) return prob_sum_some<4>(0.f, x, stride, m, rl, r0, r1);
     float acc = 0.f;
-    for (int r = r0; r < r1; r += 8) acc = prob_sum_some<8>(acc, x, stride, m, rl, r, r1);
+    for (int r = r0; r < r1; r += U) acc = prob_sum_some<U>(acc, x, stride, m, rl, r, r1);
     return acc;
 }
 
