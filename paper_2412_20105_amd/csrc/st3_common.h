@@ -68,15 +68,13 @@ inline float scale_log2(const st3_attn_shape* s) {
 // ---------------------------------------------------------------------------------------------
 constexpr int kMaxWindow = 16;
 #ifndef ST3_DECODE_TARGET_WGS
-#define ST3_DECODE_TARGET_WGS 256      // one workgroup per compute unit; 512-1024 measured 5-14 % slower at B*H = 320-512
+#define ST3_DECODE_TARGET_WGS 256      // one workgroup per compute unit, where a cut costs a merge launch
 #endif
 constexpr int kDecodeTargetWgs = ST3_DECODE_TARGET_WGS;     // split the KV range until about this many workgroups exist
 #ifndef ST3_DECODE_TARGET_WGS_MERGED
 #define ST3_DECODE_TARGET_WGS_MERGED 1024
 #endif
-// ... and this many for a call that finishes its mass in a second launch, where merging the chunk partials costs no launch
-// of its own (13B shape, attend launch: B = 4 14.1 -> 11.7 us, B = 8 21.7 -> 20.2 us; 256, 512, 1024, 1536, 2048 measured),
-// unless B*H alone reaches half of it (B*H >= 512 ran the same or slower when cut)
+// ... and at most this many where it costs none: a call that finishes its mass in a second launch (merged_target)
 constexpr int kDecodeTargetWgsMerged = ST3_DECODE_TARGET_WGS_MERGED;
 constexpr int kDecodeTargetWgsMax = kDecodeTargetWgs > kDecodeTargetWgsMerged ? kDecodeTargetWgs : kDecodeTargetWgsMerged;
 constexpr int kDecodeMaxSplit = 64;
@@ -128,6 +126,19 @@ inline int step_nsplit(int B, int H, int len, int64_t rows) {
     if (chunk > kLogitStageMaxRows) chunk = kLogitStageMaxRows;
     const int64_t ns = (len + chunk - 1) / chunk;
     return ns < 1 ? 1 : ns > kDecodeMaxSplit ? kDecodeMaxSplit : (int)ns;
+}
+// The target of a call that finishes its mass in a second launch (decode_finish_kernel merges chunks one after the other, so many
+// of them cost it more than they save).  us a call at targets of 256 / 512 / 1024, equal lengths, bf16 d = 128 unless said:
+//   B*H 16: 250 rows 7.5 / 7.1 / 7.0, 739 rows 9.1 / 9.4 / 9.4, 3136 rows 12.7 / 15.1 / 21.5 (d = 64 250 rows 6.9 / 7.2 / 7.0)
+//   B*H 64: 1400 rows 14.2 / 12.9 / 15.1, float32 3136 rows 48.6 / 37.4 / 40.3;  B*H 128: 1400 rows 26.1 / 19.0 / 20.8
+//   B*H 140: 1400 rows 29.0 / 22.8 / 21.4;  B*H 180, E4M3 d = 64, 300 rows 8.3 / 9.1 / 9.9;  B*H 200: 1111 rows 24.6 / 24.2 / 23.9
+//   B*H 320: 1111 rows 40.5 / - / 33.4 (256: one chunk), float32 3136 rows 162 / - / 170;  B*H 360: 3136 rows 104 / - / 100,
+//   ragged 71 / - / 62, float32 189 / - / 193;  B*H 440: 3136 rows 116.5 / - / 122.5, ragged 92 / - / 80;  480: 126 / - / 127
+inline int merged_target(int64_t bh, int max_kv, int head_dim, int cache_eb) {
+    if (bh > (cache_eb < 4 ? 400 : 320)) return kDecodeTargetWgs;
+    if (head_dim * cache_eb < 256 && max_kv <= 5 * kDecodeMinChunk) return kDecodeTargetWgs;
+    if (bh < 48) return max_kv <= 4 * kDecodeMinChunk ? kDecodeTargetWgsMerged : kDecodeTargetWgs;
+    return bh <= 128 && cache_eb < 4 ? kDecodeTargetWgsMerged / 2 : kDecodeTargetWgsMerged;
 }
 // Chunk length for that split count: a multiple of 32 rows.
 inline int decode_chunk(int max_kv, int nsplit) {

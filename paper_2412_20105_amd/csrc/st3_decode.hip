@@ -818,7 +818,8 @@ st3_status enqueue_decode(const st3_attn_shape* shape, const void* q, const st3_
     const bool mass_now = want_mass && !defer_mass;
     // a call that finishes its mass has a second launch anyway, so that a cut costs it no launch (13B shape, five sequences
     // of 173 to 1111 rows, attention + finish: 26 us in 200 workgroups, 20.5 us in 1000)
-    da.nsplit = decode_nsplit(B, H, max_kv_len, mass_now ? kDecodeTargetWgsMerged : kDecodeTargetWgs);
+    const int target = mass_now ? merged_target((int64_t)B * H, max_kv_len, D, kv_elem_bytes(shape, kv)) : kDecodeTargetWgs;
+    da.nsplit = decode_nsplit(B, H, max_kv_len, target);
     if (da.nsplit > wl.nsplit_cap) da.nsplit = wl.nsplit_cap;
     da.nsplit_cap = wl.nsplit_cap;
     da.chunk = decode_chunk(max_kv_len, da.nsplit);

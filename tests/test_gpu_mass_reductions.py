@@ -40,7 +40,9 @@ def test_prefill_mass(B, H, n, sys_len, vis, window):
 @pytest.mark.parametrize("noalloc", [False, True])
 @pytest.mark.parametrize("B,H,lens", [
     (1, 1, [1]),
-    (1, 3, [4000]),                 # as many chunks as a strip may have
+    (1, 3, [4096]),                 # 63 chunks, the most that this call cuts
+    (1, 16, [256]), (1, 16, [257]), (1, 47, [700]), (1, 48, [700]),        # few strips: finer cuts for short ones only
+    (2, 64, [700, 31]), (3, 43, [700, 64, 1]), (8, 40, [600, 1, 65, 300, 64, 128, 599, 2]), (3, 107, [600, 33, 257]),
     (3, 1, [64, 65, 700]),
     (5, 40, [173, 1111, 600, 64, 999]),
     (2, 65, [513, 300]),
