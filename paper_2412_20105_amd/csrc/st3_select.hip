@@ -167,11 +167,12 @@ struct GatherArgs {
 #define ST3_GATHER_NT 1
 #endif
 constexpr int kGatherUR = ST3_GATHER_UR;
-// Written bytes from which the rows go past the caches: source and destination together no longer fit the last-level cache
-// (256 MB), so that nothing that reads the rows next would find them there.  A prune event of the 13B shape, us, ordinary ->
-// non-temporal stores: batch 4 (63 MB written) 45.0 -> 46.0, batch 8 (126 MB) 57.1 -> 60.1, batch 10 (158 MB) 74.4 -> 70.8, batch 16
-// 109.5 -> 102.2, batch 32 199.5 -> 186.0; a job of layers of 8 to 33 MB 4855 -> 4902.
-constexpr int64_t kGatherStreamBytes = (int64_t)128 << 20;
+// Written bytes above which the rows go past the caches.  The launch itself is 10 % faster so from 128 MB on, but what reads the
+// rows next (the layer's attention) finds most of them in the last-level cache (256 MB) after ordinary stores, up to well
+// beyond its size.  us, ordinary -> non-temporal stores, gather alone and gather + one read of its output, buffers in rotation:
+// 128 MB written 54 -> 49, 141 -> 157; 187 MB 84 -> 73, 222 -> 246; 250 MB 110 -> 96, 284 -> 305; 375 MB 162 -> 141, 449 -> 455;
+// 437 MB 171 -> 154, 514 -> 505.
+constexpr int64_t kGatherStreamBytes = (int64_t)400 << 20;
 template <bool NTS>        // NTS: non-temporal stores
 __global__ __launch_bounds__(256) void gather_rows_kernel(GatherArgs a) {
     constexpr int UR = kGatherUR;
