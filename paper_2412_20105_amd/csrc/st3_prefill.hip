@@ -63,12 +63,12 @@ struct PrefillMassArgs {
 
 // grid (ceil(vis_len/64), B).  mass[b,j] = (1/H) sum_h sum_w p_{h,w}[sys_len+j]; a window row
 // that precedes key sys_len+j cannot see it (causal mask) and contributes nothing.  Latency bound (4 bytes per head, window
-// row and key): one of 16 waves takes a sixteenth of the (head, row) pairs, eight loads in flight, and the sixteenths are
-// added in order.  One thread per key that walked all heads took 12 us for one sequence and 24 us for 32; a prefill call
+// row and key): one of 16 waves takes a sixteenth of the (head, row) pairs, kUR loads in flight (eight, or the power of two that
+// covers its pairs when they are fewer: each pair left over costs a division), and the sixteenths are added in order.  One thread per key that walked all heads took 12 us for one sequence and 24 us for 32; a prefill call
 // of one 7B layer, 310 tokens, went from 30.9 to 21.2 us, of one 13B layer, batch 32, 739 tokens, from 403 to 398.
 constexpr int kMassWaves = 16;
+template <int kUR>
 __global__ __launch_bounds__(kMassWaves * kWave) void prefill_mass_kernel(PrefillMassArgs a) {
-    constexpr int kUR = 8;
     __shared__ float part[kMassWaves][kWave];
     const int b = blockIdx.y, lane = threadIdx.x % kWave, g = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int j = blockIdx.x * kWave + lane;
@@ -172,7 +172,12 @@ extern "C" st3_status st3_prefill_attention(const st3_attn_shape* shape, const s
     }
     if (want_mass) {
         PrefillMassArgs m{a.pre_logits, a.pre_ml, vis_mass, mass_stride, n, sys_len, vis_len, score_window, H};
-        prefill_mass_kernel<<<dim3((vis_len + kWave - 1) / kWave, B), kMassWaves * kWave, 0, st>>>(m);
+        const dim3 grid((vis_len + kWave - 1) / kWave, B);
+        const int per = (H * score_window + kMassWaves - 1) / kMassWaves;
+        if (per <= 1) prefill_mass_kernel<1><<<grid, kMassWaves * kWave, 0, st>>>(m);
+        else if (per <= 2) prefill_mass_kernel<2><<<grid, kMassWaves * kWave, 0, st>>>(m);
+        else if (per <= 4) prefill_mass_kernel<4><<<grid, kMassWaves * kWave, 0, st>>>(m);
+        else prefill_mass_kernel<8><<<grid, kMassWaves * kWave, 0, st>>>(m);
     }
     return check_launch();
 }
