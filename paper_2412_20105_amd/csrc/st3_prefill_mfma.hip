@@ -613,8 +613,10 @@ __global__ __launch_bounds__(256, 1) void prefill_mfma_split_kernel(PrefillArgs 
 // the lanes stay balanced a little beyond that.  Measured, us a call, 1 / 2 / 4 groups, D = 128 (strips x tokens): 8 x 739
 // 29.4 / 23.0 / 18.7, 16 x 420 22.1 / 20.0 / 15.9, 32 x 310 18.1 / 16.8 / 17.3, 32 x 739 30.6 / 24.2 / 32.6, 64 x 420 23.6 /
 // 20.8 / 33.3, but 24 x 739 30.5 / 32.6, 40 x 420 22.7 / 25.3, 64 x 560 26.9 / 29.9, 96 x 224 17.3 / 19.8; D = 64: 32 x 420
-// 18.5 / 16.7 / 14.3, 64 x 739 26.3 / 21.7 / 26.7, 96 x 560 22.9 / 23.5 / 27.1.
+// 18.5 / 16.7 / 14.3, 64 x 739 26.3 / 21.7 / 26.7, 96 x 560 22.9 / 23.5 / 27.1.  Prompts of one key tile leave a second group
+// nothing: 32 x 64, D = 128, 10.7 us with one group, 12.9 with four.
 int key_groups(int D, int n, int64_t strips) {
+    if (n <= kBN) return 1;
     const int64_t places = D == 128 ? 256 : 512;
     if ((n + 31) / 32 * strips <= places) return 4;
     const int64_t two = (n + 63) / 64 * strips;
