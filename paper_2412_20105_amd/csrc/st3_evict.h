@@ -9,99 +9,12 @@
 #include "st3_decode.h"
 
 namespace st3 {
-constexpr int kSelThreads = 256;
-constexpr int kSelWaves = kSelThreads / kWave;
 constexpr int kSelLdsKeys = 8192;
 
 __device__ __forceinline__ uint32_t score_key(float f) {
     uint32_t u = __float_as_uint(f);
     if (u == 0x80000000u) u = 0u;                       // -0.0 ranks with +0.0
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);  // larger float <-> larger key
-}
-
-struct SelShared {
-    uint32_t keys[kSelLdsKeys];
-    int hist[256];
-    int wave_tot[kSelWaves];
-    int sel_bin, sel_want, sel_cnt;
-};
-
-// Inclusive scan of one int per thread over the 256 threads of the block, in thread order.
-__device__ __forceinline__ int block_incl_scan(int v, SelShared& sm) {
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        int t = __shfl_up(v, off);
-        if (lane >= off) v += t;
-    }
-    __syncthreads();                                    // protects wave_tot from the previous use
-    if (lane == kWave - 1) sm.wave_tot[wave] = v;
-    __syncthreads();
-    int base = 0;
-#pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) base += (w < wave) ? sm.wave_tot[w] : 0;
-    return v + base;
-}
-
-// Finds, among the elements i in [0,n) for which f(i, key) is true, the key of rank `want`
-// (1-based, descending).  Returns it; `want` becomes the number of elements equal to that key
-// that still belong to the top set, `ties` the number of elements equal to it.
-template <class F>
-__device__ __forceinline__ uint32_t radix_select_desc(F f, int n, int& want, int& ties, SelShared& sm) {
-    uint32_t prefix = 0, pmask = 0;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        sm.hist[threadIdx.x] = 0;
-        __syncthreads();
-        for (int i = threadIdx.x; i < n; i += kSelThreads) {
-            uint32_t key;
-            if (f(i, key) && (key & pmask) == prefix) atomicAdd(&sm.hist[(key >> shift) & 255u], 1);
-        }
-        __syncthreads();
-        int v = sm.hist[255 - threadIdx.x];             // thread order = descending bin order
-        int incl = block_incl_scan(v, sm);
-        if (incl >= want && incl - v < want) {
-            sm.sel_bin = 255 - threadIdx.x;
-            sm.sel_want = want - (incl - v);
-            sm.sel_cnt = v;
-        }
-        __syncthreads();
-        prefix |= (uint32_t)sm.sel_bin << shift;
-        pmask |= 255u << shift;
-        want = sm.sel_want;
-        ties = sm.sel_cnt;
-        __syncthreads();
-    }
-    return prefix;
-}
-
-// The threshold of the top-k entries of one row (is_kept tells which they are).  Requires n <= kSelLdsKeys
-// when `staged`; otherwise keys are recomputed from global memory on every pass.
-// ids == nullptr: the position is the id.
-__device__ __forceinline__ void mark_topk(const float* scores, const int32_t* ids, int n, int k, bool staged, SelShared& sm,
-                          uint32_t& thr, uint32_t& thr_id, bool& all_ties) {
-    auto key_at = [&](int i) -> uint32_t { return staged ? sm.keys[i] : score_key(scores[i]); };
-    if (staged) {
-        for (int i = threadIdx.x; i < n; i += kSelThreads) sm.keys[i] = score_key(scores[i]);
-        __syncthreads();
-    }
-    int want = k, ties = 0;
-    thr = radix_select_desc([&](int i, uint32_t& key) { key = key_at(i); return true; }, n, want, ties, sm);
-    all_ties = (want == ties);
-    thr_id = 0;
-    if (!all_ties) {
-        const uint32_t t = thr;
-        int want2 = want, ties2 = 0;
-        thr_id = radix_select_desc(
-            [&](int i, uint32_t& key) {
-                key = ~(uint32_t)(ids ? ids[i] : i);    // descending on ~id == ascending on id
-                return key_at(i) == t;
-            },
-            n, want2, ties2, sm);
-    }
-}
-
-__device__ __forceinline__ bool is_kept(uint32_t key, uint32_t idkey, uint32_t thr, uint32_t thr_id, bool all_ties) {
-    return key > thr || (key == thr && (all_ties || idkey >= thr_id));
 }
 
 struct EvictArgs {
@@ -282,6 +195,33 @@ __device__ __forceinline__ uint32_t plan_select(F f, int n, int& want, int& ties
     return prefix;
 }
 
+// Which elements are among the top k by (key descending, id ascending): those for which keeps() holds.  `key` may be the leading
+// digits of the kept keys only (then `all` is set, and every key that is not below it stays).
+struct TopSet {
+    uint32_t key, idkey;        // idkey: ~id, so that the lowest ids rank first
+    bool all;                   // all elements at `key` belong to the set
+    // element i (its id is read only where the k-th key is shared)
+    template <class Key, class IdKey>
+    __device__ __forceinline__ bool keeps(Key key_at, IdKey idkey_at, int i) const {
+        const uint32_t k = key_at(i);
+        return k > key || (k == key && (all || idkey_at(i) >= idkey));
+    }
+};
+
+// The set for 0 < k < n; key_at(i) and idkey_at(i) give element i's.  What the caller staged for them is read behind a barrier.
+template <int NT, class Key, class IdKey>
+__device__ __forceinline__ TopSet top_set(Key key_at, IdKey idkey_at, int n, int k, SelectShared& sm) {
+    int want = k, ties = 0;
+    TopSet t{0, 0, true};
+    t.key = plan_select<NT>([&](int i, uint32_t& key) { key = key_at(i); return true; }, n, want, ties, sm);
+    t.all = want == ties;
+    if (!t.all) {                                       // the k-th key is shared: the lowest ids of its holders
+        int want2 = want, ties2 = 0;
+        t.idkey = plan_select<NT>([&](int i, uint32_t& key) { key = idkey_at(i); return key_at(i) == t.key; }, n, want2, ties2, sm);
+    }
+    return t;
+}
+
 // Copies rows dst(i) <- src(i), i < count, on all strips of sequence b.  Callers guarantee that no destination of the batch
 // is a source of it.  A wave moves one row of as many strips as 64 lanes of 16 bytes cover, kUR such pieces in flight.
 template <int NT, class Dst, class Src>
@@ -414,25 +354,14 @@ __device__ __forceinline__ void evict_plan_body(const EvictArgs& a, int b, PlanS
         float* scores = a.score_col + b * a.col_stride;
         int32_t* ids = a.id_col + b * a.col_stride;
         int32_t* mv = a.moves + (int64_t)b * a.max_moves * 2;
-        uint32_t thr = 0, thr_id = 0;
-        bool all_ties = true;
+        TopSet top{0, 0, true};
+        auto key_at = [&](int i) { return sm.keys[i]; };
+        auto idkey_at = [&](int i) { return ~(uint32_t)ids[i]; };
         if (k > 0) {
-            for (int i = tid; i < n; i += NT) sm.keys[i] = score_key(scores[i]);      // (read back behind a barrier)
-            int want = k, ties = 0;
-            thr = plan_select<NT>([&](int i, uint32_t& key) { key = sm.keys[i]; return true; }, n, want, ties, sm);
-            all_ties = want == ties;
-            if (!all_ties) {                            // the k-th score is shared: the lowest ids of its holders
-                int want2 = want, ties2 = 0;
-                thr_id = plan_select<NT>([&](int i, uint32_t& key) { key = ~(uint32_t)ids[i]; return sm.keys[i] == thr; }, n, want2,
-                                     ties2, sm);
-            }
+            for (int i = tid; i < n; i += NT) sm.keys[i] = score_key(scores[i]);
+            top = top_set<NT>(key_at, idkey_at, n, k, sm);
         }
-        auto kept_at = [&](int p) -> bool {
-            if (p >= n || k == 0) return false;
-            const uint32_t key = sm.keys[p];
-            return key > thr || (key == thr && (all_ties || ~(uint32_t)ids[p] >= thr_id));
-        };
-        // all_ties: thr may be the leading digits of the kept keys only; every key with larger or the same digits is kept
+        auto kept_at = [&](int p) -> bool { return p < n && k > 0 && top.keeps(key_at, idkey_at, p); };
         const int n_pad = (n + NT - 1) / NT * NT;
         const int g = n - k;                            // rows evicted
         // rows behind the visual segment that have to close up; none when the tail keeps its place

@@ -3,9 +3,9 @@
 // (Eq. 7, Alg. 3 VTA branch).
 //
 // Selection is an exact radix select on the order-preserving 32-bit image of the float32 score
-// (4 passes of 8 bits, histogram in LDS), followed - only when the k-th score is shared - by a
-// second radix select on the tie ids, so that the result is the unique top-k set under the total
-// order (score descending, id ascending).  One workgroup per sequence.
+// (8 bits a pass, at most four, histograms in LDS), followed - only when the k-th score is shared -
+// by a second radix select on the tie ids, so that the result is the unique top-k set under the
+// total order (score descending, id ascending).  One workgroup per sequence.
 #include <algorithm>
 
 #include "st3_evict.h"
@@ -13,7 +13,6 @@
 namespace st3 {
 
 namespace {
-
 
 // ---------------------------------------------------------------------------------------------
 // st3_select_topk
@@ -44,33 +43,18 @@ __global__ __launch_bounds__(NT) void select_topk_kernel(TopkArgs a) {
     int32_t* idx = a.idx ? a.idx + (int64_t)b * a.idx_stride : nullptr;
     const bool staged = n <= kSelLdsKeys;
     auto key_at = [&](int i) -> uint32_t { return staged ? sm.keys[i] : score_key(scores[i]); };
-    uint32_t thr = 0, thr_id = 0;
-    bool all_ties = true;
+    auto idkey_at = [&](int i) { return ~(uint32_t)(ids ? ids[i] : i); };
+    TopSet top{0, 0, true};
     if (k > 0 && k < n) {
         if (staged)
-            for (int i = tid; i < n; i += NT) sm.keys[i] = score_key(scores[i]);    // (read back behind a barrier)
-        int want = k, ties = 0;
-        thr = plan_select<NT>([&](int i, uint32_t& key) { key = key_at(i); return true; }, n, want, ties, sm);
-        all_ties = want == ties;
-        if (!all_ties) {                                // the k-th score is shared: the lowest ids of its holders
-            int want2 = want, ties2 = 0;
-            thr_id = plan_select<NT>([&](int i, uint32_t& key) { key = ~(uint32_t)(ids ? ids[i] : i); return key_at(i) == thr; }, n,
-                                     want2, ties2, sm);
-        }
+            for (int i = tid; i < n; i += NT) sm.keys[i] = score_key(scores[i]);
+        top = top_set<NT>(key_at, idkey_at, n, k, sm);
     }
     int base = 0, parity = 0, r1, r2, t1, t2;
     const int n_pad = (a.n + NT - 1) / NT * NT;
     for (int p0 = 0; p0 < n_pad; p0 += NT, parity ^= 1) {
         const int p = p0 + tid;
-        bool keep = false;
-        if (p < n) {
-            if (k >= n) keep = true;
-            else if (k > 0) {
-                const uint32_t key = key_at(p);
-                // all_ties: thr may be the leading digits of the kept keys only, and then every key at or above it stays
-                keep = key > thr || (key == thr && (all_ties || ~(uint32_t)(ids ? ids[p] : p) >= thr_id));
-            }
-        }
+        const bool keep = p < n && (k >= n || (k > 0 && top.keeps(key_at, idkey_at, p)));
         if (mask && p < a.n) mask[p] = keep ? 1 : 0;
         plan_ranks<NT>(keep, false, parity, sm, r1, r2, t1, t2);
         if (keep && idx && base + r1 < a.k) idx[base + r1] = p;
@@ -441,6 +425,7 @@ st3_status enqueue_select_compact(const st3_attn_shape* shape, const st3_kv_laye
 namespace {
 
 constexpr int kDiagIdSpace = 16384;
+constexpr int kDiagThreads = 256;
 
 struct OverlapArgs {
     const float* score_a; const int32_t* ids_a; int64_t stride_a; const int32_t* n_a_dev; int32_t n_a;
@@ -452,12 +437,12 @@ struct OverlapArgs {
 
 // One workgroup per sequence.  TopK(a) is marked in an LDS bitmap indexed by token id; the
 // members of TopK(b) whose id is marked are counted.
-__global__ __launch_bounds__(kSelThreads) void overlap_topk_kernel(OverlapArgs a) {
-    __shared__ SelShared sm;
+__global__ __launch_bounds__(kDiagThreads) void overlap_topk_kernel(OverlapArgs a) {
+    __shared__ SelectShared sm;
     __shared__ uint32_t seen[kDiagIdSpace / 32];
     __shared__ int sm_count;
     const int b = blockIdx.x, tid = threadIdx.x;
-    for (int i = tid; i < kDiagIdSpace / 32; i += kSelThreads) seen[i] = 0u;
+    for (int i = tid; i < kDiagIdSpace / 32; i += kDiagThreads) seen[i] = 0u;
     if (tid == 0) sm_count = 0;
     __syncthreads();
     for (int side = 0; side < 2; ++side) {
@@ -467,14 +452,16 @@ __global__ __launch_bounds__(kSelThreads) void overlap_topk_kernel(OverlapArgs a
         int n = n_dev ? n_dev[b] : (side ? a.n_b : a.n_a);
         n = max(0, min(n, side ? a.n_b : a.n_a));
         const int k = min(a.k, n);
-        uint32_t thr = 0, thr_id = 0;
-        bool all_ties = true;
-        if (k > 0 && k < n) mark_topk(scores, ids, n, k, true, sm, thr, thr_id, all_ties);
-        else __syncthreads();
+        auto key_at = [&](int i) { return sm.keys[i]; };
+        auto idkey_at = [&](int i) { return ~(uint32_t)ids[i]; };
+        TopSet top{0, 0, true};
+        if (k > 0 && k < n) {
+            for (int i = tid; i < n; i += kDiagThreads) sm.keys[i] = score_key(scores[i]);
+            top = top_set<kDiagThreads>(key_at, idkey_at, n, k, sm);
+        }
         int local = 0;
-        for (int p = tid; p < n; p += kSelThreads) {
-            bool keep = k >= n;
-            if (!keep && k > 0) keep = is_kept(sm.keys[p], ~(uint32_t)ids[p], thr, thr_id, all_ties);
+        for (int p = tid; p < n; p += kDiagThreads) {
+            const bool keep = k >= n || (k > 0 && top.keeps(key_at, idkey_at, p));
             const int id = ids[p];
             if (!keep || id < 0 || id >= a.id_space) continue;
             if (side == 0) atomicOr(&seen[id >> 5], 1u << (id & 31));
@@ -505,7 +492,7 @@ __device__ __forceinline__ float block_sum(float v, float* sm4) {
 
 // One workgroup per sequence.  Entries are matched by token id (ids_x == null: by position);
 // tokens present on one side only count as zero on the other.  fp32 sums in a fixed order.
-__global__ __launch_bounds__(kSelThreads) void cosine_kernel(CosineArgs a) {
+__global__ __launch_bounds__(kDiagThreads) void cosine_kernel(CosineArgs a) {
     __shared__ int16_t pos_b[kDiagIdSpace];
     __shared__ float sm4[4];
     const int b = blockIdx.x, tid = threadIdx.x;
@@ -515,17 +502,17 @@ __global__ __launch_bounds__(kSelThreads) void cosine_kernel(CosineArgs a) {
     const int32_t* ib = a.ids_b ? a.ids_b + b * a.stride_b : nullptr;
     const int na = max(0, min(a.n_a_dev ? a.n_a_dev[b] : a.n_a, a.n_a));
     const int nb = max(0, min(a.n_b_dev ? a.n_b_dev[b] : a.n_b, a.n_b));
-    for (int i = tid; i < a.id_space; i += kSelThreads) pos_b[i] = -1;
+    for (int i = tid; i < a.id_space; i += kDiagThreads) pos_b[i] = -1;
     __syncthreads();
     float sbb = 0.f;
-    for (int p = tid; p < nb; p += kSelThreads) {
+    for (int p = tid; p < nb; p += kDiagThreads) {
         const int id = ib ? ib[p] : p;
         if (id >= 0 && id < a.id_space) pos_b[id] = (int16_t)p;
         sbb = fmaf(vb[p], vb[p], sbb);
     }
     __syncthreads();
     float saa = 0.f, sab = 0.f;
-    for (int p = tid; p < na; p += kSelThreads) {
+    for (int p = tid; p < na; p += kDiagThreads) {
         const int id = ia ? ia[p] : p;
         const float x = va[p];
         saa = fmaf(x, x, saa);
@@ -550,7 +537,7 @@ extern "C" st3_status st3_overlap_topk(const float* score_a, const int32_t* ids_
         return ST3_ERR_UNSUPPORTED;
     st3::OverlapArgs a{score_a, ids_a, stride_a, n_a_dev, n_a, score_b, ids_b, stride_b, n_b_dev, n_b, k, id_space,
                        overlap, topk_a};
-    st3::overlap_topk_kernel<<<batch, st3::kSelThreads, 0, reinterpret_cast<hipStream_t>(stream)>>>(a);
+    st3::overlap_topk_kernel<<<batch, st3::kDiagThreads, 0, reinterpret_cast<hipStream_t>(stream)>>>(a);
     return st3::check_launch();
 }
 
@@ -562,7 +549,7 @@ extern "C" st3_status st3_cosine_similarity(const float* va, const int32_t* ids_
     if (batch <= 0 || n_a < 0 || n_b < 0 || stride_a < n_a || stride_b < n_b) return ST3_ERR_INVALID_ARG;
     if (id_space <= 0 || id_space > st3::kDiagIdSpace || n_a > 32767 || n_b > 32767) return ST3_ERR_UNSUPPORTED;
     st3::CosineArgs a{va, ids_a, stride_a, n_a_dev, n_a, vb, ids_b, stride_b, n_b_dev, n_b, id_space, cosine};
-    st3::cosine_kernel<<<batch, st3::kSelThreads, 0, reinterpret_cast<hipStream_t>(stream)>>>(a);
+    st3::cosine_kernel<<<batch, st3::kDiagThreads, 0, reinterpret_cast<hipStream_t>(stream)>>>(a);
     return st3::check_launch();
 }
 
