@@ -107,9 +107,9 @@ inline int decode_nsplit(int B, int H, int max_kv, int target_wgs = kDecodeTarge
     if (ns > kDecodeMaxSplit) ns = kDecodeMaxSplit;
     return ns < 1 ? 1 : (int)ns;
 }
-// Chunks of a strip of `len` rows in the whole-step call, where `rows` is the sum of the lengths of all layers that are
-// launched together and the chunk partials are merged inside the step's plan launch: chunks of equal LENGTH over all
-// layers, as long as about kStepTargetWgs workgroups allow.  Measured at targets of 1024 / 2048 / 3072 / 4096 / 8192, us per step:
+// Chunks of a strip of `len` rows in the whole-step call, where `rows` is the sum of the lengths of all ordinary (or all lazy)
+// layers of the step, over however many launches, and the chunk partials are merged inside the step's plan launch: chunks of
+// equal LENGTH over all layers, as long as about kStepTargetWgs workgroups in all allow.  Measured at targets of 1024 / 2048 / 3072 / 4096 / 8192, us per step:
 // 7B batch 1 72.1 / 72.6 / 73.4 / 78.2 / 93.1, 13B batch 8 with lazy layers 563 / 563 / 571 / 565 / 611, high resolution batch 8
 // E4M3 699 / 699 / 698 / 699 / 711; 13B batch 32 is not cut by any of them.
 #ifndef ST3_STEP_TARGET_WGS

@@ -466,7 +466,7 @@ st3_status build_evict_args(const st3_attn_shape* shape, const st3_kv_layer* kv,
                             int64_t mass_stride, EvictArgs& ea, bool& needs_apply, bool batched,
                             const void* mass_workspace = nullptr, int32_t mass_capacity = 0);
 void launch_evict_plan(const EvictArgs& ea, int B, hipStream_t st);
-constexpr int kPlanBatch = 16;     // plans that fit the kernel-argument block by value
+constexpr int kPlanBatch = 16;     // plans that travel by value: 200 bytes each (the argument block would hold 20)
 // Plans of n layers (device work of one decode step) with one launch per kPlanBatch layers.
 void launch_evict_plan_batch(const EvictArgs* plans, int n, int B, hipStream_t st);
 // The plans of n layers from the table entries that whole-step attention launches have left in the layers' workspaces;

@@ -102,9 +102,17 @@ BF, F32 = torch.bfloat16, torch.float32
     dict(L=4, B=2, H=4, d=128, dtype=BF, vis=[260, 90], tail=40, lazy={1: 0}, fixed_tail=False),
     dict(L=5, B=2, H=6, d=128, dtype=BF, vis=[200, 33], tail=9, e4m3=True, lazy={3: 2}),
     dict(L=3, B=2, H=4, d=128, dtype=BF, vis=[300], tail=9, drop=80),           # evictions that a launch of their own moves
-    dict(L=2, B=1, H=2, d=64, dtype=F32, vis=[8190], tail=3000),                # strips longer than the logit staging area
+    dict(L=2, B=1, H=2, d=64, dtype=F32, vis=[8190], tail=3000),                # long strips: 59 chunks
 ], ids=lambda a: "-".join(f"{k}{v}" for k, v in a.items() if k in ("L", "B", "H", "d", "drop")))
 def test_whole_step_is_the_layers_one_by_one(args):
+    _same(Step(**args).whole(), Step(**args).layer_by_layer())
+
+
+@pytest.mark.parametrize("args", [
+    dict(L=1, B=1, H=1, d=64, dtype=F32, vis=[4000], tail=92),                  # 64 chunks, a lane of the wave for each
+    dict(L=1, B=42, H=50, d=64, dtype=F32, vis=[4150], tail=20),                # cut for the logit staging area alone
+], ids=["64_chunks", "staging"])
+def test_cuts_of_long_strips(args):
     _same(Step(**args).whole(), Step(**args).layer_by_layer())
 
 
