@@ -129,14 +129,17 @@ inline int step_nsplit(int B, int H, int len, int64_t rows) {
 }
 // The target of a call that finishes its mass in a second launch (decode_finish_kernel merges chunks one after the other, so many
 // of them cost it more than they save).  us a call at targets of 256 / 512 / 1024, equal lengths, bf16 d = 128 unless said:
-//   B*H 16: 250 rows 7.5 / 7.1 / 7.0, 739 rows 9.1 / 9.4 / 9.4, 3136 rows 12.7 / 15.1 / 21.5 (d = 64 250 rows 6.9 / 7.2 / 7.0)
+//   B*H 16: 250 rows 7.5 / 7.1 / 7.0, 739 rows 9.1 / 9.4 / 9.4, 3136 rows 12.7 / 15.1 / 21.5
 //   B*H 64: 1400 rows 14.2 / 12.9 / 15.1, float32 3136 rows 48.6 / 37.4 / 40.3;  B*H 128: 1400 rows 26.1 / 19.0 / 20.8
-//   B*H 140: 1400 rows 29.0 / 22.8 / 21.4;  B*H 180, E4M3 d = 64, 300 rows 8.3 / 9.1 / 9.9;  B*H 200: 1111 rows 24.6 / 24.2 / 23.9
-//   B*H 320: 1111 rows 40.5 / - / 33.4 (256: one chunk), float32 3136 rows 162 / - / 170;  B*H 360: 3136 rows 104 / - / 100,
-//   ragged 71 / - / 62, float32 189 / - / 193;  B*H 440: 3136 rows 116.5 / - / 122.5, ragged 92 / - / 80;  480: 126 / - / 127
+//   B*H 140: 1400 rows 29.0 / 22.8 / 21.4;  B*H 200: 1111 rows 24.6 / 24.2 / 23.9;  B*H 320: 1111 rows 40.5 / - / 33.4
+//   rows of 64 bytes, B*H 180, 300 rows 8.3 / 9.1 / 9.9;  rows of 128 bytes, 250 rows, B*H 8 6.7 / 7.1 / 7.0, B*H 128 8.0 / 8.5 / 8.6
+// From B*H = 257 on the lower target leaves strips whole.  Above 400 of them that is up to 5 % faster where all are equally long
+// (B*H 440, 3136 rows 116.5 / - / 122.5; float32 352 strips 174 / - / 191), and up to 26 % slower where lengths differ, which the host
+// does not know (one sequence of 3136 rows among ten of 400, B*H 440: 54.3 / - / 50.9, float32 135 / - / 110, E4M3 34.7 / - / 25.7):
+// they are cut.
 inline int merged_target(int64_t bh, int max_kv, int head_dim, int cache_eb) {
-    if (bh > (cache_eb < 4 ? 400 : 320)) return kDecodeTargetWgs;
-    if (head_dim * cache_eb < 256 && max_kv <= 5 * kDecodeMinChunk) return kDecodeTargetWgs;
+    const int row_bytes = head_dim * cache_eb;
+    if (max_kv <= 5 * kDecodeMinChunk && (row_bytes < 128 || (row_bytes < 256 && bh < 16))) return kDecodeTargetWgs;
     if (bh < 48) return max_kv <= 4 * kDecodeMinChunk ? kDecodeTargetWgsMerged : kDecodeTargetWgs;
     return bh <= 128 && cache_eb < 4 ? kDecodeTargetWgsMerged / 2 : kDecodeTargetWgsMerged;
 }
