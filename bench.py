@@ -158,7 +158,7 @@ def committed_traffic(workload, batch, kv_format, alg_bytes_per_launch):
     measured in this run (counters need the profiler attached): None when no summary covers the
     workload, and the source is always named next to the number."""
     tag = f"{workload}_b{batch}" + ("" if kv_format == "plain" else f"_{kv_format}")
-    path = os.path.join("profiles", f"decode_attend_kernel_{tag}_pmc.txt")
+    path = os.path.join("profiles", f"decode_attend_layers_kernel_{tag}_pmc.txt")
     try:
         with open(os.path.join(ROOT, path)) as f:
             for line in f:
