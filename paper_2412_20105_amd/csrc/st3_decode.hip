@@ -92,11 +92,20 @@ __device__ __forceinline__ void store_out(void* out, int64_t idx, float o) {
 // This lane's 16-byte slice of a new token's row, in the format of the cache it is going into
 // (lane map of RowMap<KT, D>): a plain copy when the cache holds elements of T, the E4M3 quantiser
 // otherwise.  What the attention then reads is exactly what later steps will find in the cache.
+// load(): each lane for itself.  load_by_wave(): the K and the V row (k_row may be null) of one token by a whole wave, for the
+// one wave of an attention workgroup that takes the appended row while the others wait for it at the end: the quantiser costs
+// about 45 instructions an element (an exactly rounded division), so every element is quantised by one lane only and the codes
+// are exchanged, 4 elements a lane instead of 32.  E4M3 caches, us a step, before -> after: 7B batch 1 49.4 -> 43.5, 7B batch 16
+// layer by layer 536 -> 443, 13B batch 8 with lazy layers 300 -> 282, batch 32 1304 -> 1275, high resolution batch 8 637 -> 630.
 template <typename T, typename KT, int D>
 struct NewRow {
     static __device__ __forceinline__ u32x4_t load(const T* row, int lane, float) {
         using M = RowMap<KT, D>;
         return *reinterpret_cast<const u32x4_t*>(row + (lane % M::LPR) * M::EPL);
+    }
+    static __device__ __forceinline__ void load_by_wave(const T* k_row, const T* v_row, int lane, float, float, u32x4_t& k, u32x4_t& v) {
+        if (k_row != nullptr) k = load(k_row, lane, 1.0f);
+        v = load(v_row, lane, 1.0f);
     }
 };
 template <typename T, int D>
@@ -106,10 +115,29 @@ struct NewRow<T, e4m3_t, D> {
         load_row_slice<T, e4m3_t, D>(row, lane, f);
         u32x4_t r;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            r[i] = quantize_e4m3(f[4 * i], scale) | (quantize_e4m3(f[4 * i + 1], scale) << 8) |
-                   (quantize_e4m3(f[4 * i + 2], scale) << 16) | (quantize_e4m3(f[4 * i + 3], scale) << 24);
+        for (int i = 0; i < 4; ++i) r[i] = four(f + 4 * i, scale);
         return r;
+    }
+    static __device__ __forceinline__ void load_by_wave(const T* k_row, const T* v_row, int lane, float k_scale, float v_scale,
+                                                        u32x4_t& k, u32x4_t& v) {
+        static_assert(sizeof(T) == 2 && D / 4 <= 32, "half a wave covers a row, four bf16 elements a lane");
+        const bool is_k = lane < 32 && k_row != nullptr;        // lanes 0..31: K, 32..63: V
+        const T* src = (is_k ? k_row : v_row) + 4 * (lane % (D / 4));
+        const uint2 raw = *reinterpret_cast<const uint2*>(src);
+        const float f[4] = {bf16_lo(raw.x), bf16_hi(raw.x), bf16_lo(raw.y), bf16_hi(raw.y)};
+        const int word = (int)four(f, is_k ? k_scale : v_scale);
+        const int first = 4 * (lane % RowMap<e4m3_t, D>::LPR);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (k_row != nullptr) k[i] = (uint32_t)__shfl(word, first + i);
+            v[i] = (uint32_t)__shfl(word, 32 + first + i);
+        }
+    }
+
+private:
+    static __device__ __forceinline__ uint32_t four(const float* f, float scale) {
+        return quantize_e4m3(f[0], scale) | (quantize_e4m3(f[1], scale) << 8) | (quantize_e4m3(f[2], scale) << 16) |
+               (quantize_e4m3(f[3], scale) << 24);
     }
 };
 
@@ -176,8 +204,8 @@ __device__ __forceinline__ void attend_chunk(const DecodeArgs& a, const int spli
     // the appended token's row is fetched now and used after the cached rows: off the critical path
     u32x4_t kn_raw = {0, 0, 0, 0}, vn_raw = {0, 0, 0, 0};       // native vectors: the uint4 class would live in scratch
     if (has_new && wave == 0) {
-        kn_raw = NewRow<T, KT, D>::load(reinterpret_cast<const T*>(a.k_new) + bh * D, lane, k_unit);
-        vn_raw = NewRow<T, KT, D>::load(reinterpret_cast<const T*>(a.v_new) + bh * D, lane, v_unit);
+        NewRow<T, KT, D>::load_by_wave(reinterpret_cast<const T*>(a.k_new) + bh * D, reinterpret_cast<const T*>(a.v_new) + bh * D,
+                                       lane, k_unit, v_unit, kn_raw, vn_raw);
     }
     // waves take the tiles of the chunk round-robin, so all four stay busy to the end
     // the early tile placed its rows by the host's guess: fetch it again if that put a row this
@@ -407,14 +435,17 @@ __device__ __forceinline__ void inherit_chunk(const InheritArgs& a, const int sp
     const int c1_cached = has_new ? c1 - 1 : c1;
     wave_inherit<KT, D, U>(vbase, a.stride_t, c0 + wave * TILE, c1_cached, kDecodeWaves * TILE, c0, lg, m, rl, lane, acc,
                            lay.shift());
-    if (has_new && wave == 0 && lane < LPR) {
-        const u32x4_t raw = NewRow<T, KT, D>::load(reinterpret_cast<const T*>(a.v_new) + bh * D, lane, v_unit);
-        const float p = exp2_fast(lg[len - 1] - m) * rl;
-        float vf[EPL];
-        ElemTraits<KT>::unpack(make_uint4(raw.x, raw.y, raw.z, raw.w), vf);
+    if (has_new && wave == 0) {
+        u32x4_t none = {0, 0, 0, 0}, raw = {0, 0, 0, 0};
+        NewRow<T, KT, D>::load_by_wave(nullptr, reinterpret_cast<const T*>(a.v_new) + bh * D, lane, 1.0f, v_unit, none, raw);
+        if (lane < LPR) {
+            const float p = exp2_fast(lg[len - 1] - m) * rl;
+            float vf[EPL];
+            ElemTraits<KT>::unpack(make_uint4(raw.x, raw.y, raw.z, raw.w), vf);
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] = fmaf(p, vf[e], acc[e]);
-        *reinterpret_cast<u32x4_t*>(vbase + (int64_t)(len_phys - 1) * a.stride_t + lane * EPL) = raw;
+            for (int e = 0; e < EPL; ++e) acc[e] = fmaf(p, vf[e], acc[e]);
+            *reinterpret_cast<u32x4_t*>(vbase + (int64_t)(len_phys - 1) * a.stride_t + lane * EPL) = raw;
+        }
     }
 #pragma unroll
     for (int off = LPR; off < kWave; off <<= 1) {
