@@ -61,7 +61,7 @@ st3_status enqueue_decode(const st3_attn_shape* shape, const void* q, const st3_
                           bool keep_all_logits, void* workspace, size_t workspace_bytes, hipStream_t st);
 st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const st3_layer_step* layers, int mode,
                                const char* has_heirs, const EvictArgs* plan, StepCommon& common, const StepLayer** entry,
-                               bool& split, hipStream_t st);
+                               PlanNeeds& needs, hipStream_t st);
 
 }  // namespace st3
 
@@ -324,12 +324,10 @@ extern "C" st3_status st3_decode_step(const st3_attn_shape* shape, int32_t n_lay
     if (!layers_share_rows(shape, n_layers, layers)) {
         StepCommon common{};
         std::vector<const StepLayer*> entry((size_t)n_layers, nullptr);
-        bool split = false;
-        s = enqueue_step_attend(shape, n_layers, layers, mode, has_heirs.data(), plan.data(), common, entry.data(), split, st);
+        PlanNeeds needs{};
+        s = enqueue_step_attend(shape, n_layers, layers, mode, has_heirs.data(), plan.data(), common, entry.data(), needs, st);
         if (s == ST3_OK) {
-            int most_vis = 0;
-            for (const EvictArgs& p : plan) most_vis = p.max_vis > most_vis ? p.max_vis : most_vis;
-            launch_evict_plan_table(common, entry.data(), n_layers, most_vis, split, st);
+            launch_evict_plan_table(common, entry.data(), n_layers, needs, st);
             enqueue_applies(plan, needs_apply, shape->batch, st);
             return check_launch();
         }

@@ -190,6 +190,7 @@ struct StepLayer {
 };
 static_assert(sizeof(StepLayer) == 184, "kStepLayersMax entries must fit the kernel-argument block");
 constexpr uint8_t kStepInlineApply = 1, kStepKeepAll = 2, kStepLazy = 4, kStepWantMass = 8, kStepE4M3 = 16;
+constexpr uint8_t kStepApart = 32;      // the next eviction does not rank by this step's mass
 constexpr int kStepLayersMax = 21;
 constexpr int kStepLayerWords = sizeof(StepLayer) / 4;
 struct StepTable {

@@ -69,7 +69,7 @@ struct DecodeArgs {
     float* part_ml;         // [B,H,nsplit_cap,2]
     float* logits;          // [B,H,capacity]; null when no mass is wanted
     int32_t stage_rows;     // floats of LDS in which a workgroup collects the logits it keeps (0 when it keeps none)
-    int32_t* pending;       // [B][4]: {mass still to be finished | rows attended << 1, nsplit, chunk, logits of this call present}
+    int32_t* pending;       // [B][4]: {mass still to be finished | rows attended << 1, nsplit, chunk, logits of every key present | visual rows << 1}
     const void* k_new;      // [B,H,D] rows of the token being appended (null: none); the cache row
     const void* v_new;      //         kv_len[b] is then taken from here and written to the cache
     void* out;              // [B,H,D]
@@ -179,7 +179,7 @@ __device__ __forceinline__ void attend_chunk(const DecodeArgs& a, const int spli
         a.pending[b * 4 + 0] = ((a.logits != nullptr && len > 0 && a.defer) ? 1 : 0) | (max(len, 0) << 1);
         a.pending[b * 4 + 1] = a.nsplit;
         a.pending[b * 4 + 2] = a.chunk;
-        a.pending[b * 4 + 3] = (a.logits != nullptr && len > 0 && a.keep_all_logits) ? 1 : 0;
+        a.pending[b * 4 + 3] = ((a.logits != nullptr && len > 0 && a.keep_all_logits) ? 1 : 0) | (lay.nv << 1);
     }
     if (len <= 0) {                                  // empty sequence: out = 0, no mass
         if (split == 0 && tid < D) store_out<T>(a.out, bh * D + tid, 0.f);
@@ -288,7 +288,16 @@ __device__ __forceinline__ void leave_entry(const StepCommon& c, const StepLayer
         reinterpret_cast<uint32_t*>(e.ws + wl.step_entry)[threadIdx.x] = reinterpret_cast<const uint32_t*>(&e)[threadIdx.x];
 }
 
-// The attention of several layers of a step that do not depend on each other; grid (most chunks of any of them, H,
+// Workgroup (0, H) of a sequence and layer of a whole-step launch ranks the rows of a layer whose next eviction does not wait for
+// the mass of this step (kStepApart, evict_rank_early).  (Behind the attention's workgroups of the same layer; all of them are
+// resident long before the last one ends.)
+__device__ __forceinline__ void rank_workgroup(const StepCommon& c, const StepLayer& e, int split, int b) {
+    if (split != 0 || !(e.flags & kStepApart) || e.keep_count < 0) return;
+    __shared__ SelectShared sm;
+    evict_rank_early<kDecodeThreads>(plan_from_entry(c, e), b, sm);
+}
+
+// The attention of several layers of a step that do not depend on each other; grid (most chunks of any of them, H + 1,
 // B * layers), layers in order, so the longest strips (early layers keep the most rows) start first.  Bound by HBM; as a
 // launch per layer it was bound by the ramp and the tail of each launch and the gap behind it (about 9 us a layer, whatever
 // its bytes).  Whole step, us, one launch per layer -> up to 21 layers per launch: 7B batch 1 191 -> 75 (209 MB), 13B batch 8
@@ -302,6 +311,7 @@ void decode_attend_layers_kernel(StepTable t) {
     const int li = __builtin_amdgcn_readfirstlane((int)blockIdx.z / c.B), b = (int)blockIdx.z - li * c.B;
     const int split = blockIdx.x, h = blockIdx.y;
     const StepLayer& e = t.layer[li];
+    if (h == c.H) return rank_workgroup(c, e, split, b);
     if (split >= e.nsplit) return;
     const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
     const bool want = (e.flags & kStepWantMass) != 0, all = (e.flags & kStepKeepAll) != 0;
@@ -340,6 +350,7 @@ struct InheritArgs {
     const float* src_part_ml;   // [B,H,src_nsplit_cap,2]
     const int32_t* src_pending; // [B][4]
     int32_t src_capacity, src_nsplit_cap;
+    int32_t* own_pending;       // [B][4] of this layer: the visual rows are left there (the rest is the source's)
     float* part_o;              // [B,H,nsplit_cap,D]   (nsplit > 1 only)
     const void* v_new;          // [B,H,D] value row of the token being appended (null: none)
     const float* v_scale;       // [B*H] value of one V code unit (E4M3 caches; null: 1)
@@ -406,7 +417,8 @@ __device__ __forceinline__ void inherit_chunk(const InheritArgs& a, const int sp
     const int c0 = split * a.chunk;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int64_t bh = (int64_t)b * a.H + h;
-    const bool have = a.src_pending[b * 4 + 3] != 0;        // the source attended a non-empty sequence
+    if (split == 0 && h == 0 && tid == 0) a.own_pending[b * 4 + 3] = lay.nv << 1;
+    const bool have = (a.src_pending[b * 4 + 3] & 1) != 0;        // the source attended a non-empty sequence
     if (len <= 0 || !have) {                                // nothing to inherit: out = 0
         if (split == 0 && tid < D) store_out<T>(a.out, bh * D + tid, 0.f);
         if (len > 0 && a.nsplit > 1 && c0 < len && tid < D) a.part_o[(bh * a.nsplit_cap + split) * D + tid] = 0.f;
@@ -480,6 +492,7 @@ __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_
     const int li = __builtin_amdgcn_readfirstlane((int)blockIdx.z / c.B), b = (int)blockIdx.z - li * c.B;
     const int split = blockIdx.x, h = blockIdx.y;
     const StepLayer& e = t.layer[li];
+    if (h == c.H) return rank_workgroup(c, e, split, b);
     if (split >= e.nsplit) return;
     const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
     const DecodeWs sl = decode_ws_sized(c.B, c.H, D, e.hint_base, e.src_nsplit_cap);
@@ -493,6 +506,7 @@ __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_
     a.src_part_ml = reinterpret_cast<const float*>(sws + sl.part_ml);
     a.src_pending = reinterpret_cast<const int32_t*>(sws + sl.pending);
     a.src_capacity = e.hint_base; a.src_nsplit_cap = e.src_nsplit_cap;
+    a.own_pending = reinterpret_cast<int32_t*>(e.ws + wl.pending);
     a.part_o = reinterpret_cast<float*>(e.ws + wl.part_o);
     a.v_new = e.v_new; a.v_scale = e.v_scale; a.out = e.out;
     if (split == 0 && h == 0 && b == 0) leave_entry(c, e, wl);
@@ -731,9 +745,9 @@ void launch_attend(const DecodeArgs& da, int B, hipStream_t st) {
 // 7B batch 1 72.6 / 71.8 / 75.6 / 78.9, 13B batch 8 with lazy layers 563 / 571 / 560 / 565, 13B batch 32 2441 / 2457 / 2433 /
 // 2421, 13B batch 32 E4M3 1327 / 1404 / 1423, high resolution batch 8 E4M3 700 / 696 / 721.
 template <typename T, typename KT, int D>
-void launch_attend_layers(const StepTable& t, int most, int stage_rows, bool stream, hipStream_t st) {
-    const dim3 grid(most, t.c.H, t.c.B * t.c.layers);
-    const size_t lds = (size_t)stage_rows * sizeof(float);
+void launch_attend_layers(const StepTable& t, int most, int lds_words, bool stream, hipStream_t st) {
+    const dim3 grid(most, t.c.H + 1, t.c.B * t.c.layers);
+    const size_t lds = (size_t)lds_words * sizeof(float);
     with_tile(AttendTiles<KT>{}, 0, [&](auto u) {
         if (stream) launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, true>, grid, lds, st, t.c.layers, t);
         else launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, false>, grid, lds, st, t.c.layers, t);
@@ -741,8 +755,9 @@ void launch_attend_layers(const StepTable& t, int most, int stage_rows, bool str
 }
 
 template <typename T, typename KT, int D>
-void launch_inherit_layers(const StepTable& t, int most, hipStream_t st) {
-    decode_inherit_layers_kernel<T, KT, D, 4><<<dim3(most, t.c.H, t.c.B * t.c.layers), kDecodeThreads, 0, st>>>(t);
+void launch_inherit_layers(const StepTable& t, int most, int lds_words, hipStream_t st) {
+    decode_inherit_layers_kernel<T, KT, D, 4><<<dim3(most, t.c.H + 1, t.c.B * t.c.layers), kDecodeThreads,
+                                                (size_t)lds_words * sizeof(uint32_t), st>>>(t);
 }
 
 // The V-only kernel of lazy layers: 4 loads per lane and tile (4 KB per wave) were the fastest or
@@ -934,6 +949,7 @@ st3_status enqueue_inherit(const st3_attn_shape* shape, const st3_kv_layer* kv, 
     ia.src_part_ml = reinterpret_cast<const float*>(sws + sl.part_ml);
     ia.src_pending = reinterpret_cast<const int32_t*>(sws + sl.pending);
     ia.src_capacity = src_capacity; ia.src_nsplit_cap = sl.nsplit_cap;
+    ia.own_pending = reinterpret_cast<int32_t*>(ws + wl.pending);
     ia.part_o = reinterpret_cast<float*>(ws + wl.part_o);
     ia.v_new = v_new; ia.out = out;
     if (kv->format == ST3_KV_E4M3) ia.v_scale = kv->v_scale;
@@ -966,12 +982,12 @@ constexpr int64_t kStreamStoreBytes = (int64_t)7 << 20;
 // Attention of every layer of a checked step: the ordinary layers, up to kStepLayersMax per launch, then the lazy ones, caches of
 // either format in launches of their own (32 layers of the 7B shape, every other cache E4M3, us a step, layer by layer -> so:
 // batch 1 377 -> 60, batch 8 482 -> 290).
-// entry[i] receives where layer i's table entry will lie once the launches have run; split: some strip was cut and its
-// partials are left for the plan to merge.  Returns ST3_ERR_UNSUPPORTED, with nothing enqueued, for a step that a table
+// entry[i] receives where layer i's table entry will lie once the launches have run; needs: what is left for the launch behind
+// them.  The ranking goes along with the attention when no layer's columns take its mass.  Returns ST3_ERR_UNSUPPORTED, with nothing enqueued, for a step that a table
 // cannot describe.
 st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const st3_layer_step* layers, int mode,
                                const char* has_heirs, const EvictArgs* plan, StepCommon& common, const StepLayer** entry,
-                               bool& split, hipStream_t st) {
+                               PlanNeeds& needs, hipStream_t st) {
     const int B = shape->batch, H = shape->heads, D = shape->head_dim;
     common = StepCommon{B, H, D, mode, elem_bytes(shape->dtype), scale_log2(shape), 0};
     int64_t rows[2] = {0, 0};           // of the ordinary and of the lazy layers
@@ -986,7 +1002,12 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
     if (per < 1) return ST3_ERR_UNSUPPORTED;
     std::vector<StepLayer> e((size_t)n_layers);
     std::vector<int> stage((size_t)n_layers, 0), groups[4];     // layers that may share launches, in launch order
-    split = false;
+    needs = PlanNeeds{0, false, true, false};
+    for (int i = 0; i < n_layers; ++i) {
+        needs.most_vis = std::max(needs.most_vis, plan[i].max_vis);
+        needs.apart = needs.apart && plan[i].mass_apart;
+        needs.moves = needs.moves || plan[i].inline_apply;
+    }
     for (int i = 0; i < n_layers; ++i) {
         const st3_layer_step& L = layers[i];
         const bool lazy = L.inherit_from >= 0, coded = L.kv.format == ST3_KV_E4M3;
@@ -1007,8 +1028,8 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
         s.chunk = decode_chunk(len, nsplit);
         nsplit = (len + s.chunk - 1) / s.chunk;
         s.nsplit = (uint8_t)nsplit; s.nsplit_cap = (uint8_t)wl.nsplit_cap;
-        split = split || nsplit > 1;
-        s.flags = (uint8_t)((plan[i].inline_apply ? kStepInlineApply : 0) | (coded ? kStepE4M3 : 0));
+        needs.merge = needs.merge || nsplit > 1;
+        s.flags = (uint8_t)((plan[i].inline_apply ? kStepInlineApply : 0) | (coded ? kStepE4M3 : 0) | (needs.apart ? kStepApart : 0));
         if (lazy) {
             const st3_layer_step& S = layers[L.inherit_from];
             const DecodeWs sl = decode_ws(B, H, D, S.kv.capacity);
@@ -1040,16 +1061,17 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
             const st3_kv_layer* kv = &layers[first].kv;
             StepTable t{};
             t.c = common; t.c.layers = cnt;
-            int most = 1, stage_rows = 0;
+            int most = 1, lds_words = 0;        // dynamic LDS: the logits a workgroup collects, or the keys it ranks
             for (int j = 0; j < cnt; ++j) {
                 const int i = members[(size_t)(i0 + j)];
                 t.layer[j] = e[(size_t)i];
                 most = std::max(most, (int)e[(size_t)i].nsplit);
-                stage_rows = std::max(stage_rows, stage[(size_t)i]);
+                lds_words = std::max(lds_words, stage[(size_t)i]);
+                if (e[(size_t)i].flags & kStepApart && e[(size_t)i].keep_count >= 0) lds_words = std::max(lds_words, e[(size_t)i].max_vis);
             }
             const int64_t row_bytes = (int64_t)cnt * B * H * D * (2 * kv_elem_bytes(shape, kv) + elem_bytes(shape->dtype));
-            if (lazy) ST3_DISPATCH_KV(launch_inherit_layers, shape, kv, t, most, st);
-            else ST3_DISPATCH_KV(launch_attend_layers, shape, kv, t, most, stage_rows, row_bytes > kStreamStoreBytes, st);
+            if (lazy) ST3_DISPATCH_KV(launch_inherit_layers, shape, kv, t, most, lds_words, st);
+            else ST3_DISPATCH_KV(launch_attend_layers, shape, kv, t, most, lds_words, row_bytes > kStreamStoreBytes, st);
             i0 += cnt;
         }
     }

@@ -43,6 +43,8 @@ struct EvictArgs {
     int32_t nsplit_cap;
     float* mass_dst;
     int64_t mass_stride;
+    const int32_t* own_pending; // descriptor of this layer's own attention (its visual rows); `pending` unless the layer is lazy
+    int32_t mass_apart;         // 1: score_col does not take this step's mass: whoever ranks it need not wait for the mass
 };
 
 // The plan of a layer whose table entry a whole-step attention launch has left in the layer's workspace.
@@ -71,10 +73,14 @@ __device__ __forceinline__ EvictArgs plan_from_entry(const StepCommon& c, const 
     a.pending = reinterpret_cast<const int32_t*>(mws + ml.pending);
     a.nsplit_cap = ml.nsplit_cap; a.capacity = lazy ? e.hint_base : e.capacity;
     a.mass_dst = e.mass; a.mass_stride = e.mass_stride;
+    a.own_pending = reinterpret_cast<const int32_t*>(e.ws + wl.pending);
+    a.mass_apart = (e.flags & kStepApart) != 0;
     return a;
 }
 
 typedef uint32_t u32x4_v __attribute__((ext_vector_type(4)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x4_a4_t __attribute__((ext_vector_type(4), aligned(4)));
 
 // ---------------------------------------------------------------------------------------------
 // The plan workgroup.  Latency bound: a chain of dependent steps over a few kilobytes per (layer, sequence), and at small
@@ -116,9 +122,9 @@ void with_threads(int threads, Go go) {
 }
 constexpr int kPlanMaxInline = 64;          // moves of an eviction that the plan workgroup applies itself (at most 48 evicted rows)
 
-// What ranking a row of scores needs, and what a plan needs besides.
+// What ranking a row of scores needs, and what a plan needs besides.  The keys lie in dynamic LDS (sel_keys(): a word for each row
+// that is ranked, and for each thread of a plan), which takes no more of it than the call's rows need.
 struct SelectShared {
-    alignas(16) uint32_t keys[kSelLdsKeys];
     alignas(16) int hist[4][256];       // scanned as int4
     int wave_tot[2][kPlanThreadsMost / kWave];
     int sel_bin, sel_want, sel_cnt, red;
@@ -128,6 +134,11 @@ struct PlanShared : SelectShared {
     float hm[1024], hrl[1024];
     int mv[kPlanMaxInline][2];
 };
+__device__ __forceinline__ uint32_t* sel_keys() {
+    extern __shared__ uint32_t sm_sel_keys[];
+    return sm_sel_keys;
+}
+inline size_t plan_lds(int most_vis, int threads) { return sizeof(uint32_t) * (size_t)(most_vis > threads ? most_vis : threads); }
 
 // Ranks of two flags over the workgroup in thread order: r1 / r2 = how many threads before this one have the flag,
 // t1 / t2 = how many in all.  One barrier; calls in a row alternate `parity`.
@@ -222,16 +233,17 @@ __device__ __forceinline__ TopSet top_set(Key key_at, IdKey idkey_at, int n, int
     return t;
 }
 
-// Copies rows dst(i) <- src(i), i < count, on all strips of sequence b.  Callers guarantee that no destination of the batch
-// is a source of it.  A wave moves one row of as many strips as 64 lanes of 16 bytes cover, kUR such pieces in flight.
+// Copies rows dst(i) <- src(i), i < count, on strips part, part + parts, ... (in groups) of sequence b.  Callers guarantee that no
+// destination of the batch is a source of it.  A wave moves one row of as many strips as 64 lanes of 16 bytes cover, kUR such
+// pieces in flight.
 template <int NT, class Dst, class Src>
-__device__ __forceinline__ void copy_rows_all_strips(const EvictArgs& a, int b, int count, Dst dst, Src src) {
+__device__ __forceinline__ void copy_rows(const EvictArgs& a, int b, int part, int parts, int count, Dst dst, Src src) {
     constexpr int kUR = 8;
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int strips = (a.k ? 2 : 1) * a.H;             // K may be absent (layers that keep V only)
     const int vpr = a.vecs_per_row, spw = kWave / vpr;  // 4 ... 32, a power of two
-    const int groups = (strips + spw - 1) / spw;        // pieces per row
-    const int total = count * groups;
+    const int all = (strips + spw - 1) / spw, groups = (all - part + parts - 1) / parts;       // pieces per row: of all strips, of these
+    const int total = part < all ? count * groups : 0;
     for (int q0 = wave; q0 < total; q0 += kUR * (NT / kWave)) {
         u32x4_v tmp[kUR];
         char* to[kUR];
@@ -241,7 +253,7 @@ __device__ __forceinline__ void copy_rows_all_strips(const EvictArgs& a, int b, 
             to[u] = nullptr;
             if (q >= total) continue;
             const int i = q / groups;
-            const int strip = (q - i * groups) * spw + lane / vpr;
+            const int strip = ((q - i * groups) * parts + part) * spw + lane / vpr;
             if (strip >= strips) continue;
             const bool in_k = a.k && strip < a.H;
             char* base = (in_k ? a.k : a.v) + b * a.stride_b + (int64_t)(strip >= a.H ? strip - a.H : strip) * a.stride_h +
@@ -309,7 +321,7 @@ __device__ __forceinline__ void plan_mass(const EvictArgs& a, int b, int n, int 
     const int h0 = g * per, h1 = min(H, h0 + per);
     const float* lg = a.logits + a.sys_len + (int64_t)b * H * a.capacity;
     float* row = a.mass_dst + b * a.mass_stride;
-    float* part = reinterpret_cast<float*>(sm.keys);    // (the keys are staged later)
+    float* part = reinterpret_cast<float*>(sel_keys());  // (the keys are staged later)
     for (int j = tid & (keys - 1); j < n; j += keys) {  // (one round unless n > NT, and then there is one group)
         // (8 loads in flight and not 12: 7B batch 1 57.9 us a step instead of 58.7; up to 4 heads do not take the work of 8)
         const float acc = h1 - h0 <= 4 ? prob_sum<4>(lg + j, a.capacity, sm.hm, sm.hrl, h0, h1)
@@ -317,7 +329,7 @@ __device__ __forceinline__ void plan_mass(const EvictArgs& a, int b, int n, int 
         if (groups == 1) row[j] = acc * (1.0f / (float)H);
         else part[tid] = acc;
     }
-    __syncthreads();                                    // the ranking may read these scores, or reuse sm.keys
+    __syncthreads();                                    // the ranking may read these scores, or reuse the keys' place
     if (groups > 1) {
         if (tid < n && tid < keys) {
             float acc = part[tid];
@@ -328,128 +340,243 @@ __device__ __forceinline__ void plan_mass(const EvictArgs& a, int b, int n, int 
     }
 }
 
+// What an eviction of sequence b starts from: visual rows, rows that exist (the appended one included), visual rows to keep.
+struct EvictCounts {
+    int n, len, k;
+    bool evicts;        // something to evict, lengths consistent
+};
+__device__ __forceinline__ EvictCounts evict_counts(const EvictArgs& a, int b) {
+    EvictCounts c;
+    c.n = max(0, min(a.vis_len[b], a.max_vis));
+    c.len = max(0, min(a.kv_len[b] + (a.appended ? 1 : 0), a.max_kv + (a.appended ? 1 : 0)));
+    c.k = a.keep_count < 0 ? c.n : min(a.keep_count, c.n);
+    c.evicts = c.k < c.n && a.sys_len + c.n <= c.len;
+    return c;
+}
+
+// The moves of an eviction: `inner` inside the visual segment, then `tail` rows that close up behind it.
+struct EvictMoves {
+    int inner, tail;
+};
+
+// Ranks the visual rows of sequence b by score_col, compacts the columns to the kept rows and lists the row moves: in LDS
+// (in_lds, at most kPlanMaxInline) or, for other workgroups, in global memory.  HOLE_FILL: a row move fills the i-th hole
+// among the first k rows with the i-th survivor behind them (sources >= k, destinations < k: disjoint), and the vacated end
+// [k, n) is refilled from the END of the cache when at least n - k rows follow the segment, else all rows that follow move down:
+// either way sources and destinations are disjoint (r >= g -> src >= len - g >= sys + n; r < g -> dst < sys + k + r < sys + n).
+// The global list holds both kinds, the LDS list the inner ones.
+template <int NT>
+__device__ __forceinline__ EvictMoves evict_rank(const EvictArgs& a, int b, const EvictCounts& c, SelectShared& sm, const bool in_lds,
+                                                 int (*lds_list)[2]) {
+    const int tid = threadIdx.x, n = c.n, k = c.k;
+    uint32_t* keys = sel_keys();
+    float* scores = a.score_col + b * a.col_stride;
+    int32_t* ids = a.id_col + b * a.col_stride;
+    int32_t* mv = a.moves + (int64_t)b * a.max_moves * 2;
+    TopSet top{0, 0, true};
+    auto key_at = [&](int i) { return keys[i]; };
+    auto idkey_at = [&](int i) { return ~(uint32_t)ids[i]; };
+    if (k > 0) {
+        for (int i = tid; i < n; i += NT) keys[i] = score_key(scores[i]);
+        top = top_set<NT>(key_at, idkey_at, n, k, sm);
+    }
+    auto kept_at = [&](int p) -> bool { return p < n && k > 0 && top.keeps(key_at, idkey_at, p); };
+    const int n_pad = (n + NT - 1) / NT * NT;
+    const int g = n - k;                                // rows evicted
+    // rows behind the visual segment that have to close up; none when the tail keeps its place
+    const int r = a.tail_start ? 0 : c.len - (a.sys_len + n);
+    int parity = 0, r1, r2, t1, t2;
+    if (a.mode == ST3_HOLE_FILL) {
+        int base_h = 0, base_f = 0;
+        for (int p0 = 0; p0 < n_pad; p0 += NT, parity ^= 1) {
+            const int p = p0 + tid;
+            const bool kept = kept_at(p);
+            const bool hole = p < k && !kept;
+            const bool fill = p >= k && kept;
+            plan_ranks<NT>(hole, fill, parity, sm, r1, r2, t1, t2);
+            if (in_lds) {                  // (ids that repeat could keep more rows than the list holds)
+                if (hole && base_h + r1 < kPlanMaxInline) lds_list[base_h + r1][0] = a.sys_len + p;
+                if (fill && base_f + r2 < kPlanMaxInline) lds_list[base_f + r2][1] = a.sys_len + p;
+            } else {
+                if (hole) mv[2 * (base_h + r1)] = a.sys_len + p;
+                if (fill) mv[2 * (base_f + r2) + 1] = a.sys_len + p;
+            }
+            base_h += t1; base_f += t2;
+        }
+        const int m = min(min(base_h, base_f), in_lds ? kPlanMaxInline : n);  // all equal when the ids are distinct
+        __syncthreads();                                // move list visible to the whole block
+        for (int i = tid; i < m; i += NT) {
+            const int dst = (in_lds ? lds_list[i][0] : mv[2 * i]) - a.sys_len;
+            const int src = (in_lds ? lds_list[i][1] : mv[2 * i + 1]) - a.sys_len;
+            scores[dst] = scores[src];
+            ids[dst] = ids[src];
+        }
+        const int cnt = min(g, r);
+        if (!in_lds) {
+            const int src0 = (r >= g) ? c.len - g : a.sys_len + n;
+            for (int j = tid; j < cnt; j += NT) {
+                mv[2 * (m + j)] = a.sys_len + k + j;
+                mv[2 * (m + j) + 1] = src0 + j;
+            }
+        }
+        return EvictMoves{m, cnt};
+    }
+    // first hole = number of leading kept positions
+    if (tid == 0) sm.red = n;
+    __syncthreads();
+    for (int p = tid; p < n; p += NT)
+        if (!kept_at(p)) { atomicMin(&sm.red, p); break; }
+    __syncthreads();
+    const int fh = sm.red;
+    int base = 0;
+    for (int p0 = 0; p0 < n_pad; p0 += NT, parity ^= 1) {
+        const int p = p0 + tid;
+        const bool kept = kept_at(p);
+        float sv = 0.f; int32_t iv = 0;
+        if (kept) { sv = scores[p]; iv = ids[p]; }
+        plan_ranks<NT>(kept, false, parity, sm, r1, r2, t1, t2);    // contains a barrier: loads precede stores
+        const int rank = base + r1;
+        if (kept && p > fh) {
+            scores[rank] = sv; ids[rank] = iv;
+            mv[2 * (rank - fh)] = a.sys_len + rank;
+            mv[2 * (rank - fh) + 1] = a.sys_len + p;
+        }
+        base += t1;
+    }
+    const int m = k - fh;
+    for (int j = tid; j < r; j += NT) {
+        mv[2 * (m + j)] = a.sys_len + k + j;
+        mv[2 * (m + j) + 1] = a.sys_len + n + j;
+    }
+    return EvictMoves{m, r};
+}
+
+// The lengths behind an eviction (or behind a step that evicts nothing); one thread.
+__device__ __forceinline__ void evict_publish(const EvictArgs& a, int b, const EvictCounts& c) {
+    if (c.evicts) a.vis_len[b] = c.k;
+    a.kv_len[b] = c.evicts && !a.tail_start ? c.len - (c.n - c.k) : c.len;
+}
+
 // The whole per-sequence plan, run by one workgroup of NT threads for sequence b:
-//   1. finish the visual mass the attention kernel left pending,
+//   1. finish the visual mass the attention kernel left pending (unless workgroups of their own do, mass_block),
 //   2. rank the visual rows by score_col and evict down to keep_count (columns, and - when
 //      inline_apply - the K/V rows themselves),
 //   3. publish the new lengths (including the row the attention kernel appended).
 template <int NT>
 __device__ __forceinline__ void evict_plan_body(const EvictArgs& a, int b, PlanShared& sm) {
     const int tid = threadIdx.x;
-    const int n = max(0, min(a.vis_len[b], a.max_vis));
-    const int len = max(0, min(a.kv_len[b] + (a.appended ? 1 : 0), a.max_kv + (a.appended ? 1 : 0)));
-    const int k = a.keep_count < 0 ? n : min(a.keep_count, n);
-    int new_len = len, moves_left = 0;
-    if (a.pending != nullptr && a.mass_dst != nullptr) {
-        // `len` and `n` are the lengths the attention call saw
+    const EvictCounts c = evict_counts(a, b);
+    int moves_left = 0;
+    if (a.pending != nullptr && a.mass_dst != nullptr && !a.mass_apart) {
+        // the lengths are those the attention call saw
         const int4 d = *reinterpret_cast<const int4*>(a.pending + b * 4);
         if (d.x & 1) {
             const int chunk = max(d.z, 32);
-            const int seen = seq_layout(a.sys_len, n, a.max_vis, len, a.tail_start, b).vlen;    // rows the attend launch saw
+            const int seen = seq_layout(a.sys_len, c.n, a.max_vis, c.len, a.tail_start, b).vlen;    // rows the attend launch saw
             const int ns = seen > 0 ? min((seen + chunk - 1) / chunk, min(d.y, a.nsplit_cap)) : 0;
-            if (ns > 0) plan_mass<NT>(a, b, n, ns, sm);
+            if (ns > 0) plan_mass<NT>(a, b, c.n, ns, sm);
         }
     }
-    if (k < n && a.sys_len + n <= len) {                // something to evict, lengths consistent
-        float* scores = a.score_col + b * a.col_stride;
-        int32_t* ids = a.id_col + b * a.col_stride;
-        int32_t* mv = a.moves + (int64_t)b * a.max_moves * 2;
-        TopSet top{0, 0, true};
-        auto key_at = [&](int i) { return sm.keys[i]; };
-        auto idkey_at = [&](int i) { return ~(uint32_t)ids[i]; };
-        if (k > 0) {
-            for (int i = tid; i < n; i += NT) sm.keys[i] = score_key(scores[i]);
-            top = top_set<NT>(key_at, idkey_at, n, k, sm);
-        }
-        auto kept_at = [&](int p) -> bool { return p < n && k > 0 && top.keeps(key_at, idkey_at, p); };
-        const int n_pad = (n + NT - 1) / NT * NT;
-        const int g = n - k;                            // rows evicted
-        // rows behind the visual segment that have to close up; none when the tail keeps its place
-        const int r = a.tail_start ? 0 : len - (a.sys_len + n);
-        int parity = 0, r1, r2, t1, t2;
-        if (a.mode == ST3_HOLE_FILL) {
-            const bool inl = a.inline_apply && g <= kPlanMaxInline;
-            int base_h = 0, base_f = 0;
-            for (int p0 = 0; p0 < n_pad; p0 += NT, parity ^= 1) {
-                const int p = p0 + tid;
-                const bool kept = kept_at(p);
-                const bool hole = p < k && !kept;
-                const bool fill = p >= k && kept;
-                plan_ranks<NT>(hole, fill, parity, sm, r1, r2, t1, t2);
-                if (inl) {                              // (ids that repeat could keep more rows than the list holds)
-                    if (hole && base_h + r1 < kPlanMaxInline) sm.mv[base_h + r1][0] = a.sys_len + p;
-                    if (fill && base_f + r2 < kPlanMaxInline) sm.mv[base_f + r2][1] = a.sys_len + p;
-                } else {
-                    if (hole) mv[2 * (base_h + r1)] = a.sys_len + p;
-                    if (fill) mv[2 * (base_f + r2) + 1] = a.sys_len + p;
-                }
-                base_h += t1; base_f += t2;
-            }
-            const int m = min(min(base_h, base_f), inl ? kPlanMaxInline : n);      // all equal when the ids are distinct
-            __syncthreads();                            // move list visible to the whole block
-            for (int i = tid; i < m; i += NT) {   // sources >= k, destinations < k: disjoint
-                int dst, src;
-                if (inl) { dst = sm.mv[i][0]; src = sm.mv[i][1]; }
-                else { dst = mv[2 * i]; src = mv[2 * i + 1]; }
-                dst -= a.sys_len; src -= a.sys_len;
-                scores[dst] = scores[src];
-                ids[dst] = ids[src];
-            }
-            // refill the vacated end of the segment [k, n): from the END of the cache when at least
-            // g rows follow the segment, else all r following rows move down.  Either way sources
-            // and destinations are disjoint: r >= g -> src >= len-g >= sys+n; r < g -> dst < sys+k+r < sys+n.
-            const int cnt = min(g, r);
-            const int src0 = (r >= g) ? len - g : a.sys_len + n;
-            if (inl) {
-                copy_rows_all_strips<NT>(a, b, m, [&](int i) { return (int64_t)sm.mv[i][0]; }, [&](int i) { return (int64_t)sm.mv[i][1]; });
-                if (cnt > 0) {
-                    __syncthreads();                    // those reads are done before [k, n) is overwritten
-                    copy_rows_all_strips<NT>(a, b, cnt, [&](int i) { return (int64_t)(a.sys_len + k + i); },
+    if (c.evicts) {
+        const bool inl = a.mode == ST3_HOLE_FILL && a.inline_apply && c.n - c.k <= kPlanMaxInline;
+        const EvictMoves m = evict_rank<NT>(a, b, c, sm, inl, sm.mv);
+        if (inl) {
+            const int g = c.n - c.k, r = c.len - (a.sys_len + c.n);
+            const int src0 = (r >= g) ? c.len - g : a.sys_len + c.n;
+            copy_rows<NT>(a, b, 0, 1, m.inner, [&](int i) { return (int64_t)sm.mv[i][0]; }, [&](int i) { return (int64_t)sm.mv[i][1]; });
+            if (m.tail > 0) {
+                __syncthreads();                        // those reads are done before [k, n) is overwritten
+                copy_rows<NT>(a, b, 0, 1, m.tail, [&](int i) { return (int64_t)(a.sys_len + c.k + i); },
                                          [&](int i) { return (int64_t)(src0 + i); });
-                }
-            } else {
-                for (int j = tid; j < cnt; j += NT) {
-                    mv[2 * (m + j)] = a.sys_len + k + j;
-                    mv[2 * (m + j) + 1] = src0 + j;
-                }
-                moves_left = m + cnt;
             }
         } else {
-            // first hole = number of leading kept positions
-            if (tid == 0) sm.red = n;
-            __syncthreads();
-            for (int p = tid; p < n; p += NT)
-                if (!kept_at(p)) { atomicMin(&sm.red, p); break; }
-            __syncthreads();
-            const int fh = sm.red;
-            int base = 0;
-            for (int p0 = 0; p0 < n_pad; p0 += NT, parity ^= 1) {
-                const int p = p0 + tid;
-                const bool kept = kept_at(p);
-                float sv = 0.f; int32_t iv = 0;
-                if (kept) { sv = scores[p]; iv = ids[p]; }
-                plan_ranks<NT>(kept, false, parity, sm, r1, r2, t1, t2);    // contains a barrier: loads precede stores
-                const int rank = base + r1;
-                if (kept && p > fh) {
-                    scores[rank] = sv; ids[rank] = iv;
-                    mv[2 * (rank - fh)] = a.sys_len + rank;
-                    mv[2 * (rank - fh) + 1] = a.sys_len + p;
-                }
-                base += t1;
-            }
-            const int m = k - fh;
-            for (int j = tid; j < r; j += NT) {
-                mv[2 * (m + j)] = a.sys_len + k + j;
-                mv[2 * (m + j) + 1] = a.sys_len + n + j;
-            }
-            moves_left = m + r;
+            moves_left = m.inner + m.tail;
         }
-        new_len = a.tail_start ? len : len - g;
-        if (tid == 0) a.vis_len[b] = k;
     }
     if (tid == 0) {
         a.move_cnt[b] = moves_left;
-        a.kv_len[b] = new_len;
+        evict_publish(a, b, c);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same plan in independent parts, for columns that do not take this step's mass (EvictArgs::mass_apart): the ranking needs
+// nothing of the step's attention and the mass nothing of the ranking.  The whole-step call ranks in spare workgroups of its
+// attention launch (evict_rank_early), whose chain of a dozen dependent steps is then hidden behind the reads of K and V, and
+// what is left for the launch behind it - masses, row moves, lengths, merges - are short chains in many small workgroups.  The
+// parts do not read the lengths that one of them advances: rows attended and visual rows come from the attention's descriptor,
+// the number of moves from the ranking.  us a launch of plans, whole plan in one workgroup -> in parts: two layers of 64 rows in
+// float32 8.5 -> 5.2, 7B batch 1 12.5 -> 8.9, batch 4 17.9 -> 13.2, 13B batch 8 with fast annealing 32.5 -> 30 (its row moves),
+// batch 32 37 -> 29, high resolution batch 8 27.6 -> 20.
+// ---------------------------------------------------------------------------------------------
+
+// How many moves the ranking has left to the rows' workgroups: inner | tail << kMoveTailShift (both below 2^6 + 1 rows).
+constexpr int kMoveTailShift = 8;
+
+// Ranking, columns and the move list of sequence b, beside the attention.  (Moves of a launch of their own: counted in one.)
+template <int NT>
+__device__ __forceinline__ void evict_rank_early(const EvictArgs& a, int b, SelectShared& sm) {
+    const EvictCounts c = evict_counts(a, b);
+    EvictMoves m{0, 0};
+    if (c.evicts) m = evict_rank<NT>(a, b, c, sm, false, nullptr);
+    if (threadIdx.x == 0) a.move_cnt[b] = a.inline_apply ? m.inner | (m.tail << kMoveTailShift) : m.inner + m.tail;
+}
+
+// Applies the moves that evict_rank_early has listed to a part of the strips of sequence b.
+template <int NT>
+__device__ __forceinline__ void move_rows_block(const EvictArgs& a, int b, int part, int parts) {
+    const int packed = a.move_cnt[b], inner = packed & ((1 << kMoveTailShift) - 1), tail = packed >> kMoveTailShift;
+    const int32_t* mv = a.moves + (int64_t)b * a.max_moves * 2;
+    copy_rows<NT>(a, b, part, parts, inner, [&](int i) { return (int64_t)mv[2 * i]; }, [&](int i) { return (int64_t)mv[2 * i + 1]; });
+    if (tail > 0) {                                     // (uniform)
+        __syncthreads();                                // those reads are done before the segment's end is overwritten
+        mv += 2 * inner;
+        copy_rows<NT>(a, b, part, parts, tail, [&](int i) { return (int64_t)mv[2 * i]; }, [&](int i) { return (int64_t)mv[2 * i + 1]; });
+    }
+}
+
+// kMassKeys mass entries of sequence b from key j0 on, by a workgroup of NT threads: a wave takes a share of the heads, a lane four
+// keys of a row (one 16-byte load), and the shares are added in order.
+constexpr int kMassKeys = 4 * kWave;
+struct MassShared {
+    float hm[1024], hrl[1024];
+    f32x4_t part[kPlanThreadsMost / kWave][kWave];
+};
+template <int NT>
+__device__ __forceinline__ void mass_block(const EvictArgs& a, int b, int j0, MassShared& sm) {
+    constexpr int kWaves = NT / kWave, kUR = 8;
+    const int4 d = *reinterpret_cast<const int4*>(a.pending + b * 4);
+    const int n = min(a.own_pending[b * 4 + 3] >> 1, a.max_vis);
+    const int chunk = max(d.z, 32), seen = d.x >> 1;
+    const int ns = seen > 0 ? min((seen + chunk - 1) / chunk, min(d.y, a.nsplit_cap)) : 0;
+    if (!(d.x & 1) || ns <= 0 || j0 >= n) return;       // (uniform)
+    head_norms<NT>(a.part_ml, b, a.H, ns, a.nsplit_cap, sm.hm, sm.hrl);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), lane = threadIdx.x % kWave, j = j0 + 4 * lane;
+    const int per = (a.H + kWaves - 1) / kWaves, h1 = min(a.H, (wave + 1) * per);
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    if (j < n) {
+        // (a load may reach three floats past the visual rows: more of the row, the next one or what lies behind the logits)
+        const float* lg = a.logits + a.sys_len + (int64_t)b * a.H * a.capacity + j;
+        for (int h = wave * per; h < h1; h += kUR) {
+            f32x4_t v[kUR];
+#pragma unroll
+            for (int u = 0; u < kUR; ++u) v[u] = *reinterpret_cast<const f32x4_a4_t*>(lg + (int64_t)min(h + u, h1 - 1) * a.capacity);
+#pragma unroll
+            for (int u = 0; u < kUR; ++u) {
+                if (h + u >= h1) break;
+                const float m = sm.hm[h + u], rl = sm.hrl[h + u];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[i] += exp2_fast(v[u][i] - m) * rl;
+            }
+        }
+        sm.part[wave][lane] = acc;
+    }
+    __syncthreads();
+    if (wave == 0 && j < n) {
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) acc += sm.part[w][lane];
+        float* out = a.mass_dst + b * a.mass_stride + j;
+        for (int i = 0; i < min(4, n - j); ++i) out[i] = acc[i] * (1.0f / (float)a.H);
     }
 }
 
@@ -466,14 +593,19 @@ st3_status build_evict_args(const st3_attn_shape* shape, const st3_kv_layer* kv,
                             int64_t mass_stride, EvictArgs& ea, bool& needs_apply, bool batched,
                             const void* mass_workspace = nullptr, int32_t mass_capacity = 0);
 void launch_evict_plan(const EvictArgs& ea, int B, hipStream_t st);
-constexpr int kPlanBatch = 16;     // plans that travel by value: 200 bytes each (the argument block would hold 20)
+constexpr int kPlanBatch = 16;     // plans that travel by value: 216 bytes each (the argument block would hold 18)
 // Plans of n layers (device work of one decode step) with one launch per kPlanBatch layers.
 void launch_evict_plan_batch(const EvictArgs* plans, int n, int B, hipStream_t st);
 // The plans of n layers from the table entries that whole-step attention launches have left in the layers' workspaces;
 // merge: some strips were cut into chunks, whose partials are merged here too.  One launch per kPlanTableMax layers.
 constexpr int kPlanTableMax = 64;
-// most_vis: the largest bound of any layer's visual rows.
-void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry, int n, int most_vis, bool merge, hipStream_t st);
+struct PlanNeeds {
+    int most_vis;       // the largest bound of any layer's visual rows
+    bool merge;         // some strip was cut
+    bool apart;         // every layer's rows have been ranked beside the attention (kStepApart)
+    bool moves;         // some layer's rows are moved by the launch
+};
+void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry, int n, const PlanNeeds& needs, hipStream_t st);
 void launch_evict_apply(const EvictArgs& ea, int B, hipStream_t st);
 
 }  // namespace st3

@@ -34,6 +34,7 @@ template <int NT>
 __global__ __launch_bounds__(NT) void select_topk_kernel(TopkArgs a) {
     __shared__ SelectShared sm;
     const int b = blockIdx.x, tid = threadIdx.x;
+    uint32_t* keys = sel_keys();
     int n = a.n_dev ? a.n_dev[b] : a.n;
     n = max(0, min(n, a.n));
     const int k = min(a.k, n);
@@ -42,12 +43,12 @@ __global__ __launch_bounds__(NT) void select_topk_kernel(TopkArgs a) {
     uint8_t* mask = a.mask ? a.mask + (int64_t)b * a.n : nullptr;
     int32_t* idx = a.idx ? a.idx + (int64_t)b * a.idx_stride : nullptr;
     const bool staged = n <= kSelLdsKeys;
-    auto key_at = [&](int i) -> uint32_t { return staged ? sm.keys[i] : score_key(scores[i]); };
+    auto key_at = [&](int i) -> uint32_t { return staged ? keys[i] : score_key(scores[i]); };
     auto idkey_at = [&](int i) { return ~(uint32_t)(ids ? ids[i] : i); };
     TopSet top{0, 0, true};
     if (k > 0 && k < n) {
         if (staged)
-            for (int i = tid; i < n; i += NT) sm.keys[i] = score_key(scores[i]);
+            for (int i = tid; i < n; i += NT) keys[i] = score_key(scores[i]);
         top = top_set<NT>(key_at, idkey_at, n, k, sm);
     }
     int base = 0, parity = 0, r1, r2, t1, t2;
@@ -272,6 +273,19 @@ constexpr int kInlineEvictBatched = 48;
 constexpr int kInlineEvictAloneFixedTail = 8;
 constexpr int kInlineEvictAlone = 4;
 
+// Whether the mass of this step may land in what the eviction ranks by, or moves (mode "current" writes it into the score column).
+static bool columns_take_mass(const EvictArgs& ea, int B) {
+    if (ea.mass_dst == nullptr || ea.keep_count < 0) return false;
+    const uintptr_t bytes = sizeof(float);
+    const uintptr_t m0 = reinterpret_cast<uintptr_t>(ea.mass_dst), m1 = m0 + ((uintptr_t)(B - 1) * ea.mass_stride + ea.max_vis) * bytes;
+    const uintptr_t span = ((uintptr_t)(B - 1) * ea.col_stride + ea.max_vis) * bytes;
+    for (const void* col : {(const void*)ea.score_col, (const void*)ea.id_col}) {
+        const uintptr_t c0 = reinterpret_cast<uintptr_t>(col);
+        if (m0 < c0 + span && c0 < m1) return true;
+    }
+    return false;
+}
+
 st3_status build_evict_args(const st3_attn_shape* shape, const st3_kv_layer* kv, const st3_segments* seg,
                             float* score_col, int32_t* id_col, int64_t col_stride, int32_t keep_count, int32_t mode,
                             void* workspace, size_t workspace_bytes, int appended, float* mass_dst,
@@ -309,13 +323,16 @@ st3_status build_evict_args(const st3_attn_shape* shape, const st3_kv_layer* kv,
         if (mass_workspace) ea.capacity = mass_capacity;
         ea.mass_dst = mass_dst; ea.mass_stride = mass_stride;
     }
+    ea.own_pending = reinterpret_cast<const int32_t*>(ws + wl.pending);
+    ea.mass_apart = batched && !columns_take_mass(ea, B);
     needs_apply = evicting && !ea.inline_apply;
     return ST3_OK;
 }
 
 void launch_evict_plan(const EvictArgs& ea, int B, hipStream_t st) {
     with_threads(plan_threads(B, ea.max_vis, ea.mass_dst != nullptr ? ea.H : 1), [&](auto nt) {
-        evict_plan_kernel<decltype(nt)::value><<<B, decltype(nt)::value, 0, st>>>(ea);
+        constexpr int NT = decltype(nt)::value;
+        evict_plan_kernel<NT><<<B, NT, plan_lds(ea.max_vis, NT), st>>>(ea);
     });
 }
 
@@ -325,25 +342,34 @@ struct EvictBatch {
 };
 static_assert(sizeof(EvictBatch) <= 4000, "plans of one batch must fit the kernel argument segment");
 
-// grid (B, layers of the batch)
+// grid (B, layers of the batch, 1 + mass workgroups): z = 0 runs the plan, z >= 1 finish kMassKeys entries of the mass each where
+// the plan need not wait for them.
 template <int NT>
 __global__ __launch_bounds__(NT) void evict_plan_batch_kernel(EvictBatch batch) {
-    __shared__ PlanShared sm;
-    evict_plan_body<NT>(batch.layer[blockIdx.y], blockIdx.x, sm);
+    __shared__ union { PlanShared plan; MassShared mass; } sm;
+    const EvictArgs& a = batch.layer[blockIdx.y];
+    if (blockIdx.z == 0) evict_plan_body<NT>(a, blockIdx.x, sm.plan);
+    else if (a.mass_apart && a.mass_dst != nullptr) mass_block<NT>(a, blockIdx.x, ((int)blockIdx.z - 1) * kMassKeys, sm.mass);
 }
 
 void launch_evict_plan_batch(const EvictArgs* plans, int n, int B, hipStream_t st) {
     for (int i0 = 0; i0 < n; i0 += kPlanBatch) {
         const int cnt = n - i0 < kPlanBatch ? n - i0 : kPlanBatch;
         EvictBatch batch;
-        int most_vis = 0;
+        int most_vis = 0, apart_vis = 0;
+        bool mass_in_plan = false;
         for (int i = 0; i < cnt; ++i) {
-            batch.layer[i] = plans[i0 + i];
-            most_vis = std::max(most_vis, plans[i0 + i].max_vis);
+            const EvictArgs& p = plans[i0 + i];
+            batch.layer[i] = p;
+            most_vis = std::max(most_vis, p.max_vis);
+            if (p.mass_apart && p.mass_dst != nullptr) apart_vis = std::max(apart_vis, p.max_vis);
+            mass_in_plan = mass_in_plan || !p.mass_apart;
         }
         for (int i = cnt; i < kPlanBatch; ++i) batch.layer[i] = EvictArgs{};
-        with_threads(plan_threads((int64_t)B * cnt, most_vis, plans[i0].H), [&](auto nt) {
-            evict_plan_batch_kernel<decltype(nt)::value><<<dim3(B, cnt), decltype(nt)::value, 0, st>>>(batch);
+        const dim3 grid(B, cnt, 1 + (apart_vis + kMassKeys - 1) / kMassKeys);
+        with_threads(plan_threads((int64_t)B * cnt, most_vis, mass_in_plan ? plans[i0].H : 1), [&](auto nt) {
+            constexpr int NT = decltype(nt)::value;
+            evict_plan_batch_kernel<NT><<<grid, NT, plan_lds(most_vis, NT), st>>>(batch);
         });
     }
 }
@@ -363,7 +389,8 @@ __global__ __launch_bounds__(NT) void evict_plan_table_kernel(PlanTable table) {
     // read once, ahead of every store of this kernel: uniform address, so the fields arrive in scalar registers
     const StepLayer e = *table.layer[blockIdx.y];
     if (blockIdx.z == 0) {
-        const EvictArgs a = plan_from_entry(table.c, e);
+        EvictArgs a = plan_from_entry(table.c, e);
+        a.mass_apart = 0;
         evict_plan_body<NT>(a, blockIdx.x, sm);
     } else if (e.nsplit > 1) {
         const int h0 = ((int)blockIdx.z - 1) * kMergeHeads;
@@ -371,17 +398,55 @@ __global__ __launch_bounds__(NT) void evict_plan_table_kernel(PlanTable table) {
     }
 }
 
-void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry, int n, int most_vis, bool merge, hipStream_t st) {
+// What is left of the plans when the rows have been ranked beside the attention.  grid (B, layers, moves + masses + merges), 256
+// threads: workgroups z < move_wgs move rows (the first one advances the lengths too), the next mass_wgs finish kMassKeys
+// entries of the mass each, the rest merge the chunk partials of kMergeHeads heads each.
+struct FinishTable {
+    PlanTable t;
+    int32_t move_wgs, mass_wgs;
+};
+static_assert(sizeof(FinishTable) <= 4000, "the table travels by value");
+__global__ __launch_bounds__(256) void step_finish_kernel(FinishTable f) {
+    __shared__ MassShared sm;
+    const StepLayer e = *f.t.layer[blockIdx.y];
+    const int z = blockIdx.z, b = blockIdx.x;
+    if (z < f.move_wgs + f.mass_wgs) {
+        const EvictArgs a = plan_from_entry(f.t.c, e);
+        if (z >= f.move_wgs) {
+            if (a.mass_dst != nullptr) mass_block<256>(a, b, (z - f.move_wgs) * kMassKeys, sm);
+            return;
+        }
+        if (z == 0 && threadIdx.x == 0) evict_publish(a, b, evict_counts(a, b));
+        if (a.inline_apply) move_rows_block<256>(a, b, z, f.move_wgs);
+    } else if (e.nsplit > 1) {
+        const int h0 = (z - f.move_wgs - f.mass_wgs) * kMergeHeads;
+        if (h0 < f.t.c.H) merge_chunks(f.t.c, e, b, h0, h0 + kMergeHeads);
+    }
+}
+
+// Workgroups that move rows, over all plans of a launch.  us a step at 512 / 1024 / 2048 / 4096: 7B batch 1 54.4 / 55.0 / 55.0 / 55.9,
+// 13B batch 8 with fast annealing 533 / 507 / 504 / 503, batch 32 2403 / 2408 / 2402 / 2403, high resolution batch 8 630 / 628 / 628 / 627.
+constexpr int kFinishMoveWgs = 2048;
+void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry, int n, const PlanNeeds& needs, hipStream_t st) {
     for (int i0 = 0; i0 < n; i0 += kPlanTableMax) {
         const int cnt = n - i0 < kPlanTableMax ? n - i0 : kPlanTableMax;
-        PlanTable table;
+        FinishTable f;
+        PlanTable& table = f.t;
         table.c = c; table.c.layers = cnt;
         for (int i = 0; i < cnt; ++i) table.layer[i] = entry[i0 + i];
         for (int i = cnt; i < kPlanTableMax; ++i) table.layer[i] = nullptr;
-        const int merge_wgs = merge ? (c.H + kMergeHeads - 1) / kMergeHeads : 0;
+        const int merge_wgs = needs.merge ? (c.H + kMergeHeads - 1) / kMergeHeads : 0;
+        if (needs.apart) {
+            const int64_t plans = (int64_t)c.B * cnt, pieces = 2 * c.H * (c.D * c.elem_bytes / 16) / 256;
+            f.move_wgs = needs.moves ? (int)std::max<int64_t>(1, std::min<int64_t>(pieces, kFinishMoveWgs / plans)) : 1;
+            f.mass_wgs = (needs.most_vis + kMassKeys - 1) / kMassKeys;
+            step_finish_kernel<<<dim3(c.B, cnt, f.move_wgs + f.mass_wgs + merge_wgs), 256, 0, st>>>(f);
+            continue;
+        }
         const dim3 grid(c.B, cnt, 1 + merge_wgs);
-        with_threads(plan_threads((int64_t)c.B * cnt, most_vis, c.H), [&](auto nt) {
-            evict_plan_table_kernel<decltype(nt)::value><<<grid, decltype(nt)::value, 0, st>>>(table);
+        with_threads(plan_threads((int64_t)c.B * cnt, needs.most_vis, c.H), [&](auto nt) {
+            constexpr int NT = decltype(nt)::value;
+            evict_plan_table_kernel<NT><<<grid, NT, plan_lds(needs.most_vis, NT), st>>>(table);
         });
     }
 }
@@ -442,6 +507,7 @@ __global__ __launch_bounds__(kDiagThreads) void overlap_topk_kernel(OverlapArgs 
     __shared__ uint32_t seen[kDiagIdSpace / 32];
     __shared__ int sm_count;
     const int b = blockIdx.x, tid = threadIdx.x;
+    uint32_t* keys = sel_keys();
     for (int i = tid; i < kDiagIdSpace / 32; i += kDiagThreads) seen[i] = 0u;
     if (tid == 0) sm_count = 0;
     __syncthreads();
@@ -452,11 +518,11 @@ __global__ __launch_bounds__(kDiagThreads) void overlap_topk_kernel(OverlapArgs 
         int n = n_dev ? n_dev[b] : (side ? a.n_b : a.n_a);
         n = max(0, min(n, side ? a.n_b : a.n_a));
         const int k = min(a.k, n);
-        auto key_at = [&](int i) { return sm.keys[i]; };
+        auto key_at = [&](int i) { return keys[i]; };
         auto idkey_at = [&](int i) { return ~(uint32_t)ids[i]; };
         TopSet top{0, 0, true};
         if (k > 0 && k < n) {
-            for (int i = tid; i < n; i += kDiagThreads) sm.keys[i] = score_key(scores[i]);
+            for (int i = tid; i < n; i += kDiagThreads) keys[i] = score_key(scores[i]);
             top = top_set<kDiagThreads>(key_at, idkey_at, n, k, sm);
         }
         int local = 0;
@@ -537,7 +603,7 @@ extern "C" st3_status st3_overlap_topk(const float* score_a, const int32_t* ids_
         return ST3_ERR_UNSUPPORTED;
     st3::OverlapArgs a{score_a, ids_a, stride_a, n_a_dev, n_a, score_b, ids_b, stride_b, n_b_dev, n_b, k, id_space,
                        overlap, topk_a};
-    st3::overlap_topk_kernel<<<batch, st3::kDiagThreads, 0, reinterpret_cast<hipStream_t>(stream)>>>(a);
+    st3::overlap_topk_kernel<<<batch, st3::kDiagThreads, sizeof(uint32_t) * std::max(n_a, n_b), reinterpret_cast<hipStream_t>(stream)>>>(a);
     return st3::check_launch();
 }
 
@@ -565,7 +631,8 @@ extern "C" st3_status st3_select_topk(const float* scores, int64_t score_stride,
     a.scores = scores; a.score_stride = score_stride; a.ids = tie_ids; a.id_stride = id_stride;
     a.n_dev = n_dev; a.n = n; a.k = k; a.mask = keep_mask; a.idx = keep_idx; a.idx_stride = idx_stride;
     st3::with_threads(st3::topk_threads(batch, n), [&](auto nt) {
-        st3::select_topk_kernel<decltype(nt)::value><<<batch, decltype(nt)::value, 0, reinterpret_cast<hipStream_t>(stream)>>>(a);
+        st3::select_topk_kernel<decltype(nt)::value><<<batch, decltype(nt)::value, sizeof(uint32_t) * std::min(n, st3::kSelLdsKeys),
+                                                     reinterpret_cast<hipStream_t>(stream)>>>(a);
     });
     return st3::check_launch();
 }
