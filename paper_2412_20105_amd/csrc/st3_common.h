@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "st3.h"
+#include "st3_step.h"
 
 namespace st3 {
 
@@ -108,12 +109,18 @@ inline int decode_nsplit(int B, int H, int max_kv, int target_wgs = kDecodeTarge
     return ns < 1 ? 1 : (int)ns;
 }
 // Chunks of a strip of `len` rows in the whole-step call, where `rows` is the sum of the lengths of all ordinary (or all lazy)
-// layers of the step, over however many launches, and the chunk partials are merged inside the step's plan launch: chunks of
-// equal LENGTH over all layers, as long as about kStepTargetWgs workgroups in all allow.  Measured at targets of 1024 / 2048 / 3072 / 4096 / 8192, us per step:
-// 7B batch 1 72.1 / 72.6 / 73.4 / 78.2 / 93.1, 13B batch 8 with lazy layers 563 / 563 / 571 / 565 / 611, high resolution batch 8
-// E4M3 699 / 699 / 698 / 699 / 711; 13B batch 32 is not cut by any of them.
+// layers of the step, over however many launches, and the chunk partials are merged by the launch behind the attention: chunks of
+// equal LENGTH over all layers, as long as about kStepTargetWgs workgroups in all allow (two for each compute unit), but no
+// shorter than kStepMinChunk.  us per step at targets of 256 / 384 / 512 / 768 / 1024 / 2048 / 4096: 7B batch 1 42 / 42 / 42 / 44 /
+// 46 / 45 / 50, E4M3 28 / 28 / 28 / 32 / 34 / 34 / 42, batch 2 74 / 74 / 74 / 74 / 74 / 78 / 79, 8 layers 24 / 23 / 22 / 26 / 26 / 29 / 34, 4 layers of
+// batch 4 30 / 30 / 31 / 31 / 30 / 33 / 36, 4 layers of 2000 visual rows 33 / 31 / 28 / 30 / 29 / - / -, 13B batch 1 97 / 97 / 96 / 96 / 96 / 100 /
+// 94, high resolution batch 1 E4M3 84 / 84 / 84 / 88 / 93 / 94 / 98.  Shortest chunk of 64 / 96 / 128 / 192 rows: 2 layers of the 7B
+// shape 14.8 / 15.2 / 14.9 / 15.2, of 20 heads and batch 3 16.0 / 16.1 / 16.0 / 17.2, 12 layers of 8 heads 17.8 / 17.7 / 17.5 / 18.1, 5 layers
+// of 12 heads 15.8 / 15.5 / 15.9 / 17.0.  (A chunk index must not meet the same XCDs in every strip: workgroup ids go round-robin to
+// the 8 XCDs, so the launches number heads fastest and chunks next.  With chunks fastest a layer cut in one beside layers cut in two
+// left half of the XCDs idle: 7B batch 4 143 -> 182 us from one target to the next.)
 #ifndef ST3_STEP_TARGET_WGS
-#define ST3_STEP_TARGET_WGS 2048
+#define ST3_STEP_TARGET_WGS 512
 #endif
 #ifndef ST3_STEP_MIN_CHUNK
 #define ST3_STEP_MIN_CHUNK 64
@@ -150,57 +157,8 @@ inline int decode_chunk(int max_kv, int nsplit) {
     return c < 32 ? 32 : c;
 }
 
-// ---------------------------------------------------------------------------------------------
-// The whole-step call serves many layers with one attention launch.  What differs from layer to layer travels by value:
-// 184 bytes a layer, kStepLayersMax layers in the 4 KB argument block.  The launch leaves each entry in its layer's
-// workspace, where the step's one plan launch (which covers more layers than fit one argument block) reads it.
-// ---------------------------------------------------------------------------------------------
-struct StepCommon {
-    int32_t B, H, D, mode;      // mode: st3_compact_mode
-    int32_t elem_bytes;         // of q, the new rows, the outputs and plain caches: 2 (bf16) or 4 (float32)
-    float scale_l2;
-    int32_t layers;             // entries of the table
-};
-struct StepLayer {
-    const void* q;              // lazy layer: the source layer's workspace
-    void* k;                    // lazy layer: null unless it caches keys all the same (they move with an eviction)
-    void* v;
-    const void* k_new;          // lazy layer: unused
-    const void* v_new;
-    void* out;
-    int32_t* kv_len;
-    int32_t* vis_len;
-    const int32_t* tail_start;
-    float* score_col;
-    int32_t* id_col;
-    float* mass;                // null: no mass
-    char* ws;
-    const float* k_scale;
-    const float* v_scale;
-    int64_t stride_b, stride_h; // cache elements
-    int32_t stride_t, col_stride, mass_stride;
-    int32_t sys_len, max_vis, max_kv;       // bounds BEFORE the step (max_kv does not count the appended row)
-    int32_t keep_count;         // < 0: no eviction
-    int32_t chunk;              // rows per chunk of a strip
-    int32_t hint_base, hint_gap;            // lazy layer: hint_base is the source cache's capacity
-    int32_t capacity;
-    uint8_t nsplit, nsplit_cap; // chunks per strip of this launch / that the workspace has room for (at most 64)
-    uint8_t src_nsplit_cap;     // lazy layer: of the source's workspace
-    uint8_t flags;
-};
-static_assert(sizeof(StepLayer) == 184, "kStepLayersMax entries must fit the kernel-argument block");
-constexpr uint8_t kStepInlineApply = 1, kStepKeepAll = 2, kStepLazy = 4, kStepWantMass = 8, kStepE4M3 = 16;
-constexpr uint8_t kStepApart = 32;      // the next eviction does not rank by this step's mass
-constexpr int kStepLayersMax = 21;
-constexpr int kStepLayerWords = sizeof(StepLayer) / 4;
-struct StepTable {
-    StepCommon c;
-    StepLayer layer[kStepLayersMax];
-};
-static_assert(sizeof(StepTable) <= 4000, "the table travels by value");
-
 struct DecodeWs {
-    size_t part_o, part_ml, logits, pending, step_entry, moves_cnt, moves, total;
+    size_t part_o, part_ml, logits, pending, moves_cnt, moves, total;
     int nsplit_cap;
     int max_moves;
 };
@@ -216,7 +174,6 @@ __host__ __device__ inline DecodeWs decode_ws_sized(int B, int H, int D, int cap
     w.part_ml = off;    off = align_up(off + BH * w.nsplit_cap * 2 * sizeof(float), 256);
     w.logits = off;     off = align_up(off + BH * (size_t)capacity * sizeof(float), 256);   // [B,H,capacity]
     w.pending = off;    off = align_up(off + (size_t)B * 4 * sizeof(int32_t), 256);         // [B][4]
-    w.step_entry = off; off = align_up(off + sizeof(StepLayer), 256);                        // what a whole-step launch leaves
     w.moves_cnt = off;  off = align_up(off + (size_t)B * sizeof(int32_t), 256);
     w.moves = off;      off = align_up(off + (size_t)B * w.max_moves * 2 * sizeof(int32_t), 256);
     w.total = off;

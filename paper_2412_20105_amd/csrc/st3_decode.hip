@@ -281,13 +281,6 @@ void decode_attend_kernel(DecodeArgs a) {
     attend_chunk<T, KT, D, U, false>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-// Workgroup (split, h, b) = (0, 0, 0) of a layer leaves the layer's table entry in its workspace (plain vector
-// stores): the step's plan launch reads it there.
-__device__ __forceinline__ void leave_entry(const StepCommon& c, const StepLayer& e, const DecodeWs& wl) {
-    if (threadIdx.x < kStepLayerWords)
-        reinterpret_cast<uint32_t*>(e.ws + wl.step_entry)[threadIdx.x] = reinterpret_cast<const uint32_t*>(&e)[threadIdx.x];
-}
-
 // Workgroup (0, H) of a sequence and layer of a whole-step launch ranks the rows of a layer whose next eviction does not wait for
 // the mass of this step (kStepApart, evict_rank_early).  (Behind the attention's workgroups of the same layer; all of them are
 // resident long before the last one ends.)
@@ -297,20 +290,21 @@ __device__ __forceinline__ void rank_workgroup(const StepCommon& c, const StepLa
     evict_rank_early<kDecodeThreads>(plan_from_entry(c, e), b, sm);
 }
 
-// The attention of several layers of a step that do not depend on each other; grid (most chunks of any of them, H + 1,
+// The attention of several layers of a step that do not depend on each other; grid (H + 1, most chunks of any of them,
 // B * layers), layers in order, so the longest strips (early layers keep the most rows) start first.  Bound by HBM; as a
 // launch per layer it was bound by the ramp and the tail of each launch and the gap behind it (about 9 us a layer, whatever
-// its bytes).  Whole step, us, one launch per layer -> up to 21 layers per launch: 7B batch 1 191 -> 75 (209 MB), 13B batch 8
-// with lazy layers 707 -> 557 (2.9 GB), high resolution batch 8 E4M3 830 -> 700 (3.6 GB), 13B batch 32 2514 -> 2437 (15.4 GB,
-// 6.3 TB/s; a kernel that only reads the same rows takes 2155).
+// its bytes).  Whole step, us, one launch per layer -> up to 35 layers per launch: 7B batch 1 191 -> 42 (209 MB), 13B batch 8
+// with lazy layers 707 -> 496 (2.9 GB), high resolution batch 8 E4M3 830 -> 618 (3.6 GB), 13B batch 32 2514 -> 2407 (15.4 GB,
+// 6.4 TB/s; a kernel that only reads the same rows takes 2155).
 template <typename T, typename KT, int D, int U, bool NTS>
 __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS)
 __attribute__((amdgpu_waves_per_eu(ST3_DECODE_MIN_BLOCKS, ST3_DECODE_MIN_BLOCKS)))
 void decode_attend_layers_kernel(StepTable t) {
     const StepCommon& c = t.c;
     const int li = __builtin_amdgcn_readfirstlane((int)blockIdx.z / c.B), b = (int)blockIdx.z - li * c.B;
-    const int split = blockIdx.x, h = blockIdx.y;
-    const StepLayer& e = t.layer[li];
+    const int split = blockIdx.y, h = blockIdx.x;
+    constexpr bool coded = sizeof(KT) == 1;
+    const StepLayer e = unpack_attend<coded>(t.w + li * (coded ? kAttendWordsE4M3 : kAttendWords), sizeof(KT));
     if (h == c.H) return rank_workgroup(c, e, split, b);
     if (split >= e.nsplit) return;
     const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
@@ -330,7 +324,6 @@ void decode_attend_layers_kernel(StepTable t) {
     a.stage_rows = 0;           // (the launcher's)
     a.pending = reinterpret_cast<int32_t*>(e.ws + wl.pending);
     a.k_new = e.k_new; a.v_new = e.v_new; a.out = e.out;
-    if (split == 0 && h == 0 && b == 0) leave_entry(c, e, wl);
     attend_chunk<T, KT, D, U, NTS>(a, split, h, b);
 }
 
@@ -490,8 +483,9 @@ template <typename T, typename KT, int D, int U>
 __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_inherit_layers_kernel(StepTable t) {
     const StepCommon& c = t.c;
     const int li = __builtin_amdgcn_readfirstlane((int)blockIdx.z / c.B), b = (int)blockIdx.z - li * c.B;
-    const int split = blockIdx.x, h = blockIdx.y;
-    const StepLayer& e = t.layer[li];
+    const int split = blockIdx.y, h = blockIdx.x;
+    constexpr bool coded = sizeof(KT) == 1;
+    const StepLayer e = unpack_attend<coded>(t.w + li * (coded ? kAttendWordsE4M3 : kAttendWords), sizeof(KT));
     if (h == c.H) return rank_workgroup(c, e, split, b);
     if (split >= e.nsplit) return;
     const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
@@ -509,7 +503,6 @@ __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_
     a.own_pending = reinterpret_cast<int32_t*>(e.ws + wl.pending);
     a.part_o = reinterpret_cast<float*>(e.ws + wl.part_o);
     a.v_new = e.v_new; a.v_scale = e.v_scale; a.out = e.out;
-    if (split == 0 && h == 0 && b == 0) leave_entry(c, e, wl);
     inherit_chunk<T, KT, D, U>(a, split, h, b);
 }
 
@@ -543,22 +536,8 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(FinishArgs a) {
         const int h = blockIdx.x;
         const int64_t bh = (int64_t)b * a.H + h;
         if (tid >= D || ns == 0) return;                // empty sequence: the attend kernel wrote zeros
-        if (a.plain_sum) {
-            float o = 0.f;
-            for (int s = 0; s < ns; ++s) o += a.part_o[(bh * a.nsplit_cap + s) * D + tid];   // chunk order
-            store_out<T>(a.out, bh * D + tid, o);
-            return;
-        }
-        const float* ml = a.part_ml + bh * a.nsplit_cap * 2;
-        float m = ml[0];
-        for (int s = 1; s < ns; ++s) m = fmaxf(m, ml[2 * s]);
-        float l = 0.f, o = 0.f;
-        for (int s = 0; s < ns; ++s) {                  // fixed order: chunk 0, 1, ...
-            float f = exp2_fast(ml[2 * s] - m);
-            l = fmaf(ml[2 * s + 1], f, l);
-            o = fmaf(a.part_o[(bh * a.nsplit_cap + s) * D + tid], f, o);
-        }
-        store_out<T>(a.out, bh * D + tid, o / l);
+        const float* po = a.part_o + bh * a.nsplit_cap * D + tid;
+        store_out<T>(a.out, bh * D + tid, merge_partials(a.plain_sum, po, D, a.part_ml + bh * a.nsplit_cap * 2, ns));
         return;
     }
     if (a.mass == nullptr) return;
@@ -746,7 +725,7 @@ void launch_attend(const DecodeArgs& da, int B, hipStream_t st) {
 // 2421, 13B batch 32 E4M3 1327 / 1404 / 1423, high resolution batch 8 E4M3 700 / 696 / 721.
 template <typename T, typename KT, int D>
 void launch_attend_layers(const StepTable& t, int most, int lds_words, bool stream, hipStream_t st) {
-    const dim3 grid(most, t.c.H + 1, t.c.B * t.c.layers);
+    const dim3 grid(t.c.H + 1, most, t.c.B * t.c.layers);
     const size_t lds = (size_t)lds_words * sizeof(float);
     with_tile(AttendTiles<KT>{}, 0, [&](auto u) {
         if (stream) launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, true>, grid, lds, st, t.c.layers, t);
@@ -756,7 +735,7 @@ void launch_attend_layers(const StepTable& t, int most, int lds_words, bool stre
 
 template <typename T, typename KT, int D>
 void launch_inherit_layers(const StepTable& t, int most, int lds_words, hipStream_t st) {
-    decode_inherit_layers_kernel<T, KT, D, 4><<<dim3(most, t.c.H + 1, t.c.B * t.c.layers), kDecodeThreads,
+    decode_inherit_layers_kernel<T, KT, D, 4><<<dim3(t.c.H + 1, most, t.c.B * t.c.layers), kDecodeThreads,
                                                 (size_t)lds_words * sizeof(uint32_t), st>>>(t);
 }
 
@@ -973,20 +952,20 @@ st3_status enqueue_inherit(const st3_attn_shape* shape, const st3_kv_layer* kv, 
 // A launch writes one output row and two cache rows per strip, and the logits.  Left to the caches, those lines are evicted
 // between the reads of K and V, and every turn of the memory from reading to writing costs: with ordinary stores a plain
 // strip-reading kernel that writes as little (0.4 % of what it reads) falls from 7.04 to 6.18 TB/s, with non-temporal ones
-// to 6.61.  But what stays in the caches is found there by the plan launch that follows.  Measured, us per step, ordinary ->
-// non-temporal, by the bytes of the rows a launch writes: 7B batch 1 (0.4 MB) 74.3 -> 76.6, batch 4 (1.6 MB) 173 -> 184, high
-// resolution batch 8 E4M3 (2 MB) 700 -> 713, 13B batch 8 with lazy layers (4 MB) 563 -> 574, 13B batch 8 (4.9 MB) 659 -> 657,
-// batch 12 (7.4 MB) 975 -> 963, batch 16 (9.8 MB) 1290 -> 1270, batch 32 E4M3 (13 MB) 1352 -> 1327, batch 32 (20 MB) 2569 -> 2437.
-constexpr int64_t kStreamStoreBytes = (int64_t)7 << 20;
+// to 6.61.  But what stays in the caches is found there by the launch that follows.  Measured, us per step, ordinary ->
+// non-temporal, by the bytes a launch writes: 13B batch 2 (3 MB) 170 -> 175, 7B batch 2 (3 MB) 74.0 -> 77.0, 13B batch 4 (6 MB) 317.5 ->
+// 320, 7B batch 4 (6.4 MB) 143.2 -> 144.8, batch 6 (9.7 MB) 213.4 -> 211.9, 13B batch 8 (12 MB) 636 -> 622, high resolution batch 2
+// (15 MB) 298.7 -> 300, batch 4 (29 MB) 599 -> 584, batch 8 (58 MB) 1201 -> 1154, E4M3 batch 4 (28 MB) 312 -> 311, batch 8 (57 MB) 624 -> 618,
+// 13B batch 16 1265 -> 1219, batch 24 1892 -> 1815.
+constexpr int64_t kStreamStoreBytes = (int64_t)8 << 20;
 
-// Attention of every layer of a checked step: the ordinary layers, up to kStepLayersMax per launch, then the lazy ones, caches of
+// Attention of every layer of a checked step: the ordinary layers, as many per launch as its table holds, then the lazy ones, caches of
 // either format in launches of their own (32 layers of the 7B shape, every other cache E4M3, us a step, layer by layer -> so:
 // batch 1 377 -> 60, batch 8 482 -> 290).
-// entry[i] receives where layer i's table entry will lie once the launches have run; needs: what is left for the launch behind
-// them.  The ranking goes along with the attention when no layer's columns take its mass.  Returns ST3_ERR_UNSUPPORTED, with nothing enqueued, for a step that a table
+// e[i] receives layer i's entry, for the launch behind them; needs: what is left for that launch.  The ranking goes along with the attention when no layer's columns take its mass.  Returns ST3_ERR_UNSUPPORTED, with nothing enqueued, for a step that a table
 // cannot describe.
 st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const st3_layer_step* layers, int mode,
-                               const char* has_heirs, const EvictArgs* plan, StepCommon& common, const StepLayer** entry,
+                               const char* has_heirs, const EvictArgs* plan, StepCommon& common, StepLayer* e,
                                PlanNeeds& needs, hipStream_t st) {
     const int B = shape->batch, H = shape->heads, D = shape->head_dim;
     common = StepCommon{B, H, D, mode, elem_bytes(shape->dtype), scale_log2(shape), 0};
@@ -998,9 +977,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
             return ST3_ERR_UNSUPPORTED;
         rows[L.inherit_from >= 0] += L.seg.max_kv_len + 1;
     }
-    const int per = std::min(kStepLayersMax, 65535 / B);        // grid z is B * layers
-    if (per < 1) return ST3_ERR_UNSUPPORTED;
-    std::vector<StepLayer> e((size_t)n_layers);
+    if (B > 65535) return ST3_ERR_UNSUPPORTED;
     std::vector<int> stage((size_t)n_layers, 0), groups[4];     // layers that may share launches, in launch order
     needs = PlanNeeds{0, false, true, false};
     for (int i = 0; i < n_layers; ++i) {
@@ -1013,8 +990,8 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
         const bool lazy = L.inherit_from >= 0, coded = L.kv.format == ST3_KV_E4M3;
         const int len = L.seg.max_kv_len + 1;
         const DecodeWs wl = decode_ws(B, H, D, L.kv.capacity);
-        StepLayer& s = e[(size_t)i];
-        memset(&s, 0, sizeof(s));
+        StepLayer& s = e[i];
+        s = StepLayer{};
         s.v = L.kv.v; s.v_new = L.v_new; s.out = L.out;
         s.kv_len = L.seg.kv_len; s.vis_len = L.seg.vis_len; s.tail_start = L.seg.tail_start;
         s.score_col = L.score_col; s.id_col = L.id_col; s.mass = plan[i].mass_dst; s.ws = reinterpret_cast<char*>(L.workspace);
@@ -1048,30 +1025,36 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
             else if (want) stage[(size_t)i] = std::min(s.chunk, L.seg.max_vis_len);
             if (stage[(size_t)i] > 3 * kLogitStageMaxRows) return ST3_ERR_UNSUPPORTED;
         }
-        entry[i] = reinterpret_cast<const StepLayer*>(s.ws + wl.step_entry);
+        if (!step_layer_fits(s, kv_elem_bytes(shape, &L.kv))) return ST3_ERR_UNSUPPORTED;
         groups[2 * lazy + coded].push_back(i);
     }
     for (const std::vector<int>& members : groups) {
         const int n = (int)members.size();
+        if (n == 0) continue;
+        const bool coded = layers[members[0]].kv.format == ST3_KV_E4M3;
+        const int words = coded ? kAttendWordsE4M3 : kAttendWords;
+        const int per = std::min(kStepTableWords / words, 65535 / B);       // grid z is B * layers
         const int launches = (n + per - 1) / per;
         for (int g = 0, i0 = 0; g < launches; ++g) {
             const int cnt = (n - i0 + launches - g - 1) / (launches - g);       // as equal as can be
             const int first = members[(size_t)i0];
             const bool lazy = layers[first].inherit_from >= 0;
             const st3_kv_layer* kv = &layers[first].kv;
-            StepTable t{};
+            StepTable t;
             t.c = common; t.c.layers = cnt;
+            int64_t written = (int64_t)cnt * B * H * D * (2 * kv_elem_bytes(shape, kv) + elem_bytes(shape->dtype));
             int most = 1, lds_words = 0;        // dynamic LDS: the logits a workgroup collects, or the keys it ranks
             for (int j = 0; j < cnt; ++j) {
                 const int i = members[(size_t)(i0 + j)];
-                t.layer[j] = e[(size_t)i];
-                most = std::max(most, (int)e[(size_t)i].nsplit);
+                pack_attend(t.w + j * words, e[i], coded, kv_elem_bytes(shape, kv));
+                most = std::max(most, (int)e[i].nsplit);
                 lds_words = std::max(lds_words, stage[(size_t)i]);
-                if (e[(size_t)i].flags & kStepApart && e[(size_t)i].keep_count >= 0) lds_words = std::max(lds_words, e[(size_t)i].max_vis);
+                if (e[i].flags & kStepKeepAll) written += (int64_t)B * H * e[i].max_kv * sizeof(float);
+                else if (e[i].flags & kStepWantMass) written += (int64_t)B * H * e[i].max_vis * sizeof(float);
+                if ((e[i].flags & kStepApart) && e[i].keep_count >= 0) lds_words = std::max(lds_words, e[i].max_vis);
             }
-            const int64_t row_bytes = (int64_t)cnt * B * H * D * (2 * kv_elem_bytes(shape, kv) + elem_bytes(shape->dtype));
             if (lazy) ST3_DISPATCH_KV(launch_inherit_layers, shape, kv, t, most, lds_words, st);
-            else ST3_DISPATCH_KV(launch_attend_layers, shape, kv, t, most, lds_words, row_bytes > kStreamStoreBytes, st);
+            else ST3_DISPATCH_KV(launch_attend_layers, shape, kv, t, most, lds_words, written > kStreamStoreBytes, st);
             i0 += cnt;
         }
     }

@@ -47,7 +47,7 @@ struct EvictArgs {
     int32_t mass_apart;         // 1: score_col does not take this step's mass: whoever ranks it need not wait for the mass
 };
 
-// The plan of a layer whose table entry a whole-step attention launch has left in the layer's workspace.
+// The plan of a layer of a whole step, from its table entry.
 __device__ __forceinline__ EvictArgs plan_from_entry(const StepCommon& c, const StepLayer& e) {
     const DecodeWs wl = decode_ws_sized(c.B, c.H, c.D, e.capacity, e.nsplit_cap);
     EvictArgs a;
@@ -287,21 +287,7 @@ __device__ __forceinline__ void merge_chunks(const StepCommon& c, const StepLaye
         const int h = h0 + idx / D, d = idx % D;
         const int64_t bh = (int64_t)b * c.H + h;
         const float* po = part_o + bh * wl.nsplit_cap * D + d;
-        float o = 0.f;
-        if (lazy) {                                     // partials of a lazy layer are normalised already
-            for (int s = 0; s < ns; ++s) o += po[(int64_t)s * D];
-        } else {
-            const float* ml = part_ml + bh * wl.nsplit_cap * 2;
-            float m = ml[0];
-            for (int s = 1; s < ns; ++s) m = fmaxf(m, ml[2 * s]);
-            float l = 0.f;
-            for (int s = 0; s < ns; ++s) {
-                const float f = exp2_fast(ml[2 * s] - m);
-                l = fmaf(ml[2 * s + 1], f, l);
-                o = fmaf(po[(int64_t)s * D], f, o);
-            }
-            o /= l;
-        }
+        const float o = merge_partials(lazy, po, D, part_ml + bh * wl.nsplit_cap * 2, ns);
         if (c.elem_bytes == 2) reinterpret_cast<uint16_t*>(e.out)[bh * D + d] = (uint16_t)f32_to_bf16_bits(o);
         else reinterpret_cast<float*>(e.out)[bh * D + d] = o;
     }
@@ -538,39 +524,42 @@ __device__ __forceinline__ void move_rows_block(const EvictArgs& a, int b, int p
 // kMassKeys mass entries of sequence b from key j0 on, by a workgroup of NT threads: a wave takes a share of the heads, a lane four
 // keys of a row (one 16-byte load), and the shares are added in order.
 constexpr int kMassKeys = 4 * kWave;
+template <int NT>
 struct MassShared {
     float hm[1024], hrl[1024];
-    f32x4_t part[kPlanThreadsMost / kWave][kWave];
+    f32x4_t part[NT / kWave][kWave];
 };
 template <int NT>
-__device__ __forceinline__ void mass_block(const EvictArgs& a, int b, int j0, MassShared& sm) {
+__device__ __forceinline__ void mass_block(const EvictArgs& a, int b, int j0, MassShared<NT>& sm) {
     constexpr int kWaves = NT / kWave, kUR = 8;
-    const int4 d = *reinterpret_cast<const int4*>(a.pending + b * 4);
-    const int n = min(a.own_pending[b * 4 + 3] >> 1, a.max_vis);
-    const int chunk = max(d.z, 32), seen = d.x >> 1;
-    const int ns = seen > 0 ? min((seen + chunk - 1) / chunk, min(d.y, a.nsplit_cap)) : 0;
-    if (!(d.x & 1) || ns <= 0 || j0 >= n) return;       // (uniform)
-    head_norms<NT>(a.part_ml, b, a.H, ns, a.nsplit_cap, sm.hm, sm.hrl);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), lane = threadIdx.x % kWave, j = j0 + 4 * lane;
-    const int per = (a.H + kWaves - 1) / kWaves, h1 = min(a.H, (wave + 1) * per);
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-    if (j < n) {
-        // (a load may reach three floats past the visual rows: more of the row, the next one or what lies behind the logits)
-        const float* lg = a.logits + a.sys_len + (int64_t)b * a.H * a.capacity + j;
-        for (int h = wave * per; h < h1; h += kUR) {
-            f32x4_t v[kUR];
+    const int per = (a.H + kWaves - 1) / kWaves, h0 = min(a.H, wave * per), h1 = min(a.H, h0 + per);
+    // (a load may reach three floats past the visual rows: more of the row, the next one or what lies behind the logits)
+    const float* lg = a.logits + a.sys_len + (int64_t)b * a.H * a.capacity + j;
+    f32x4_t v[kUR], acc = {0.f, 0.f, 0.f, 0.f};
+    auto load = [&](int h) {
 #pragma unroll
-            for (int u = 0; u < kUR; ++u) v[u] = *reinterpret_cast<const f32x4_a4_t*>(lg + (int64_t)min(h + u, h1 - 1) * a.capacity);
+        for (int u = 0; u < kUR; ++u)
+            if (j < a.max_vis && h + u < h1) v[u] = *reinterpret_cast<const f32x4_a4_t*>(lg + (int64_t)(h + u) * a.capacity);
+    };
+    load(h0);                                           // (on their way while the descriptor and the norms arrive)
+    const int4 d = *reinterpret_cast<const int4*>(a.pending + b * 4);
+    const int chunk = max(d.z, 32), seen = (d.x & 1) ? d.x >> 1 : 0;
+    const int ns = seen > 0 ? min((seen + chunk - 1) / chunk, min(d.y, a.nsplit_cap)) : 0;
+    const int n = ns > 0 ? min(a.own_pending[b * 4 + 3] >> 1, a.max_vis) : 0;      // (0: no mass is pending)
+    head_norms<NT>(a.part_ml, b, a.H, ns, a.nsplit_cap, sm.hm, sm.hrl);
+    if (j0 >= n) return;                                // (uniform)
+    for (int h = h0; h < h1; h += kUR) {
+        if (h > h0) load(h);
 #pragma unroll
-            for (int u = 0; u < kUR; ++u) {
-                if (h + u >= h1) break;
-                const float m = sm.hm[h + u], rl = sm.hrl[h + u];
+        for (int u = 0; u < kUR; ++u) {
+            if (h + u >= h1) break;
+            const float m = sm.hm[h + u], rl = sm.hrl[h + u];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] += exp2_fast(v[u][i] - m) * rl;
-            }
+            for (int i = 0; i < 4; ++i) acc[i] += exp2_fast(v[u][i] - m) * rl;
         }
-        sm.part[wave][lane] = acc;
     }
+    sm.part[wave][lane] = acc;
     __syncthreads();
     if (wave == 0 && j < n) {
 #pragma unroll
@@ -596,16 +585,14 @@ void launch_evict_plan(const EvictArgs& ea, int B, hipStream_t st);
 constexpr int kPlanBatch = 16;     // plans that travel by value: 216 bytes each (the argument block would hold 18)
 // Plans of n layers (device work of one decode step) with one launch per kPlanBatch layers.
 void launch_evict_plan_batch(const EvictArgs* plans, int n, int B, hipStream_t st);
-// The plans of n layers from the table entries that whole-step attention launches have left in the layers' workspaces;
-// merge: some strips were cut into chunks, whose partials are merged here too.  One launch per kPlanTableMax layers.
-constexpr int kPlanTableMax = 64;
+// The plans of the n layers of a whole step whose attention has been enqueued, as many per launch as a table holds.
 struct PlanNeeds {
     int most_vis;       // the largest bound of any layer's visual rows
     bool merge;         // some strip was cut
     bool apart;         // every layer's rows have been ranked beside the attention (kStepApart)
     bool moves;         // some layer's rows are moved by the launch
 };
-void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry, int n, const PlanNeeds& needs, hipStream_t st);
+void launch_evict_plan_table(const StepCommon& c, const StepLayer* entry, int n, const PlanNeeds& needs, hipStream_t st);
 void launch_evict_apply(const EvictArgs& ea, int B, hipStream_t st);
 
 }  // namespace st3

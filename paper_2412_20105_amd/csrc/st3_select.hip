@@ -346,7 +346,7 @@ static_assert(sizeof(EvictBatch) <= 4000, "plans of one batch must fit the kerne
 // the plan need not wait for them.
 template <int NT>
 __global__ __launch_bounds__(NT) void evict_plan_batch_kernel(EvictBatch batch) {
-    __shared__ union { PlanShared plan; MassShared mass; } sm;
+    __shared__ union { PlanShared plan; MassShared<NT> mass; } sm;
     const EvictArgs& a = batch.layer[blockIdx.y];
     if (blockIdx.z == 0) evict_plan_body<NT>(a, blockIdx.x, sm.plan);
     else if (a.mass_apart && a.mass_dst != nullptr) mass_block<NT>(a, blockIdx.x, ((int)blockIdx.z - 1) * kMassKeys, sm.mass);
@@ -376,78 +376,72 @@ void launch_evict_plan_batch(const EvictArgs* plans, int n, int B, hipStream_t s
 
 constexpr int kMergeHeads = 8;      // heads whose chunk partials one merge workgroup combines
 
-struct PlanTable {
-    StepCommon c;
-    const StepLayer* layer[kPlanTableMax];
-};
-
 // grid (B, layers, 1 + merge workgroups): z = 0 runs the plan of (sequence x, layer y); z >= 1 merges the chunk partials
 // of that layer's attention output for kMergeHeads heads (only launched when some layer left partials to merge).
 template <int NT>
-__global__ __launch_bounds__(NT) void evict_plan_table_kernel(PlanTable table) {
+__global__ __launch_bounds__(NT) void evict_plan_table_kernel(StepTable t) {
     __shared__ PlanShared sm;
-    // read once, ahead of every store of this kernel: uniform address, so the fields arrive in scalar registers
-    const StepLayer e = *table.layer[blockIdx.y];
+    const StepLayer e = unpack_plan<true>(t.w + blockIdx.y * kPlanWords, t.c.elem_bytes);
     if (blockIdx.z == 0) {
-        EvictArgs a = plan_from_entry(table.c, e);
+        EvictArgs a = plan_from_entry(t.c, e);
         a.mass_apart = 0;
         evict_plan_body<NT>(a, blockIdx.x, sm);
     } else if (e.nsplit > 1) {
         const int h0 = ((int)blockIdx.z - 1) * kMergeHeads;
-        if (h0 < table.c.H) merge_chunks(table.c, e, blockIdx.x, h0, h0 + kMergeHeads);
+        if (h0 < t.c.H) merge_chunks(t.c, e, blockIdx.x, h0, h0 + kMergeHeads);
     }
 }
 
 // What is left of the plans when the rows have been ranked beside the attention.  grid (B, layers, moves + masses + merges), 256
 // threads: workgroups z < move_wgs move rows (the first one advances the lengths too), the next mass_wgs finish kMassKeys
 // entries of the mass each, the rest merge the chunk partials of kMergeHeads heads each.
-struct FinishTable {
-    PlanTable t;
-    int32_t move_wgs, mass_wgs;
-};
-static_assert(sizeof(FinishTable) <= 4000, "the table travels by value");
-__global__ __launch_bounds__(256) void step_finish_kernel(FinishTable f) {
-    __shared__ MassShared sm;
-    const StepLayer e = *f.t.layer[blockIdx.y];
+__global__ __launch_bounds__(256) void step_finish_kernel(StepTable t, int move_wgs, int mass_wgs) {
+    __shared__ MassShared<256> sm;
+    const StepLayer e = unpack_plan<false>(t.w + blockIdx.y * kFinishWords, t.c.elem_bytes);
     const int z = blockIdx.z, b = blockIdx.x;
-    if (z < f.move_wgs + f.mass_wgs) {
-        const EvictArgs a = plan_from_entry(f.t.c, e);
-        if (z >= f.move_wgs) {
-            if (a.mass_dst != nullptr) mass_block<256>(a, b, (z - f.move_wgs) * kMassKeys, sm);
+    if (z < move_wgs + mass_wgs) {
+        const EvictArgs a = plan_from_entry(t.c, e);
+        if (z >= move_wgs) {
+            if (a.mass_dst != nullptr) mass_block<256>(a, b, (z - move_wgs) * kMassKeys, sm);
             return;
         }
         if (z == 0 && threadIdx.x == 0) evict_publish(a, b, evict_counts(a, b));
-        if (a.inline_apply) move_rows_block<256>(a, b, z, f.move_wgs);
+        if (a.inline_apply) move_rows_block<256>(a, b, z, move_wgs);
     } else if (e.nsplit > 1) {
-        const int h0 = (z - f.move_wgs - f.mass_wgs) * kMergeHeads;
-        if (h0 < f.t.c.H) merge_chunks(f.t.c, e, b, h0, h0 + kMergeHeads);
+        const int h0 = (z - move_wgs - mass_wgs) * kMergeHeads;
+        if (h0 < t.c.H) merge_chunks(t.c, e, b, h0, h0 + kMergeHeads);
     }
 }
 
 // Workgroups that move rows, over all plans of a launch.  us a step at 512 / 1024 / 2048 / 4096: 7B batch 1 54.4 / 55.0 / 55.0 / 55.9,
 // 13B batch 8 with fast annealing 533 / 507 / 504 / 503, batch 32 2403 / 2408 / 2402 / 2403, high resolution batch 8 630 / 628 / 628 / 627.
 constexpr int kFinishMoveWgs = 2048;
-void launch_evict_plan_table(const StepCommon& c, const StepLayer* const* entry, int n, const PlanNeeds& needs, hipStream_t st) {
-    for (int i0 = 0; i0 < n; i0 += kPlanTableMax) {
-        const int cnt = n - i0 < kPlanTableMax ? n - i0 : kPlanTableMax;
-        FinishTable f;
-        PlanTable& table = f.t;
-        table.c = c; table.c.layers = cnt;
-        for (int i = 0; i < cnt; ++i) table.layer[i] = entry[i0 + i];
-        for (int i = cnt; i < kPlanTableMax; ++i) table.layer[i] = nullptr;
-        const int merge_wgs = needs.merge ? (c.H + kMergeHeads - 1) / kMergeHeads : 0;
-        if (needs.apart) {
-            const int64_t plans = (int64_t)c.B * cnt, pieces = 2 * c.H * (c.D * c.elem_bytes / 16) / 256;
-            f.move_wgs = needs.moves ? (int)std::max<int64_t>(1, std::min<int64_t>(pieces, kFinishMoveWgs / plans)) : 1;
-            f.mass_wgs = (needs.most_vis + kMassKeys - 1) / kMassKeys;
-            step_finish_kernel<<<dim3(c.B, cnt, f.move_wgs + f.mass_wgs + merge_wgs), 256, 0, st>>>(f);
-            continue;
+void launch_evict_plan_table(const StepCommon& c, const StepLayer* entry, int n, const PlanNeeds& needs, hipStream_t st) {
+    const int words = needs.apart ? kFinishWords : kPlanWords, per = kStepTableWords / words;
+    const int launches = (n + per - 1) / per;
+    for (int g = 0, i0 = 0; g < launches; ++g) {
+        const int cnt = (n - i0 + launches - g - 1) / (launches - g);       // as equal as can be
+        StepTable t;
+        t.c = c; t.c.layers = cnt;
+        for (int i = 0; i < cnt; ++i) {
+            const StepLayer& e = entry[i0 + i];
+            pack_plan(t.w + i * words, e, !needs.apart, (e.flags & kStepE4M3) ? 1 : c.elem_bytes);
         }
-        const dim3 grid(c.B, cnt, 1 + merge_wgs);
-        with_threads(plan_threads((int64_t)c.B * cnt, needs.most_vis, c.H), [&](auto nt) {
-            constexpr int NT = decltype(nt)::value;
-            evict_plan_table_kernel<NT><<<grid, NT, plan_lds(needs.most_vis, NT), st>>>(table);
-        });
+        i0 += cnt;
+        const int merge_wgs = needs.merge ? (c.H + kMergeHeads - 1) / kMergeHeads : 0;
+        const int64_t plans = (int64_t)c.B * cnt;
+        if (needs.apart) {
+            const int64_t pieces = 2 * c.H * (c.D * c.elem_bytes / 16) / 256;
+            const int move_wgs = needs.moves ? (int)std::max<int64_t>(1, std::min<int64_t>(pieces, kFinishMoveWgs / plans)) : 1;
+            const int mass_wgs = (needs.most_vis + kMassKeys - 1) / kMassKeys;
+            step_finish_kernel<<<dim3(c.B, cnt, move_wgs + mass_wgs + merge_wgs), 256, 0, st>>>(t, move_wgs, mass_wgs);
+        } else {
+            const dim3 grid(c.B, cnt, 1 + merge_wgs);
+            with_threads(plan_threads(plans, needs.most_vis, c.H), [&](auto nt) {
+                constexpr int NT = decltype(nt)::value;
+                evict_plan_table_kernel<NT><<<grid, NT, plan_lds(needs.most_vis, NT), st>>>(t);
+            });
+        }
     }
 }
 

@@ -1,0 +1,82 @@
+// Packs random layers into the entries of a step's tables and unpacks them again: what fits comes back as it was, for both kinds of
+// either table, and what does not fit is refused.
+#include <cstdio>
+#include <cstring>
+#include <random>
+
+#include "st3_step.h"
+
+using namespace st3;
+
+static std::mt19937_64 rng(7);
+static int64_t upto(int64_t n) { return (int64_t)(rng() % (uint64_t)(n + 1)); }
+template <typename P>
+static void ptr(P& p) { p = reinterpret_cast<P>(upto(3) == 0 ? 0 : (rng() >> (16 + upto(20))) & ~15ull); }
+
+static StepLayer random_layer(int eb) {
+    StepLayer e{};
+    ptr(e.q); ptr(e.k); ptr(e.v); ptr(e.k_new); ptr(e.v_new); ptr(e.out); ptr(e.kv_len); ptr(e.vis_len); ptr(e.tail_start);
+    ptr(e.score_col); ptr(e.id_col); ptr(e.mass); ptr(e.ws); ptr(e.k_scale); ptr(e.v_scale);
+    const int64_t unit = 16 / eb;
+    e.stride_b = (upto(1) ? 0xffffffffll : upto(1 << 20)) * unit; e.stride_h = upto(0xffffffffll) * unit;
+    e.stride_t = (int32_t)((upto(1) ? 0xffff : 1 + upto(100)) * unit);
+    e.col_stride = (int32_t)upto(0x7fffffff); e.mass_stride = (int32_t)upto(0x7fffffff);
+    e.sys_len = (int32_t)(upto(1) ? 0xffff : upto(50)); e.max_vis = (int32_t)upto(8192); e.max_kv = (int32_t)upto(0x7ffffff0);
+    e.keep_count = (int32_t)upto(8193) - 1; e.chunk = 32 * (int32_t)(1 + upto(0xfffe)); e.capacity = (int32_t)upto(0x7fffffff);
+    e.nsplit = (uint8_t)(1 + upto(63)); e.nsplit_cap = (uint8_t)(1 + upto(63)); e.src_nsplit_cap = (uint8_t)upto(64);
+    e.flags = (uint8_t)(upto(63) & ~kStepE4M3) | (eb == 1 ? kStepE4M3 : 0);
+    if (e.flags & kStepLazy) { e.hint_base = e.capacity / 2; e.hint_gap = 0; }
+    else if (upto(2) == 0) { e.hint_base = 0x7fffffff; e.hint_gap = 0; }
+    else { e.hint_base = e.sys_len + (int32_t)upto(8192); e.hint_gap = (int32_t)upto(0x7fffffff); }
+    return e;
+}
+
+#define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
+#define SAME(f) CHECK(a.f == e.f)
+
+static int check(int eb) {
+    for (int i = 0; i < 20000; ++i) {
+        const StepLayer e = random_layer(eb);
+        CHECK(step_layer_fits(e, eb));
+        uint32_t w[64];
+        std::memset(w, i % 2 ? 0xff : 0, sizeof(w));        // (a table's words start out as anything)
+        const uint32_t guard = w[63];
+        pack_attend(w, e, eb == 1, eb);
+        CHECK(w[eb == 1 ? kAttendWordsE4M3 : kAttendWords] == guard);
+        StepLayer a = eb == 1 ? unpack_attend<true>(w, eb) : unpack_attend<false>(w, eb);
+        SAME(q); SAME(k); SAME(v); SAME(k_new); SAME(v_new); SAME(out); SAME(kv_len); SAME(vis_len); SAME(tail_start); SAME(score_col);
+        SAME(id_col); SAME(ws); SAME(stride_b); SAME(stride_h); SAME(stride_t); SAME(col_stride); SAME(sys_len); SAME(max_vis);
+        SAME(max_kv); SAME(keep_count); SAME(chunk); SAME(hint_base); SAME(hint_gap); SAME(capacity); SAME(nsplit); SAME(nsplit_cap);
+        SAME(src_nsplit_cap); SAME(flags);
+        if (eb == 1) { SAME(k_scale); SAME(v_scale); }
+        for (int ranking = 0; ranking < 2; ++ranking) {
+            std::memset(w, i % 2 ? 0xff : 0, sizeof(w));
+            pack_plan(w, e, ranking, eb);
+            CHECK(w[ranking ? kPlanWords : kFinishWords] == guard);
+            a = ranking ? unpack_plan<true>(w, eb == 1 ? 2 : eb) : unpack_plan<false>(w, eb == 1 ? 2 : eb);
+            SAME(k); SAME(v); SAME(out); SAME(kv_len); SAME(vis_len); SAME(tail_start); SAME(ws); SAME(mass); SAME(stride_b);
+            SAME(stride_h); SAME(stride_t); SAME(mass_stride); SAME(sys_len); SAME(max_vis); SAME(max_kv); SAME(keep_count); SAME(chunk);
+            SAME(capacity); SAME(nsplit); SAME(nsplit_cap); SAME(src_nsplit_cap); SAME(flags);
+            if (e.flags & kStepLazy) { SAME(q); SAME(hint_base); }
+            if (ranking) { SAME(score_col); SAME(id_col); SAME(col_stride); }
+        }
+    }
+    StepLayer e = random_layer(eb);
+    const StepLayer good = e;
+    e.q = reinterpret_cast<const void*>(1ull << 48); CHECK(!step_layer_fits(e, eb)); e = good;
+    e.stride_b = (1ll << 32) * 16 / eb; CHECK(!step_layer_fits(e, eb)); e = good;
+    e.stride_h = (1ll << 32) * 16 / eb; CHECK(!step_layer_fits(e, eb)); e = good;
+    e.stride_t = (1 << 16) * 16 / eb; CHECK(!step_layer_fits(e, eb)); e = good;
+    e.stride_t = 16 / eb + 1; CHECK(eb == 16 || !step_layer_fits(e, eb)); e = good;
+    e.sys_len = 1 << 16; CHECK(!step_layer_fits(e, eb)); e = good;
+    e.chunk = 32 << 16; CHECK(!step_layer_fits(e, eb)); e = good;
+    e.flags &= (uint8_t)~kStepLazy; e.hint_base = e.sys_len + 0xffff; CHECK(!step_layer_fits(e, eb));
+    return 0;
+}
+
+int main() {
+    for (int eb : {1, 2, 4})
+        if (check(eb)) return 1;
+    std::printf("ok\n");
+    return 0;
+}
