@@ -60,7 +60,7 @@ st3_status enqueue_decode(const st3_attn_shape* shape, const void* q, const st3_
                           void* out, float* vis_mass, int64_t mass_stride, bool want_mass, bool defer_mass,
                           bool keep_all_logits, void* workspace, size_t workspace_bytes, hipStream_t st);
 st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const st3_layer_step* layers, int mode,
-                               const char* has_heirs, const EvictArgs* plan, StepCommon& common, StepLayer* entry,
+                               const char* has_heirs, const EvictArgs* plan, char* needs_apply, StepCommon& common, StepLayer* entry,
                                PlanNeeds& needs, hipStream_t st);
 
 }  // namespace st3
@@ -325,7 +325,8 @@ extern "C" st3_status st3_decode_step(const st3_attn_shape* shape, int32_t n_lay
         StepCommon common{};
         std::vector<StepLayer> entry((size_t)n_layers);
         PlanNeeds needs{};
-        s = enqueue_step_attend(shape, n_layers, layers, mode, has_heirs.data(), plan.data(), common, entry.data(), needs, st);
+        s = enqueue_step_attend(shape, n_layers, layers, mode, has_heirs.data(), plan.data(), needs_apply.data(), common, entry.data(),
+                                needs, st);
         if (s == ST3_OK) {
             launch_evict_plan_table(common, entry.data(), n_layers, needs, st);
             enqueue_applies(plan, needs_apply, shape->batch, st);

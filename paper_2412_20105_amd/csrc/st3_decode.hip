@@ -962,10 +962,11 @@ constexpr int64_t kStreamStoreBytes = (int64_t)8 << 20;
 // Attention of every layer of a checked step: the ordinary layers, as many per launch as its table holds, then the lazy ones, caches of
 // either format in launches of their own (32 layers of the 7B shape, every other cache E4M3, us a step, layer by layer -> so:
 // batch 1 377 -> 60, batch 8 482 -> 290).
-// e[i] receives layer i's entry, for the launch behind them; needs: what is left for that launch.  The ranking goes along with the attention when no layer's columns take its mass.  Returns ST3_ERR_UNSUPPORTED, with nothing enqueued, for a step that a table
+// e[i] receives layer i's entry, for the launch behind them; needs: what is left for that launch; needs_apply[i] is cleared where
+// it moves the layer's rows.  The ranking goes along with the attention when no layer's columns take its mass.  Returns ST3_ERR_UNSUPPORTED, with nothing enqueued, for a step that a table
 // cannot describe.
 st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const st3_layer_step* layers, int mode,
-                               const char* has_heirs, const EvictArgs* plan, StepCommon& common, StepLayer* e,
+                               const char* has_heirs, const EvictArgs* plan, char* needs_apply, StepCommon& common, StepLayer* e,
                                PlanNeeds& needs, hipStream_t st) {
     const int B = shape->batch, H = shape->heads, D = shape->head_dim;
     common = StepCommon{B, H, D, mode, elem_bytes(shape->dtype), scale_log2(shape), 0};
@@ -978,12 +979,12 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
         rows[L.inherit_from >= 0] += L.seg.max_kv_len + 1;
     }
     if (B > 65535) return ST3_ERR_UNSUPPORTED;
+    std::vector<char> moves_here((size_t)n_layers, 0);
     std::vector<int> stage((size_t)n_layers, 0), groups[4];     // layers that may share launches, in launch order
-    needs = PlanNeeds{0, false, true, false};
+    needs = PlanNeeds{0, false, true, 0};
     for (int i = 0; i < n_layers; ++i) {
         needs.most_vis = std::max(needs.most_vis, plan[i].max_vis);
         needs.apart = needs.apart && plan[i].mass_apart;
-        needs.moves = needs.moves || plan[i].inline_apply;
     }
     for (int i = 0; i < n_layers; ++i) {
         const st3_layer_step& L = layers[i];
@@ -1006,7 +1007,15 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
         nsplit = (len + s.chunk - 1) / s.chunk;
         s.nsplit = (uint8_t)nsplit; s.nsplit_cap = (uint8_t)wl.nsplit_cap;
         needs.merge = needs.merge || nsplit > 1;
-        s.flags = (uint8_t)((plan[i].inline_apply ? kStepInlineApply : 0) | (coded ? kStepE4M3 : 0) | (needs.apart ? kStepApart : 0));
+        // Rows are moved by as many workgroups as they need, so however many an eviction moves, unless the order of the moves
+        // matters (STABLE) or a strip's moves must stay together (a tail that closes up) and are many.  A launch of its own per
+        // layer for more than 48 rows, as the other forms have it, before -> after, us a step: 7B shape evicting 50 rows a layer, batch 1
+        // 106 -> 41, batch 8 301 -> 266, 3 layers 43 -> 19; high resolution batch 8 E4M3, 90 rows 559 -> 449.
+        const bool moved = plan[i].inline_apply ||
+                           (needs.apart && plan[i].keep_count >= 0 && mode == ST3_HOLE_FILL && L.seg.tail_start != nullptr);
+        if (moved) needs.moves = std::max(needs.moves, (int64_t)(plan[i].max_vis - plan[i].keep_count) * 2 * H * plan[i].vecs_per_row);
+        moves_here[(size_t)i] = moved;
+        s.flags = (uint8_t)((moved ? kStepInlineApply : 0) | (coded ? kStepE4M3 : 0) | (needs.apart ? kStepApart : 0));
         if (lazy) {
             const st3_layer_step& S = layers[L.inherit_from];
             const DecodeWs sl = decode_ws(B, H, D, S.kv.capacity);
@@ -1028,6 +1037,8 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
         if (!step_layer_fits(s, kv_elem_bytes(shape, &L.kv))) return ST3_ERR_UNSUPPORTED;
         groups[2 * lazy + coded].push_back(i);
     }
+    for (int i = 0; i < n_layers; ++i)                  // (from here on nothing is refused)
+        if (moves_here[(size_t)i]) needs_apply[i] = 0;
     for (const std::vector<int>& members : groups) {
         const int n = (int)members.size();
         if (n == 0) continue;

@@ -233,27 +233,29 @@ __device__ __forceinline__ TopSet top_set(Key key_at, IdKey idkey_at, int n, int
     return t;
 }
 
-// Copies rows dst(i) <- src(i), i < count, on strips part, part + parts, ... (in groups) of sequence b.  Callers guarantee that no
-// destination of the batch is a source of it.  A wave moves one row of as many strips as 64 lanes of 16 bytes cover, kUR such
-// pieces in flight.
+// Copies rows dst(i) <- src(i), i < count, on all strips of sequence b.  Callers guarantee that no destination of the batch is a
+// source of it.  A wave moves one row of as many strips as 64 lanes of 16 bytes cover, kUR such pieces in flight.  The pieces are
+// dealt to `parts` workgroups; by_strip: so that all pieces of a strip go to the same one.
 template <int NT, class Dst, class Src>
-__device__ __forceinline__ void copy_rows(const EvictArgs& a, int b, int part, int parts, int count, Dst dst, Src src) {
-    constexpr int kUR = 8;
+__device__ __forceinline__ void copy_rows(const EvictArgs& a, int b, int part, int parts, bool by_strip, int count, Dst dst, Src src) {
+    constexpr int kUR = 8, kWaves = NT / kWave;
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int strips = (a.k ? 2 : 1) * a.H;             // K may be absent (layers that keep V only)
     const int vpr = a.vecs_per_row, spw = kWave / vpr;  // 4 ... 32, a power of two
-    const int all = (strips + spw - 1) / spw, groups = (all - part + parts - 1) / parts;       // pieces per row: of all strips, of these
-    const int total = part < all ? count * groups : 0;
-    for (int q0 = wave; q0 < total; q0 += kUR * (NT / kWave)) {
+    const int all = (strips + spw - 1) / spw;           // pieces per row
+    const int g0 = by_strip ? part : 0, gstep = by_strip ? parts : 1, groups = g0 < all ? (all - g0 + gstep - 1) / gstep : 1;
+    const int total = g0 < all ? count * groups : 0;
+    const int qstep = by_strip ? kWaves : parts * kWaves;
+    for (int q0 = by_strip ? wave : part * kWaves + wave; q0 < total; q0 += kUR * qstep) {
         u32x4_v tmp[kUR];
         char* to[kUR];
 #pragma unroll
         for (int u = 0; u < kUR; ++u) {
-            const int q = q0 + u * (NT / kWave);
+            const int q = q0 + u * qstep;
             to[u] = nullptr;
             if (q >= total) continue;
             const int i = q / groups;
-            const int strip = ((q - i * groups) * parts + part) * spw + lane / vpr;
+            const int strip = ((q - i * groups) * gstep + g0) * spw + lane / vpr;
             if (strip >= strips) continue;
             const bool in_k = a.k && strip < a.H;
             char* base = (in_k ? a.k : a.v) + b * a.stride_b + (int64_t)(strip >= a.H ? strip - a.H : strip) * a.stride_h +
@@ -469,10 +471,10 @@ __device__ __forceinline__ void evict_plan_body(const EvictArgs& a, int b, PlanS
         if (inl) {
             const int g = c.n - c.k, r = c.len - (a.sys_len + c.n);
             const int src0 = (r >= g) ? c.len - g : a.sys_len + c.n;
-            copy_rows<NT>(a, b, 0, 1, m.inner, [&](int i) { return (int64_t)sm.mv[i][0]; }, [&](int i) { return (int64_t)sm.mv[i][1]; });
+            copy_rows<NT>(a, b, 0, 1, true, m.inner, [&](int i) { return (int64_t)sm.mv[i][0]; }, [&](int i) { return (int64_t)sm.mv[i][1]; });
             if (m.tail > 0) {
                 __syncthreads();                        // those reads are done before [k, n) is overwritten
-                copy_rows<NT>(a, b, 0, 1, m.tail, [&](int i) { return (int64_t)(a.sys_len + c.k + i); },
+                copy_rows<NT>(a, b, 0, 1, true, m.tail, [&](int i) { return (int64_t)(a.sys_len + c.k + i); },
                                          [&](int i) { return (int64_t)(src0 + i); });
             }
         } else {
@@ -496,8 +498,8 @@ __device__ __forceinline__ void evict_plan_body(const EvictArgs& a, int b, PlanS
 // batch 32 37 -> 29, high resolution batch 8 27.6 -> 20.
 // ---------------------------------------------------------------------------------------------
 
-// How many moves the ranking has left to the rows' workgroups: inner | tail << kMoveTailShift (both below 2^6 + 1 rows).
-constexpr int kMoveTailShift = 8;
+// How many moves the ranking has left to the rows' workgroups: inner | tail << kMoveTailShift (at most 8192 rows are ranked).
+constexpr int kMoveTailShift = 16;
 
 // Ranking, columns and the move list of sequence b, beside the attention.  (Moves of a launch of their own: counted in one.)
 template <int NT>
@@ -508,16 +510,20 @@ __device__ __forceinline__ void evict_rank_early(const EvictArgs& a, int b, Sele
     if (threadIdx.x == 0) a.move_cnt[b] = a.inline_apply ? m.inner | (m.tail << kMoveTailShift) : m.inner + m.tail;
 }
 
-// Applies the moves that evict_rank_early has listed to a part of the strips of sequence b.
+// Applies a part of the moves that evict_rank_early has listed.  Moves inside the segment are independent of each other; what closes
+// up behind it overwrites their sources, so then a strip's moves stay with one workgroup.
 template <int NT>
 __device__ __forceinline__ void move_rows_block(const EvictArgs& a, int b, int part, int parts) {
     const int packed = a.move_cnt[b], inner = packed & ((1 << kMoveTailShift) - 1), tail = packed >> kMoveTailShift;
     const int32_t* mv = a.moves + (int64_t)b * a.max_moves * 2;
-    copy_rows<NT>(a, b, part, parts, inner, [&](int i) { return (int64_t)mv[2 * i]; }, [&](int i) { return (int64_t)mv[2 * i + 1]; });
+    auto apply = [&](int count) {
+        copy_rows<NT>(a, b, part, parts, tail > 0, count, [&](int i) { return (int64_t)mv[2 * i]; }, [&](int i) { return (int64_t)mv[2 * i + 1]; });
+    };
+    apply(inner);
     if (tail > 0) {                                     // (uniform)
         __syncthreads();                                // those reads are done before the segment's end is overwritten
         mv += 2 * inner;
-        copy_rows<NT>(a, b, part, parts, tail, [&](int i) { return (int64_t)mv[2 * i]; }, [&](int i) { return (int64_t)mv[2 * i + 1]; });
+        apply(tail);
     }
 }
 
@@ -590,7 +596,7 @@ struct PlanNeeds {
     int most_vis;       // the largest bound of any layer's visual rows
     bool merge;         // some strip was cut
     bool apart;         // every layer's rows have been ranked beside the attention (kStepApart)
-    bool moves;         // some layer's rows are moved by the launch
+    int64_t moves;      // 16-byte pieces of rows that the launch moves for a sequence of a layer, at most
 };
 void launch_evict_plan_table(const StepCommon& c, const StepLayer* entry, int n, const PlanNeeds& needs, hipStream_t st);
 void launch_evict_apply(const EvictArgs& ea, int B, hipStream_t st);

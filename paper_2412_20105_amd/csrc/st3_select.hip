@@ -431,8 +431,9 @@ void launch_evict_plan_table(const StepCommon& c, const StepLayer* entry, int n,
         const int merge_wgs = needs.merge ? (c.H + kMergeHeads - 1) / kMergeHeads : 0;
         const int64_t plans = (int64_t)c.B * cnt;
         if (needs.apart) {
-            const int64_t pieces = 2 * c.H * (c.D * c.elem_bytes / 16) / 256;
-            const int move_wgs = needs.moves ? (int)std::max<int64_t>(1, std::min<int64_t>(pieces, kFinishMoveWgs / plans)) : 1;
+            // (a round of a workgroup's loads: eight of 16 bytes for each thread)
+            const int64_t rounds = (needs.moves + 8 * 256 - 1) / (8 * 256), strips = 2 * c.H * (c.D * c.elem_bytes / 16) / 256;
+            const int move_wgs = (int)std::max<int64_t>(1, std::min<int64_t>(std::max(rounds, strips), kFinishMoveWgs / plans));
             const int mass_wgs = (needs.most_vis + kMassKeys - 1) / kMassKeys;
             step_finish_kernel<<<dim3(c.B, cnt, move_wgs + mass_wgs + merge_wgs), 256, 0, st>>>(t, move_wgs, mass_wgs);
         } else {

@@ -65,3 +65,14 @@ def test_columns_that_take_the_mass(args, layer):
                 got = torch.tensor([by_id[x] for x in kept], device=st["score"].device)
                 assert torch.allclose(st["score"][i, :k], got.float(), rtol=5e-5, atol=1e-9)
         assert torch.equal(s["kv_len"], t["kv_len"]) and torch.equal(s["vis_len"], t["vis_len"])
+
+
+@pytest.mark.parametrize("args", [
+    dict(L=3, B=2, H=5, d=128, dtype=BF, vis=[700, 120], tail=9, drop=90, lazy={1: 0}),
+    dict(L=2, B=1, H=3, d=64, dtype=F32, vis=[1500], tail=3, drop=900),
+    dict(L=30, B=40, H=4, d=64, dtype=BF, vis=[90], tail=2, drop=60),               # fewer workgroups than a sequence's moves fill
+    dict(L=3, B=2, H=5, d=128, dtype=BF, vis=[300], tail=9, drop=60, e4m3={1}),
+    dict(L=3, B=2, H=5, d=128, dtype=BF, vis=[300], tail=200, drop=60, fixed_tail=False),       # by launches of their own
+], ids=["bf16", "f32", "many_plans", "mixed", "closing_tail"])
+def test_large_evictions(args):
+    _same(Step(**args).whole(), Step(**args).layer_by_layer())
