@@ -250,6 +250,17 @@ ST3_EXPORT st3_status st3_select_topk(const float* scores, int64_t score_stride,
                            uint8_t* keep_mask, int32_t* keep_idx, int64_t idx_stride, void* stream);
 
 /* ---------------------------------------------------------------------------------------------
+ * The same selection where what is wanted are the kept entries themselves (a prune event of the
+ * prefill: the next layer's ids and ranking scores), in one launch:
+ *   out_ids[b][r], out_scores[b][r] <- ids[b][i_r], scores[b][i_r]   for r in [0, k)
+ * with i_0 < i_1 < ... the positions st3_select_topk keeps of the n entries of row b.  k <= n <=
+ * 16384; the outputs must not overlap the inputs.
+ * ------------------------------------------------------------------------------------------- */
+ST3_EXPORT st3_status st3_select_columns(const float* scores, int64_t score_stride, const int32_t* ids, int64_t id_stride,
+                              int32_t batch, int32_t n, int32_t k, float* out_scores, int64_t out_score_stride,
+                              int32_t* out_ids, int64_t out_id_stride, void* stream);
+
+/* ---------------------------------------------------------------------------------------------
  * Stable in-place row compaction (Alg. 1/3: V = V[T]; X = [S, V, I] rebuilt, order preserved).
  * For every (b, i) with b < batch, i < inner, on the strip that starts at
  * rows + b*stride_b_bytes + i*stride_inner_bytes:
@@ -403,6 +414,13 @@ ST3_EXPORT st3_status st3_decode_layer_attend(const st3_attn_shape* shape, int32
                                               int32_t layer, int32_t mode, void* stream);
 ST3_EXPORT st3_status st3_decode_plans(const st3_attn_shape* shape, int32_t n_layers, const st3_layer_step* layers,
                                        int32_t mode, void* stream);
+
+/* st3_select_compact_layer for several layers at once (the evictions that precede the first decode
+ * step of a generation), 16 layers a launch: layers[i] is brought down to keep_after visual rows
+ * (keep_after < 0: left alone).  kv, seg, score_col, id_col, col_stride, keep_after and workspace of
+ * an entry are read; kv.k may be NULL as there. */
+ST3_EXPORT st3_status st3_select_compact_layers(const st3_attn_shape* shape, int32_t n_layers, const st3_layer_step* layers,
+                                     int32_t mode, void* stream);
 
 /* ---------------------------------------------------------------------------------------------
  * Retention schedules: HOST-only pure functions that fill integer tables.

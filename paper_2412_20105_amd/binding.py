@@ -30,7 +30,7 @@ EXPORTED = [
     "st3_prefill_attention", "st3_quantize_rows", "st3_kv_append", "st3_decode_attention", "st3_decode_attention_inherit",
     "st3_decode_attention_noalloc", "st3_select_topk",
     "st3_compact_rows", "st3_gather_rows", "st3_select_compact_layer", "st3_decode_layer_step", "st3_decode_step",
-    "st3_decode_layer_attend", "st3_decode_plans",
+    "st3_decode_layer_attend", "st3_decode_plans", "st3_select_columns", "st3_select_compact_layers",
     "st3_schedule_pvtp", "st3_schedule_linear", "st3_schedule_anneal", "st3_kv_bytes",
     "st3_debug_enabled", "st3_debug_set_prefill_path", "st3_debug_set_attend_tile", "st3_profile_enable", "st3_profile_read", "st3_overlap_topk",
     "st3_cosine_similarity",
@@ -138,6 +138,11 @@ def lib() -> C.CDLL:
         L.st3_decode_layer_attend.restype = C.c_int
         L.st3_decode_plans.argtypes = [P(AttnShape), C.c_int32, P(LayerStep), C.c_int32, C.c_void_p]
         L.st3_decode_plans.restype = C.c_int
+        L.st3_select_columns.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.c_void_p,
+                                         C.c_int64, C.c_void_p, C.c_int64, C.c_void_p]
+        L.st3_select_columns.restype = C.c_int
+        L.st3_select_compact_layers.argtypes = [P(AttnShape), C.c_int32, P(LayerStep), C.c_int32, C.c_void_p]
+        L.st3_select_compact_layers.restype = C.c_int
         L.st3_schedule_pvtp.argtypes = [C.c_int32] * 6 + [C.c_void_p]
         L.st3_schedule_linear.argtypes = [C.c_int32] * 4 + [C.c_void_p]
         L.st3_schedule_anneal.argtypes = [C.c_int32, C.c_double, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p]
@@ -302,6 +307,14 @@ def st3_select_topk(scores, tie_ids, n_dev, n, k, keep_mask, keep_idx, stream=No
                                  _stream(stream)), "st3_select_topk")
 
 
+def st3_select_columns(scores, ids, n, k, out_scores, out_ids, stream=None):
+    """The k best of the first n entries of each row, in ascending order of position: scores and ids."""
+    assert scores.dtype == out_scores.dtype == torch.float32 and ids.dtype == out_ids.dtype == torch.int32
+    _check(lib().st3_select_columns(scores.data_ptr(), scores.stride(0), ids.data_ptr(), ids.stride(0), scores.shape[0], n, k,
+                                    out_scores.data_ptr(), out_scores.stride(0), out_ids.data_ptr(), out_ids.stride(0),
+                                    _stream(stream)), "st3_select_columns")
+
+
 def st3_compact_rows(rows_ptr: int, batch, inner, stride_b_bytes, stride_inner_bytes, stride_row_bytes, row_bytes,
                      keep_idx, k, n, tail_rows, stream=None):
     _check(lib().st3_compact_rows(rows_ptr, batch, inner, stride_b_bytes, stride_inner_bytes, stride_row_bytes,
@@ -358,6 +371,10 @@ def st3_decode_layer_attend(shape, layer_steps, n_layers, layer, mode, stream=No
 
 def st3_decode_plans(shape, layer_steps, n_layers, mode, stream=None):
     _check(lib().st3_decode_plans(C.byref(shape), n_layers, layer_steps, mode, _stream(stream)), "st3_decode_plans")
+
+
+def st3_select_compact_layers(shape, layer_steps, n_layers, mode, stream=None):
+    _check(lib().st3_select_compact_layers(C.byref(shape), n_layers, layer_steps, mode, _stream(stream)), "st3_select_compact_layers")
 
 
 # -- host-only schedule helpers ---------------------------------------------------------------

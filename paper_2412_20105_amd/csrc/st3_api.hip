@@ -311,6 +311,34 @@ extern "C" st3_status st3_decode_plans(const st3_attn_shape* shape, int32_t n_la
     return enqueue_plans(plan, needs_apply, shape->batch, reinterpret_cast<hipStream_t>(stream));
 }
 
+extern "C" st3_status st3_select_compact_layers(const st3_attn_shape* shape, int32_t n_layers, const st3_layer_step* layers,
+                                                int32_t mode, void* stream) {
+    using namespace st3;
+    st3_status s = check_shape(shape);
+    if (s != ST3_OK) return s;
+    if (n_layers <= 0 || !layers) return ST3_ERR_INVALID_ARG;
+    if (mode != ST3_STABLE && mode != ST3_HOLE_FILL) return ST3_ERR_INVALID_ARG;
+    std::vector<EvictArgs> plan;
+    std::vector<char> needs_apply;
+    for (int i = 0; i < n_layers; ++i) {
+        const st3_layer_step& L = layers[i];
+        if (L.keep_after < 0) continue;
+        s = !L.kv.k ? validate_kv_value_only(shape, &L.kv, &L.seg) : validate_kv(shape, &L.kv, &L.seg);
+        if (s != ST3_OK) return s;
+        if (!L.score_col || !L.id_col || !L.workspace || !aligned16(L.workspace) || L.col_stride < L.seg.max_vis_len)
+            return ST3_ERR_INVALID_ARG;
+        EvictArgs ea;
+        bool na = false;
+        s = build_evict_args(shape, &L.kv, &L.seg, L.score_col, L.id_col, L.col_stride, L.keep_after, mode, L.workspace,
+                             L.workspace_bytes, 0, nullptr, 0, ea, na, true);
+        if (s != ST3_OK) return s;
+        plan.push_back(ea);
+        needs_apply.push_back(na ? 1 : 0);
+    }
+    if (plan.empty()) return ST3_OK;
+    return enqueue_plans(plan, needs_apply, shape->batch, reinterpret_cast<hipStream_t>(stream));
+}
+
 extern "C" st3_status st3_decode_step(const st3_attn_shape* shape, int32_t n_layers, const st3_layer_step* layers,
                                       int32_t mode, void* stream) {
     using namespace st3;

@@ -27,6 +27,10 @@ struct TopkArgs {
     uint8_t* mask;
     int32_t* idx;
     int64_t idx_stride;
+    float* out_scores;      // the kept entries themselves, in ascending order of position (null: not wanted)
+    int64_t out_score_stride;
+    int32_t* out_ids;
+    int64_t out_id_stride;
 };
 
 // One workgroup per row, latency bound (topk_threads).
@@ -58,10 +62,23 @@ __global__ __launch_bounds__(NT) void select_topk_kernel(TopkArgs a) {
         const bool keep = p < n && (k >= n || (k > 0 && top.keeps(key_at, idkey_at, p)));
         if (mask && p < a.n) mask[p] = keep ? 1 : 0;
         plan_ranks<NT>(keep, false, parity, sm, r1, r2, t1, t2);
-        if (keep && idx && base + r1 < a.k) idx[base + r1] = p;
+        if (keep && base + r1 < a.k) {
+            if (idx) idx[base + r1] = p;
+            if (a.out_ids) {
+                a.out_ids[b * a.out_id_stride + base + r1] = ids[p];
+                a.out_scores[b * a.out_score_stride + base + r1] = scores[p];
+            }
+        }
         base += t1;
     }
     if (idx) for (int i = k + tid; i < a.k; i += NT) idx[i] = -1;
+}
+
+void launch_topk(const TopkArgs& a, int batch, hipStream_t st) {
+    with_threads(topk_threads(batch, a.n), [&](auto nt) {
+        constexpr int NT = decltype(nt)::value;
+        select_topk_kernel<NT><<<batch, NT, sizeof(uint32_t) * std::min(a.n, kSelLdsKeys), st>>>(a);
+    });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -625,10 +642,29 @@ extern "C" st3_status st3_select_topk(const float* scores, int64_t score_stride,
     st3::TopkArgs a{};
     a.scores = scores; a.score_stride = score_stride; a.ids = tie_ids; a.id_stride = id_stride;
     a.n_dev = n_dev; a.n = n; a.k = k; a.mask = keep_mask; a.idx = keep_idx; a.idx_stride = idx_stride;
-    st3::with_threads(st3::topk_threads(batch, n), [&](auto nt) {
-        st3::select_topk_kernel<decltype(nt)::value><<<batch, decltype(nt)::value, sizeof(uint32_t) * std::min(n, st3::kSelLdsKeys),
-                                                     reinterpret_cast<hipStream_t>(stream)>>>(a);
-    });
+    st3::launch_topk(a, batch, reinterpret_cast<hipStream_t>(stream));
+    return st3::check_launch();
+}
+
+extern "C" st3_status st3_select_columns(const float* scores, int64_t score_stride, const int32_t* ids, int64_t id_stride,
+                                         int32_t batch, int32_t n, int32_t k, float* out_scores, int64_t out_score_stride,
+                                         int32_t* out_ids, int64_t out_id_stride, void* stream) {
+    if (!scores || !ids || !out_scores || !out_ids || batch <= 0 || n < 0 || k < 0 || k > n) return ST3_ERR_INVALID_ARG;
+    if (n > 16384 || batch > 65535 * 32) return ST3_ERR_UNSUPPORTED;
+    if (score_stride < n || id_stride < n || out_score_stride < k || out_id_stride < k) return ST3_ERR_INVALID_ARG;
+    if (k == 0) return ST3_OK;
+    auto meet = [&](const void* x, int64_t xs, int64_t xn, const void* y, int64_t ys, int64_t yn) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(x), b = reinterpret_cast<uintptr_t>(y);
+        return a < b + ((uintptr_t)(batch - 1) * ys + yn) * 4 && b < a + ((uintptr_t)(batch - 1) * xs + xn) * 4;
+    };
+    if (meet(scores, score_stride, n, out_scores, out_score_stride, k) || meet(scores, score_stride, n, out_ids, out_id_stride, k) ||
+        meet(ids, id_stride, n, out_scores, out_score_stride, k) || meet(ids, id_stride, n, out_ids, out_id_stride, k) ||
+        meet(out_scores, out_score_stride, k, out_ids, out_id_stride, k))
+        return ST3_ERR_INVALID_ARG;
+    st3::TopkArgs a{};
+    a.scores = scores; a.score_stride = score_stride; a.ids = ids; a.id_stride = id_stride; a.n = n; a.k = k;
+    a.out_scores = out_scores; a.out_score_stride = out_score_stride; a.out_ids = out_ids; a.out_id_stride = out_id_stride;
+    st3::launch_topk(a, batch, reinterpret_cast<hipStream_t>(stream));
     return st3::check_launch();
 }
 

@@ -118,7 +118,6 @@ class Generation:
         self.dec_out = torch.empty((batch, heads, head_dim), dtype=dtype, device=device)
         self.dec_out_all = torch.empty((layers, batch, heads, head_dim), dtype=dtype, device=device)
         self._steps = None                  # ctypes array of LayerStep, built on first decode_step()
-        self.keep_idx = torch.empty((batch, max(n_vis, 1)), dtype=torch.int32, device=device)
         self._alive = n_vis                 # visual tokens alive in the layer being prefetched
         self._inherit: Optional[torch.Tensor] = None
         # (visual rows, device image [3, B] of [vis_len, kv_len, tail_start]) of each layer as its prefill leaves them
@@ -145,9 +144,6 @@ class Generation:
         # (a copy from ordinary host memory: finished, on whatever stream, when it returns)
         return torch.tensor(rows, dtype=torch.int32).to(self.device)
 
-    def _compact_column(self, col: torch.Tensor, idx: torch.Tensor, k: int, n: int, stream=None):
-        st3.st3_compact_rows(col.data_ptr(), self.B, 1, col.stride(0) * 4, 0, 4, 4, idx, k, n, 0, stream)
-
     def prefill_layer(self, l: int, Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor):
         """Q, K, V: device tensors [B,H,N0,d] over the unpruned prompt (Alg. 3, PVTP branch).
         A lazy layer ignores Q and K (may be None): Eq. 6 attends with its source's.
@@ -166,16 +162,14 @@ class Generation:
             lc.ids[:, :nv] = torch.arange(nv, dtype=torch.int32, device=self.device)
         else:
             prev = self.layers[l - 1]
-            lc.ids.copy_(prev.ids)
             if k_l < self._alive:
-                # Eq. 3: keep the k_l visual tokens the PREVIOUS layer's last row attended to most
-                st3.st3_select_topk(prev.mass, prev.ids, None, self._alive, k_l, None, self.keep_idx, stream)
-                self._compact_column(lc.ids, self.keep_idx, k_l, self._alive, stream)
-                # ... and their scores, which rank this layer and the ones behind it up to the next prune event
-                lc.score.copy_(prev.mass)
-                self._compact_column(lc.score, self.keep_idx, k_l, self._alive, stream)
+                # Eq. 3: keep the k_l visual tokens the PREVIOUS layer's last row attended to most, and their scores, which
+                # rank this layer and the ones behind it up to the next prune event
+                st3.st3_select_columns(prev.mass, prev.ids, self._alive, k_l, lc.score, lc.ids, stream)
                 self._inherit = lc.score
                 self._alive = k_l
+            else:
+                lc.ids.copy_(prev.ids)
         alive = self._alive
         n_l = ns + alive + nx
         # stage the layer's inputs, K and V straight into the cache and Q into scratch, in ONE gather
@@ -213,15 +207,20 @@ class Generation:
     def begin_decode(self):
         """The eviction that precedes the FIRST decode step (Alg. 3 truncates a layer's cache before
         its attention at every step; later steps do it right after the previous step's attention)."""
+        arr, evicts = self._step_array(), False
         for l, lc in enumerate(self.layers):
             target = min(self.keep[l][1], lc.h_vis) if self.T >= 1 else lc.h_vis
+            s = arr[l]
+            s.keep_after = -1
             if target < lc.h_vis:
-                seg = st3.segments(self.n_sys, lc.h_vis, lc.h_kv, lc.vis_len, lc.kv_len, lc.tail_start)
-                st3.st3_select_compact_layer(self.shape, lc.kv, seg, lc.score, lc.ids, target, self.compact_mode,
-                                             lc.ws)
+                evicts = True
+                s.keep_after = target
+                s.seg.max_vis_len, s.seg.max_kv_len = lc.h_vis, lc.h_kv
                 if not self.fixed_tail:
                     lc.h_kv -= lc.h_vis - target
                 lc.h_vis = target
+        if evicts:
+            st3.st3_select_compact_layers(self.shape, arr, self.L, self.compact_mode)
         self._decoding = True
 
     def _keep_after(self, l: int, t: int) -> int:
