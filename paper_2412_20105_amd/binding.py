@@ -224,8 +224,8 @@ def segments(sys_len: int, max_vis_len: int, max_kv_len: int, vis_len: torch.Ten
 
 
 def _stream(stream) -> int:
-    if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+    if stream is None:      # the handle alone: a Stream object around it takes 2.8 us a call, of 13 for the smallest step
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

@@ -154,7 +154,7 @@ class Generation:
         src = self.lazy.get(l)
         ns, nv, nx = self.n_sys, self.n_vis, self.n_txt
         k_l = self.keep[l][0]
-        stream = torch.cuda.current_stream().cuda_stream        # looked up once, not once per call
+        stream = st3._stream(None)        # looked up once, not once per call
         if l == 0:                  # a new job: nothing is inherited from the previous one
             self._alive = nv
             self._inherit = None
@@ -312,7 +312,7 @@ class Generation:
             self.begin_decode()
         self._set_step_bounds(t)
         self._open_step = t
-        self._step_stream = torch.cuda.current_stream().cuda_stream    # looked up once per step, not once per layer
+        self._step_stream = st3._stream(None)    # looked up once per step, not once per layer
         if getattr(self, "_out_views", None) is None:
             self._out_views = [self.dec_out_all[l] for l in range(self.L)]
 
