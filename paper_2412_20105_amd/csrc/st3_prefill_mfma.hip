@@ -30,6 +30,8 @@
 // (P_hi the upper 16 bits of the float, P_lo the rounded rest: 16 mantissa bits together), and both
 // are multiplied by V: rounding P to one bf16 would put an error of 2^-9 of the row's magnitude on
 // every output element, far above the element-wise tolerance for outputs that happen to be small.
+#include <algorithm>
+
 #include "st3_prefill.h"
 
 namespace st3 {
@@ -350,6 +352,8 @@ __device__ __forceinline__ void store_block(const PrefillArgs& a, int b, int h, 
     }
 }
 
+constexpr int kLanes = 32;
+
 // Workgroup -> (query tile, strip).  Workgroups go round-robin by linear id to the 8 XCDs (checked
 // with a probe: XCC id == id % 8) and, within an XCD, in turn to its 4 shader engines; each XCD
 // has an L2 of its own; a causal query tile costs in proportion to its index.  With the query
@@ -358,7 +362,6 @@ __device__ __forceinline__ void store_block(const PrefillArgs& a, int b, int h, 
 // (id % 32) owns the strips congruent to it and receives the tiles of one strip back to back,
 // heaviest first: all lanes see the same cost sequence and a strip's K and V stay in one L2.
 __device__ __forceinline__ void place_workgroup(const PrefillArgs& a, int& strip, int& qt) {
-    constexpr int kLanes = 32;
     const int n_qt = a.n_qt, strips = a.H * a.B;
     const int full = strips / kLanes * kLanes;
     const int lin = blockIdx.x;
@@ -373,6 +376,27 @@ __device__ __forceinline__ void place_workgroup(const PrefillArgs& a, int& strip
     }
 }
 
+// The same where not all workgroups find a place at once.  Such a launch ends with its last tiles, and a strip's heaviest tile can
+// take as long as the strip's whole share of a compute unit: so the last strips of each lane (spread_strips) are dealt heaviest
+// tiles first over all of them, and the strips left over come first of all, heaviest tiles first, instead of last.  us a call,
+// before -> so (strips x tokens): 128 x 675 45.6 -> 37.4, 128 x 400 27.5 -> 23.4, 256 x 675 74.2 -> 62.7, 320 x 739 97.8 -> 88.6, 1280 x 739
+// 371.5 -> 368.3, 80 x 739 42.0 -> 35.9, 140 x 1500 151.6 -> 127.4, 72 x 900 49.1 -> 38.5, 64 x 3136 234 -> 225.  (The kernel with key
+// groups has all its workgroups in place at once and keeps the plain order: this one took its smallest calls 0.2 of 17 us.)
+__device__ __forceinline__ void place_spread(const PrefillArgs& a, int& strip, int& qt) {
+    const uint32_t n_qt = (uint32_t)a.n_qt, strips = (uint32_t)(a.H * a.B);
+    const uint32_t per = strips / kLanes, over = strips % kLanes;       // strips of a lane, strips left over
+    const uint32_t ahead = over * n_qt, spread = (uint32_t)a.spread, whole = (per - spread) * n_qt;
+    const bool left = blockIdx.x < ahead;
+    const uint32_t lin = blockIdx.x - ahead, m = lin / kLanes;          // (not used of a left-over strip)
+    const bool apart = !left && m < whole;                              // a strip whose tiles come one after the other
+    // (one division and no branch: behind a branch the other arguments are loaded in a second trip to memory)
+    const uint32_t x = left ? blockIdx.x : apart ? m : m - whole, by = left ? over : apart ? n_qt : spread;
+    const uint32_t quot = x / by, rest = x - quot * by;
+    const uint32_t q = apart ? rest : quot;                             // the tile, counted from the heaviest
+    strip = (int)(left ? per * kLanes + rest : ((apart ? quot : per - spread + rest) * kLanes + lin % kLanes));
+    qt = (int)(n_qt - 1 - q);
+}
+
 // One-dimensional grid of ceil(n/128) * H * B workgroups (the mapping to query tile and strip is in the kernel).
 // Register budget: two waves per SIMD (256 registers each; the kernel takes 214), i.e. two workgroups
 // per compute unit: while one waits for a tile, a barrier or its first loads, the other one runs.
@@ -382,7 +406,7 @@ __device__ __forceinline__ void place_workgroup(const PrefillArgs& a, int& strip
 // batch 32 / high resolution batch 8: as it is 369 / 902; softmax of one sub-tile between the MFMAs of the other 368 / 905;
 // half of the waves loading after S^T 378 / 940, all of them 376 / 920).  Tiles and the cost of an item (8400 cycles) add up to
 // 292 of the 369 us (15 rounds of 7 tiles) and 722 of 902: where the last fifth goes has not been measured.
-template <int D>
+template <int D, bool SPREAD>
 __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(PrefillArgs a) {
     using L = TileLayout<D>;
     constexpr int KS = D / 16;          // contraction steps of S^T
@@ -392,7 +416,8 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(PrefillArgs a) {
     __shared__ __attribute__((aligned(1024))) uint16_t buf1[2 * L::TILE];
 
     int strip, qt;
-    place_workgroup(a, strip, qt);
+    if (SPREAD) place_spread(a, strip, qt);
+    else place_workgroup(a, strip, qt);
     const int h = strip % a.H, b = strip / a.H;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 5, c = lane & 31;
@@ -626,6 +651,15 @@ int key_groups(int D, int n, int64_t strips) {
     return 1;
 }
 
+// Strips of a dispatch lane whose tiles are dealt together at the end of a launch: as many as keep the K and V of an XCD's four
+// lanes within about twice its L2 (4 MB), but two to four.  us a call at 1 / 2 / 4 / 8 strips, D = 128: 256 x 675 74.2 / 68.7 / 62.7 /
+// 70.2, 320 x 739 97.8 / 94.6 / 88.6 / 88.5, 1280 x 739 371.5 / 371.8 / 368.3 / 367.6, but 140 x 1500 (the first with its left-over
+// strips last) 151.6 / 127.4 / 131.3 / 134.3, 256 x 3136 907 / 907 / 917 / 1049.
+int spread_strips(int D, int n, int64_t strips) {
+    const int64_t bytes = (int64_t)n * D * 16;          // of one strip of each of the four lanes
+    return (int)std::min<int64_t>(strips / kLanes, std::max<int64_t>(2, std::min<int64_t>(4, ((int64_t)8 << 20) / bytes)));
+}
+
 }  // namespace
 
 st3_status launch_prefill_mfma(const PrefillArgs& a, int B, int D, hipStream_t st) {
@@ -636,15 +670,19 @@ st3_status launch_prefill_mfma(const PrefillArgs& a, int B, int D, hipStream_t s
     pa.n_qt = (a.n + bm - 1) / bm;
     pa.q_shift = (pa.n_qt * bm - a.n) / 32 * 32;        // whole empty 32-row blocks, moved to the front
     pa.B = B;
-    const int64_t wgs = (int64_t)pa.n_qt * a.H * B;
+    const int64_t strips = (int64_t)a.H * B, wgs = pa.n_qt * strips;
     if (wgs > 0x7fffffff) return ST3_ERR_UNSUPPORTED;
+    pa.spread = spread_strips(D, a.n, strips);
     // the direct loads address a strip as a scalar base plus a 32-bit byte offset
     if ((int64_t)a.n * a.k_st * 2 >= (int64_t)1 << 31 || (int64_t)a.n * a.v_st * 2 >= (int64_t)1 << 31) return ST3_ERR_UNSUPPORTED;
     dim3 grid((unsigned)wgs);
     if (D != 128 && D != 64) return ST3_ERR_UNSUPPORTED;
     if (ks == 1) {
-        if (D == 128) prefill_mfma_kernel<128><<<grid, 256, 0, st>>>(pa);
-        else prefill_mfma_kernel<64><<<grid, 256, 0, st>>>(pa);
+        // (prompts of one query tile have no order to choose, and the choice costs them 0.2 of 11 us)
+        if (D == 128 && pa.n_qt > 1) prefill_mfma_kernel<128, true><<<grid, 256, 0, st>>>(pa);
+        else if (D == 128) prefill_mfma_kernel<128, false><<<grid, 256, 0, st>>>(pa);
+        else if (pa.n_qt > 1) prefill_mfma_kernel<64, true><<<grid, 256, 0, st>>>(pa);
+        else prefill_mfma_kernel<64, false><<<grid, 256, 0, st>>>(pa);
     } else if (ks == 2) {
         if (D == 128) prefill_mfma_split_kernel<128, 2><<<grid, 256, 0, st>>>(pa);
         else prefill_mfma_split_kernel<64, 2><<<grid, 256, 0, st>>>(pa);
