@@ -354,10 +354,10 @@ ST3_EXPORT st3_status st3_decode_layer_step(const st3_attn_shape* shape, const s
  * loop over l).  `layers` is a HOST array; entry i carries exactly the arguments
  * st3_decode_layer_step takes for that layer.  The result is the same as calling
  * st3_decode_layer_step for i = 0 .. n_layers-1 in order.  Step (2) of a layer depends on that
- * layer's attention only, so all layers attend first (up to 21 layers per launch; lazy layers
- * behind the ordinary ones) and their steps (2) then run side by side in one launch (up to 64
- * layers; the attention launch leaves each layer's step-(2) arguments in the layer's workspace,
- * where that launch reads them).  Every layer needs buffers and a workspace of its own; a layer
+ * layer's attention only, so all layers attend first (up to 35 layers per launch; lazy layers
+ * behind the ordinary ones) and their steps (2) then run side by side in one launch (rows are
+ * ranked beside the attention already where the ranking does not need the step's mass).  Every
+ * layer needs buffers and a workspace of its own; a layer
  * whose `out` shares memory with another layer's out, q, k_new or v_new makes the step run layer
  * by layer, one launch each.
  * Lazy layers (inherit_from >= 0) are available through this call only: a group's evictions must
