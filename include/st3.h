@@ -227,7 +227,8 @@ ST3_EXPORT st3_status st3_decode_attention_noalloc(const st3_attn_shape* shape, 
  * same row order as the source's did during that call (same lengths, same evictions applied
  * with the same ranking column).  Only kv->v is read (kv->k may be NULL): half the bytes of
  * st3_decode_attention.  The visual mass of a lazy layer is its source's and is not recomputed.
- * A sequence whose source call saw no keys gets out = 0.
+ * A sequence whose source call saw no keys gets out = 0.  `workspace` is scratch; it may be the source's own where both caches
+ * have the same capacity, and what the source left there stays as it is, for further lazy layers.
  * ------------------------------------------------------------------------------------------- */
 ST3_EXPORT st3_status st3_decode_attention_inherit(const st3_attn_shape* shape, const st3_kv_layer* kv,
                                                    const st3_segments* seg, const void* src_workspace,

@@ -54,7 +54,7 @@ st3_status validate_kv_value_only(const st3_attn_shape* s, const st3_kv_layer* k
 st3_status enqueue_inherit(const st3_attn_shape* shape, const st3_kv_layer* kv, const st3_segments* seg,
                            int32_t max_kv_len, const void* v_new, const void* src_workspace,
                            size_t src_workspace_bytes, int32_t src_capacity, void* out, void* workspace,
-                           size_t workspace_bytes, hipStream_t st);
+                           size_t workspace_bytes, bool plan_follows, hipStream_t st);
 st3_status enqueue_decode(const st3_attn_shape* shape, const void* q, const st3_kv_layer* kv,
                           const st3_segments* seg, int32_t max_kv_len, const void* k_new, const void* v_new,
                           void* out, float* vis_mass, int64_t mass_stride, bool want_mass, bool defer_mass,
@@ -240,7 +240,7 @@ static st3_status enqueue_layer_attend(const st3_attn_shape* shape, const st3_la
     if (L.inherit_from >= 0) {
         const st3_layer_step& S = layers[L.inherit_from];
         return enqueue_inherit(shape, &L.kv, &L.seg, L.seg.max_kv_len + 1, L.v_new, S.workspace, S.workspace_bytes,
-                               S.kv.capacity, L.out, L.workspace, L.workspace_bytes, st);
+                               S.kv.capacity, L.out, L.workspace, L.workspace_bytes, true, st);
     }
     return enqueue_decode(shape, L.q, &L.kv, &L.seg, L.seg.max_kv_len + 1, L.k_new, L.v_new, L.out, L.vis_mass,
                           L.mass_stride, L.vis_mass != nullptr, true, has_heirs, L.workspace, L.workspace_bytes, st);

@@ -343,7 +343,8 @@ struct InheritArgs {
     const float* src_part_ml;   // [B,H,src_nsplit_cap,2]
     const int32_t* src_pending; // [B][4]
     int32_t src_capacity, src_nsplit_cap;
-    int32_t* own_pending;       // [B][4] of this layer: the visual rows are left there (the rest is the source's)
+    int32_t* own_pending;       // [B][4] of this layer: the visual rows are left there for a plan (the rest is the source's); null where
+                                // no plan follows: then the workspace may be the source's own, whose descriptor other workgroups read
     float* part_o;              // [B,H,nsplit_cap,D]   (nsplit > 1 only)
     const void* v_new;          // [B,H,D] value row of the token being appended (null: none)
     const float* v_scale;       // [B*H] value of one V code unit (E4M3 caches; null: 1)
@@ -410,7 +411,7 @@ __device__ __forceinline__ void inherit_chunk(const InheritArgs& a, const int sp
     const int c0 = split * a.chunk;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int64_t bh = (int64_t)b * a.H + h;
-    if (split == 0 && h == 0 && tid == 0) a.own_pending[b * 4 + 3] = lay.nv << 1;
+    if (a.own_pending != nullptr && split == 0 && h == 0 && tid == 0) a.own_pending[b * 4 + 3] = lay.nv << 1;
     const bool have = (a.src_pending[b * 4 + 3] & 1) != 0;        // the source attended a non-empty sequence
     if (len <= 0 || !have) {                                // nothing to inherit: out = 0
         if (split == 0 && tid < D) store_out<T>(a.out, bh * D + tid, 0.f);
@@ -901,11 +902,12 @@ st3_status validate_kv_value_only(const st3_attn_shape* s, const st3_kv_layer* k
 
 // Enqueues a lazy layer's attention (Eq. 6): the probabilities come from the attend launch that last
 // used `src_workspace` (same batch, heads and lengths; cache capacity src_capacity), the values
-// from `kv->v` plus - when v_new is given - the row being appended, which is stored on the way.
+// from `kv->v` plus - when v_new is given - the row being appended, which is stored on the way.  plan_follows: the layer's mass
+// is finished by a plan, and the workspace is another than the source's.
 st3_status enqueue_inherit(const st3_attn_shape* shape, const st3_kv_layer* kv, const st3_segments* seg,
                            int32_t max_kv_len, const void* v_new, const void* src_workspace,
                            size_t src_workspace_bytes, int32_t src_capacity, void* out, void* workspace,
-                           size_t workspace_bytes, hipStream_t st) {
+                           size_t workspace_bytes, bool plan_follows, hipStream_t st) {
     const int B = shape->batch, H = shape->heads, D = shape->head_dim;
     const DecodeWs wl = decode_ws(B, H, D, kv->capacity);
     const DecodeWs sl = decode_ws(B, H, D, src_capacity);
@@ -928,7 +930,7 @@ st3_status enqueue_inherit(const st3_attn_shape* shape, const st3_kv_layer* kv, 
     ia.src_part_ml = reinterpret_cast<const float*>(sws + sl.part_ml);
     ia.src_pending = reinterpret_cast<const int32_t*>(sws + sl.pending);
     ia.src_capacity = src_capacity; ia.src_nsplit_cap = sl.nsplit_cap;
-    ia.own_pending = reinterpret_cast<int32_t*>(ws + wl.pending);
+    if (plan_follows) ia.own_pending = reinterpret_cast<int32_t*>(ws + wl.pending);
     ia.part_o = reinterpret_cast<float*>(ws + wl.part_o);
     ia.v_new = v_new; ia.out = out;
     if (kv->format == ST3_KV_E4M3) ia.v_scale = kv->v_scale;
@@ -1100,7 +1102,7 @@ extern "C" st3_status st3_decode_attention_inherit(const st3_attn_shape* shape, 
     if (!out || !workspace || !src_workspace || src_kv_capacity <= 0) return ST3_ERR_INVALID_ARG;
     if (!st3::aligned16(workspace) || !st3::aligned16(src_workspace)) return ST3_ERR_INVALID_ARG;
     return st3::enqueue_inherit(shape, kv, seg, seg->max_kv_len, nullptr, src_workspace, src_workspace_bytes,
-                                src_kv_capacity, out, workspace, workspace_bytes,
+                                src_kv_capacity, out, workspace, workspace_bytes, false,
                                 reinterpret_cast<hipStream_t>(stream));
 }
 
