@@ -304,7 +304,8 @@ void decode_attend_layers_kernel(StepTable t) {
     const int li = __builtin_amdgcn_readfirstlane((int)blockIdx.z / c.B), b = (int)blockIdx.z - li * c.B;
     const int split = blockIdx.y, h = blockIdx.x;
     constexpr bool coded = sizeof(KT) == 1;
-    const StepLayer e = unpack_attend<coded>(t.w + li * (coded ? kAttendWordsE4M3 : kAttendWords), sizeof(KT));
+    const int words = (coded ? kAttendWordsE4M3 : kAttendWords) + (c.wide ? kWideWords : 0);
+    const StepLayer e = unpack_attend<coded>(t.w + li * words, sizeof(KT), c.wide != 0);
     if (h == c.H) return rank_workgroup(c, e, split, b);
     if (split >= e.nsplit) return;
     const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
@@ -486,7 +487,8 @@ __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_
     const int li = __builtin_amdgcn_readfirstlane((int)blockIdx.z / c.B), b = (int)blockIdx.z - li * c.B;
     const int split = blockIdx.y, h = blockIdx.x;
     constexpr bool coded = sizeof(KT) == 1;
-    const StepLayer e = unpack_attend<coded>(t.w + li * (coded ? kAttendWordsE4M3 : kAttendWords), sizeof(KT));
+    const int words = (coded ? kAttendWordsE4M3 : kAttendWords) + (c.wide ? kWideWords : 0);
+    const StepLayer e = unpack_attend<coded>(t.w + li * words, sizeof(KT), c.wide != 0);
     if (h == c.H) return rank_workgroup(c, e, split, b);
     if (split >= e.nsplit) return;
     const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
@@ -971,7 +973,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
                                const char* has_heirs, const EvictArgs* plan, char* needs_apply, StepCommon& common, StepLayer* e,
                                PlanNeeds& needs, hipStream_t st) {
     const int B = shape->batch, H = shape->heads, D = shape->head_dim;
-    common = StepCommon{B, H, D, mode, elem_bytes(shape->dtype), scale_log2(shape), 0};
+    common = StepCommon{B, H, D, mode, elem_bytes(shape->dtype), scale_log2(shape), 0, 0};
     int64_t rows[2] = {0, 0};           // of the ordinary and of the lazy layers
     for (int i = 0; i < n_layers; ++i) {
         const st3_layer_step& L = layers[i];
@@ -1036,7 +1038,9 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
             else if (want) stage[(size_t)i] = std::min(s.chunk, L.seg.max_vis_len);
             if (stage[(size_t)i] > 3 * kLogitStageMaxRows) return ST3_ERR_UNSUPPORTED;
         }
-        if (!step_layer_fits(s, kv_elem_bytes(shape, &L.kv))) return ST3_ERR_UNSUPPORTED;
+        const int eb = kv_elem_bytes(shape, &L.kv);
+        if (!step_layer_fits(s, eb)) common.wide = 1;
+        if (!step_layer_fits(s, eb, true)) return ST3_ERR_UNSUPPORTED;
         groups[2 * lazy + coded].push_back(i);
     }
     for (int i = 0; i < n_layers; ++i)                  // (from here on nothing is refused)
@@ -1045,8 +1049,8 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
         const int n = (int)members.size();
         if (n == 0) continue;
         const bool coded = layers[members[0]].kv.format == ST3_KV_E4M3;
-        const int words = coded ? kAttendWordsE4M3 : kAttendWords;
-        const int per = std::min(kStepTableWords / words, 65535 / B);       // grid z is B * layers
+        const int words = coded ? kAttendWordsE4M3 : kAttendWords, stride = words + (common.wide ? kWideWords : 0);
+        const int per = std::min(entries_per_table(words, common.wide), 65535 / B);     // grid z is B * layers
         const int launches = (n + per - 1) / per;
         for (int g = 0, i0 = 0; g < launches; ++g) {
             const int cnt = (n - i0 + launches - g - 1) / (launches - g);       // as equal as can be
@@ -1059,7 +1063,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
             int most = 1, lds_words = 0;        // dynamic LDS: the logits a workgroup collects, or the keys it ranks
             for (int j = 0; j < cnt; ++j) {
                 const int i = members[(size_t)(i0 + j)];
-                pack_attend(t.w + j * words, e[i], coded, kv_elem_bytes(shape, kv));
+                pack_attend(t.w + j * stride, e[i], coded, kv_elem_bytes(shape, kv), common.wide != 0);
                 most = std::max(most, (int)e[i].nsplit);
                 lds_words = std::max(lds_words, stage[(size_t)i]);
                 if (e[i].flags & kStepKeepAll) written += (int64_t)B * H * e[i].max_kv * sizeof(float);

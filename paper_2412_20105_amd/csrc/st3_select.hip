@@ -450,7 +450,7 @@ constexpr int kMergeHeads = 8;      // heads whose chunk partials one merge work
 template <int NT>
 __global__ __launch_bounds__(NT) void evict_plan_table_kernel(StepTable t) {
     __shared__ PlanShared sm;
-    const StepLayer e = unpack_plan<true>(t.w + blockIdx.y * kPlanWords, t.c.elem_bytes);
+    const StepLayer e = unpack_plan<true>(t.w + blockIdx.y * (kPlanWords + (t.c.wide ? kWideWords : 0)), t.c.elem_bytes, t.c.wide != 0);
     if (blockIdx.z == 0) {
         EvictArgs a = plan_from_entry(t.c, e);
         a.mass_apart = 0;
@@ -466,7 +466,7 @@ __global__ __launch_bounds__(NT) void evict_plan_table_kernel(StepTable t) {
 // entries of the mass each, the rest merge the chunk partials of kMergeHeads heads each.
 __global__ __launch_bounds__(256) void step_finish_kernel(StepTable t, int move_wgs, int mass_wgs) {
     __shared__ MassShared<256> sm;
-    const StepLayer e = unpack_plan<false>(t.w + blockIdx.y * kFinishWords, t.c.elem_bytes);
+    const StepLayer e = unpack_plan<false>(t.w + blockIdx.y * (kFinishWords + (t.c.wide ? kWideWords : 0)), t.c.elem_bytes, t.c.wide != 0);
     const int z = blockIdx.z, b = blockIdx.x;
     if (z < move_wgs + mass_wgs) {
         const EvictArgs a = plan_from_entry(t.c, e);
@@ -486,7 +486,8 @@ __global__ __launch_bounds__(256) void step_finish_kernel(StepTable t, int move_
 // 13B batch 8 with fast annealing 533 / 507 / 504 / 503, batch 32 2403 / 2408 / 2402 / 2403, high resolution batch 8 630 / 628 / 628 / 627.
 constexpr int kFinishMoveWgs = 2048;
 void launch_evict_plan_table(const StepCommon& c, const StepLayer* entry, int n, const PlanNeeds& needs, hipStream_t st) {
-    const int words = needs.apart ? kFinishWords : kPlanWords, per = kStepTableWords / words;
+    const int words = needs.apart ? kFinishWords : kPlanWords, stride = words + (c.wide ? kWideWords : 0);
+    const int per = entries_per_table(words, c.wide);
     const int launches = (n + per - 1) / per;
     for (int g = 0, i0 = 0; g < launches; ++g) {
         const int cnt = (n - i0 + launches - g - 1) / (launches - g);       // as equal as can be
@@ -494,7 +495,7 @@ void launch_evict_plan_table(const StepCommon& c, const StepLayer* entry, int n,
         t.c = c; t.c.layers = cnt;
         for (int i = 0; i < cnt; ++i) {
             const StepLayer& e = entry[i0 + i];
-            pack_plan(t.w + i * words, e, !needs.apart, (e.flags & kStepE4M3) ? 1 : c.elem_bytes);
+            pack_plan(t.w + i * stride, e, !needs.apart, (e.flags & kStepE4M3) ? 1 : c.elem_bytes, c.wide != 0);
         }
         i0 += cnt;
         const int merge_wgs = needs.merge ? (c.H + kMergeHeads - 1) / kMergeHeads : 0;

@@ -6,6 +6,10 @@
 // be ranked) in the table of the launch behind it: 35, 32, 41 and 35 layers a launch.  us a step, 21 layers a launch and entries
 // left in the workspaces for the launch behind it -> so: 7B batch 1 55 -> 45, 13B batch 8 with lazy layers 504 -> 496, high resolution batch
 // 8 E4M3 629 -> 624; a generation of 16 steps, 7B batch 4, 4824 -> 4758.
+//
+// A table is wide where some layer needs it (token-major caches, whose rows can lie megabytes apart): its entries have three words
+// more, with the upper halves of what the others hold in 16 or 32 bits.  Rows of 2 MB, us a step, layer by layer -> wide: 32 layers of
+// the 7B shape, batch 4 285 -> 90, 40 layers of 40 heads, batch 2 341 -> 83.
 #pragma once
 
 #include <stdint.h>
@@ -22,6 +26,7 @@ struct StepCommon {
     int32_t elem_bytes;         // of q, the new rows, the outputs and plain caches: 2 (bf16) or 4 (float32)
     float scale_l2;
     int32_t layers;             // entries of the table
+    int32_t wide;               // 1: the table's entries are wide
 };
 
 struct StepLayer {
@@ -59,7 +64,9 @@ constexpr int kAttendPtrs = 12, kAttendPtrsE4M3 = 14, kFinishPtrs = 9, kPlanPtrs
 constexpr int ptr_words(int n) { return n + (n + 1) / 2; }
 constexpr int kAttendWords = ptr_words(kAttendPtrs) + 10, kAttendWordsE4M3 = ptr_words(kAttendPtrsE4M3) + 10;
 constexpr int kFinishWords = ptr_words(kFinishPtrs) + 10, kPlanWords = ptr_words(kPlanPtrs) + 11;
+constexpr int kWideWords = 3;
 constexpr int kStepTableWords = 992;
+inline int entries_per_table(int words, int wide) { return kStepTableWords / (words + (wide ? kWideWords : 0)); }
 
 struct StepTable {
     StepCommon c;
@@ -79,33 +86,40 @@ __host__ __device__ inline void get_ptr(const uint32_t* w, int n, int i, P& p) {
     p = reinterpret_cast<P>(hi << 32 | w[i]);
 }
 
-// Whether an entry of a layer whose cache elements are eb bytes wide holds these values.
-inline bool step_layer_fits(const StepLayer& e, int eb) {
+// Whether an entry, wide or not, of a layer whose cache elements are eb bytes wide holds these values.
+inline bool step_layer_fits(const StepLayer& e, int eb, bool wide = false) {
     const void* ptrs[] = {e.q, e.k, e.v, e.k_new, e.v_new, e.out, e.kv_len, e.vis_len, e.tail_start, e.score_col, e.id_col, e.mass, e.ws,
                           e.k_scale, e.v_scale};
     for (const void* p : ptrs)
         if (reinterpret_cast<uint64_t>(p) >> 48) return false;
     const bool lazy = (e.flags & kStepLazy) != 0, hinted = !lazy && e.hint_base != 0x7fffffff;
-    const int64_t nv = (int64_t)e.hint_base - e.sys_len;
+    const int64_t nv = (int64_t)e.hint_base - e.sys_len, unit = 16 / eb;
+    const int more = wide ? 16 : 0;
     for (int64_t s : {e.stride_b, e.stride_h, (int64_t)e.stride_t})
-        if (s < 0 || (s * eb) % 16) return false;
-    return (e.stride_b * eb / 16) >> 32 == 0 && (e.stride_h * eb / 16) >> 32 == 0 && ((int64_t)e.stride_t * eb / 16) >> 16 == 0 &&
-           e.sys_len >= 0 && e.sys_len >> 16 == 0 && e.max_vis >= 0 && e.max_vis >> 16 == 0 && e.keep_count < 0xffff && e.chunk % 32 == 0 &&
-           e.chunk / 32 >> 16 == 0 && (!hinted || (nv >= 0 && nv < 0xffff));
+        if (s < 0 || s % unit) return false;
+    return (e.stride_b / unit) >> (32 + more) == 0 && (e.stride_h / unit) >> (32 + more) == 0 && (e.stride_t / unit) >> (16 + more) == 0 &&
+           e.sys_len >= 0 && (int64_t)e.sys_len >> (16 + more) == 0 && e.max_vis >= 0 && e.max_vis >> 16 == 0 && e.keep_count < 0xffff &&
+           e.chunk % 32 == 0 && (int64_t)(e.chunk / 32) >> (16 + more) == 0 && (!hinted || (nv >= 0 && nv < 0xffff));
 }
 
 inline uint32_t pair16(int lo, int hi) { return ((uint32_t)lo & 0xffffu) | (uint32_t)hi << 16; }
-// The ten words that both tables have, but for two of them (a, b).
-inline void pack_numbers(uint32_t* w, const StepLayer& e, int eb, uint32_t a, uint32_t b) {
-    w[0] = (uint32_t)(e.stride_b * eb / 16); w[1] = (uint32_t)(e.stride_h * eb / 16);
-    w[2] = pair16((int)((int64_t)e.stride_t * eb / 16), e.sys_len);
+// The ten words that both tables have, but for two of them (a, b); high: where a wide entry's last words go (null: not wide).
+inline void pack_numbers(uint32_t* w, const StepLayer& e, int eb, uint32_t a, uint32_t b, uint32_t* high) {
+    const int64_t unit = 16 / eb, sb = e.stride_b / unit, sh = e.stride_h / unit, st = e.stride_t / unit;
+    if (high != nullptr) {
+        high[0] = pair16((int)(st >> 16), e.sys_len >> 16);
+        high[1] = pair16((int)(sb >> 32), (int)(sh >> 32));
+        high[2] = (uint32_t)(e.chunk / 32) >> 16;
+    }
+    w[0] = (uint32_t)sb; w[1] = (uint32_t)sh;
+    w[2] = pair16((int)st, e.sys_len);
     w[3] = pair16(e.max_vis, e.keep_count < 0 ? 0 : e.keep_count + 1);
     w[4] = (uint32_t)e.max_kv; w[5] = (uint32_t)e.capacity;
     w[6] = (uint32_t)e.nsplit | (uint32_t)e.nsplit_cap << 8 | (uint32_t)e.src_nsplit_cap << 16 | (uint32_t)e.flags << 24;
     w[7] = pair16(e.chunk / 32, (e.flags & kStepLazy) || e.hint_base == 0x7fffffff ? 0xffff : e.hint_base - e.sys_len);
     w[8] = a; w[9] = b;
 }
-__host__ __device__ inline void unpack_numbers(const uint32_t* w, StepLayer& e, int eb) {
+__host__ __device__ inline void unpack_numbers(const uint32_t* w, StepLayer& e, int eb, const uint32_t* high) {
     const int64_t unit = 16 / eb;
     e.stride_b = (int64_t)w[0] * unit; e.stride_h = (int64_t)w[1] * unit;
     e.stride_t = (int32_t)((w[2] & 0xffffu) * (uint32_t)unit); e.sys_len = (int32_t)(w[2] >> 16);
@@ -113,18 +127,24 @@ __host__ __device__ inline void unpack_numbers(const uint32_t* w, StepLayer& e, 
     e.max_kv = (int32_t)w[4]; e.capacity = (int32_t)w[5];
     e.nsplit = (uint8_t)w[6]; e.nsplit_cap = (uint8_t)(w[6] >> 8); e.src_nsplit_cap = (uint8_t)(w[6] >> 16); e.flags = (uint8_t)(w[6] >> 24);
     e.chunk = (int32_t)(w[7] & 0xffffu) * 32;
+    if (high != nullptr) {
+        e.stride_t += (int32_t)((high[0] << 16) * (uint32_t)unit); e.sys_len += (int32_t)(high[0] & 0xffff0000u);
+        e.stride_b += (int64_t)((uint64_t)(high[1] & 0xffffu) << 32) * unit; e.stride_h += (int64_t)((uint64_t)(high[1] >> 16) << 32) * unit;
+        e.chunk += (int32_t)(high[2] << 21);
+    }
 }
 
 // The attention's entry: everything but the mass's place.
-inline void pack_attend(uint32_t* w, const StepLayer& e, bool coded, int eb) {
+inline void pack_attend(uint32_t* w, const StepLayer& e, bool coded, int eb, bool wide = false) {
     const int n = coded ? kAttendPtrsE4M3 : kAttendPtrs;
     const void* ptrs[kAttendPtrsE4M3] = {e.q, e.k, e.v, e.k_new, e.v_new, e.out, e.kv_len, e.vis_len, e.tail_start, e.ws, e.score_col,
                                          e.id_col, e.k_scale, e.v_scale};
     for (int i = 0; i < n; ++i) put_ptr(w, n, i, ptrs[i]);
-    pack_numbers(w + ptr_words(n), e, eb, (uint32_t)e.col_stride, (uint32_t)((e.flags & kStepLazy) ? e.hint_base : e.hint_gap));
+    pack_numbers(w + ptr_words(n), e, eb, (uint32_t)e.col_stride, (uint32_t)((e.flags & kStepLazy) ? e.hint_base : e.hint_gap),
+                 wide ? w + (coded ? kAttendWordsE4M3 : kAttendWords) : nullptr);
 }
 template <bool CODED>
-__host__ __device__ inline StepLayer unpack_attend(const uint32_t* w, int eb) {
+__host__ __device__ inline StepLayer unpack_attend(const uint32_t* w, int eb, bool wide = false) {
     constexpr int n = CODED ? kAttendPtrsE4M3 : kAttendPtrs;
     StepLayer e{};
     get_ptr(w, n, 0, e.q); get_ptr(w, n, 1, e.k); get_ptr(w, n, 2, e.v); get_ptr(w, n, 3, e.k_new); get_ptr(w, n, 4, e.v_new);
@@ -132,7 +152,7 @@ __host__ __device__ inline StepLayer unpack_attend(const uint32_t* w, int eb) {
     get_ptr(w, n, 9, e.ws); get_ptr(w, n, 10, e.score_col); get_ptr(w, n, 11, e.id_col);
     if (CODED) { get_ptr(w, n, 12, e.k_scale); get_ptr(w, n, 13, e.v_scale); }
     const uint32_t* num = w + ptr_words(n);
-    unpack_numbers(num, e, eb);
+    unpack_numbers(num, e, eb, wide ? w + (CODED ? kAttendWordsE4M3 : kAttendWords) : nullptr);
     e.col_stride = (int32_t)num[8];
     const int nv = (int)(num[7] >> 16);
     if (e.flags & kStepLazy) e.hint_base = (int32_t)num[9];
@@ -141,24 +161,25 @@ __host__ __device__ inline StepLayer unpack_attend(const uint32_t* w, int eb) {
 }
 
 // The entry of the launch behind the attention; ranking: with the columns.  (q is the source's workspace of a lazy layer, null else.)
-inline void pack_plan(uint32_t* w, const StepLayer& e, bool ranking, int eb) {
+inline void pack_plan(uint32_t* w, const StepLayer& e, bool ranking, int eb, bool wide = false) {
     const int n = ranking ? kPlanPtrs : kFinishPtrs;
     const bool lazy = (e.flags & kStepLazy) != 0;
     const void* ptrs[kPlanPtrs] = {lazy ? e.q : nullptr, e.k, e.v, e.out, e.kv_len, e.vis_len, e.tail_start, e.ws, e.mass, e.score_col, e.id_col};
     for (int i = 0; i < n; ++i) put_ptr(w, n, i, ptrs[i]);
     uint32_t* num = w + ptr_words(n);
-    pack_numbers(num, e, eb, (uint32_t)e.mass_stride, lazy ? (uint32_t)e.hint_base : 0u);
+    pack_numbers(num, e, eb, (uint32_t)e.mass_stride, lazy ? (uint32_t)e.hint_base : 0u,
+                 wide ? w + (ranking ? kPlanWords : kFinishWords) : nullptr);
     if (ranking) num[10] = (uint32_t)e.col_stride;
 }
 template <bool RANKING>
-__host__ __device__ inline StepLayer unpack_plan(const uint32_t* w, int plain_eb) {
+__host__ __device__ inline StepLayer unpack_plan(const uint32_t* w, int plain_eb, bool wide = false) {
     constexpr int n = RANKING ? kPlanPtrs : kFinishPtrs;
     StepLayer e{};
     get_ptr(w, n, 0, e.q); get_ptr(w, n, 1, e.k); get_ptr(w, n, 2, e.v); get_ptr(w, n, 3, e.out); get_ptr(w, n, 4, e.kv_len);
     get_ptr(w, n, 5, e.vis_len); get_ptr(w, n, 6, e.tail_start); get_ptr(w, n, 7, e.ws); get_ptr(w, n, 8, e.mass);
     const uint32_t* num = w + ptr_words(n);
     const bool coded = (num[6] >> 24 & kStepE4M3) != 0;
-    unpack_numbers(num, e, coded ? 1 : plain_eb);
+    unpack_numbers(num, e, coded ? 1 : plain_eb, wide ? w + (RANKING ? kPlanWords : kFinishWords) : nullptr);
     e.mass_stride = (int32_t)num[8]; e.hint_base = (int32_t)num[9];
     if (RANKING) { get_ptr(w, n, 9, e.score_col); get_ptr(w, n, 10, e.id_col); e.col_stride = (int32_t)num[10]; }
     return e;

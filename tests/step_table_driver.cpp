@@ -13,7 +13,7 @@ static int64_t upto(int64_t n) { return (int64_t)(rng() % (uint64_t)(n + 1)); }
 template <typename P>
 static void ptr(P& p) { p = reinterpret_cast<P>(upto(3) == 0 ? 0 : (rng() >> (16 + upto(20))) & ~15ull); }
 
-static StepLayer random_layer(int eb) {
+static StepLayer random_layer(int eb, bool wide = false) {
     StepLayer e{};
     ptr(e.q); ptr(e.k); ptr(e.v); ptr(e.k_new); ptr(e.v_new); ptr(e.out); ptr(e.kv_len); ptr(e.vis_len); ptr(e.tail_start);
     ptr(e.score_col); ptr(e.id_col); ptr(e.mass); ptr(e.ws); ptr(e.k_scale); ptr(e.v_scale);
@@ -24,6 +24,10 @@ static StepLayer random_layer(int eb) {
     e.sys_len = (int32_t)(upto(1) ? 0xffff : upto(50)); e.max_vis = (int32_t)upto(8192); e.max_kv = (int32_t)upto(0x7ffffff0);
     e.keep_count = (int32_t)upto(8193) - 1; e.chunk = 32 * (int32_t)(1 + upto(0xfffe)); e.capacity = (int32_t)upto(0x7fffffff);
     e.nsplit = (uint8_t)(1 + upto(63)); e.nsplit_cap = (uint8_t)(1 + upto(63)); e.src_nsplit_cap = (uint8_t)upto(64);
+    if (wide) {         // beyond what the other entries hold, up to what a cache can have
+        e.stride_b = upto((1ll << 47)) * unit; e.stride_h = upto(1ll << 40) * unit; e.stride_t = (int32_t)(upto(0x7fffffff) / unit * unit);
+        e.sys_len = (int32_t)upto(0x7fff0000 - 0x10000); e.chunk = 32 * (int32_t)(1 + upto((1 << 26) - 2));
+    }
     e.flags = (uint8_t)(upto(63) & ~kStepE4M3) | (eb == 1 ? kStepE4M3 : 0);
     if (e.flags & kStepLazy) { e.hint_base = e.capacity / 2; e.hint_gap = 0; }
     else if (upto(2) == 0) { e.hint_base = 0x7fffffff; e.hint_gap = 0; }
@@ -34,16 +38,17 @@ static StepLayer random_layer(int eb) {
 #define CHECK(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
 #define SAME(f) CHECK(a.f == e.f)
 
-static int check(int eb) {
+static int check(int eb, bool wide) {
     for (int i = 0; i < 20000; ++i) {
-        const StepLayer e = random_layer(eb);
-        CHECK(step_layer_fits(e, eb));
+        const StepLayer e = random_layer(eb, wide && i % 4 != 0);
+        CHECK(step_layer_fits(e, eb, wide));
+        const int more = wide ? kWideWords : 0;
         uint32_t w[64];
         std::memset(w, i % 2 ? 0xff : 0, sizeof(w));        // (a table's words start out as anything)
         const uint32_t guard = w[63];
-        pack_attend(w, e, eb == 1, eb);
-        CHECK(w[eb == 1 ? kAttendWordsE4M3 : kAttendWords] == guard);
-        StepLayer a = eb == 1 ? unpack_attend<true>(w, eb) : unpack_attend<false>(w, eb);
+        pack_attend(w, e, eb == 1, eb, wide);
+        CHECK(w[(eb == 1 ? kAttendWordsE4M3 : kAttendWords) + more] == guard);
+        StepLayer a = eb == 1 ? unpack_attend<true>(w, eb, wide) : unpack_attend<false>(w, eb, wide);
         SAME(q); SAME(k); SAME(v); SAME(k_new); SAME(v_new); SAME(out); SAME(kv_len); SAME(vis_len); SAME(tail_start); SAME(score_col);
         SAME(id_col); SAME(ws); SAME(stride_b); SAME(stride_h); SAME(stride_t); SAME(col_stride); SAME(sys_len); SAME(max_vis);
         SAME(max_kv); SAME(keep_count); SAME(chunk); SAME(hint_base); SAME(hint_gap); SAME(capacity); SAME(nsplit); SAME(nsplit_cap);
@@ -51,9 +56,9 @@ static int check(int eb) {
         if (eb == 1) { SAME(k_scale); SAME(v_scale); }
         for (int ranking = 0; ranking < 2; ++ranking) {
             std::memset(w, i % 2 ? 0xff : 0, sizeof(w));
-            pack_plan(w, e, ranking, eb);
-            CHECK(w[ranking ? kPlanWords : kFinishWords] == guard);
-            a = ranking ? unpack_plan<true>(w, eb == 1 ? 2 : eb) : unpack_plan<false>(w, eb == 1 ? 2 : eb);
+            pack_plan(w, e, ranking, eb, wide);
+            CHECK(w[(ranking ? kPlanWords : kFinishWords) + more] == guard);
+            a = ranking ? unpack_plan<true>(w, eb == 1 ? 2 : eb, wide) : unpack_plan<false>(w, eb == 1 ? 2 : eb, wide);
             SAME(k); SAME(v); SAME(out); SAME(kv_len); SAME(vis_len); SAME(tail_start); SAME(ws); SAME(mass); SAME(stride_b);
             SAME(stride_h); SAME(stride_t); SAME(mass_stride); SAME(sys_len); SAME(max_vis); SAME(max_kv); SAME(keep_count); SAME(chunk);
             SAME(capacity); SAME(nsplit); SAME(nsplit_cap); SAME(src_nsplit_cap); SAME(flags);
@@ -63,7 +68,16 @@ static int check(int eb) {
     }
     StepLayer e = random_layer(eb);
     const StepLayer good = e;
-    e.q = reinterpret_cast<const void*>(1ull << 48); CHECK(!step_layer_fits(e, eb)); e = good;
+    e.q = reinterpret_cast<const void*>(1ull << 48); CHECK(!step_layer_fits(e, eb) && !step_layer_fits(e, eb, true)); e = good;
+    if (wide) {         // what a wide entry is for, and what it does not hold either
+        e.stride_t = (1 << 16) * 16 / eb; CHECK(!step_layer_fits(e, eb) && step_layer_fits(e, eb, true)); e = good;
+        e.stride_t = 0x7fffffff / 16 * 16; CHECK(step_layer_fits(e, eb, true)); e = good;
+        e.sys_len = 0x7fff0000; e.hint_base = 0x7fffffff; CHECK(step_layer_fits(e, eb, true)); e = good;
+        e.chunk = 0x7fffffe0; CHECK(step_layer_fits(e, eb, true)); e = good;
+        e.stride_b = (1ll << 48) * 16 / eb; CHECK(!step_layer_fits(e, eb, true)); e = good;
+        e.stride_t += 1; CHECK(!step_layer_fits(e, eb, true));
+        return 0;
+    }
     e.stride_b = (1ll << 32) * 16 / eb; CHECK(!step_layer_fits(e, eb)); e = good;
     e.stride_h = (1ll << 32) * 16 / eb; CHECK(!step_layer_fits(e, eb)); e = good;
     e.stride_t = (1 << 16) * 16 / eb; CHECK(!step_layer_fits(e, eb)); e = good;
@@ -76,7 +90,7 @@ static int check(int eb) {
 
 int main() {
     for (int eb : {1, 2, 4})
-        if (check(eb)) return 1;
+        if (check(eb, false) || check(eb, true)) return 1;
     std::printf("ok\n");
     return 0;
 }
