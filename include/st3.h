@@ -419,7 +419,8 @@ ST3_EXPORT st3_status st3_decode_plans(const st3_attn_shape* shape, int32_t n_la
 /* st3_select_compact_layer for several layers at once (the evictions that precede the first decode
  * step of a generation), 16 layers a launch: layers[i] is brought down to keep_after visual rows
  * (keep_after < 0: left alone).  kv, seg, score_col, id_col, col_stride, keep_after and workspace of
- * an entry are read; kv.k may be NULL as there. */
+ * an entry are read; kv.k may be NULL as there.  The result is that of the single calls in order: entries that share a workspace,
+ * a column, lengths or a cache are launched one after the other. */
 ST3_EXPORT st3_status st3_select_compact_layers(const st3_attn_shape* shape, int32_t n_layers, const st3_layer_step* layers,
                                      int32_t mode, void* stream);
 

@@ -311,6 +311,19 @@ extern "C" st3_status st3_decode_plans(const st3_attn_shape* shape, int32_t n_la
     return enqueue_plans(plan, needs_apply, shape->batch, reinterpret_cast<hipStream_t>(stream));
 }
 
+namespace st3 {
+// Whether two evictions of a call share what one of them writes, so that they mean what they mean one after the other.
+static bool evictions_meet(const EvictArgs& x, const EvictArgs& y, int B) {
+    auto scratch_meets = [B](const EvictArgs& p, const EvictArgs& q) {      // the list of moves and, in front of it, their number
+        const uintptr_t a0 = reinterpret_cast<uintptr_t>(p.move_cnt), a1 = reinterpret_cast<uintptr_t>(p.moves + (size_t)B * p.max_moves * 2);
+        const uintptr_t b0 = reinterpret_cast<uintptr_t>(q.move_cnt), b1 = reinterpret_cast<uintptr_t>(q.moves + (size_t)B * q.max_moves * 2);
+        return a0 < b1 && b0 < a1;
+    };
+    return scratch_meets(x, y) || x.score_col == y.score_col || x.id_col == y.id_col || x.vis_len == y.vis_len || x.kv_len == y.kv_len ||
+           x.v == y.v || (x.k != nullptr && x.k == y.k);
+}
+}  // namespace st3
+
 extern "C" st3_status st3_select_compact_layers(const st3_attn_shape* shape, int32_t n_layers, const st3_layer_step* layers,
                                                 int32_t mode, void* stream) {
     using namespace st3;
@@ -336,7 +349,15 @@ extern "C" st3_status st3_select_compact_layers(const st3_attn_shape* shape, int
         needs_apply.push_back(na ? 1 : 0);
     }
     if (plan.empty()) return ST3_OK;
-    return enqueue_plans(plan, needs_apply, shape->batch, reinterpret_cast<hipStream_t>(stream));
+    bool meet = false;
+    for (size_t i = 0; i < plan.size() && !meet; ++i)
+        for (size_t j = 0; j < i && !meet; ++j) meet = evictions_meet(plan[i], plan[j], shape->batch);
+    if (!meet) return enqueue_plans(plan, needs_apply, shape->batch, reinterpret_cast<hipStream_t>(stream));
+    for (size_t i = 0; i < plan.size(); ++i) {
+        s = enqueue_plans({plan[i]}, {needs_apply[i]}, shape->batch, reinterpret_cast<hipStream_t>(stream));
+        if (s != ST3_OK) return s;
+    }
+    return ST3_OK;
 }
 
 extern "C" st3_status st3_decode_step(const st3_attn_shape* shape, int32_t n_layers, const st3_layer_step* layers,

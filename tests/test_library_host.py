@@ -123,6 +123,34 @@ def test_argument_errors_are_reported_before_any_launch():
                                         None) == st3.ST3_ERR_INVALID_ARG
     assert lib.st3_select_compact_layer(C.byref(sh), C.byref(kv), C.byref(seg), fake, fake, 64, -1, 0, fake, 1 << 30,
                                         None) == st3.ST3_ERR_INVALID_ARG
+    # the same for several layers at once: no layers, a bad mode, no columns, columns shorter than the rows, no or a small workspace
+    several = (st3.LayerStep * 2)()
+    for s in several:
+        s.kv, s.seg, s.keep_after, s.inherit_from = kv, seg, 10, -1
+        s.score_col, s.id_col, s.col_stride, s.workspace, s.workspace_bytes = fake, fake, 64, fake, 1 << 30
+    layers_call = lambda n=2, mode=st3.ST3_HOLE_FILL, shape=sh: lib.st3_select_compact_layers(C.byref(shape), n, several, mode, None)  # noqa: E731
+    assert layers_call(shape=bad) == st3.ST3_ERR_UNSUPPORTED
+    assert layers_call(n=0) == layers_call(mode=7) == st3.ST3_ERR_INVALID_ARG
+    assert lib.st3_select_compact_layers(C.byref(sh), 1, None, 0, None) == st3.ST3_ERR_INVALID_ARG
+    for field, value, want in [("score_col", None, st3.ST3_ERR_INVALID_ARG), ("id_col", None, st3.ST3_ERR_INVALID_ARG),
+                               ("col_stride", 63, st3.ST3_ERR_INVALID_ARG), ("workspace", None, st3.ST3_ERR_INVALID_ARG),
+                               ("workspace", fake + 8, st3.ST3_ERR_INVALID_ARG), ("workspace_bytes", 16, st3.ST3_ERR_WORKSPACE_TOO_SMALL)]:
+        was = getattr(several[1], field)
+        setattr(several[1], field, value)
+        assert layers_call() == want, field
+        setattr(several[1], field, was)
+    several[1].seg = st3.Segments(8, 64, 129, fake, fake)
+    assert layers_call() == st3.ST3_ERR_INVALID_ARG
+    several[0].keep_after = several[1].keep_after = -1          # nothing to do, whatever else the entries say
+    assert layers_call() == st3.ST3_OK
+    # the kept entries of rows: no input or output, strides below the rows, more kept than there are, too many, outputs on inputs
+    cols = lambda sc=fake, ss=64, i=fake + 0x10000, si=64, n=64, k=10, o=fake + 0x20000, so=10, oi=fake + 0x30000, soi=10, b=2: \
+        lib.st3_select_columns(sc, ss, i, si, b, n, k, o, so, oi, soi, None)  # noqa: E731
+    assert cols(sc=None) == cols(i=None) == cols(o=None) == cols(oi=None) == cols(b=0) == cols(k=65) == cols(k=-1) == st3.ST3_ERR_INVALID_ARG
+    assert cols(ss=63) == cols(si=63) == cols(so=9) == cols(soi=9) == st3.ST3_ERR_INVALID_ARG
+    assert cols(n=16385, ss=16385, si=16385) == st3.ST3_ERR_UNSUPPORTED
+    assert cols(o=fake) == cols(oi=fake + 0x10000) == cols(oi=fake + 0x20000) == cols(o=fake + 4 * 63) == st3.ST3_ERR_INVALID_ARG
+    assert cols(k=0) == st3.ST3_OK
     # prefill: segment layout outside the sequence, window too large
     t4 = st3.Tensor4(fake, 4 * 128 * 64, 128 * 64, 64)
     assert lib.st3_prefill_attention(C.byref(sh), C.byref(t4), C.byref(t4), C.byref(t4), 100, 50, 60, 1, C.byref(t4),
