@@ -255,7 +255,7 @@ ST3_EXPORT st3_status st3_select_topk(const float* scores, int64_t score_stride,
  * prefill: the next layer's ids and ranking scores), in one launch:
  *   out_ids[b][r], out_scores[b][r] <- ids[b][i_r], scores[b][i_r]   for r in [0, k)
  * with i_0 < i_1 < ... the positions st3_select_topk keeps of the n entries of row b.  k <= n <=
- * 16384; the outputs must not overlap the inputs.
+ * 16384; no row of an output may overlap a row of an input or of the other output (rows of one buffer may alternate).
  * ------------------------------------------------------------------------------------------- */
 ST3_EXPORT st3_status st3_select_columns(const float* scores, int64_t score_stride, const int32_t* ids, int64_t id_stride,
                               int32_t batch, int32_t n, int32_t k, float* out_scores, int64_t out_score_stride,

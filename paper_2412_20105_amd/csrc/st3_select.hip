@@ -706,9 +706,16 @@ extern "C" st3_status st3_select_columns(const float* scores, int64_t score_stri
     if (n > 16384 || batch > 65535 * 32) return ST3_ERR_UNSUPPORTED;
     if (score_stride < n || id_stride < n || out_score_stride < k || out_id_stride < k) return ST3_ERR_INVALID_ARG;
     if (k == 0) return ST3_OK;
+    // whether a row of x shares memory with a row of y (rows of one buffer may alternate); rows follow each other without overlap
     auto meet = [&](const void* x, int64_t xs, int64_t xn, const void* y, int64_t ys, int64_t yn) {
         const uintptr_t a = reinterpret_cast<uintptr_t>(x), b = reinterpret_cast<uintptr_t>(y);
-        return a < b + ((uintptr_t)(batch - 1) * ys + yn) * 4 && b < a + ((uintptr_t)(batch - 1) * xs + xn) * 4;
+        if (a >= b + ((uintptr_t)(batch - 1) * ys + yn) * 4 || b >= a + ((uintptr_t)(batch - 1) * xs + xn) * 4) return false;
+        for (int32_t i = 0, j = 0; i < batch && j < batch;) {
+            const uintptr_t p = a + (uintptr_t)i * xs * 4, q = b + (uintptr_t)j * ys * 4, p1 = p + xn * 4, q1 = q + yn * 4;
+            if (p < q1 && q < p1) return true;
+            p1 <= q ? ++i : ++j;
+        }
+        return false;
     };
     if (meet(scores, score_stride, n, out_scores, out_score_stride, k) || meet(scores, score_stride, n, out_ids, out_id_stride, k) ||
         meet(ids, id_stride, n, out_scores, out_score_stride, k) || meet(ids, id_stride, n, out_ids, out_id_stride, k) ||

@@ -28,6 +28,23 @@ def test_select_columns(rows, n, k, ties):
         st3.st3_select_columns(score, ids, n, k, score, out_i)
 
 
+@pytest.mark.parametrize("layout", ["outputs", "all"])
+def test_rows_of_one_buffer_alternate(layout):
+    """Scores and ids of a row side by side: rows of outputs lie between rows of outputs, or of inputs, without touching them."""
+    rows, n, k = 5, 70, 40
+    g = torch.Generator(device=DEV).manual_seed(9)
+    score, ids = torch.rand((rows, n), generator=g, device=DEV), torch.rand((rows, n), generator=g, device=DEV).argsort(dim=1).to(torch.int32)
+    want_s, want_i = torch.empty((rows, k), device=DEV), torch.empty((rows, k), dtype=torch.int32, device=DEV)
+    st3.st3_select_columns(score, ids, n, k, want_s, want_i)
+    buf = torch.zeros((rows, 2 * n + 2 * k), device=DEV)
+    out_s, out_i = buf[:, 2 * n:2 * n + k], buf[:, 2 * n + k:].view(torch.int32)
+    if layout == "all":
+        buf[:, :n], buf[:, n:2 * n].view(torch.int32)[:] = score, ids
+        score, ids = buf[:, :n], buf[:, n:2 * n].view(torch.int32)
+    st3.st3_select_columns(score, ids, n, k, out_s, out_i)
+    assert torch.equal(out_s, want_s) and torch.equal(out_i, want_i)
+
+
 @pytest.mark.parametrize("mode", [st3.ST3_STABLE, MODE])
 @pytest.mark.parametrize("args", [
     dict(L=35, B=2, H=3, d=64, dtype=BF, vis=[60, 9], tail=4, drop=5),                      # three launches

@@ -150,6 +150,9 @@ def test_argument_errors_are_reported_before_any_launch():
     assert cols(ss=63) == cols(si=63) == cols(so=9) == cols(soi=9) == st3.ST3_ERR_INVALID_ARG
     assert cols(n=16385, ss=16385, si=16385) == st3.ST3_ERR_UNSUPPORTED
     assert cols(o=fake) == cols(oi=fake + 0x10000) == cols(oi=fake + 0x20000) == cols(o=fake + 4 * 63) == st3.ST3_ERR_INVALID_ARG
+    # rows of one buffer: a row of outputs that reaches into the next row of inputs
+    assert cols(ss=100, o=fake + 4 * 91, so=100) == cols(ss=100, o=fake + 4 * 63, so=100) == st3.ST3_ERR_INVALID_ARG
+    assert cols(ss=100, o=fake + 4 * 64 + 4 * 95, so=100, b=3) == st3.ST3_ERR_INVALID_ARG
     assert cols(k=0) == st3.ST3_OK
     # prefill: segment layout outside the sequence, window too large
     t4 = st3.Tensor4(fake, 4 * 128 * 64, 128 * 64, 64)
