@@ -207,20 +207,17 @@ class Generation:
     def begin_decode(self):
         """The eviction that precedes the FIRST decode step (Alg. 3 truncates a layer's cache before
         its attention at every step; later steps do it right after the previous step's attention)."""
-        arr, evicts = self._step_array(), False
-        for l, lc in enumerate(self.layers):
-            target = min(self.keep[l][1], lc.h_vis) if self.T >= 1 else lc.h_vis
-            s = arr[l]
-            s.keep_after = -1
-            if target < lc.h_vis:
-                evicts = True
-                s.keep_after = target
-                s.seg.max_vis_len, s.seg.max_kv_len = lc.h_vis, lc.h_kv
-                if not self.fixed_tail:
-                    lc.h_kv -= lc.h_vis - target
-                lc.h_vis = target
-        if evicts:
+        arr = self._step_array()
+        targets = [min(self.keep[l][1], lc.h_vis) if self.T >= 1 else lc.h_vis for l, lc in enumerate(self.layers)]
+        for s, lc, target in zip(arr, self.layers, targets):
+            s.keep_after = target if target < lc.h_vis else -1
+            s.seg.max_vis_len, s.seg.max_kv_len = lc.h_vis, lc.h_kv
+        if any(target < lc.h_vis for lc, target in zip(self.layers, targets)):
             st3.st3_select_compact_layers(self.shape, arr, self.L, self.compact_mode)
+        for lc, target in zip(self.layers, targets):        # (an error above leaves the lengths as they are on the device)
+            if not self.fixed_tail:
+                lc.h_kv -= lc.h_vis - target
+            lc.h_vis = target
         self._decoding = True
 
     def _keep_after(self, l: int, t: int) -> int:
