@@ -29,3 +29,18 @@ def test_a_refused_eviction_leaves_the_lengths(monkeypatch, fixed_tail):
     assert calls[1] == calls[0] == [(15, 20, 30), (-1, 20, 30), (7, 10, 20)]
     closed = 0 if fixed_tail else 1
     assert [(lc.h_vis, lc.h_kv) for lc in gen.layers] == [(15, 30 - 5 * closed), (20, 30), (7, 20 - 3 * closed)]
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """A torch that lacks the two functions behind the raw handle: the public interface is asked."""
+    class Stream:
+        cuda_stream = 0x1234
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    monkeypatch.setattr(st3, "_raw_stream", lambda device: 0x5678 + device)
+    monkeypatch.setattr(st3, "_raw_device", lambda: 1)
+    assert st3._stream(None) == 0x5679 and st3._stream(7) == 7 and st3._stream(Stream) == 0x1234
+    for missing in ("_raw_stream", "_raw_device"):
+        with monkeypatch.context() as m:
+            m.setattr(st3, missing, None)
+            assert st3._stream(None) == 0x1234
