@@ -18,6 +18,8 @@ def test_a_refused_eviction_leaves_the_lengths(monkeypatch, fixed_tail):
 
     monkeypatch.setattr(st3, "st3_workspace_init", lambda *a, **k: None)
     monkeypatch.setattr(st3, "st3_select_compact_layers", refuse)
+    monkeypatch.setattr(st3, "kv_layer", lambda *a: st3.KvLayer())                  # (they take device tensors only)
+    monkeypatch.setattr(st3, "segments", lambda *a: st3.Segments(*a[:3]))
     gen = pipeline.Generation(3, 2, 64, torch.float32, 1, 4, 20, 6, 2, [[20, 15, 12], [20, 20, 20], [10, 7, 7]], device="cpu",
                               fixed_tail=fixed_tail)
     for lc, vis in zip(gen.layers, (20, 20, 10)):
