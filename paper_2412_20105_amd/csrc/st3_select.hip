@@ -443,7 +443,11 @@ void launch_evict_plan_batch(const EvictArgs* plans, int n, int B, hipStream_t s
     }
 }
 
-constexpr int kMergeHeads = 8;      // heads whose chunk partials one merge workgroup combines
+constexpr int kMergeHeads = 8;      // heads whose chunk partials one merge workgroup of the plan launch combines
+// ... and of the finish launch: an output for each of its 256 threads, who take their chunks' partials in rounds of loads.  (Eight
+// heads, four outputs one after the other for each thread -> so, us a step of one layer of 8 heads: 1024 visual rows, 17 chunks 26.1 -> 18.3,
+// 2048 rows, 33 chunks 24.5 -> 13.2, 4096 rows, 64 chunks 26.7 -> 15.3; 32 heads, 100 rows, 2 chunks 11.7 -> 10.5.)
+inline __host__ __device__ int finish_merge_heads(int D) { return D == 64 ? 4 : 2; }
 
 // grid (B, layers, 1 + merge workgroups): z = 0 runs the plan of (sequence x, layer y); z >= 1 merges the chunk partials
 // of that layer's attention output for kMergeHeads heads (only launched when some layer left partials to merge).
@@ -463,7 +467,7 @@ __global__ __launch_bounds__(NT) void evict_plan_table_kernel(StepTable t) {
 
 // What is left of the plans when the rows have been ranked beside the attention.  grid (B, layers, moves + masses + merges), 256
 // threads: workgroups z < move_wgs move rows (the first one advances the lengths too), the next mass_wgs finish kMassKeys
-// entries of the mass each, the rest merge the chunk partials of kMergeHeads heads each.
+// entries of the mass each, the rest merge the chunk partials of finish_merge_heads heads each.
 __global__ __launch_bounds__(256) void step_finish_kernel(StepTable t, int move_wgs, int mass_wgs) {
     __shared__ MassShared<256> sm;
     const StepLayer e = unpack_plan<false>(t.w + blockIdx.y * (kFinishWords + (t.c.wide ? kWideWords : 0)), t.c.elem_bytes, t.c.wide != 0);
@@ -477,8 +481,8 @@ __global__ __launch_bounds__(256) void step_finish_kernel(StepTable t, int move_
         if (z == 0 && threadIdx.x == 0) evict_publish(a, b, evict_counts(a, b));
         if (a.inline_apply) move_rows_block<256>(a, b, z, move_wgs);
     } else if (e.nsplit > 1) {
-        const int h0 = (z - move_wgs - mass_wgs) * kMergeHeads;
-        if (h0 < t.c.H) merge_chunks(t.c, e, b, h0, h0 + kMergeHeads);
+        const int heads = finish_merge_heads(t.c.D), h0 = (z - move_wgs - mass_wgs) * heads;
+        if (h0 < t.c.H) merge_chunks(t.c, e, b, h0, h0 + heads);
     }
 }
 
@@ -498,7 +502,8 @@ void launch_evict_plan_table(const StepCommon& c, const StepLayer* entry, int n,
             pack_plan(t.w + i * stride, e, !needs.apart, (e.flags & kStepE4M3) ? 1 : c.elem_bytes, c.wide != 0);
         }
         i0 += cnt;
-        const int merge_wgs = needs.merge ? (c.H + kMergeHeads - 1) / kMergeHeads : 0;
+        const int merge_heads = needs.apart ? finish_merge_heads(c.D) : kMergeHeads;
+        const int merge_wgs = needs.merge ? (c.H + merge_heads - 1) / merge_heads : 0;
         const int64_t plans = (int64_t)c.B * cnt;
         if (needs.apart) {
             // (a round of a workgroup's loads: eight of 16 bytes for each thread)
