@@ -76,9 +76,10 @@ class Step:
 
 def _same(a, b):
     # Both add the same float32 products, cut into other chunks: an output differs by a few roundings of a sum whose
-    # terms are at most max|v| <= 6 in all (weights add to 1), i.e. 1e-5; a bf16 output then by one step (2^-8) more.
+    # terms are at most max|v| <= 6 in all (weights add to 1), i.e. 1e-5; a bf16 output then by one step more, to the next
+    # number of 8 significant bits: at most 2^-7 of the value (two sums on either side of a rounding boundary).
     x, y = a.out.double(), b.out.double()
-    step = 2.0 ** -8 if a.out.dtype == torch.bfloat16 else 0.0
+    step = 2.0 ** -7 if a.out.dtype == torch.bfloat16 else 0.0
     assert bool(((x - y).abs() <= 1e-5 + step * y.abs()).all()), float((x - y).abs().max())
     for l, (s, t) in enumerate(zip(a.state, b.state)):
         # masses: probabilities, relative error of a float32 exponent and normaliser
