@@ -281,16 +281,38 @@ void decode_attend_kernel(DecodeArgs a) {
     attend_chunk<T, KT, D, U, false>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-// Workgroup (0, H) of a sequence and layer of a whole-step launch ranks the rows of a layer whose next eviction does not wait for
-// the mass of this step (kStepApart, evict_rank_early).  (Behind the attention's workgroups of the same layer; all of them are
-// resident long before the last one ends.)
-__device__ __forceinline__ void rank_workgroup(const StepCommon& c, const StepLayer& e, int split, int b) {
-    if (split != 0 || !(e.flags & kStepApart) || e.keep_count < 0) return;
+// What a workgroup of a whole-step launch does: chunk `split` of strip (b, h) of the table's entry li, or, with the launch's first
+// workgroups, the ranking of (li, b) for a layer whose next eviction does not wait for the mass of this step (kStepApart,
+// evict_rank_early).  A ranking takes as long as the attention of a small step (2048 rows 15 us), so all of them have to start at
+// once: as workgroups behind the attention's of their sequence, the last ones started when the launch's last strips did, and with them
+// the grid was one head wider.  us a step, so -> first: 16 layers of 16 heads, 2880 visual rows 82.5 -> 74.0, 32 layers of 8 heads, batch 2,
+// 2048 rows, E4M3 60.7 -> 56.0, 32 layers of 4 heads 44.3 -> 45.7, 4 layers of 40 heads 49.6 -> 53.0 (behind a first slice of strips:
+// 82.4, 61.9, 45.5, 48.9); without evictions 8 layers of 8 heads, batch 4, 1500 rows 44.5 -> 39.7, 40 layers of 12 heads, 2000 rows 110 ->
+// 94.0, 32 layers of 8 heads, batch 4, 2880 rows 267 -> 254.
+struct StepWork {
+    bool ranks;
+    int li, b, split, h;
+};
+__device__ __forceinline__ StepWork step_work(const StepCommon& c) {
+    StepWork w;
+    w.split = blockIdx.y; w.h = blockIdx.x;
+    w.ranks = (int)blockIdx.z < c.rank_z;
+    const int z = w.ranks ? ((int)blockIdx.z * c.chunks + w.split) * c.H + w.h : (int)blockIdx.z - c.rank_z;
+    w.li = __builtin_amdgcn_readfirstlane(z / c.B);
+    w.b = z - w.li * c.B;
+    return w;
+}
+__device__ __forceinline__ void rank_workgroup(const StepCommon& c, const StepLayer& e, int b) {
+    if (!(e.flags & kStepApart) || e.keep_count < 0) return;
     __shared__ SelectShared sm;
     evict_rank_early<kDecodeThreads>(plan_from_entry(c, e), b, sm);
 }
+// z of the grid that ranking takes: a workgroup for each (layer, sequence) of the launch.
+static int rank_rows_z(int B, int H, int chunks, int layers) { return (int)(((int64_t)B * layers + (int64_t)H * chunks - 1) / ((int64_t)H * chunks)); }
+// Layers of a launch that may rank: rank_z + B * layers is at most 65535 however many chunks there are.
+static int max_layers_ranked(int B, int H) { return (int)((int64_t)65534 * H / (H + 1) / B); }
 
-// The attention of several layers of a step that do not depend on each other; grid (H + 1, most chunks of any of them,
+// The attention of several layers of a step that do not depend on each other; grid (H, most chunks of any of them, rank_z +
 // B * layers), layers in order, so the longest strips (early layers keep the most rows) start first.  Bound by HBM; as a
 // launch per layer it was bound by the ramp and the tail of each launch and the gap behind it (about 9 us a layer, whatever
 // its bytes).  Whole step, us, one launch per layer -> up to 35 layers per launch: 7B batch 1 191 -> 42 (209 MB), 13B batch 8
@@ -301,13 +323,13 @@ __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS)
 __attribute__((amdgpu_waves_per_eu(ST3_DECODE_MIN_BLOCKS, ST3_DECODE_MIN_BLOCKS)))
 void decode_attend_layers_kernel(StepTable t) {
     const StepCommon& c = t.c;
-    const int li = __builtin_amdgcn_readfirstlane((int)blockIdx.z / c.B), b = (int)blockIdx.z - li * c.B;
-    const int split = blockIdx.y, h = blockIdx.x;
+    const StepWork w = step_work(c);
+    if (w.li >= c.layers) return;
     constexpr bool coded = sizeof(KT) == 1;
     const int words = (coded ? kAttendWordsE4M3 : kAttendWords) + (c.wide ? kWideWords : 0);
-    const StepLayer e = unpack_attend<coded>(t.w + li * words, sizeof(KT), c.wide != 0);
-    if (h == c.H) return rank_workgroup(c, e, split, b);
-    if (split >= e.nsplit) return;
+    const StepLayer e = unpack_attend<coded>(t.w + w.li * words, sizeof(KT), c.wide != 0);
+    if (w.ranks) return rank_workgroup(c, e, w.b);
+    if (w.split >= e.nsplit) return;
     const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
     const bool want = (e.flags & kStepWantMass) != 0, all = (e.flags & kStepKeepAll) != 0;
     DecodeArgs a;
@@ -325,7 +347,7 @@ void decode_attend_layers_kernel(StepTable t) {
     a.stage_rows = 0;           // (the launcher's)
     a.pending = reinterpret_cast<int32_t*>(e.ws + wl.pending);
     a.k_new = e.k_new; a.v_new = e.v_new; a.out = e.out;
-    attend_chunk<T, KT, D, U, NTS>(a, split, h, b);
+    attend_chunk<T, KT, D, U, NTS>(a, w.split, w.h, w.b);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -484,13 +506,13 @@ __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_
 template <typename T, typename KT, int D, int U>
 __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_inherit_layers_kernel(StepTable t) {
     const StepCommon& c = t.c;
-    const int li = __builtin_amdgcn_readfirstlane((int)blockIdx.z / c.B), b = (int)blockIdx.z - li * c.B;
-    const int split = blockIdx.y, h = blockIdx.x;
+    const StepWork w = step_work(c);
+    if (w.li >= c.layers) return;
     constexpr bool coded = sizeof(KT) == 1;
     const int words = (coded ? kAttendWordsE4M3 : kAttendWords) + (c.wide ? kWideWords : 0);
-    const StepLayer e = unpack_attend<coded>(t.w + li * words, sizeof(KT), c.wide != 0);
-    if (h == c.H) return rank_workgroup(c, e, split, b);
-    if (split >= e.nsplit) return;
+    const StepLayer e = unpack_attend<coded>(t.w + w.li * words, sizeof(KT), c.wide != 0);
+    if (w.ranks) return rank_workgroup(c, e, w.b);
+    if (w.split >= e.nsplit) return;
     const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
     const DecodeWs sl = decode_ws_sized(c.B, c.H, D, e.hint_base, e.src_nsplit_cap);
     const char* sws = reinterpret_cast<const char*>(e.q);
@@ -506,7 +528,7 @@ __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_
     a.own_pending = reinterpret_cast<int32_t*>(e.ws + wl.pending);
     a.part_o = reinterpret_cast<float*>(e.ws + wl.part_o);
     a.v_new = e.v_new; a.v_scale = e.v_scale; a.out = e.out;
-    inherit_chunk<T, KT, D, U>(a, split, h, b);
+    inherit_chunk<T, KT, D, U>(a, w.split, w.h, w.b);
 }
 
 struct FinishArgs {
@@ -727,8 +749,8 @@ void launch_attend(const DecodeArgs& da, int B, hipStream_t st) {
 // 7B batch 1 72.6 / 71.8 / 75.6 / 78.9, 13B batch 8 with lazy layers 563 / 571 / 560 / 565, 13B batch 32 2441 / 2457 / 2433 /
 // 2421, 13B batch 32 E4M3 1327 / 1404 / 1423, high resolution batch 8 E4M3 700 / 696 / 721.
 template <typename T, typename KT, int D>
-void launch_attend_layers(const StepTable& t, int most, int lds_words, bool stream, hipStream_t st) {
-    const dim3 grid(t.c.H + 1, most, t.c.B * t.c.layers);
+void launch_attend_layers(const StepTable& t, int lds_words, bool stream, hipStream_t st) {
+    const dim3 grid(t.c.H, t.c.chunks, t.c.rank_z + t.c.B * t.c.layers);
     const size_t lds = (size_t)lds_words * sizeof(float);
     with_tile(AttendTiles<KT>{}, 0, [&](auto u) {
         if (stream) launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, true>, grid, lds, st, t.c.layers, t);
@@ -737,9 +759,9 @@ void launch_attend_layers(const StepTable& t, int most, int lds_words, bool stre
 }
 
 template <typename T, typename KT, int D>
-void launch_inherit_layers(const StepTable& t, int most, int lds_words, hipStream_t st) {
-    decode_inherit_layers_kernel<T, KT, D, 4><<<dim3(t.c.H + 1, most, t.c.B * t.c.layers), kDecodeThreads,
-                                                (size_t)lds_words * sizeof(uint32_t), st>>>(t);
+void launch_inherit_layers(const StepTable& t, int lds_words, hipStream_t st) {
+    const dim3 grid(t.c.H, t.c.chunks, t.c.rank_z + t.c.B * t.c.layers);
+    decode_inherit_layers_kernel<T, KT, D, 4><<<grid, kDecodeThreads, (size_t)lds_words * sizeof(uint32_t), st>>>(t);
 }
 
 // The V-only kernel of lazy layers: 4 loads per lane and tile (4 KB per wave) were the fastest or
@@ -973,7 +995,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
                                const char* has_heirs, const EvictArgs* plan, char* needs_apply, StepCommon& common, StepLayer* e,
                                PlanNeeds& needs, hipStream_t st) {
     const int B = shape->batch, H = shape->heads, D = shape->head_dim;
-    common = StepCommon{B, H, D, mode, elem_bytes(shape->dtype), scale_log2(shape), 0, 0};
+    common = StepCommon{B, H, D, (int16_t)mode, (int16_t)elem_bytes(shape->dtype), scale_log2(shape), 0, 0, 0, 0};
     int64_t rows[2] = {0, 0};           // of the ordinary and of the lazy layers
     for (int i = 0; i < n_layers; ++i) {
         const st3_layer_step& L = layers[i];
@@ -985,7 +1007,8 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
     if (B > 65535) return ST3_ERR_UNSUPPORTED;
     std::vector<char> moves_here((size_t)n_layers, 0);
     std::vector<int> stage((size_t)n_layers, 0), groups[4];     // layers that may share launches, in launch order
-    needs = PlanNeeds{0, false, true, 0};
+    // (grid z is rank_z + B * layers, at most 65535)
+    needs = PlanNeeds{0, false, B + rank_rows_z(B, H, 1, 1) <= 65535, 0};
     for (int i = 0; i < n_layers; ++i) {
         needs.most_vis = std::max(needs.most_vis, plan[i].max_vis);
         needs.apart = needs.apart && plan[i].mass_apart;
@@ -1050,7 +1073,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
         if (n == 0) continue;
         const bool coded = layers[members[0]].kv.format == ST3_KV_E4M3;
         const int words = coded ? kAttendWordsE4M3 : kAttendWords, stride = words + (common.wide ? kWideWords : 0);
-        const int per = std::min(entries_per_table(words, common.wide), 65535 / B);     // grid z is B * layers
+        const int per = std::min(entries_per_table(words, common.wide), needs.apart ? max_layers_ranked(B, H) : 65535 / B);
         const int launches = (n + per - 1) / per;
         for (int g = 0, i0 = 0; g < launches; ++g) {
             const int cnt = (n - i0 + launches - g - 1) / (launches - g);       // as equal as can be
@@ -1060,7 +1083,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
             StepTable t;
             t.c = common; t.c.layers = cnt;
             int64_t written = (int64_t)cnt * B * H * D * (2 * kv_elem_bytes(shape, kv) + elem_bytes(shape->dtype));
-            int most = 1, lds_words = 0;        // dynamic LDS: the logits a workgroup collects, or the keys it ranks
+            int most = 1, lds_words = 0, ranked = 0;    // dynamic LDS: the logits a workgroup collects, or the keys it ranks
             for (int j = 0; j < cnt; ++j) {
                 const int i = members[(size_t)(i0 + j)];
                 pack_attend(t.w + j * stride, e[i], coded, kv_elem_bytes(shape, kv), common.wide != 0);
@@ -1068,10 +1091,12 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
                 lds_words = std::max(lds_words, stage[(size_t)i]);
                 if (e[i].flags & kStepKeepAll) written += (int64_t)B * H * e[i].max_kv * sizeof(float);
                 else if (e[i].flags & kStepWantMass) written += (int64_t)B * H * e[i].max_vis * sizeof(float);
-                if ((e[i].flags & kStepApart) && e[i].keep_count >= 0) lds_words = std::max(lds_words, e[i].max_vis);
+                if ((e[i].flags & kStepApart) && e[i].keep_count >= 0) { lds_words = std::max(lds_words, e[i].max_vis); ranked += 1; }
             }
-            if (lazy) ST3_DISPATCH_KV(launch_inherit_layers, shape, kv, t, most, lds_words, st);
-            else ST3_DISPATCH_KV(launch_attend_layers, shape, kv, t, most, lds_words, written > kStreamStoreBytes, st);
+            t.c.chunks = (int16_t)most;
+            t.c.rank_z = ranked > 0 ? rank_rows_z(B, H, most, cnt) : 0;
+            if (lazy) ST3_DISPATCH_KV(launch_inherit_layers, shape, kv, t, lds_words, st);
+            else ST3_DISPATCH_KV(launch_attend_layers, shape, kv, t, lds_words, written > kStreamStoreBytes, st);
             i0 += cnt;
         }
     }

@@ -22,11 +22,14 @@
 namespace st3 {
 
 struct StepCommon {
-    int32_t B, H, D, mode;      // mode: st3_compact_mode
-    int32_t elem_bytes;         // of q, the new rows, the outputs and plain caches: 2 (bf16) or 4 (float32)
+    int32_t B, H, D;
+    int16_t mode;               // st3_compact_mode
+    int16_t elem_bytes;         // of q, the new rows, the outputs and plain caches: 2 (bf16) or 4 (float32)
     float scale_l2;
     int32_t layers;             // entries of the table
-    int32_t wide;               // 1: the table's entries are wide
+    int16_t wide;               // 1: the table's entries are wide
+    int16_t chunks;             // most chunks of any layer: the attention's grid is (H, chunks, rank_z + B * layers)
+    int32_t rank_z;             // the grid's first z: its workgroups rank rows, one for each (layer, sequence); 0: no row is ranked
 };
 
 struct StepLayer {
