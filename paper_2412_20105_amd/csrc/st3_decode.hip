@@ -985,6 +985,22 @@ st3_status enqueue_inherit(const st3_attn_shape* shape, const st3_kv_layer* kv, 
 // 13B batch 16 1265 -> 1219, batch 24 1892 -> 1815.
 constexpr int64_t kStreamStoreBytes = (int64_t)8 << 20;
 
+// Whether a step's rows are ranked beside its attention, by 256 threads a plan, or in the plans behind it, by up to 1024.  Beside it
+// a ranking is hidden as long as the attention lasts (that grows with the strips of all layers), and the masses have workgroups of
+// their own, which a plan finishes by itself, heads times rows of them; a layer that evicts more rows than a plan moves takes a
+// launch more behind it.  The line is fitted to these, us a step, beside / behind, bf16 d = 128, one sequence, by layers x heads:
+//   1024 rows  1 x 4 17.8 / 19.3, 8 x 4 20.2 / 21.9, 1 x 32 21.7 / 24.4
+//   2048 rows  1 x 4 24.3 / 22.6, 4 x 4 25.7 / 24.8, 8 x 4 26.5 / 27.9, 1 x 32 26.4 / 30.4
+//   2880 rows  1 x 4 28.0 / 24.2, 4 x 4 30.1 / 28.3, 8 x 4 31.9 / 30.6, 16 x 4 35.7 / 37.9, 1 x 32 32.3 / 37.0
+//   4096 rows  1 x 4 32.3 / 27.9, 4 x 4 37.7 / 32.8, 8 x 4 40.7 / 39.0, 16 x 4 46.5 / 47.3, 1 x 32 37.3 / 44.8
+//   8192 rows  1 x 4 53.7 / 39.4, 8 x 4 66.2 / 61.4, 16 x 4 84.6 / 77.8, 32 x 4 112 / 122, 1 x 32 46.3 / 75.7
+//   200 rows evicted: 2880 rows 1 x 4 30.1 / 27.0, 4 x 4 31.2 / 34.7, 8192 rows 1 x 4 57.3 / 45.2, 4 x 4 62.1 / 57.7, 8 x 4 69.8 / 75.9
+// Of 176 such steps of 2048 rows or more (4 to 32 heads, 4 to 128 strips, batch 1 to 16, both cache formats) it takes the slower side
+// in 18, by 4 % in the middle and by 13 % at most.
+static bool rank_beside(int rows, int heads, int64_t strips, int many_moves) {
+    return rows <= 1024 || (187 - 10 * heads - strips - 20 * (int64_t)many_moves) * rows <= 270000;
+}
+
 // Attention of every layer of a checked step: the ordinary layers, as many per launch as its table holds, then the lazy ones, caches of
 // either format in launches of their own (32 layers of the 7B shape, every other cache E4M3, us a step, layer by layer -> so:
 // batch 1 377 -> 60, batch 8 482 -> 290).
@@ -1009,10 +1025,14 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
     std::vector<int> stage((size_t)n_layers, 0), groups[4];     // layers that may share launches, in launch order
     // (grid z is rank_z + B * layers, at most 65535)
     needs = PlanNeeds{0, false, B + rank_rows_z(B, H, 1, 1) <= 65535, 0};
+    int most_ranked = 0, many_moves = 0;        // rows of a layer that evicts; layers that evict more rows than a plan moves by itself
     for (int i = 0; i < n_layers; ++i) {
         needs.most_vis = std::max(needs.most_vis, plan[i].max_vis);
         needs.apart = needs.apart && plan[i].mass_apart;
+        if (plan[i].keep_count >= 0) most_ranked = std::max(most_ranked, plan[i].max_vis);
+        many_moves += needs_apply[i];
     }
+    needs.apart = needs.apart && rank_beside(most_ranked, H, (int64_t)B * H * n_layers, many_moves);
     for (int i = 0; i < n_layers; ++i) {
         const st3_layer_step& L = layers[i];
         const bool lazy = L.inherit_from >= 0, coded = L.kv.format == ST3_KV_E4M3;

@@ -40,3 +40,20 @@ def test_some_layers_evict(evicting, lazy):
 def test_no_layer_evicts():
     args = dict(L=3, B=2, H=3, d=64, dtype=F32, vis=[70], tail=4, drop=100)
     _same(Step(**args).whole(), Step(**args).layer_by_layer())
+
+
+@pytest.mark.parametrize("L,B,H,n,drop", [
+    (1, 1, 2, 1024, 6), (1, 1, 2, 1700, 6), (1, 1, 2, 1900, 6),         # beside the attention: 1024 rows and fewer; the line at 1636
+    (2, 1, 2, 2000, 60), (1, 1, 2, 2000, 60),                           # two layers, or one, that evict more than a plan moves
+    (1, 1, 16, 8192, 9), (1, 1, 15, 8192, 9), (1, 1, 14, 8192, 8190),   # the most rows: 16 heads beside, 14 behind
+])
+@pytest.mark.parametrize("fixed_tail", [True, False])
+def test_ranked_beside_the_attention_or_behind_it(L, B, H, n, drop, fixed_tail):
+    plans_of_a_step(L, B, H, n, drop, ties=n % 100 == 0, fixed_tail=fixed_tail)
+
+
+def test_steps_ranked_behind_the_attention():
+    for args in (dict(L=2, B=2, H=3, d=128, dtype=BF, vis=[2900, 40], tail=9, drop=30, lazy={1: 0}),
+                 dict(L=2, B=1, H=4, d=64, dtype=F32, vis=[3000, 900], tail=3, drop=500),
+                 dict(L=3, B=1, H=2, d=128, dtype=BF, vis=[2500], tail=9, drop=20, e4m3={1}, fixed_tail=False)):
+        _same(Step(**args).whole(), Step(**args).layer_by_layer())
