@@ -115,7 +115,8 @@ typedef struct {
  * the value most sequences have in vis_len[b] / tail_start[b] right now.  The decode attention
  * addresses its first loads with them while the device values are still on their way; a sequence
  * whose values differ has those loads repeated, so a wrong guess costs time and never changes a
- * result.  Ignored when tail_start is NULL. */
+ * result.  Ignored when tail_start is NULL - but for one thing: a whole-step call takes vis_len_hint >= max_vis_len in all layers
+ * that have visual rows as word that most sequences are as long as the bounds, and cuts strips accordingly. */
 typedef struct {
     int32_t  sys_len;
     int32_t  max_vis_len;

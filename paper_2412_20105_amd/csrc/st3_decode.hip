@@ -1013,13 +1013,16 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
     const int B = shape->batch, H = shape->heads, D = shape->head_dim;
     common = StepCommon{B, H, D, (int16_t)mode, (int16_t)elem_bytes(shape->dtype), scale_log2(shape), 0, 0, 0, 0};
     int64_t rows[2] = {0, 0};           // of the ordinary and of the lazy layers
+    int as_long = 0, shorter = 0;       // layers in which most sequences hold as many rows as the bound says, by the hint, or may not
     for (int i = 0; i < n_layers; ++i) {
         const st3_layer_step& L = layers[i];
         const int64_t most32 = 0x7fffffff;
         if (L.kv.stride_t > most32 || L.col_stride < 0 || L.col_stride > most32 || L.mass_stride < 0 || L.mass_stride > most32)
             return ST3_ERR_UNSUPPORTED;
         rows[L.inherit_from >= 0] += L.seg.max_kv_len + 1;
+        if (L.seg.max_vis_len > 0) (L.seg.vis_len_hint >= L.seg.max_vis_len ? as_long : shorter) += 1;
     }
+    const bool alike = B == 1 || (as_long > 0 && shorter == 0);
     if (B > 65535) return ST3_ERR_UNSUPPORTED;
     std::vector<char> moves_here((size_t)n_layers, 0);
     std::vector<int> stage((size_t)n_layers, 0), groups[4];     // layers that may share launches, in launch order
@@ -1048,7 +1051,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
         s.col_stride = (int32_t)L.col_stride; s.mass_stride = (int32_t)L.mass_stride;
         s.sys_len = L.seg.sys_len; s.max_vis = L.seg.max_vis_len; s.max_kv = L.seg.max_kv_len;
         s.keep_count = plan[i].keep_count; s.capacity = L.kv.capacity;
-        int nsplit = step_nsplit(B, H, len, rows[lazy]);
+        int nsplit = step_nsplit(B, H, len, rows[lazy], alike);
         if (nsplit > wl.nsplit_cap) nsplit = wl.nsplit_cap;
         s.chunk = decode_chunk(len, nsplit);
         nsplit = (len + s.chunk - 1) / s.chunk;
