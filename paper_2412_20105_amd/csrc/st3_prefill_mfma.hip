@@ -652,12 +652,15 @@ int key_groups(int D, int n, int64_t strips) {
 }
 
 // Strips of a dispatch lane whose tiles are dealt together at the end of a launch: as many as keep the K and V of an XCD's four
-// lanes within about twice its L2 (4 MB), but two to four.  us a call at 1 / 2 / 4 / 8 strips, D = 128: 256 x 675 74.2 / 68.7 / 62.7 /
+// lanes within about twice its L2 (4 MB), but two to four, or one where one strip of each is more than that.  us a call at 1 / 2 / 4 / 8 strips, D = 128: 256 x 675 74.2 / 68.7 / 62.7 /
 // 70.2, 320 x 739 97.8 / 94.6 / 88.6 / 88.5, 1280 x 739 371.5 / 371.8 / 368.3 / 367.6, but 140 x 1500 (the first with its left-over
-// strips last) 151.6 / 127.4 / 131.3 / 134.3, 256 x 3136 907 / 907 / 917 / 1049.
+// strips last) 151.6 / 127.4 / 131.3 / 134.3, 256 x 3136 907 / 907 / 917 / 1049.  One / two strips, long prompts: 64 x 4096 410 / 378, 128 x
+// 4096 771 / 767, 96 x 5120 853 / 892, 128 x 5120 1160 / 1179, 64 x 6144 834 / 839, 96 x 8192 2162 / 2217, 64 x 12288 3209 / 3393, 64 x 16384
+// 5719 / 6134 (left-over strips come first either way: 40 x 8192 1103 -> 927).
 int spread_strips(int D, int n, int64_t strips) {
     const int64_t bytes = (int64_t)n * D * 16;          // of one strip of each of the four lanes
-    return (int)std::min<int64_t>(strips / kLanes, std::max<int64_t>(2, std::min<int64_t>(4, ((int64_t)8 << 20) / bytes)));
+    const int64_t fit = ((int64_t)8 << 20) / bytes;
+    return (int)std::min<int64_t>(strips / kLanes, fit < 1 ? 1 : std::max<int64_t>(2, std::min<int64_t>(4, fit)));
 }
 
 }  // namespace

@@ -31,3 +31,19 @@ def test_every_tile_once(B, H, n, D):
         assert bool(((out[b].float() - want).abs() <= want.abs() / 256 + 2e-4).all()), b
         m = p[:, -1, 10:n - 10].mean(dim=0)
         assert bool(((mass[b] - m).abs() <= 1e-4 * m + 1e-9).all()), b
+
+
+# prompts around the length from which a strip's tiles come one after the other: 4096 rows of 128, 8192 of 64; strips left over or not
+@pytest.mark.parametrize("B,H,n,D", [(1, 33, 4096, 128), (1, 33, 4097, 128), (2, 32, 4200, 128), (3, 32, 8192, 64), (3, 33, 8193, 64)])
+def test_order_of_long_prompts(B, H, n, D):
+    g = torch.Generator(device=DEV).manual_seed(n)
+    q, k, v = [torch.randn((B, H, n, D), generator=g, device=DEV).to(torch.bfloat16) for _ in range(3)]
+    out = torch.full_like(q, float("nan"))
+    st3.st3_prefill_attention(st3.make_shape(B, H, D, st3.ST3_BF16), q, k, v, n, 0, 0, 1, out, None, None)
+    assert not bool(out.isnan().any())          # every row has been written
+    rows = torch.tensor(sorted({0, n - 1, *range(37, n, 128), *range(127, n, 128)}), device=DEV)    # two of every tile
+    causal = torch.arange(n, device=DEV)[None] <= rows[:, None]
+    for b in range(B):
+        p = torch.matmul(q[b][:, rows].float(), k[b].float().transpose(1, 2).contiguous()) / math.sqrt(D)
+        want = torch.matmul(torch.softmax(p.masked_fill_(~causal, float("-inf")), dim=-1), v[b].float())
+        assert bool(((out[b][:, rows].float() - want).abs() <= want.abs() / 256 + 2e-4).all()), b      # (as above)
