@@ -307,6 +307,11 @@ __device__ __forceinline__ void rank_workgroup(const StepCommon& c, const StepLa
     __shared__ SelectShared sm;
     evict_rank_early<kDecodeThreads>(plan_from_entry(c, e), b, sm);
 }
+// The first workgroup of a layer leaves the layer's entry, as it stands in the table, behind the layer's decode workspace.
+__device__ __forceinline__ void leave_entry(const StepTable& t, const StepLayer& e, const DecodeWs& wl, const StepWork& w, int words) {
+    if (!t.c.leave || w.split != 0 || w.h != 0 || w.b != 0 || (int)threadIdx.x >= words) return;
+    reinterpret_cast<uint32_t*>(e.ws + wl.total)[threadIdx.x] = t.w[w.li * words + threadIdx.x];
+}
 // z of the grid that ranking takes: a workgroup for each (layer, sequence) of the launch.
 static int rank_rows_z(int B, int H, int chunks, int layers) { return (int)(((int64_t)B * layers + (int64_t)H * chunks - 1) / ((int64_t)H * chunks)); }
 // Layers of a launch that may rank: rank_z + B * layers is at most 65535 however many chunks there are.
@@ -331,6 +336,7 @@ void decode_attend_layers_kernel(StepTable t) {
     if (w.ranks) return rank_workgroup(c, e, w.b);
     if (w.split >= e.nsplit) return;
     const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
+    leave_entry(t, e, wl, w, words);
     const bool want = (e.flags & kStepWantMass) != 0, all = (e.flags & kStepKeepAll) != 0;
     DecodeArgs a;
     a.q = e.q; a.k = e.k; a.v = e.v;
@@ -514,6 +520,7 @@ __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_
     if (w.ranks) return rank_workgroup(c, e, w.b);
     if (w.split >= e.nsplit) return;
     const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
+    leave_entry(t, e, wl, w, words);
     const DecodeWs sl = decode_ws_sized(c.B, c.H, D, e.hint_base, e.src_nsplit_cap);
     const char* sws = reinterpret_cast<const char*>(e.q);
     InheritArgs a;
@@ -1011,7 +1018,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
                                const char* has_heirs, const EvictArgs* plan, char* needs_apply, StepCommon& common, StepLayer* e,
                                PlanNeeds& needs, hipStream_t st) {
     const int B = shape->batch, H = shape->heads, D = shape->head_dim;
-    common = StepCommon{B, H, D, (int16_t)mode, (int16_t)elem_bytes(shape->dtype), scale_log2(shape), 0, 0, 0, 0};
+    common = StepCommon{B, H, D, (int16_t)mode, (int16_t)elem_bytes(shape->dtype), scale_log2(shape), 0, 0, 0, 0, 0};
     int64_t rows[2] = {0, 0};           // of the ordinary and of the lazy layers
     int as_long = 0, shorter = 0;       // layers in which most sequences hold as many rows as the bound says, by the hint, or may not
     for (int i = 0; i < n_layers; ++i) {
@@ -1088,6 +1095,11 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
         if (!step_layer_fits(s, eb)) common.wide = 1;
         if (!step_layer_fits(s, eb, true)) return ST3_ERR_UNSUPPORTED;
         groups[2 * lazy + coded].push_back(i);
+    }
+    if (!needs.apart && n_layers > entries_per_table(kPlanWords, common.wide)) {
+        common.leave = 1;                               // (not where a workspace ends with what the decode calls need)
+        for (int i = 0; i < n_layers; ++i)
+            if (layers[i].workspace_bytes < decode_ws(B, H, D, layers[i].kv.capacity).total + kLeftBytes) common.leave = 0;
     }
     for (int i = 0; i < n_layers; ++i)                  // (from here on nothing is refused)
         if (moves_here[(size_t)i]) needs_apply[i] = 0;

@@ -451,10 +451,12 @@ inline __host__ __device__ int finish_merge_heads(int D) { return D == 64 ? 4 : 
 
 // grid (B, layers, 1 + merge workgroups): z = 0 runs the plan of (sequence x, layer y); z >= 1 merges the chunk partials
 // of that layer's attention output for kMergeHeads heads (only launched when some layer left partials to merge).
-template <int NT>
+// LEFT: from the entries that the attention has left in the layers' workspaces.
+template <int NT, bool LEFT>
 __global__ __launch_bounds__(NT) void evict_plan_table_kernel(StepTable t) {
     __shared__ PlanShared sm;
-    const StepLayer e = unpack_plan<true>(t.w + blockIdx.y * (kPlanWords + (t.c.wide ? kWideWords : 0)), t.c.elem_bytes, t.c.wide != 0);
+    const StepLayer e = LEFT ? unpack_left(t.w + blockIdx.y * kLeftWords, t.c.elem_bytes, t.c.wide != 0)
+                             : unpack_plan<true>(t.w + blockIdx.y * (kPlanWords + (t.c.wide ? kWideWords : 0)), t.c.elem_bytes, t.c.wide != 0);
     if (blockIdx.z == 0) {
         EvictArgs a = plan_from_entry(t.c, e);
         a.mass_apart = 0;
@@ -490,8 +492,8 @@ __global__ __launch_bounds__(256) void step_finish_kernel(StepTable t, int move_
 // 13B batch 8 with fast annealing 533 / 507 / 504 / 503, batch 32 2403 / 2408 / 2402 / 2403, high resolution batch 8 630 / 628 / 628 / 627.
 constexpr int kFinishMoveWgs = 2048;
 void launch_evict_plan_table(const StepCommon& c, const StepLayer* entry, int n, const PlanNeeds& needs, hipStream_t st) {
-    const int words = needs.apart ? kFinishWords : kPlanWords, stride = words + (c.wide ? kWideWords : 0);
-    const int per = entries_per_table(words, c.wide);
+    const int words = needs.apart ? kFinishWords : kPlanWords, stride = c.leave ? kLeftWords : words + (c.wide ? kWideWords : 0);
+    const int per = kStepTableWords / stride;
     const int launches = (n + per - 1) / per;
     for (int g = 0, i0 = 0; g < launches; ++g) {
         const int cnt = (n - i0 + launches - g - 1) / (launches - g);       // as equal as can be
@@ -499,7 +501,8 @@ void launch_evict_plan_table(const StepCommon& c, const StepLayer* entry, int n,
         t.c = c; t.c.layers = cnt;
         for (int i = 0; i < cnt; ++i) {
             const StepLayer& e = entry[i0 + i];
-            pack_plan(t.w + i * stride, e, !needs.apart, (e.flags & kStepE4M3) ? 1 : c.elem_bytes, c.wide != 0);
+            if (c.leave) pack_left(t.w + i * stride, e, e.ws + decode_ws(c.B, c.H, c.D, e.capacity).total);
+            else pack_plan(t.w + i * stride, e, !needs.apart, (e.flags & kStepE4M3) ? 1 : c.elem_bytes, c.wide != 0);
         }
         i0 += cnt;
         const int merge_heads = needs.apart ? finish_merge_heads(c.D) : kMergeHeads;
@@ -515,7 +518,8 @@ void launch_evict_plan_table(const StepCommon& c, const StepLayer* entry, int n,
             const dim3 grid(c.B, cnt, 1 + merge_wgs);
             with_threads(plan_threads(plans, needs.most_vis, c.H), [&](auto nt) {
                 constexpr int NT = decltype(nt)::value;
-                evict_plan_table_kernel<NT><<<grid, NT, plan_lds(needs.most_vis, NT), st>>>(t);
+                if (c.leave) evict_plan_table_kernel<NT, true><<<grid, NT, plan_lds(needs.most_vis, NT), st>>>(t);
+                else evict_plan_table_kernel<NT, false><<<grid, NT, plan_lds(needs.most_vis, NT), st>>>(t);
             });
         }
     }

@@ -54,6 +54,15 @@ static int check(int eb, bool wide) {
         SAME(max_kv); SAME(keep_count); SAME(chunk); SAME(hint_base); SAME(hint_gap); SAME(capacity); SAME(nsplit); SAME(nsplit_cap);
         SAME(src_nsplit_cap); SAME(flags);
         if (eb == 1) { SAME(k_scale); SAME(v_scale); }
+        uint32_t lw[kLeftWords + 1];
+        lw[kLeftWords] = 0x55u;
+        pack_left(lw, e, w);
+        a = unpack_left(lw, eb == 1 ? 2 : eb, wide);
+        CHECK(lw[kLeftWords] == 0x55u);
+        SAME(k); SAME(v); SAME(out); SAME(kv_len); SAME(vis_len); SAME(tail_start); SAME(ws); SAME(mass); SAME(score_col); SAME(id_col);
+        SAME(stride_b); SAME(stride_h); SAME(stride_t); SAME(mass_stride); SAME(col_stride); SAME(sys_len); SAME(max_vis); SAME(max_kv);
+        SAME(keep_count); SAME(chunk); SAME(capacity); SAME(nsplit); SAME(nsplit_cap); SAME(src_nsplit_cap); SAME(flags);
+        if (e.flags & kStepLazy) { SAME(q); SAME(hint_base); }
         for (int ranking = 0; ranking < 2; ++ranking) {
             std::memset(w, i % 2 ? 0xff : 0, sizeof(w));
             pack_plan(w, e, ranking, eb, wide);
