@@ -309,8 +309,9 @@ __device__ __forceinline__ void rank_workgroup(const StepCommon& c, const StepLa
 }
 // The first workgroup of a layer leaves the layer's entry, as it stands in the table, behind the layer's decode workspace.
 __device__ __forceinline__ void leave_entry(const StepTable& t, const StepLayer& e, const DecodeWs& wl, const StepWork& w, int words) {
-    if (!t.c.leave || w.split != 0 || w.h != 0 || w.b != 0 || (int)threadIdx.x >= words) return;
-    reinterpret_cast<uint32_t*>(e.ws + wl.total)[threadIdx.x] = t.w[w.li * words + threadIdx.x];
+    const int i = threadIdx.x;
+    if (!t.c.leave || w.split != 0 || w.h != 0 || w.b != 0 || i >= words + kWideWords) return;
+    reinterpret_cast<uint32_t*>(e.ws + wl.total)[i] = t.w[i < words ? w.li * words + i : kStepTableWords - kWideWords * (w.li + 1) + i - words];
 }
 // z of the grid that ranking takes: a workgroup for each (layer, sequence) of the launch.
 static int rank_rows_z(int B, int H, int chunks, int layers) { return (int)(((int64_t)B * layers + (int64_t)H * chunks - 1) / ((int64_t)H * chunks)); }
@@ -323,7 +324,9 @@ static int max_layers_ranked(int B, int H) { return (int)((int64_t)65534 * H / (
 // its bytes).  Whole step, us, one launch per layer -> up to 35 layers per launch: 7B batch 1 191 -> 42 (209 MB), 13B batch 8
 // with lazy layers 707 -> 496 (2.9 GB), high resolution batch 8 E4M3 830 -> 618 (3.6 GB), 13B batch 32 2514 -> 2407 (15.4 GB,
 // 6.4 TB/s; a kernel that only reads the same rows takes 2155).
-template <typename T, typename KT, int D, int U, bool NTS>
+// ANY: the table may be wide, and the entries may be left for the plans (a build of its own: these cost 0.1 to 0.4 us a step at the
+// start of every workgroup).
+template <typename T, typename KT, int D, int U, bool NTS, bool ANY>
 __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS)
 __attribute__((amdgpu_waves_per_eu(ST3_DECODE_MIN_BLOCKS, ST3_DECODE_MIN_BLOCKS)))
 void decode_attend_layers_kernel(StepTable t) {
@@ -331,12 +334,12 @@ void decode_attend_layers_kernel(StepTable t) {
     const StepWork w = step_work(c);
     if (w.li >= c.layers) return;
     constexpr bool coded = sizeof(KT) == 1;
-    const int words = (coded ? kAttendWordsE4M3 : kAttendWords) + (c.wide ? kWideWords : 0);
-    const StepLayer e = unpack_attend<coded>(t.w + w.li * words, sizeof(KT), c.wide != 0);
+    constexpr int words = coded ? kAttendWordsE4M3 : kAttendWords;
+    const StepLayer e = unpack_attend<coded>(t.w + w.li * words, sizeof(KT), high_words(t.w, w.li), ANY && c.wide != 0);
     if (w.ranks) return rank_workgroup(c, e, w.b);
     if (w.split >= e.nsplit) return;
     const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
-    leave_entry(t, e, wl, w, words);
+    if (ANY) leave_entry(t, e, wl, w, words);
     const bool want = (e.flags & kStepWantMass) != 0, all = (e.flags & kStepKeepAll) != 0;
     DecodeArgs a;
     a.q = e.q; a.k = e.k; a.v = e.v;
@@ -509,18 +512,18 @@ __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_
 }
 
 // Several lazy layers of a step (their sources have all attended); grid as in decode_attend_layers_kernel.
-template <typename T, typename KT, int D, int U>
+template <typename T, typename KT, int D, int U, bool ANY>
 __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS) void decode_inherit_layers_kernel(StepTable t) {
     const StepCommon& c = t.c;
     const StepWork w = step_work(c);
     if (w.li >= c.layers) return;
     constexpr bool coded = sizeof(KT) == 1;
-    const int words = (coded ? kAttendWordsE4M3 : kAttendWords) + (c.wide ? kWideWords : 0);
-    const StepLayer e = unpack_attend<coded>(t.w + w.li * words, sizeof(KT), c.wide != 0);
+    constexpr int words = coded ? kAttendWordsE4M3 : kAttendWords;
+    const StepLayer e = unpack_attend<coded>(t.w + w.li * words, sizeof(KT), high_words(t.w, w.li), ANY && c.wide != 0);
     if (w.ranks) return rank_workgroup(c, e, w.b);
     if (w.split >= e.nsplit) return;
     const DecodeWs wl = decode_ws_sized(c.B, c.H, D, e.capacity, e.nsplit_cap);
-    leave_entry(t, e, wl, w, words);
+    if (ANY) leave_entry(t, e, wl, w, words);
     const DecodeWs sl = decode_ws_sized(c.B, c.H, D, e.hint_base, e.src_nsplit_cap);
     const char* sws = reinterpret_cast<const char*>(e.q);
     InheritArgs a;
@@ -742,6 +745,9 @@ int best_tile(int64_t items, std::integer_sequence<int, Us...>) {
 template <typename KT>
 using AttendTiles = std::conditional_t<sizeof(KT) == 1, std::integer_sequence<int, 3, 4, 1>, std::integer_sequence<int, 4, 6, 8, 1>>;
 
+template <int U0, int... Us>
+constexpr int first_tile(std::integer_sequence<int, U0, Us...>) { return U0; }
+
 template <typename T, typename KT, int D>
 void launch_attend(const DecodeArgs& da, int B, hipStream_t st) {
     const dim3 grid(da.nsplit, da.H, B);
@@ -759,16 +765,24 @@ template <typename T, typename KT, int D>
 void launch_attend_layers(const StepTable& t, int lds_words, bool stream, hipStream_t st) {
     const dim3 grid(t.c.H, t.c.chunks, t.c.rank_z + t.c.B * t.c.layers);
     const size_t lds = (size_t)lds_words * sizeof(float);
+    if (t.c.wide || t.c.leave) {
+        constexpr int U = first_tile(AttendTiles<KT>{});
+        if (stream) launch_timed(decode_attend_layers_kernel<T, KT, D, U, true, true>, grid, lds, st, t.c.layers, t);
+        else launch_timed(decode_attend_layers_kernel<T, KT, D, U, false, true>, grid, lds, st, t.c.layers, t);
+        return;
+    }
     with_tile(AttendTiles<KT>{}, 0, [&](auto u) {
-        if (stream) launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, true>, grid, lds, st, t.c.layers, t);
-        else launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, false>, grid, lds, st, t.c.layers, t);
+        if (stream) launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, true, false>, grid, lds, st, t.c.layers, t);
+        else launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, false, false>, grid, lds, st, t.c.layers, t);
     });
 }
 
 template <typename T, typename KT, int D>
 void launch_inherit_layers(const StepTable& t, int lds_words, hipStream_t st) {
     const dim3 grid(t.c.H, t.c.chunks, t.c.rank_z + t.c.B * t.c.layers);
-    decode_inherit_layers_kernel<T, KT, D, 4><<<grid, kDecodeThreads, (size_t)lds_words * sizeof(uint32_t), st>>>(t);
+    const size_t lds = (size_t)lds_words * sizeof(uint32_t);
+    if (t.c.wide || t.c.leave) decode_inherit_layers_kernel<T, KT, D, 4, true><<<grid, kDecodeThreads, lds, st>>>(t);
+    else decode_inherit_layers_kernel<T, KT, D, 4, false><<<grid, kDecodeThreads, lds, st>>>(t);
 }
 
 // The V-only kernel of lazy layers: 4 loads per lane and tile (4 KB per wave) were the fastest or
@@ -1107,7 +1121,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
         const int n = (int)members.size();
         if (n == 0) continue;
         const bool coded = layers[members[0]].kv.format == ST3_KV_E4M3;
-        const int words = coded ? kAttendWordsE4M3 : kAttendWords, stride = words + (common.wide ? kWideWords : 0);
+        const int words = coded ? kAttendWordsE4M3 : kAttendWords;
         const int per = std::min(entries_per_table(words, common.wide), needs.apart ? max_layers_ranked(B, H) : 65535 / B);
         const int launches = (n + per - 1) / per;
         for (int g = 0, i0 = 0; g < launches; ++g) {
@@ -1121,7 +1135,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
             int most = 1, lds_words = 0, ranked = 0;    // dynamic LDS: the logits a workgroup collects, or the keys it ranks
             for (int j = 0; j < cnt; ++j) {
                 const int i = members[(size_t)(i0 + j)];
-                pack_attend(t.w + j * stride, e[i], coded, kv_elem_bytes(shape, kv), common.wide != 0);
+                pack_attend(t.w + j * words, e[i], coded, kv_elem_bytes(shape, kv), common.wide ? high_words(t.w, j) : nullptr);
                 most = std::max(most, (int)e[i].nsplit);
                 lds_words = std::max(lds_words, stage[(size_t)i]);
                 if (e[i].flags & kStepKeepAll) written += (int64_t)B * H * e[i].max_kv * sizeof(float);

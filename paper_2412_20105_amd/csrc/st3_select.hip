@@ -451,12 +451,14 @@ inline __host__ __device__ int finish_merge_heads(int D) { return D == 64 ? 4 : 
 
 // grid (B, layers, 1 + merge workgroups): z = 0 runs the plan of (sequence x, layer y); z >= 1 merges the chunk partials
 // of that layer's attention output for kMergeHeads heads (only launched when some layer left partials to merge).
-// LEFT: from the entries that the attention has left in the layers' workspaces.
-template <int NT, bool LEFT>
+// FORM: entries of the table, wide entries, or the entries that the attention has left in the layers' workspaces.
+enum { kFormTable, kFormWide, kFormLeft };
+template <int NT, int FORM>
 __global__ __launch_bounds__(NT) void evict_plan_table_kernel(StepTable t) {
     __shared__ PlanShared sm;
-    const StepLayer e = LEFT ? unpack_left(t.w + blockIdx.y * kLeftWords, t.c.elem_bytes, t.c.wide != 0)
-                             : unpack_plan<true>(t.w + blockIdx.y * (kPlanWords + (t.c.wide ? kWideWords : 0)), t.c.elem_bytes, t.c.wide != 0);
+    const StepLayer e = FORM == kFormLeft
+        ? unpack_left(t.w + blockIdx.y * kLeftWords, t.c.elem_bytes, t.c.wide != 0)
+        : unpack_plan<true>(t.w + blockIdx.y * kPlanWords, t.c.elem_bytes, high_words(t.w, blockIdx.y), FORM == kFormWide);
     if (blockIdx.z == 0) {
         EvictArgs a = plan_from_entry(t.c, e);
         a.mass_apart = 0;
@@ -470,9 +472,10 @@ __global__ __launch_bounds__(NT) void evict_plan_table_kernel(StepTable t) {
 // What is left of the plans when the rows have been ranked beside the attention.  grid (B, layers, moves + masses + merges), 256
 // threads: workgroups z < move_wgs move rows (the first one advances the lengths too), the next mass_wgs finish kMassKeys
 // entries of the mass each, the rest merge the chunk partials of finish_merge_heads heads each.
+template <bool WIDE>
 __global__ __launch_bounds__(256) void step_finish_kernel(StepTable t, int move_wgs, int mass_wgs) {
     __shared__ MassShared<256> sm;
-    const StepLayer e = unpack_plan<false>(t.w + blockIdx.y * (kFinishWords + (t.c.wide ? kWideWords : 0)), t.c.elem_bytes, t.c.wide != 0);
+    const StepLayer e = unpack_plan<false>(t.w + blockIdx.y * kFinishWords, t.c.elem_bytes, high_words(t.w, blockIdx.y), WIDE);
     const int z = blockIdx.z, b = blockIdx.x;
     if (z < move_wgs + mass_wgs) {
         const EvictArgs a = plan_from_entry(t.c, e);
@@ -492,8 +495,7 @@ __global__ __launch_bounds__(256) void step_finish_kernel(StepTable t, int move_
 // 13B batch 8 with fast annealing 533 / 507 / 504 / 503, batch 32 2403 / 2408 / 2402 / 2403, high resolution batch 8 630 / 628 / 628 / 627.
 constexpr int kFinishMoveWgs = 2048;
 void launch_evict_plan_table(const StepCommon& c, const StepLayer* entry, int n, const PlanNeeds& needs, hipStream_t st) {
-    const int words = needs.apart ? kFinishWords : kPlanWords, stride = c.leave ? kLeftWords : words + (c.wide ? kWideWords : 0);
-    const int per = kStepTableWords / stride;
+    const int words = c.leave ? kLeftWords : needs.apart ? kFinishWords : kPlanWords, per = entries_per_table(words, c.wide && !c.leave);
     const int launches = (n + per - 1) / per;
     for (int g = 0, i0 = 0; g < launches; ++g) {
         const int cnt = (n - i0 + launches - g - 1) / (launches - g);       // as equal as can be
@@ -501,8 +503,8 @@ void launch_evict_plan_table(const StepCommon& c, const StepLayer* entry, int n,
         t.c = c; t.c.layers = cnt;
         for (int i = 0; i < cnt; ++i) {
             const StepLayer& e = entry[i0 + i];
-            if (c.leave) pack_left(t.w + i * stride, e, e.ws + decode_ws(c.B, c.H, c.D, e.capacity).total);
-            else pack_plan(t.w + i * stride, e, !needs.apart, (e.flags & kStepE4M3) ? 1 : c.elem_bytes, c.wide != 0);
+            if (c.leave) pack_left(t.w + i * words, e, e.ws + decode_ws(c.B, c.H, c.D, e.capacity).total);
+            else pack_plan(t.w + i * words, e, !needs.apart, (e.flags & kStepE4M3) ? 1 : c.elem_bytes, c.wide ? high_words(t.w, i) : nullptr);
         }
         i0 += cnt;
         const int merge_heads = needs.apart ? finish_merge_heads(c.D) : kMergeHeads;
@@ -513,13 +515,17 @@ void launch_evict_plan_table(const StepCommon& c, const StepLayer* entry, int n,
             const int64_t rounds = (needs.moves + 8 * 256 - 1) / (8 * 256), strips = 2 * c.H * (c.D * c.elem_bytes / 16) / 256;
             const int move_wgs = (int)std::max<int64_t>(1, std::min<int64_t>(std::max(rounds, strips), kFinishMoveWgs / plans));
             const int mass_wgs = (needs.most_vis + kMassKeys - 1) / kMassKeys;
-            step_finish_kernel<<<dim3(c.B, cnt, move_wgs + mass_wgs + merge_wgs), 256, 0, st>>>(t, move_wgs, mass_wgs);
+            const dim3 grid(c.B, cnt, move_wgs + mass_wgs + merge_wgs);
+            if (c.wide) step_finish_kernel<true><<<grid, 256, 0, st>>>(t, move_wgs, mass_wgs);
+            else step_finish_kernel<false><<<grid, 256, 0, st>>>(t, move_wgs, mass_wgs);
         } else {
             const dim3 grid(c.B, cnt, 1 + merge_wgs);
             with_threads(plan_threads(plans, needs.most_vis, c.H), [&](auto nt) {
                 constexpr int NT = decltype(nt)::value;
-                if (c.leave) evict_plan_table_kernel<NT, true><<<grid, NT, plan_lds(needs.most_vis, NT), st>>>(t);
-                else evict_plan_table_kernel<NT, false><<<grid, NT, plan_lds(needs.most_vis, NT), st>>>(t);
+                const size_t lds = plan_lds(needs.most_vis, NT);
+                if (c.leave) evict_plan_table_kernel<NT, kFormLeft><<<grid, NT, lds, st>>>(t);
+                else if (c.wide) evict_plan_table_kernel<NT, kFormWide><<<grid, NT, lds, st>>>(t);
+                else evict_plan_table_kernel<NT, kFormTable><<<grid, NT, lds, st>>>(t);
             });
         }
     }

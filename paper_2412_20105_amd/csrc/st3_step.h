@@ -7,9 +7,10 @@
 // left in the workspaces for the launch behind it -> so: 7B batch 1 55 -> 45, 13B batch 8 with lazy layers 504 -> 496, high resolution batch
 // 8 E4M3 629 -> 624; a generation of 16 steps, 7B batch 4, 4824 -> 4758.
 //
-// A table is wide where some layer needs it (token-major caches, whose rows can lie megabytes apart): its entries have three words
-// more, with the upper halves of what the others hold in 16 or 32 bits.  Rows of 2 MB, us a step, layer by layer -> wide: 32 layers of
-// the 7B shape, batch 4 285 -> 90, 40 layers of 40 heads, batch 2 341 -> 83.
+// A table is wide where some layer needs it (token-major caches, whose rows can lie megabytes apart): three words more for each entry,
+// from the table's end, have the upper halves of what the entry holds in 16 or 32 bits.  (Kernels of their own read such tables: a few
+// scalar loads and a flag at the start of every workgroup cost the other steps 0.1 to 0.4 us.)  Rows of 2 MB, us a step, layer by
+// layer -> wide: 32 layers of the 7B shape, batch 4 285 -> 93, 40 layers of 40 heads, batch 2 341 -> 85.
 #pragma once
 
 #include <stdint.h>
@@ -78,6 +79,8 @@ constexpr int kStepTableWords = 992;
 constexpr int kLeftPtrs = 2, kLeftWords = ptr_words(kLeftPtrs) + 1, kLeftBytes = 256;
 static_assert((kAttendWordsE4M3 + kWideWords) * 4 <= kLeftBytes, "what is left of an entry");
 inline int entries_per_table(int words, int wide) { return kStepTableWords / (words + (wide ? kWideWords : 0)); }
+template <typename W>
+__host__ __device__ inline W* high_words(W* table, int i) { return table + kStepTableWords - kWideWords * (i + 1); }
 
 struct StepTable {
     StepCommon c;
@@ -114,7 +117,7 @@ inline bool step_layer_fits(const StepLayer& e, int eb, bool wide = false) {
 }
 
 inline uint32_t pair16(int lo, int hi) { return ((uint32_t)lo & 0xffffu) | (uint32_t)hi << 16; }
-// The ten words that both tables have, but for two of them (a, b); high: where a wide entry's last words go (null: not wide).
+// The ten words that both tables have, but for two of them (a, b); high: where a wide entry's upper halves go (null: not wide).
 inline void pack_numbers(uint32_t* w, const StepLayer& e, int eb, uint32_t a, uint32_t b, uint32_t* high) {
     const int64_t unit = 16 / eb, sb = e.stride_b / unit, sh = e.stride_h / unit, st = e.stride_t / unit;
     if (high != nullptr) {
@@ -130,32 +133,27 @@ inline void pack_numbers(uint32_t* w, const StepLayer& e, int eb, uint32_t a, ui
     w[7] = pair16(e.chunk / 32, (e.flags & kStepLazy) || e.hint_base == 0x7fffffff ? 0xffff : e.hint_base - e.sys_len);
     w[8] = a; w[9] = b;
 }
-__host__ __device__ inline void unpack_numbers(const uint32_t* w, StepLayer& e, int eb, const uint32_t* high) {
+__host__ __device__ inline void unpack_numbers(const uint32_t* w, StepLayer& e, int eb, const uint32_t* high, bool wide) {
     const int64_t unit = 16 / eb;
-    e.stride_b = (int64_t)w[0] * unit; e.stride_h = (int64_t)w[1] * unit;
-    e.stride_t = (int32_t)((w[2] & 0xffffu) * (uint32_t)unit); e.sys_len = (int32_t)(w[2] >> 16);
+    const uint32_t mask = wide ? 0xffffffffu : 0u, h0 = high[0] & mask, h1 = high[1] & mask, h2 = high[2] & mask;
+    e.stride_b = (int64_t)((uint64_t)(h1 & 0xffffu) << 32 | w[0]) * unit; e.stride_h = (int64_t)((uint64_t)(h1 >> 16) << 32 | w[1]) * unit;
+    e.stride_t = (int32_t)((h0 << 16 | (w[2] & 0xffffu)) * (uint32_t)unit); e.sys_len = (int32_t)((h0 & 0xffff0000u) | w[2] >> 16);
     e.max_vis = (int32_t)(w[3] & 0xffffu); e.keep_count = (int32_t)(w[3] >> 16) - 1;
     e.max_kv = (int32_t)w[4]; e.capacity = (int32_t)w[5];
     e.nsplit = (uint8_t)w[6]; e.nsplit_cap = (uint8_t)(w[6] >> 8); e.src_nsplit_cap = (uint8_t)(w[6] >> 16); e.flags = (uint8_t)(w[6] >> 24);
-    e.chunk = (int32_t)(w[7] & 0xffffu) * 32;
-    if (high != nullptr) {
-        e.stride_t += (int32_t)((high[0] << 16) * (uint32_t)unit); e.sys_len += (int32_t)(high[0] & 0xffff0000u);
-        e.stride_b += (int64_t)((uint64_t)(high[1] & 0xffffu) << 32) * unit; e.stride_h += (int64_t)((uint64_t)(high[1] >> 16) << 32) * unit;
-        e.chunk += (int32_t)(high[2] << 21);
-    }
+    e.chunk = (int32_t)((h2 << 16 | (w[7] & 0xffffu)) * 32u);
 }
 
 // The attention's entry: everything but the mass's place.
-inline void pack_attend(uint32_t* w, const StepLayer& e, bool coded, int eb, bool wide = false) {
+inline void pack_attend(uint32_t* w, const StepLayer& e, bool coded, int eb, uint32_t* high) {
     const int n = coded ? kAttendPtrsE4M3 : kAttendPtrs;
     const void* ptrs[kAttendPtrsE4M3] = {e.q, e.k, e.v, e.k_new, e.v_new, e.out, e.kv_len, e.vis_len, e.tail_start, e.ws, e.score_col,
                                          e.id_col, e.k_scale, e.v_scale};
     for (int i = 0; i < n; ++i) put_ptr(w, n, i, ptrs[i]);
-    pack_numbers(w + ptr_words(n), e, eb, (uint32_t)e.col_stride, (uint32_t)((e.flags & kStepLazy) ? e.hint_base : e.hint_gap),
-                 wide ? w + (coded ? kAttendWordsE4M3 : kAttendWords) : nullptr);
+    pack_numbers(w + ptr_words(n), e, eb, (uint32_t)e.col_stride, (uint32_t)((e.flags & kStepLazy) ? e.hint_base : e.hint_gap), high);
 }
 template <bool CODED>
-__host__ __device__ inline StepLayer unpack_attend(const uint32_t* w, int eb, bool wide = false) {
+__host__ __device__ inline StepLayer unpack_attend(const uint32_t* w, int eb, const uint32_t* high, bool wide) {
     constexpr int n = CODED ? kAttendPtrsE4M3 : kAttendPtrs;
     StepLayer e{};
     get_ptr(w, n, 0, e.q); get_ptr(w, n, 1, e.k); get_ptr(w, n, 2, e.v); get_ptr(w, n, 3, e.k_new); get_ptr(w, n, 4, e.v_new);
@@ -163,7 +161,7 @@ __host__ __device__ inline StepLayer unpack_attend(const uint32_t* w, int eb, bo
     get_ptr(w, n, 9, e.ws); get_ptr(w, n, 10, e.score_col); get_ptr(w, n, 11, e.id_col);
     if (CODED) { get_ptr(w, n, 12, e.k_scale); get_ptr(w, n, 13, e.v_scale); }
     const uint32_t* num = w + ptr_words(n);
-    unpack_numbers(num, e, eb, wide ? w + (CODED ? kAttendWordsE4M3 : kAttendWords) : nullptr);
+    unpack_numbers(num, e, eb, high, wide);
     e.col_stride = (int32_t)num[8];
     const int nv = (int)(num[7] >> 16);
     if (e.flags & kStepLazy) e.hint_base = (int32_t)num[9];
@@ -172,31 +170,30 @@ __host__ __device__ inline StepLayer unpack_attend(const uint32_t* w, int eb, bo
 }
 
 // The entry of the launch behind the attention; ranking: with the columns.  (q is the source's workspace of a lazy layer, null else.)
-inline void pack_plan(uint32_t* w, const StepLayer& e, bool ranking, int eb, bool wide = false) {
+inline void pack_plan(uint32_t* w, const StepLayer& e, bool ranking, int eb, uint32_t* high) {
     const int n = ranking ? kPlanPtrs : kFinishPtrs;
     const bool lazy = (e.flags & kStepLazy) != 0;
     const void* ptrs[kPlanPtrs] = {lazy ? e.q : nullptr, e.k, e.v, e.out, e.kv_len, e.vis_len, e.tail_start, e.ws, e.mass, e.score_col, e.id_col};
     for (int i = 0; i < n; ++i) put_ptr(w, n, i, ptrs[i]);
     uint32_t* num = w + ptr_words(n);
-    pack_numbers(num, e, eb, (uint32_t)e.mass_stride, lazy ? (uint32_t)e.hint_base : 0u,
-                 wide ? w + (ranking ? kPlanWords : kFinishWords) : nullptr);
+    pack_numbers(num, e, eb, (uint32_t)e.mass_stride, lazy ? (uint32_t)e.hint_base : 0u, high);
     if (ranking) num[10] = (uint32_t)e.col_stride;
 }
 template <bool RANKING>
-__host__ __device__ inline StepLayer unpack_plan(const uint32_t* w, int plain_eb, bool wide = false) {
+__host__ __device__ inline StepLayer unpack_plan(const uint32_t* w, int plain_eb, const uint32_t* high, bool wide) {
     constexpr int n = RANKING ? kPlanPtrs : kFinishPtrs;
     StepLayer e{};
     get_ptr(w, n, 0, e.q); get_ptr(w, n, 1, e.k); get_ptr(w, n, 2, e.v); get_ptr(w, n, 3, e.out); get_ptr(w, n, 4, e.kv_len);
     get_ptr(w, n, 5, e.vis_len); get_ptr(w, n, 6, e.tail_start); get_ptr(w, n, 7, e.ws); get_ptr(w, n, 8, e.mass);
     const uint32_t* num = w + ptr_words(n);
     const bool coded = (num[6] >> 24 & kStepE4M3) != 0;
-    unpack_numbers(num, e, coded ? 1 : plain_eb, wide ? w + (RANKING ? kPlanWords : kFinishWords) : nullptr);
+    unpack_numbers(num, e, coded ? 1 : plain_eb, high, wide);
     e.mass_stride = (int32_t)num[8]; e.hint_base = (int32_t)num[9];
     if (RANKING) { get_ptr(w, n, 9, e.score_col); get_ptr(w, n, 10, e.id_col); e.col_stride = (int32_t)num[10]; }
     return e;
 }
 
-// Where the attention has left a layer's entry (at `left`), and what that lacks; the layer's cache format goes along, since the entry's
+// Where the attention has left a layer's entry (at `left`, its upper halves behind it), and what that lacks; the layer's cache format goes along, since the entry's
 // layout depends on it.
 inline void pack_left(uint32_t* w, const StepLayer& e, const void* left) {
     put_ptr(w, kLeftPtrs, 0, left); put_ptr(w, kLeftPtrs, 1, e.mass);
@@ -206,7 +203,7 @@ __host__ __device__ inline StepLayer unpack_left(const uint32_t* w, int plain_eb
     const uint32_t* left;
     get_ptr(w, kLeftPtrs, 0, left);
     const uint32_t last = w[ptr_words(kLeftPtrs)];
-    StepLayer e = last >> 31 ? unpack_attend<true>(left, 1, wide) : unpack_attend<false>(left, plain_eb, wide);
+    StepLayer e = last >> 31 ? unpack_attend<true>(left, 1, left + kAttendWordsE4M3, wide) : unpack_attend<false>(left, plain_eb, left + kAttendWords, wide);
     get_ptr(w, kLeftPtrs, 1, e.mass);
     e.mass_stride = (int32_t)(last & 0x7fffffffu);
     return e;

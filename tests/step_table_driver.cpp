@@ -42,13 +42,14 @@ static int check(int eb, bool wide) {
     for (int i = 0; i < 20000; ++i) {
         const StepLayer e = random_layer(eb, wide && i % 4 != 0);
         CHECK(step_layer_fits(e, eb, wide));
-        const int more = wide ? kWideWords : 0;
         uint32_t w[64];
         std::memset(w, i % 2 ? 0xff : 0, sizeof(w));        // (a table's words start out as anything)
         const uint32_t guard = w[63];
-        pack_attend(w, e, eb == 1, eb, wide);
-        CHECK(w[(eb == 1 ? kAttendWordsE4M3 : kAttendWords) + more] == guard);
-        StepLayer a = eb == 1 ? unpack_attend<true>(w, eb, wide) : unpack_attend<false>(w, eb, wide);
+        const int words = eb == 1 ? kAttendWordsE4M3 : kAttendWords;
+        uint32_t* high = w + words;                         // (as an entry is left in a workspace)
+        pack_attend(w, e, eb == 1, eb, wide ? high : nullptr);
+        CHECK(w[words + (wide ? kWideWords : 0)] == guard);
+        StepLayer a = eb == 1 ? unpack_attend<true>(w, eb, high, wide) : unpack_attend<false>(w, eb, high, wide);
         SAME(q); SAME(k); SAME(v); SAME(k_new); SAME(v_new); SAME(out); SAME(kv_len); SAME(vis_len); SAME(tail_start); SAME(score_col);
         SAME(id_col); SAME(ws); SAME(stride_b); SAME(stride_h); SAME(stride_t); SAME(col_stride); SAME(sys_len); SAME(max_vis);
         SAME(max_kv); SAME(keep_count); SAME(chunk); SAME(hint_base); SAME(hint_gap); SAME(capacity); SAME(nsplit); SAME(nsplit_cap);
@@ -65,9 +66,10 @@ static int check(int eb, bool wide) {
         if (e.flags & kStepLazy) { SAME(q); SAME(hint_base); }
         for (int ranking = 0; ranking < 2; ++ranking) {
             std::memset(w, i % 2 ? 0xff : 0, sizeof(w));
-            pack_plan(w, e, ranking, eb, wide);
-            CHECK(w[(ranking ? kPlanWords : kFinishWords) + more] == guard);
-            a = ranking ? unpack_plan<true>(w, eb == 1 ? 2 : eb, wide) : unpack_plan<false>(w, eb == 1 ? 2 : eb, wide);
+            uint32_t* high = w + (ranking ? kPlanWords : kFinishWords) + 5;
+            pack_plan(w, e, ranking, eb, wide ? high : nullptr);
+            CHECK(w[ranking ? kPlanWords : kFinishWords] == guard && (wide || high[0] == guard) && high[kWideWords] == guard);
+            a = ranking ? unpack_plan<true>(w, eb == 1 ? 2 : eb, high, wide) : unpack_plan<false>(w, eb == 1 ? 2 : eb, high, wide);
             SAME(k); SAME(v); SAME(out); SAME(kv_len); SAME(vis_len); SAME(tail_start); SAME(ws); SAME(mass); SAME(stride_b);
             SAME(stride_h); SAME(stride_t); SAME(mass_stride); SAME(sys_len); SAME(max_vis); SAME(max_kv); SAME(keep_count); SAME(chunk);
             SAME(capacity); SAME(nsplit); SAME(nsplit_cap); SAME(src_nsplit_cap); SAME(flags);
@@ -97,7 +99,21 @@ static int check(int eb, bool wide) {
     return 0;
 }
 
+// A full table: the last entry ends where the upper halves begin.
+static int check_room() {
+    static uint32_t table[kStepTableWords];
+    for (int words : {kAttendWords, kAttendWordsE4M3, kFinishWords, kPlanWords}) {
+        const int wide = entries_per_table(words, 1), narrow = entries_per_table(words, 0);
+        CHECK(high_words(table, wide - 1) >= table + wide * words && narrow * words <= kStepTableWords);
+        CHECK(high_words(table, narrow - 1) >= table && high_words(table, 0) + kWideWords == table + kStepTableWords);      // (loaded always)
+    }
+    CHECK(entries_per_table(kAttendWords, 0) == 35 && entries_per_table(kAttendWordsE4M3, 0) == 32 && entries_per_table(kFinishWords, 0) == 41 &&
+          entries_per_table(kPlanWords, 0) == 35);
+    return 0;
+}
+
 int main() {
+    if (check_room()) return 1;
     for (int eb : {1, 2, 4})
         if (check(eb, false) || check(eb, true)) return 1;
     std::printf("ok\n");
