@@ -192,8 +192,8 @@ def _many_layers_with_a_group_across_the_fork():
 
 @pytest.mark.parametrize("mode", ["static", "current"])
 def test_many_layers_and_a_heredity_group_in_one_plan_launch(mode):
-    """34 layers, three of them lazy: every layer's plan arguments reach the step's one plan launch through the
-    layer's workspace, where the layer's attend (or inherit) launch has left them."""
+    """34 layers, three of them lazy: the entries of all of them travel to the launch behind the attention in one argument
+    block (41 entries of a finish launch, 35 where the columns take the mass)."""
     w, lazy = _many_layers_with_a_group_across_the_fork()
     _run_and_compare(w, 2, mode=mode, whole_step=True, lazy=lazy)
 

@@ -11,7 +11,7 @@ from test_gpu_step_launches import BF, DEV, F32, MODE, Step, _same
 pytestmark = pytest.mark.gpu
 
 
-def launches(step):
+def launches(step, mode=MODE):
     """How many kernels the whole-step call enqueues (nothing runs: the call is captured and the graph's nodes are counted)."""
     hip = st3.lib()             # (the runtime that the library itself is linked to)
     side = torch.cuda.Stream()
@@ -19,7 +19,7 @@ def launches(step):
     graph, count = C.c_void_p(), C.c_size_t()
     assert hip.hipStreamBeginCapture(C.c_void_p(side.cuda_stream), 2) == 0      # relaxed
     try:
-        st3.st3_decode_step(step.shape, step.arr, step.L, MODE, side)
+        st3.st3_decode_step(step.shape, step.arr, step.L, mode, side)
     finally:
         assert hip.hipStreamEndCapture(C.c_void_p(side.cuda_stream), C.byref(graph)) == 0
     assert hip.hipGraphGetNodes(graph, None, C.byref(count)) == 0
@@ -31,7 +31,7 @@ MIXED = [
     dict(L=8, B=1, H=4, d=128, dtype=BF, vis=[300, 90], tail=9, e4m3={1, 4, 5}),                            # cut strips
     dict(L=6, B=20, H=30, d=64, dtype=BF, vis=[40], tail=5, e4m3={0}),                                      # whole strips
     dict(L=7, B=2, H=5, d=128, dtype=BF, vis=[260], tail=9, e4m3={1, 2, 5}, lazy={1: 0, 2: 0, 5: 4, 6: 4}, fixed_tail=False),
-    dict(L=4, B=2, H=4, d=128, dtype=BF, vis=[300], tail=9, e4m3={0, 3}, drop=80),                          # evictions by a launch of their own
+    dict(L=4, B=2, H=4, d=128, dtype=BF, vis=[300], tail=9, e4m3={0, 3}, drop=80),                          # more moves than a plan's list holds
 ]
 
 
@@ -44,9 +44,33 @@ def test_caches_of_two_formats(args):
     (MIXED[0], 3),              # one attention launch per format, one plan launch
     (MIXED[1], 3),
     (MIXED[2], 4),              # ordinary layers of one format, lazy ones of two
+    (MIXED[3], 3),
 ])
 def test_launches_of_a_step_with_two_formats(args, most):
     assert launches(Step(**args)) <= most
+
+
+@pytest.mark.parametrize("L,e4m3,attention,behind", [
+    (35, False, 1, 1), (36, False, 2, 1), (32, True, 1, 1), (33, True, 2, 1), (41, False, 2, 1), (42, False, 2, 2), (70, False, 2, 2),
+    (71, False, 3, 2), (83, False, 3, 3),
+])
+def test_launches_of_many_layers(L, e4m3, attention, behind):
+    """35 layers to an attention launch (32 with E4M3 caches), 41 to the launch behind it."""
+    assert launches(Step(L=L, B=1, H=1, d=64, dtype=BF, vis=[20], tail=2, e4m3=e4m3)) == attention + behind
+
+
+@pytest.mark.parametrize("mode", [MODE, st3.ST3_STABLE])
+def test_evictions_by_launches_of_their_own(mode):
+    """Many rows of a tail that closes up, or moves whose order matters: a launch for each layer that evicts."""
+    args = dict(L=3, B=2, H=4, d=128, dtype=BF, vis=[300, 20], tail=9, drop=80, fixed_tail=mode != MODE)
+    a, b = Step(**args), Step(**args)
+    st3.st3_decode_step(a.shape, a.arr, a.L, mode)
+    for l in range(b.L):
+        st3.st3_decode_layer_attend(b.shape, b.arr, b.L, l, mode)
+    st3.st3_decode_plans(b.shape, b.arr, b.L, mode)
+    torch.cuda.synchronize()
+    _same(a, b)
+    assert launches(Step(**args), mode) == 2 + 2
 
 
 @pytest.mark.parametrize("field", ["q", "k_new", "v_new", "out"])

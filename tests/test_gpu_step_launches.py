@@ -95,16 +95,23 @@ BF, F32 = torch.bfloat16, torch.float32
 @pytest.mark.parametrize("args", [
     dict(L=1, B=1, H=1, d=64, dtype=F32, vis=[5], tail=0),
     dict(L=2, B=3, H=5, d=64, dtype=BF, vis=[0, 300], tail=1),                  # a layer without visual rows
-    dict(L=21, B=1, H=3, d=128, dtype=BF, vis=[130, 65, 64], tail=33),          # one full launch
-    dict(L=22, B=2, H=2, d=128, dtype=BF, vis=[700, 31, 1], tail=7),            # two launches, strips cut unevenly
-    dict(L=65, B=1, H=2, d=64, dtype=F32, vis=[40, 39], tail=2),                # two plan launches
+    dict(L=21, B=1, H=3, d=128, dtype=BF, vis=[130, 65, 64], tail=33),
+    dict(L=22, B=2, H=2, d=128, dtype=BF, vis=[700, 31, 1], tail=7),            # strips cut unevenly
+    dict(L=65, B=1, H=2, d=64, dtype=F32, vis=[40, 39], tail=2),                # two launches of either kind
     dict(L=9, B=16, H=40, d=128, dtype=F32, vis=[20], tail=3),                  # rows written past the caches (8.8 MB)
     dict(L=24, B=1, H=4, d=128, dtype=BF, vis=[500], tail=40, lazy={5: 4, 6: 4, 7: 4, 23: 22}),     # lazy strips cut too
     dict(L=4, B=2, H=4, d=128, dtype=BF, vis=[260, 90], tail=40, lazy={1: 0}, fixed_tail=False),
     dict(L=5, B=2, H=6, d=128, dtype=BF, vis=[200, 33], tail=9, e4m3=True, lazy={3: 2}),
-    dict(L=3, B=2, H=4, d=128, dtype=BF, vis=[300], tail=9, drop=80),           # evictions that a launch of their own moves
+    dict(L=3, B=2, H=4, d=128, dtype=BF, vis=[300], tail=9, drop=80),           # more moves than a plan's list holds
+    dict(L=3, B=2, H=4, d=128, dtype=BF, vis=[300], tail=9, drop=80, fixed_tail=False),         # evictions by launches of their own
     dict(L=2, B=1, H=2, d=64, dtype=F32, vis=[8190], tail=3000),                # long strips: 59 chunks
-], ids=lambda a: "-".join(f"{k}{v}" for k, v in a.items() if k in ("L", "B", "H", "d", "drop")))
+    dict(L=35, B=1, H=3, d=128, dtype=BF, vis=[130, 65, 64], tail=33),          # one full attention launch, and two
+    dict(L=36, B=1, H=3, d=128, dtype=BF, vis=[130, 65, 64], tail=33),
+    dict(L=32, B=2, H=2, d=64, dtype=BF, vis=[70], tail=3, e4m3=True),          # the same with E4M3 caches
+    dict(L=33, B=2, H=2, d=64, dtype=BF, vis=[70], tail=3, e4m3=True),
+    dict(L=41, B=1, H=2, d=64, dtype=F32, vis=[40], tail=2),                    # one full launch behind the attention, and two
+    dict(L=42, B=1, H=2, d=64, dtype=F32, vis=[40], tail=2),
+], ids=lambda a: "-".join(f"{k}{v}" for k, v in a.items() if k in ("L", "B", "H", "d", "drop", "e4m3")))
 def test_whole_step_is_the_layers_one_by_one(args):
     _same(Step(**args).whole(), Step(**args).layer_by_layer())
 
