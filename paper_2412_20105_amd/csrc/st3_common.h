@@ -143,15 +143,18 @@ inline int step_nsplit(int B, int H, int len, int64_t rows, bool alike) {
     const int64_t ns = (len + chunk - 1) / chunk;
     return ns < 1 ? 1 : ns > kDecodeMaxSplit ? kDecodeMaxSplit : (int)ns;
 }
-// The target of a call that finishes its mass in a second launch (decode_finish_kernel merges chunks one after the other, so many
-// of them cost it more than they save).  us a call at targets of 256 / 512 / 1024, equal lengths, bf16 d = 128 unless said:
-//   B*H 16: 250 rows 7.5 / 7.1 / 7.0, 739 rows 9.1 / 9.4 / 9.4, 3136 rows 12.7 / 15.1 / 21.5
-//   B*H 64: 1400 rows 14.2 / 12.9 / 15.1, float32 3136 rows 48.6 / 37.4 / 40.3;  B*H 128: 1400 rows 26.1 / 19.0 / 20.8
-//   B*H 140: 1400 rows 29.0 / 22.8 / 21.4;  B*H 200: 1111 rows 24.6 / 24.2 / 23.9;  B*H 320: 1111 rows 40.5 / - / 33.4
-//   rows of 64 bytes, B*H 180, 300 rows 8.3 / 9.1 / 9.9;  rows of 128 bytes, 250 rows, B*H 8 6.7 / 7.1 / 7.0, B*H 128 8.0 / 8.5 / 8.6
-// From B*H = 257 on the lower target leaves strips whole.  Above 400 of them that is up to 5 % faster where all are equally long
-// (B*H 440, 3136 rows 116.5 / - / 122.5; float32 352 strips 174 / - / 191), and up to 26 % slower where lengths differ, which the host
-// does not know (one sequence of 3136 rows among ten of 400, B*H 440: 54.3 / - / 50.9, float32 135 / - / 110, E4M3 34.7 / - / 25.7):
+// The target of a call that finishes its mass in a second launch.  More chunks put more workgroups on the strips and more partials
+// into the merge (decode_finish_kernel, up to sixteen loads in flight).  us a call at targets of 256 / 512 / 1024, equal lengths, bf16
+// d = 128 unless said:
+//   B*H 16: 250 rows 7.8 / 7.1 / 7.1, 739 rows 8.2 / 7.7 / 7.7, 3136 rows 10.4 / 11.7 / 13.7
+//   B*H 32: 739 rows 8.3 / 9.5 / 9.4, 1400 rows 10.1 / 10.8 / 10.8;  B*H 40: 1111 rows 10.9 / 11.7 / 11.6
+//   B*H 64: 600 rows 10.9 / 11.4 / 11.4, 1400 rows 15.7 / 14.4 / 16.2, float32 3136 rows 52.8 / 39.4 / 42.3
+//   B*H 128: 1400 rows 28.9 / 18.8 / 19.8;  B*H 140: 1400 rows 26.1 / 22.6 / 21.2;  B*H 200: 1111 rows 24.4 / 24.8 / 23.1
+//   B*H 320: 1111 rows 36.4 / 36.3 / 33.8
+//   rows of 64 bytes, B*H 180, 300 rows 8.2 / 9.2 / 10.2;  of 128 bytes, 250 rows, B*H 8 7.0 / 7.0 / 7.1, B*H 128 7.8 / 8.0 / 7.9
+// From B*H = 257 on the lower target leaves strips whole.  Above 400 of them that is up to 9 % faster where all are equally long
+// (B*H 440, 3136 rows 109.7 / - / 120.0; float32 352 strips 173.8 / - / 182.9), and up to 28 % slower where lengths differ, which the
+// host does not know (one sequence of 3136 rows among ten of 400, B*H 440: 53.6 / - / 46.7, float32 132 / - / 99, E4M3 33.1 / - / 23.8):
 // they are cut.
 inline int merged_target(int64_t bh, int max_kv, int head_dim, int cache_eb) {
     const int row_bytes = head_dim * cache_eb;

@@ -8,16 +8,18 @@
 // attend kernel saves the scaled logits of the visual keys (collected in LDS, written out as whole
 // lines at the end of the workgroup) and every chunk's (max, sum); turning
 // them into probabilities and adding them over heads - in a fixed order, so the sum is the same on
-// every run - is done by prob_sum(): in decode_finish_kernel for the stand-alone call, and by
-// the layer's eviction-plan workgroup in the fused step (it needs the scores only then).
+// every run - is done by prob_sum() in decode_finish_kernel for the stand-alone call, and behind the
+// attention of a fused step: by workgroups of their own beside the plans (mass_block), or by the plan
+// itself where it ranks by that mass, or is the only one (plan_mass).
 // The whole-step call runs the same workgroups for many layers in one launch
-// (decode_attend_layers_kernel, decode_inherit_layers_kernel).
+// (decode_attend_layers_kernel, decode_inherit_layers_kernel), and ranks rows in the launch's first workgroups.
 // The token being appended is read from k_new/v_new as cache row kv_len[b] by the workgroup that
 // owns the end of the strip, which also stores it into the cache; kv_len itself is bumped by the
 // eviction plan that follows the attention.
 // (Letting that plan ride in spare workgroups of the next layer's attend launch was measured and
-// dropped: a plan workgroup is a chain of dependent memory round trips that outlasts the attend
-// launch and halves the streaming rate of the compute unit it sits on.)
+// dropped: a plan workgroup is a chain of dependent memory round trips that outlasts the attention of one
+// layer and halves the streaming rate of the compute unit it sits on.  What rides in a whole step's attention
+// is the ranking alone, beside the strips of all layers, and where those take longer: rank_beside().)
 //
 // No kernel here communicates between workgroups of one launch: device-scope fences cost a
 // write-back and invalidate of the XCD-private L2 on this part and were measured to be ruinous.

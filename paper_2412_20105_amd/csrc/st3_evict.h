@@ -96,14 +96,16 @@ typedef float f32x4_a4_t __attribute__((ext_vector_type(4), aligned(4)));
 //             733 -> 704)
 // ---------------------------------------------------------------------------------------------
 constexpr int kPlanThreadsMost = 1024;
-// Threads of a plan workgroup: what its chain of steps is spread over (mass: rows times heads; ranking: rows), against waves that
-// start, meet at barriers and stop for nothing, and against plans that wait for each other when there are several per compute
-// unit (46 KB of LDS: three with 256 or 512 threads, two with 1024).  us a call with 256 / 512 / 1024 threads, and with the
-// 256-thread form of before: layer step of 2 heads, 16 rows, evicting 8 14.1 / 14.2 / 14.5 (14.3), 40 heads, 64 rows 15.8 / 16.4 /
-// 17.9 (17.7), 32 heads, 128 rows 19.5 / 19.1 / 20.4 (20.6); select-and-compact of 300 rows, batch 1 10.3 / 9.4 / 10.1 (10.8), batch 512
-// 12.6 / 12.1 / 19.1 (13.2), 576 rows, batch 256 13.2 / 12.4 / 12.2 (13.8), 16 rows, batch 2048 25 (256 threads) against 64 (1024);
-// whole steps, 512 -> 1024: 7B batch 1 (32 plans of up to 288 rows) 59.5 -> 58.9, 13B batch 8 (320 plans, up to 497 rows) 515 ->
-// 509, high resolution batch 8 645 -> 638; 40 layers, batch 12, 8 heads, 576 rows (480 plans) 127 -> 135, which the rule takes.
+// Threads of a plan workgroup: what its chain of steps is spread over (mass: rows times heads, unless that has workgroups of its own;
+// ranking: rows), against waves that start, meet at barriers and stop for nothing, and against plans that wait for each other when
+// there are several per compute unit: one of 1024 threads, three of 512, seven of 256, by their scalar registers (a plan's LDS, 13
+// KB and four bytes a row, allows more).  us a call with 256 / 512 / 1024 threads: layer step of 2 heads, 16 rows, evicting 8 14.1 /
+// 14.1 / 15.2, 40 heads, 64 rows 16.1 / 16.6 / 17.5, 32 heads, 128 rows 17.6 / 17.7 / 18.6, 40 heads, 500 rows, batch 8 36.3 / 32.3 /
+// 32.1; select-and-compact of 300 rows, batch 1 10.3 / 9.3 / 9.8, batch 512 12.2 / 11.6 / 18.6, 576 rows, batch 256 13.0 / 12.0 /
+// 11.5, 16 rows, batch 2048 17.3 / 25.8 / 60.4; st3_decode_plans of 32 layers of 288 rows 21.8 / 20.2 / 21.2, 40 of 400 rows, batch 8
+// 33.4 / 29.8 / 31.2, 32 of 2000 rows, batch 8 51.4 / 38.5 / 37.1, 40 of 576 rows, batch 12 37.7 / 33.7 / 40.7; whole steps whose columns
+// take the mass, 7B batch 1 46.0 / 41.9 / 43.4, 13B batch 8 489 / 496 / 498, 2000 rows, batch 8 1512 / 1495 / 1487 (1024 in all three,
+// which the first two would rather not).
 inline int plan_threads(int64_t plans, int most_vis, int heads) {       // heads: 1 when no mass is to be finished
     const int64_t mass = (int64_t)most_vis * heads;
     if ((plans <= 512 && mass > 8192) || (plans <= 256 && most_vis > 512)) return 1024;
@@ -553,8 +555,8 @@ __device__ __forceinline__ void mass_block(const EvictArgs& a, int b, int j0, Ma
     const int chunk = max(d.z, 32), seen = (d.x & 1) ? d.x >> 1 : 0;
     const int ns = seen > 0 ? min((seen + chunk - 1) / chunk, min(d.y, a.nsplit_cap)) : 0;
     const int n = ns > 0 ? min(a.own_pending[b * 4 + 3] >> 1, a.max_vis) : 0;      // (0: no mass is pending)
+    if (j0 >= n) return;                                // (uniform; always so without chunks)
     head_norms<NT>(a.part_ml, b, a.H, ns, a.nsplit_cap, sm.hm, sm.hrl);
-    if (j0 >= n) return;                                // (uniform)
     for (int h = h0; h < h1; h += kUR) {
         if (h > h0) load(h);
 #pragma unroll
