@@ -315,10 +315,6 @@ __device__ __forceinline__ void leave_entry(const StepTable& t, const StepLayer&
     if (!t.c.leave || w.split != 0 || w.h != 0 || w.b != 0 || i >= words + kWideWords) return;
     reinterpret_cast<uint32_t*>(e.ws + wl.total)[i] = t.w[i < words ? w.li * words + i : kStepTableWords - kWideWords * (w.li + 1) + i - words];
 }
-// z of the grid that ranking takes: a workgroup for each (layer, sequence) of the launch.
-static int rank_rows_z(int B, int H, int chunks, int layers) { return (int)(((int64_t)B * layers + (int64_t)H * chunks - 1) / ((int64_t)H * chunks)); }
-// Layers of a launch that may rank: rank_z + B * layers is at most 65535 however many chunks there are.
-static int max_layers_ranked(int B, int H) { return (int)((int64_t)65534 * H / (H + 1) / B); }
 
 // The attention of several layers of a step that do not depend on each other; grid (H, most chunks of any of them, rank_z +
 // B * layers), layers in order, so the longest strips (early layers keep the most rows) start first.  Bound by HBM; as a
@@ -1056,7 +1052,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
     std::vector<char> moves_here((size_t)n_layers, 0);
     std::vector<int> stage((size_t)n_layers, 0), groups[4];     // layers that may share launches, in launch order
     // (grid z is rank_z + B * layers, at most 65535)
-    needs = PlanNeeds{0, false, B + rank_rows_z(B, H, 1, 1) <= 65535, 0};
+    needs = PlanNeeds{0, false, max_layers_ranked(B, H) > 0, 0};
     int most_ranked = 0, many_moves = 0;        // rows of a layer that evicts; layers that evict more rows than a plan moves by itself
     for (int i = 0; i < n_layers; ++i) {
         needs.most_vis = std::max(needs.most_vis, plan[i].max_vis);

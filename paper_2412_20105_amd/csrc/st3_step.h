@@ -88,6 +88,14 @@ struct StepTable {
 };
 static_assert(sizeof(StepTable) <= 4000, "the table travels by value");
 
+// Slices (z) of the attention's grid that ranking takes: a workgroup for each (layer, sequence) of the launch.
+inline int rank_rows_z(int B, int H, int chunks, int layers) {
+    const int64_t slice = (int64_t)H * chunks;
+    return (int)(((int64_t)B * layers + slice - 1) / slice);
+}
+// Layers that a launch may rank for: rank_z + B * layers is at most 65535 however few chunks there are.
+inline int max_layers_ranked(int B, int H) { return (int)((int64_t)65534 * H / (H + 1) / B); }
+
 inline void put_ptr(uint32_t* w, int n, int i, const void* p) {
     const uint64_t v = reinterpret_cast<uint64_t>(p);
     w[i] = (uint32_t)v;

@@ -112,8 +112,23 @@ static int check_room() {
     return 0;
 }
 
+// The attention's grid has at most 65535 slices, whatever batch a shape may have.
+static int check_grid() {
+    for (int H = 1; H <= 1024; H += H < 70 ? 1 : 53)
+        for (int B = 1; B <= 65535; B += B < 300 || B > 32000 ? 1 : 97) {
+            const int most = max_layers_ranked(B, H);
+            for (int layers = most > 2 ? most - 2 : 1; layers <= most; ++layers)
+                for (int chunks : {1, 2, 64}) {
+                    const int64_t z = rank_rows_z(B, H, chunks, layers);
+                    CHECK(z * H * chunks >= (int64_t)B * layers && z + (int64_t)B * layers <= 65535);
+                }
+        }
+    CHECK(max_layers_ranked(43690, 2) == 0 && max_layers_ranked(43689, 2) == 1 && max_layers_ranked(1, 32) > 35);
+    return 0;
+}
+
 int main() {
-    if (check_room()) return 1;
+    if (check_room() || check_grid()) return 1;
     for (int eb : {1, 2, 4})
         if (check(eb, false) || check(eb, true)) return 1;
     std::printf("ok\n");
