@@ -142,7 +142,8 @@ ST3_EXPORT size_t st3_workspace_bytes(const st3_attn_shape* shape, int32_t kv_ca
 /* Prepares a workspace for the decode-path calls: clears the per-sequence "mass pending"
  * descriptors (a few integers) with a small kernel on `stream`.  Required once before the first
  * st3_decode_layer_step / st3_select_compact_layer on a workspace that was not zero-filled.
- * Prefill scratch lives at the end of the workspace and never overlaps those descriptors. */
+ * Prefill scratch lives at the end of the workspace and never overlaps those descriptors.  A whole-step
+ * call of more layers than a launch's arguments hold keeps a few words there between its launches. */
 ST3_EXPORT st3_status st3_workspace_init(const st3_attn_shape* shape, int32_t kv_capacity, void* workspace,
                                          size_t workspace_bytes, void* stream);
 
