@@ -2,28 +2,35 @@
 // W query rows saved for the visual mass (Sec. 3.2).
 //
 // Tiling.  A workgroup of 4 wavefronts owns 128 consecutive query rows (32 per wave) of one (b,h)
-// and walks the key tiles of 64 keys up to its diagonal.  K and V tiles live in LDS, row-major, in
-// two buffers.  They get there by direct global-to-LDS loads (no staging registers; a strip's base
-// address in scalar registers, 32 bits of offset per lane): the tile after the current one is in
+// and walks the key tiles (32 or 64 keys) up to its diagonal.  K and V tiles live in LDS, row-major, in
+// a ring of buffers.  They get there by direct global-to-LDS loads (no staging registers; a strip's base
+// address in scalar registers, 32 bits of offset per lane): later tiles are in
 // flight while the current one is consumed, and a tile costs one barrier.
 // A direct load writes the 64 x 16 bytes of a wave to consecutive LDS addresses, so rows cannot be
 // padded against bank conflicts; instead every lane chooses WHICH 16 bytes of its row it fetches,
 // which stores the row's 16-byte units permuted (unit u of row r holds column unit u ^ swz(r)).
 //
-// Per wave, with v_mfma_f32_32x32x16_bf16 (A: 32 x 16, B: 16 x 32, C: 32 x 32; lane l holds
-// A[l%32][8*(l/32)..+8], B[8*(l/32)..+8][l%32] and C[8*(r/4) + 4*(l/32) + r%4][l%32], r < 16):
+// Per wave, with v_mfma_f32_16x16x32_bf16 (A: 16 x 32, B: 32 x 16, C: 16 x 16; lane l = 16 g + c holds
+// A[c][8g..8g+7], B[8g..8g+7][c] and C[4g..4g+3][c]); its 32 queries are two columns of 16:
 //   S^T = K Q^T   A = K rows from LDS (one 16-byte read per lane), B = Q fragments kept in
-//                 registers.  A lane then owns ONE query (column l%32) and 16 of the 32 keys of a
-//                 sub-tile, so the softmax row reductions are in-lane plus one exchange with lane l^32.
+//                 registers.  A lane then holds, of ONE query of either column (c), 8 of a sub-tile's 32
+//                 keys: 4g..4g+3 and 16+4g..16+4g+3.
 //   O^T = V^T P^T B = P^T taken straight from the S^T accumulator registers, which fixes which keys
-//                 sit in which contraction slot: slots 8g..8g+3 of the MFMA over keys 16kk..16kk+15
-//                 are keys 16kk+4g..+3, slots 8g+4..8g+7 keys 16kk+8+4g..+3.  A = V^T in the same
-//                 pattern: a lane needs, for ONE column d of V, two runs of four consecutive keys,
+//                 sit in which contraction slot: slots 8g..8g+3 are keys 4g..4g+3 of the sub-tile, slots 8g+4..8g+7 keys
+//                 16+4g..16+4g+3.  A = V^T in the same
+//                 pattern: a lane needs, for ONE column of V, two runs of four consecutive keys,
 //                 which is what the LDS transpose read of gfx950 (ds_read_b64_tr_b16) returns from
 //                 a row-major tile: within 16 lanes, lane i passes the address of elements
 //                 4*(i%4)..+3 of row i/4 of a 4 x 16 block and receives column i of that block
 //                 (layout checked on the device with an index pattern).
-// A tile that lies entirely below a wave's diagonal is consumed whole (64 keys, one softmax
+// Why this shape of MFMA.  Under this kernel the card is at its power limit: with inputs of zeros (nothing toggles) the 13B layer takes
+// 257 us instead of 330, the high-resolution one 615 instead of 820.  What counts is therefore the energy of a product as much as
+// the time of one, and the shapes differ in both (loops of nothing but MFMAs, TFLOP/s, zeros / normal values):
+//   32x32x16, one wave a SIMD 2463 / 1762, two waves 1650 / 1310 (two waves that take turns lose a third of the matrix unit)
+//   16x16x32, two or three waves 2440 / 2010 to 2250, the more the longer products in a row add to the same accumulator
+// So P_hi V and P_lo V follow each other on one accumulator, and the contraction steps of S^T too; the compiler is kept from mixing the
+// chains (it would, to hide a latency that the hardware does not have: 862 us instead of 838 at the high-resolution shape).
+// A tile that lies entirely below a wave's diagonal is consumed whole (one softmax
 // update); on the diagonal the 32-key sub-tile that holds it is masked and a sub-tile above it is
 // skipped.  Online softmax in the log2 domain, fp32; the softmax scale is folded into the
 // exponent's multiply-add.  For the second MFMA P is split into two bf16 terms, P = P_hi + P_lo
@@ -42,26 +49,26 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBM = 128;            // queries per workgroup
-constexpr int kBN = 64;             // keys per tile
+constexpr int kBN = 64;             // keys per tile where a tile is two sub-tiles
 
-// An LDS tile is kBN rows of D elements, no padding.  The 64 banks are 256 bytes wide together, so
+// An LDS tile is BN rows of D elements, no padding.  The 64 banks are 256 bytes wide together, so
 // RPB rows share one pass over the banks.  K rows are read 16 bytes per lane by lanes holding
 // consecutive rows: unit u ^ ((r / RPB) % UPR) spreads 16 consecutive rows over all banks.  V rows
-// are read by the transpose read, 32 lanes covering 4 consecutive rows x 64 bytes (4 units): the
-// permutation 4 * ((r / RPB) % (UPR / 4)) puts the four rows on disjoint quarters of the banks.
-template <int D> struct TileLayout {
+// are read by the transpose read, 32 lanes covering 8 consecutive rows x 32 bytes (2 units): the
+// permutation 2 * ((r / RPB) % (UPR / 2)) puts the eight rows on disjoint eighths of the banks.
+template <int D, int BN = kBN> struct TileLayout {
     static constexpr int UPR = D / 8;                   // 16-byte units per row
     static constexpr int RPB = 256 / (2 * D);           // rows per 256 bytes: 1 or 2
     static constexpr int RPI = 1024 / (2 * D);          // rows per wave-wide direct load (1 KB): 4 or 8
-    static constexpr int NI = kBN / (RPI * 4);          // direct loads of K, and of V, per wave and tile
-    static constexpr int TILE = kBN * D;                // elements of one K (or V) tile
+    static constexpr int NI = BN / (RPI * 4);           // direct loads of K, and of V, per wave and tile
+    static constexpr int TILE = BN * D;                // elements of one K (or V) tile
     __device__ static __forceinline__ int k_swz(int row) { return (row / RPB) & (UPR - 1); }
-    __device__ static __forceinline__ int v_swz(int row) { return 4 * ((row / RPB) & (UPR / 4 - 1)); }
+    __device__ static __forceinline__ int v_swz(int row) { return 2 * ((row / RPB) & (UPR / 2 - 1)); }
 };
 
 union Frag {
@@ -105,13 +112,13 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 // Kp / Vp: row 0 of the strip (uniform).  k_lane / v_lane: byte offset of this lane's 16 bytes within
 // the first 1 KB group of a tile at key 0 (row min(row0, n-1) and permuted unit folded in).
 // Offsets from the strip's row 0 fit 32 bits (checked by the launcher).  wave_s: the wave's index, scalar.
-template <int D>
+template <int D, int BN = kBN>
 __device__ __forceinline__ void issue_tile(uint32_t lds_buf, const uint16_t* Kp, const uint16_t* Vp, uint32_t k_lane,
                                            uint32_t v_lane, int64_t k_st, int64_t v_st, int k0, int n, int lane, int wave,
                                            int wave_s) {
-    using L = TileLayout<D>;
+    using L = TileLayout<D, BN>;
     const int row0 = wave * L::RPI + lane / L::UPR;     // this lane's row in the wave's first group
-    if (k0 + kBN <= n) {                                // all rows of the tile exist: plain strides
+    if (k0 + BN <= n) {                                // all rows of the tile exist: plain strides
 #pragma unroll
         for (int i = 0; i < L::NI; ++i) {
             const uint32_t dst = lds_buf + (4 * i + wave_s) * 1024;    // which 1 KB of the tile this wave-wide load fills
@@ -132,191 +139,217 @@ __device__ __forceinline__ void issue_tile(uint32_t lds_buf, const uint16_t* Kp,
     }
 }
 
-// x of this lane and x of lane ^ 32 (v_permlane32_swap: lanes 32..63 of its first operand trade places
-// with lanes 0..31 of its second; with both operands x, the one ends up holding the lower half's
-// values in both halves and the other the upper half's).  No LDS round trip, unlike a shuffle.
-__device__ __forceinline__ void both_halves(float x, float& a, float& b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    a = __uint_as_float(r[0]);
-    b = __uint_as_float(r[1]);
-}
-
 // All direct loads this wave has issued have landed in LDS (vmcnt(0); other counters untouched).
 __device__ __forceinline__ void wait_direct_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-// LDS transpose read: 4 consecutive rows of one column (see the header comment for the lane map).
-__device__ __forceinline__ i16x4 lds_read_tr(const uint16_t* p) {
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(p));
+// The same but for this wave's last N direct loads.
+template <int N>
+__device__ __forceinline__ void wait_direct_loads_but() {
+    static_assert(N < 16, "the counter's low bits");
+    __builtin_amdgcn_s_waitcnt(0x0F70 | N);
 }
 
-// What a lane needs to find its operands in a tile (element offsets, fixed for the whole kernel).
+// LDS reads at a byte address: 16 bytes, and the transpose read (4 consecutive rows of one column; see the header comment for the lane map).
+__device__ __forceinline__ u32x4 lds_read16(uint32_t at) { return *reinterpret_cast<__attribute__((address_space(3))) const u32x4*>(at); }
+__device__ __forceinline__ i16x4 lds_read_tr(uint32_t at) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<__attribute__((address_space(3))) i16x4*>(at));
+}
+
+// Where a lane finds its operands in a tile (byte offsets, fixed for the whole kernel).  K fragment s of row c: unit (2s + g) ^ k_swz,
+// which is the first one's address ^ 32 s; transpose read of d-tile dt: row (4g + (c%16)/4), unit (4dt + 2(c/16) + (c%4)/2) ^ v_swz,
+// half c%2: the first one's ^ 64 dt.  (Tiles start at multiples of a row's bytes, so the ^ may come last: two registers, not twelve.)
 template <int D>
 struct LaneMap {
-    int koff[D / 16];       // K fragment s of row c: row * D + ((2s + g) ^ k_swz) * 8
-    int voff[D / 32];       // transpose read of d-tile dt: row (4g + (c%16)/4), unit (4dt + 2(c/16) + (c%4)/2) ^ v_swz, half c%2
+    uint32_t k, v;
     __device__ __forceinline__ void init(int c, int g) {
         using L = TileLayout<D>;
-#pragma unroll
-        for (int s = 0; s < D / 16; ++s) koff[s] = c * D + ((2 * s + g) ^ L::k_swz(c)) * 8;
-        const int row = 4 * g + ((c & 15) >> 2);
-#pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt)
-            voff[dt] = row * D + ((4 * dt + 2 * (c >> 4) + ((c & 3) >> 1)) ^ L::v_swz(row)) * 8 + 4 * (c & 1);
+        k = (uint32_t)(2 * (c * D + (g ^ L::k_swz(c)) * 8));
+        const int row = 4 * g + (c >> 2);
+        v = (uint32_t)(2 * (row * D + (((c & 3) >> 1) ^ L::v_swz(row)) * 8 + 4 * (c & 1)));
     }
 };
 
-// NSUB 32-key sub-tiles of the tile in (Kt, Vt) for one wave: S^T, one online-softmax update over
-// all NSUB * 32 keys, O^T += V^T P^T.  DIAG: the last of them lies on the wave's diagonal (its keys
+// The score window (the last W query rows), as the wave with first query q0 sees it: uniform values only, so that it costs the wave no
+// vector registers while it works on other tiles.
+struct Window {
+    float* rows;            // logits of the strip's window rows, vis_len each; null: none of the wave's queries is in the window
+    int shift;              // q0 - (n - W): a lane's query c is window row shift + c
+    int rows_end;           // W
+    int vis_lo, vis_hi;
+};
+
+// A wave's 32 queries, as two columns of 16: lane (c, g) holds query 16 qc + c of either, and of its output the columns
+// 16 dt + 4 g .. + 3.
+template <int D>
+struct WaveRows {
+    f32x4 o[D / 16][2];     // un-normalised output, transposed
+    float m[2];             // reference point of the exponents; the same for the four lanes that share a query
+    float l[2];             // sum of this lane's probabilities
+    __device__ __forceinline__ void init() {
+#pragma unroll
+        for (int dt = 0; dt < D / 16; ++dt)
+#pragma unroll
+            for (int qc = 0; qc < 2; ++qc) o[dt][qc] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int qc = 0; qc < 2; ++qc) { m[qc] = -3.402823466e38f; l[qc] = 0.f; }
+    }
+};
+
+// NSUB 32-key sub-tiles for one wave: S^T, one online-softmax update over all NSUB * 32 keys, O^T += V^T P^T.  Kt, Vt: LDS byte
+// addresses of the tile's K and V, this lane's part (LaneMap) included.  DIAG: the last sub-tile lies on the wave's diagonal (its keys
 // start at the wave's first query), the only place where some keys are invisible to some rows.
 template <int D, int NSUB, bool DIAG>
-__device__ __forceinline__ void tile_step(const uint16_t* Kt, const uint16_t* Vt, const Frag* qf, f32x16* oacc,
-                                          float& m_i, float& l_i, float scale_l2, const LaneMap<D>& lm, int c, int g,
-                                          int k0, int myq, float* lg_row, int vis_lo, int vis_hi) {
-    constexpr int KS = D / 16, DT = D / 32;
-    // LDS reads are issued in batches ahead of their use, so that their latency is paid once per
-    // batch and not once per MFMA: K fragments in groups of four contraction steps, the next group on
-    // its way while the current one is multiplied.
-    // ---- S^T = K Q^T ----------------------------------------------------------------------------
-    constexpr int KG = 4, GPS = KS / KG, NG = NSUB * GPS;       // steps per group, groups per sub-tile, groups
-    Frag ka[2][KG];
-    f32x16 sacc[NSUB];
+__device__ __forceinline__ void tile_step(uint32_t Kt, uint32_t Vt, const Frag (&qf)[2][D / 32], WaveRows<D>& st, float scale_l2, int c,
+                                          int g, int k0, const Window& win) {
+    constexpr int KS = D / 32, DT = D / 16, NG = 2 * NSUB;
+    __builtin_amdgcn_s_setprio(1);
+    // ---- S^T = K Q^T, 16 keys at a time; the next 16 keys' fragments are on their way meanwhile ----------------
+    Frag ka[2][KS];
+    f32x4 sacc[NSUB][2][2];             // [sub-tile][half of its keys][query column]
+    auto load_k = [&](int grp) {
 #pragma unroll
-    for (int sub = 0; sub < NSUB; ++sub)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sacc[sub][r] = 0.f;
-#pragma unroll
-    for (int s = 0; s < KG; ++s) ka[0][s].u4 = *reinterpret_cast<const u32x4*>(Kt + lm.koff[s]);
+        for (int s = 0; s < KS; ++s) ka[grp & 1][s].u4 = lds_read16((Kt ^ (64 * s)) + 32 * grp * D);
+    };
+    load_k(0);
 #pragma unroll
     for (int grp = 0; grp < NG; ++grp) {
-        if (grp + 1 < NG) {
-            const int sub = (grp + 1) / GPS, s0 = ((grp + 1) % GPS) * KG;
-#pragma unroll
-            for (int s = 0; s < KG; ++s)
-                ka[(grp + 1) & 1][s].u4 = *reinterpret_cast<const u32x4*>(Kt + 32 * sub * D + lm.koff[s0 + s]);
-        }
+        if (grp + 1 < NG) load_k(grp + 1);
         __builtin_amdgcn_sched_barrier(0);
-        const int sub = grp / GPS, s0 = (grp % GPS) * KG;
 #pragma unroll
-        for (int s = 0; s < KG; ++s)
-            sacc[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[grp & 1][s].v, qf[s0 + s].v, sacc[sub], 0, 0, 0);
-    }
-    Frag va[2][DT];                     // V^T fragments of the 16-key group in use and of the next one
+        for (int qc = 0; qc < 2; ++qc) {
+            f32x4 x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {   // the first group lands while the softmax runs
-        va[0][dt].h[0] = lds_read_tr(Vt + lm.voff[dt]);
-        va[0][dt].h[1] = lds_read_tr(Vt + 8 * D + lm.voff[dt]);
+            for (int s = 0; s < KS; ++s) x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[grp & 1][s].v, qf[qc][s].v, x, 0, 0, 0);
+            sacc[grp / 2][grp % 2][qc] = x;
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
+    constexpr int VB = DT < 4 ? DT : 4;     // V^T fragments in flight
+    Frag va[VB];
+    auto load_v = [&](int i) {              // i-th of NSUB * DT: sub-tile i / DT, columns 16 (i % DT)
+        const uint32_t at = (Vt ^ (32 * (i % DT))) + 64 * (i / DT) * D;
+        va[i % VB].h[0] = lds_read_tr(at);
+        va[i % VB].h[1] = lds_read_tr(at + 32 * D);
+    };
+#pragma unroll
+    for (int i = 0; i < VB; ++i) load_v(i);             // these land while the softmax runs
     __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
     // ---- causal mask (diagonal sub-tile only), row maximum ----------------------------------------
     if (DIAG) {
+        int last = c - 4 * g;                           // (opaque: else the comparisons wait in registers for this one tile)
+        asm volatile("" : "+v"(last));
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-            if (8 * (r / 4) + 4 * g + (r % 4) > c) sacc[NSUB - 1][r] = -INFINITY;
+        for (int kr = 0; kr < 2; ++kr)
+#pragma unroll
+            for (int qc = 0; qc < 2; ++qc)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (16 * kr - 16 * qc + r > last) sacc[NSUB - 1][kr][qc][r] = -INFINITY;
     }
     // A row of the score window keeps the scaled logits of its visual keys.  The wave that holds it sets the pace of the
-    // strip's heaviest workgroup, so the usual case - every key of the tile visible and visual - is eight 16-byte stores.
+    // strip's heaviest workgroup, so the usual case - every key of the tile visible and visual - is 16-byte stores.
     // (With a comparison and a store per key such a tile took 7200 cycles instead of 4250; 13B layer, batch 32: 396 -> 380 us a
     // call, high resolution, batch 8: 1010 -> 940.)
-    if (!DIAG && k0 >= vis_lo && k0 + 32 * NSUB <= vis_hi) {
-        if (lg_row != nullptr) {
-            float* p = lg_row + (k0 - vis_lo) + 4 * g;      // (4-byte aligned, which is all a global store asks for)
+    if (win.rows != nullptr) {
+        int cw = c, first = 4 * g;                      // (opaque: what follows is not worked out ahead of the one wave that needs it)
+        asm volatile("" : "+v"(cw), "+v"(first));
+        first += k0 - win.vis_lo;                       // this lane's first key among the visual ones
+        const int n_vis = win.vis_hi - win.vis_lo;
+        const bool whole = !DIAG && k0 >= win.vis_lo && k0 + 32 * NSUB <= win.vis_hi;
 #pragma unroll
-            for (int sub = 0; sub < NSUB; ++sub)
+        for (int qc = 0; qc < 2; ++qc) {
+            const int w = win.shift + 16 * qc + cw;     // window row
+            if (w < 0 || w >= win.rows_end) continue;
+            float* row = win.rows + (int64_t)w * n_vis;
+            // (a masked key's logit is -inf here and is not kept)
+            const int end = DIAG ? min(n_vis, k0 + 32 * (NSUB - 1) + 16 * qc + cw + 1 - win.vis_lo) : n_vis;
 #pragma unroll
-                for (int rq = 0; rq < 4; ++rq) {
-                    const f32x4_a4 v = {sacc[sub][4 * rq] * scale_l2, sacc[sub][4 * rq + 1] * scale_l2,
-                                        sacc[sub][4 * rq + 2] * scale_l2, sacc[sub][4 * rq + 3] * scale_l2};
-                    *reinterpret_cast<f32x4_a4*>(p + 32 * sub + 8 * rq) = v;
+            for (int x = 0; x < 2 * NSUB; ++x) {
+                const f32x4 v = sacc[x / 2][x % 2][qc] * scale_l2;
+                if (whole) {
+                    *reinterpret_cast<f32x4_a4*>(row + first + 16 * x) = v;     // (4-byte aligned, which is all a global store asks for)
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int j = first + 16 * x + r;
+                        if (j >= 0 && j < end) row[j] = v[r];
+                    }
                 }
-        }
-    } else if (lg_row != nullptr) {
-#pragma unroll
-        for (int sub = 0; sub < NSUB; ++sub)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = k0 + 32 * sub + 8 * (r / 4) + 4 * g + (r % 4);
-                if (key >= vis_lo && key < vis_hi && key <= myq) lg_row[key - vis_lo] = sacc[sub][r] * scale_l2;
             }
+        }
     }
-    float mx = sacc[0][0];
-#pragma unroll
-    for (int sub = 0; sub < NSUB; ++sub)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[sub][r]);
-    {
-        float lo_half, hi_half;
-        both_halves(mx, lo_half, hi_half);
-        mx = fmaxf(lo_half, hi_half);
-    }
-    // every row sees the first key of every tile it gets here (k0 <= q0 <= myq): mx is -inf only where keys of logit -inf are
-    // all it sees.
-    // The reference point m_i of the exponents only follows the row maximum when that has moved by
+    // The reference point m of the exponents only follows the row maximum when that has moved by
     // more than kLazy (probabilities then reach 2^kLazy at most, far inside fp32 and bf16 range):
     // a softmax is invariant to the reference point, and the accumulator rescaling it triggers
-    // becomes rare instead of happening in nearly every tile.
+    // becomes rare instead of happening in nearly every tile.  Only then do the four lanes of a query need each other's maxima.
+    // (Every row sees the first key of every tile it gets here, k0 <= q0: a maximum is -inf only where keys of logit -inf are all it
+    // sees; they weigh nothing, whatever the reference.)
     constexpr float kLazy = 8.0f;
-    const float m_cand = fmaxf(m_i, mx * scale_l2);
-    const bool moved = m_cand - m_i > kLazy;            // m_i = -inf before the first key: moved
-    const float m_new = moved ? m_cand : m_i;
-    // (a group of waves can meet keys of logit -inf only; they weigh nothing, whatever the reference)
-    const float m_ref = m_new == -INFINITY ? 0.f : m_new;
-    const float alpha = exp2_fast(m_i - m_ref);         // 1 when not moved; 0 before the first key
-    m_i = m_new;
-    float psum = 0.f;
+    float mx[2];
+#pragma unroll
+    for (int qc = 0; qc < 2; ++qc) {
+        mx[qc] = sacc[0][0][qc][0];
+#pragma unroll
+        for (int x = 0; x < 2 * NSUB; ++x)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mx[qc] = fmaxf(mx[qc], sacc[x / 2][x % 2][qc][r]);
+        mx[qc] *= scale_l2;
+    }
+    if (__any(mx[0] - st.m[0] > kLazy || mx[1] - st.m[1] > kLazy)) {   // m = -inf before the first key: it moves
+#pragma unroll
+        for (int qc = 0; qc < 2; ++qc) {
+            const float m_cand = fmaxf(st.m[qc], wave_max_from<16>(mx[qc]));
+            const float m_new = m_cand - st.m[qc] > kLazy ? m_cand : st.m[qc];
+            const float alpha = exp2_fast(st.m[qc] - m_new);            // 1 when not moved; 0 before the first key
+            st.m[qc] = m_new;
+            st.l[qc] *= alpha;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) st.o[dt][qc] *= alpha;
+        }
+    }
     Frag pb[NSUB][2], pl[NSUB][2];
 #pragma unroll
     for (int sub = 0; sub < NSUB; ++sub)
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
+        for (int qc = 0; qc < 2; ++qc)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float p0 = exp2_fast(fmaf(sacc[sub][8 * kk + 2 * j], scale_l2, -m_ref));      // masked: exp2(-inf) = 0
-                const float p1 = exp2_fast(fmaf(sacc[sub][8 * kk + 2 * j + 1], scale_l2, -m_ref));
-                psum += p0 + p1;
+                const f32x4& x = sacc[sub][j / 2][qc];
+                const float p0 = exp2_fast(fmaf(x[2 * (j & 1)], scale_l2, -st.m[qc]));        // masked: exp2(-inf) = 0
+                const float p1 = exp2_fast(fmaf(x[2 * (j & 1) + 1], scale_l2, -st.m[qc]));
+                st.l[qc] += p0 + p1;
                 const uint32_t b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
-                pb[sub][kk].w[j] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);      // upper halves of (p0, p1)
+                pb[sub][qc].w[j] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);      // upper halves of (p0, p1)
                 const f32x2 lo = {p0 - __uint_as_float(b0 & 0xffff0000u), p1 - __uint_as_float(b1 & 0xffff0000u)};
-                pl[sub][kk].w[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
+                pl[sub][qc].w[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
             }
-    l_i = l_i * alpha + psum;
-    if (__any(moved)) {                                 // rescale only when some row's maximum moved
+    // ---- O^T += V^T P^T, 16 columns at a time; a fragment's place takes the one VB further on as soon as it is used ----------
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
-    }
-    // ---- O^T += V^T P^T, 16 keys (one contraction) at a time ------------------------------------
-#pragma unroll
-    for (int grp = 0; grp < 2 * NSUB; ++grp) {
-        if (grp + 1 < 2 * NSUB) {       // the next group's fragments are on their way while this one is used
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                va[(grp + 1) & 1][dt].h[0] = lds_read_tr(Vt + 16 * (grp + 1) * D + lm.voff[dt]);
-                va[(grp + 1) & 1][dt].h[1] = lds_read_tr(Vt + (16 * (grp + 1) + 8) * D + lm.voff[dt]);
-            }
-        }
+    for (int i = 0; i < NSUB * DT; ++i) {
+        const int sub = i / DT, dt = i % DT;
+        if (i + VB - 1 < NSUB * DT && i > 0) load_v(i + VB - 1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-            oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[grp & 1][dt].v, pb[grp / 2][grp % 2].v, oacc[dt], 0, 0, 0);
-            oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[grp & 1][dt].v, pl[grp / 2][grp % 2].v, oacc[dt], 0, 0, 0);
+        for (int qc = 0; qc < 2; ++qc) {
+            st.o[dt][qc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[i % VB].v, pb[sub][qc].v, st.o[dt][qc], 0, 0, 0);
+            st.o[dt][qc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[i % VB].v, pl[sub][qc].v, st.o[dt][qc], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
 }
 
-// The part of the tile at k0 that the wave with first query q0 can see (k0 <= q0).
+// The part of the tile at k0 (at LDS byte address `tile`) that the wave with first query q0 can see (k0 <= q0).
 template <int D>
-__device__ __forceinline__ void consume_tile(const uint16_t* buf, int k0, int q0, const Frag* qf, f32x16* oacc,
-                                             float& m_i, float& l_i, float scale_l2, const LaneMap<D>& lm, int c, int g,
-                                             int myq, float* lg_row, int vis_lo, int vis_hi) {
-    const uint16_t* Kt = buf;
-    const uint16_t* Vt = buf + TileLayout<D>::TILE;
+__device__ __forceinline__ void consume_tile(uint32_t tile, int k0, int q0, const Frag (&qf)[2][D / 32], WaveRows<D>& st, float scale_l2,
+                                             const LaneMap<D>& lm, int c, int g, const Window& win) {
+    const uint32_t Kt = tile + lm.k, Vt = tile + 2 * TileLayout<D>::TILE + lm.v;
     if (k0 + kBN <= q0)         // below the diagonal: all 64 keys visible to all 32 rows
-        tile_step<D, 2, false>(Kt, Vt, qf, oacc, m_i, l_i, scale_l2, lm, c, g, k0, myq, lg_row, vis_lo, vis_hi);
+        tile_step<D, 2, false>(Kt, Vt, qf, st, scale_l2, c, g, k0, win);
     else if (k0 + 32 == q0)     // first half visible, second half on the diagonal
-        tile_step<D, 2, true>(Kt, Vt, qf, oacc, m_i, l_i, scale_l2, lm, c, g, k0, myq, lg_row, vis_lo, vis_hi);
+        tile_step<D, 2, true>(Kt, Vt, qf, st, scale_l2, c, g, k0, win);
     else                        // k0 == q0: first half on the diagonal, second half above it
-        tile_step<D, 1, true>(Kt, Vt, qf, oacc, m_i, l_i, scale_l2, lm, c, g, k0, myq, lg_row, vis_lo, vis_hi);
+        tile_step<D, 1, true>(Kt, Vt, qf, st, scale_l2, c, g, k0, win);
 }
 
 // Normalises and stores a wave's 32 x D block of outputs.
@@ -325,30 +358,62 @@ __device__ __forceinline__ void consume_tile(const uint16_t* buf, int k0, int q0
 // So the wave's 32 x D block goes through LDS (obuf: 32 rows of D + 8 elements, this wave's own)
 // and leaves as whole rows, 16 bytes per lane.
 template <int D>
-__device__ __forceinline__ void store_block(const PrefillArgs& a, int b, int h, uint16_t* obuf, const f32x16* oacc, float rl,
+__device__ __forceinline__ void store_block(const PrefillArgs& a, int b, int h, uint16_t* obuf, const WaveRows<D>& st, const float (&l)[2],
                                             int q0, int n, bool wave_live, int lane, int g, int c) {
-    constexpr int DT = D / 32;
+    constexpr int DT = D / 16;
     constexpr int OSTR = D + 8;                     // padded row, 16-byte aligned
     constexpr int VPR = D / 8;                      // 16-byte vectors (lanes) per row
     constexpr int RPI = 64 / VPR;                   // rows per wave-wide store
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+    for (int qc = 0; qc < 2; ++qc) {
+        const float rl = 1.0f / l[qc];
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq) {
-            const int dd = 32 * dt + 8 * rq + 4 * g;
-            const f32x2 o01 = {oacc[dt][4 * rq] * rl, oacc[dt][4 * rq + 1] * rl};
-            const f32x2 o23 = {oacc[dt][4 * rq + 2] * rl, oacc[dt][4 * rq + 3] * rl};
+        for (int dt = 0; dt < DT; ++dt) {
+            const f32x4 o = st.o[dt][qc] * rl;
+            const f32x2 o01 = {o[0], o[1]}, o23 = {o[2], o[3]};
             uint2 pk;                               // packed conversion, round to nearest even
             pk.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(o01, bf16x2));
             pk.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(o23, bf16x2));
-            *reinterpret_cast<uint2*>(obuf + c * OSTR + dd) = pk;
+            *reinterpret_cast<uint2*>(obuf + (16 * qc + c) * OSTR + 16 * dt + 4 * g) = pk;
         }
+    }
     uint16_t* obase = reinterpret_cast<uint16_t*>(a.out) + b * a.o_sb + h * a.o_sh;
 #pragma unroll
     for (int i = 0; i < 32 / RPI; ++i) {
         const int r = i * RPI + lane / VPR;
         const u32x4 val = *reinterpret_cast<const u32x4*>(obuf + r * OSTR + (lane % VPR) * 8);
         if (wave_live && q0 + r < n) *reinterpret_cast<u32x4*>(obase + (int64_t)(q0 + r) * a.o_st + (lane % VPR) * 8) = val;
+    }
+}
+
+// q0 is the same for all lanes of a wave.
+__device__ __forceinline__ Window window_of(const PrefillArgs& a, int64_t bh, int q0) {
+    const int q = __builtin_amdgcn_readfirstlane(q0);
+    const bool any = a.pre_logits != nullptr && q + 31 >= a.n - a.window && q < a.n && q >= 0;
+    return Window{any ? a.pre_logits + bh * a.window * a.vis_len : nullptr, q - (a.n - a.window), a.window, a.sys_len, a.sys_len + a.vis_len};
+}
+
+// The window rows' maxima and sums.
+__device__ __forceinline__ void keep_row_sums(const PrefillArgs& a, const Window& win, int64_t bh, int c, int g, const float (&m)[2],
+                                              const float (&l)[2]) {
+    if (win.rows == nullptr || g != 0) return;
+#pragma unroll
+    for (int qc = 0; qc < 2; ++qc) {
+        const int w = win.shift + 16 * qc + c;
+        if (w < 0 || w >= win.rows_end) continue;
+        a.pre_ml[(bh * a.window + w) * 2] = m[qc];
+        a.pre_ml[(bh * a.window + w) * 2 + 1] = l[qc];
+    }
+}
+
+// A wave's query fragments: 32 rows from q0 on (rows that do not exist: the nearest that does).
+template <int D>
+__device__ __forceinline__ void load_queries(const uint16_t* Qp, int64_t q_st, int q0, int n, int c, int g, Frag (&qf)[2][D / 32]) {
+#pragma unroll
+    for (int qc = 0; qc < 2; ++qc) {
+        const uint16_t* qrow = Qp + (int64_t)max(0, min(q0 + 16 * qc + c, n - 1)) * q_st;
+#pragma unroll
+        for (int s = 0; s < D / 32; ++s) qf[qc][s].u4 = *reinterpret_cast<const u32x4*>(qrow + 32 * s + 8 * g);
     }
 }
 
@@ -379,7 +444,7 @@ __device__ __forceinline__ void place_workgroup(const PrefillArgs& a, int& strip
 // The same where not all workgroups find a place at once.  Such a launch ends with its last tiles, and a strip's heaviest tile can
 // take as long as the strip's whole share of a compute unit: so the last strips of each lane (spread_strips) are dealt heaviest
 // tiles first over all of them, and the strips left over come first of all, heaviest tiles first, instead of last.  us a call,
-// before -> so (strips x tokens): 128 x 675 45.6 -> 37.4, 128 x 400 27.5 -> 23.4, 256 x 675 74.2 -> 62.7, 320 x 739 97.8 -> 88.6, 1280 x 739
+// before -> so (strips x tokens, with 32x32x16 MFMAs): 128 x 675 45.6 -> 37.4, 128 x 400 27.5 -> 23.4, 256 x 675 74.2 -> 62.7, 320 x 739 97.8 -> 88.6, 1280 x 739
 // 371.5 -> 368.3, 80 x 739 42.0 -> 35.9, 140 x 1500 151.6 -> 127.4, 72 x 900 49.1 -> 38.5, 64 x 3136 234 -> 225.  (The kernel with key
 // groups has all its workgroups in place at once and keeps the plain order: this one took its smallest calls 0.2 of 17 us.)
 __device__ __forceinline__ void place_spread(const PrefillArgs& a, int& strip, int& qt) {
@@ -398,37 +463,34 @@ __device__ __forceinline__ void place_spread(const PrefillArgs& a, int& strip, i
 }
 
 // One-dimensional grid of ceil(n/128) * H * B workgroups (the mapping to query tile and strip is in the kernel).
-// Register budget: two waves per SIMD (256 registers each; the kernel takes 214), i.e. two workgroups
-// per compute unit: while one waits for a tile, a barrier or its first loads, the other one runs.
-// Cycles of a tile (64 keys below the diagonal, stamps inside the kernel): 630 issue of the next tile's loads, 760 S^T, 1250
-// softmax, 1110 O^T, 140 wait and barrier - for a wave that has its SIMD to itself, at a shader clock of 2.35 GHz, and for two
-// that share it alike, at 1.83 GHz: under full load the clock falls, and rearranging the tile moves nothing (us a call, 13B layer
-// batch 32 / high resolution batch 8: as it is 369 / 902; softmax of one sub-tile between the MFMAs of the other 368 / 905;
-// half of the waves loading after S^T 378 / 940, all of them 376 / 920).  Tiles and the cost of an item (8400 cycles) add up to
-// 292 of the 369 us (15 rounds of 7 tiles) and 722 of 902: where the last fifth goes has not been measured.
-template <int D, bool SPREAD>
-__global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(PrefillArgs a) {
-    using L = TileLayout<D>;
-    constexpr int KS = D / 16;          // contraction steps of S^T
-    constexpr int DT = D / 32;          // 32-row tiles of O^T
-    // two buffers as two objects, so that the compiler can tell a direct load into one from the reads of the other
-    __shared__ __attribute__((aligned(1024))) uint16_t buf0[2 * L::TILE];
-    __shared__ __attribute__((aligned(1024))) uint16_t buf1[2 * L::TILE];
+// BN = 32: three waves per SIMD (168 registers, none spilled: a spill's reload would wait for every direct load in flight), three tiles
+// of 16 KB in LDS (D = 128).  The tile two ahead is loaded behind the current one's products: issued in front of them, the loads hold
+// up all waves of a compute unit at the same point (zeros, 13B layer / high resolution: 263 / 608 us behind, 289 / 648 in front).  The
+// products of S^T run at raised wave priority, so that one wave's softmax meets another's products (normal values 354 / 866 with,
+// 357 / 880 without).
+// BN = 64: two waves per SIMD, two tiles of 32 KB; a wave that is alone on its SIMD takes a tile of 64 keys faster than two of 32.
+// us a call, 32x32x16 MFMAs on 64-key tiles at two waves per SIMD -> BN = 32 (where not every launch below is at its rule's side: long_tiles):
+// 13B layer batch 32 370 -> 330, high resolution batch 8 908 -> 820, 320 strips x 739 94.4 -> 85.8, 1280 x 200 64.6 -> 52.2, 96 x 8192 2170 ->
+// 1921, D = 64: 1280 x 739 208 -> 196.
+template <int D, bool SPREAD, int BN>
+__global__ __launch_bounds__(256, BN == 32 ? 3 : 2) void prefill_mfma_kernel(PrefillArgs a) {
+    using L = TileLayout<D, BN>;
+    constexpr int kRing = BN == 32 ? 3 : 2;             // tiles in LDS
+    __shared__ __attribute__((aligned(1024))) uint16_t buf[kRing * 2 * L::TILE];
 
     int strip, qt;
     if (SPREAD) place_spread(a, strip, qt);
     else place_workgroup(a, strip, qt);
     const int h = strip % a.H, b = strip / a.H;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int g = lane >> 5, c = lane & 31;
+    const int g = lane >> 4, c = lane & 15;
     const int n = a.n;
     // Query tiles are cut from the END of the prompt in whole 32-row blocks: the blocks that a prompt
     // of no multiple of 128 rows leaves empty then sit at the front of a strip's FIRST tile, the one
     // that walks the fewest key tiles, and not behind its last (the one that walks them all).  Such a
     // wave has q0 < 0 and only helps to load tiles.  (Blocks stay aligned to 32 rows and key tiles to
-    // 64, which is what the diagonal handling relies on.)
+    // their size, which is what the diagonal handling relies on.)
     const int q0 = qt * kBM + wave * 32 - a.q_shift;
-    const int myq = q0 + c;
     const int64_t bh = (int64_t)b * a.H + h;
 
     const uint16_t* Qp = reinterpret_cast<const uint16_t*>(a.q) + b * a.q_sb + h * a.q_sh;
@@ -446,64 +508,56 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(PrefillArgs a) {
         v_lane = (uint32_t)(2 * (rowc * a.v_st + (u ^ L::v_swz(row0)) * 8));
     }
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);     // for scalar address arithmetic only
-    const uint32_t lds0 = lds_addr(buf0), lds1 = lds_addr(buf1);
-    issue_tile<D>(lds0, Kp, Vp, k_lane, v_lane, a.k_st, a.v_st, 0, n, lane, wave, wave_s);
-    Frag qf[KS];
-    {
-        const uint16_t* qrow = Qp + (int64_t)max(0, min(myq, n - 1)) * a.q_st;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) qf[s].u4 = *reinterpret_cast<const u32x4*>(qrow + 16 * s + 8 * g);
-    }
+    const uint32_t lds0 = lds_addr(buf);
+    constexpr int kBufBytes = 4 * L::TILE;
+    const int k_end = min(n, qt * kBM + kBM - a.q_shift);   // keys this workgroup can see
+    const int nt = (k_end + BN - 1) / BN;
+    auto issue = [&](int t, int slot) {
+        issue_tile<D, BN>(lds0 + slot * kBufBytes, Kp, Vp, k_lane, v_lane, a.k_st, a.v_st, t * BN, n, lane, wave, wave_s);
+    };
+    issue(0, 0);
+    Frag qf[2][D / 32];
+    load_queries<D>(Qp, a.q_st, q0, n, c, g, qf);
     LaneMap<D> lm;
     lm.init(c, g);
-    f32x16 oacc[DT];
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
-    float m_i = -INFINITY, l_i = 0.f;
+    WaveRows<D> rows;
+    rows.init();
 
-    // window rows (the last W queries) held by this wave?
-    const bool wave_has_window = a.pre_logits != nullptr && q0 + 31 >= n - a.window && q0 < n && q0 >= 0;
-    const int w_idx = myq - (n - a.window);
-    const bool lane_in_window = wave_has_window && w_idx >= 0 && myq < n;
-    float* lg_row = lane_in_window ? a.pre_logits + (bh * a.window + w_idx) * a.vis_len : nullptr;
-    const int vis_lo = a.sys_len, vis_hi = a.sys_len + a.vis_len;
-
-    const int k_end = min(n, qt * kBM + kBM - a.q_shift);   // keys this workgroup can see
-    const int nt = (k_end + kBN - 1) / kBN;
+    const Window win = window_of(a, bh, q0);
     const bool wave_live = q0 >= 0 && q0 < n;           // else all 32 queries lie outside the prompt
-    wait_direct_loads();
+    // Tile t is in slot t % kRing.  A slot is refilled only behind a barrier that every wave has passed since its last read, and a
+    // tile is read behind a barrier in front of which every wave has waited for its own loads of it.
+    if (kRing == 3 && nt > 1) { issue(1, 1); wait_direct_loads_but<2 * L::NI>(); }
+    else wait_direct_loads();
     __syncthreads();
-    // Tiles alternate between the buffers; the loop body handles one pair.  A buffer is refilled one
-    // iteration after its last read, and every wave has passed a barrier in between.
-    for (int t = 0; t < nt; t += 2) {
-        if (t + 1 < nt) issue_tile<D>(lds1, Kp, Vp, k_lane, v_lane, a.k_st, a.v_st, (t + 1) * kBN, n, lane, wave, wave_s);
-        if (wave_live && t * kBN <= q0)                 // else the tile lies entirely above this wave's diagonal
-            consume_tile<D>(buf0, t * kBN, q0, qf, oacc, m_i, l_i, a.scale_l2, lm, c, g, myq, lg_row, vis_lo, vis_hi);
-        wait_direct_loads();
+    int slot = 0, next = kRing - 1;
+    for (int t = 0; t < nt; ++t) {
+        if (kRing == 2 && t + 1 < nt) issue(t + 1, next);
+        const int k0 = t * BN;
+        const uint32_t tile = lds0 + slot * kBufBytes;
+        if (BN == 64) {
+            if (wave_live && k0 <= q0) consume_tile<D>(tile, k0, q0, qf, rows, a.scale_l2, lm, c, g, win);
+        } else {
+            const uint32_t Kt = tile + lm.k, Vt = tile + 2 * L::TILE + lm.v;
+            if (wave_live && k0 < q0) tile_step<D, 1, false>(Kt, Vt, qf, rows, a.scale_l2, c, g, k0, win);
+            else if (wave_live && k0 == q0) tile_step<D, 1, true>(Kt, Vt, qf, rows, a.scale_l2, c, g, k0, win);
+        }
+        if (kRing == 3 && t + 2 < nt) {
+            issue(t + 2, next);
+            wait_direct_loads_but<2 * L::NI>();
+        } else {
+            wait_direct_loads();
+        }
         __syncthreads();
-        if (t + 1 >= nt) break;
-        if (t + 2 < nt) issue_tile<D>(lds0, Kp, Vp, k_lane, v_lane, a.k_st, a.v_st, (t + 2) * kBN, n, lane, wave, wave_s);
-        if (wave_live && (t + 1) * kBN <= q0)
-            consume_tile<D>(buf1, (t + 1) * kBN, q0, qf, oacc, m_i, l_i, a.scale_l2, lm, c, g, myq, lg_row, vis_lo, vis_hi);
-        wait_direct_loads();
-        __syncthreads();
+        slot = slot == kRing - 1 ? 0 : slot + 1;
+        next = next == kRing - 1 ? 0 : next + 1;
     }
     // ---- normalise and store -----------------------------------------------------------------
-    float l_lo, l_hi;
-    both_halves(l_i, l_lo, l_hi);
-    const float l_tot = l_lo + l_hi;
-    const float rl = 1.0f / l_tot;
-    uint16_t* obuf = (wave < 2 ? buf0 : buf1) + (wave & 1) * (32 * (D + 8));      // (both tile buffers are free after the last barrier)
-    static_assert(2 * 32 * (D + 8) <= 2 * L::TILE, "two waves' output blocks fit one tile buffer");
-    store_block<D>(a, b, h, obuf, oacc, rl, q0, n, wave_live, lane, g, c);
-    if (myq < n) {
-        if (lane_in_window && g == 0) {
-            a.pre_ml[(bh * a.window + w_idx) * 2] = m_i;
-            a.pre_ml[(bh * a.window + w_idx) * 2 + 1] = l_tot;
-        }
-    }
+    const float l_tot[2] = {wave_sum_from<16>(rows.l[0]), wave_sum_from<16>(rows.l[1])};
+    uint16_t* obuf = buf + wave * (32 * (D + 8));      // (the tile buffers are free after the last barrier)
+    static_assert(4 * 32 * (D + 8) <= kRing * 2 * L::TILE, "the waves' output blocks fit the tile buffers");
+    store_block<D>(a, b, h, obuf, rows, l_tot, q0, n, wave_live, lane, g, c);
+    keep_row_sums(a, win, bh, c, g, rows.m, l_tot);
 }
 
 // The same attention for launches that leave compute units idle (a short prompt, a single sequence).  128 / KS queries per
@@ -514,22 +568,21 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(PrefillArgs a) {
 template <int D, int KS>
 __global__ __launch_bounds__(256, 1) void prefill_mfma_split_kernel(PrefillArgs a) {
     using L = TileLayout<D>;
-    constexpr int KSTEPS = D / 16, DT = D / 32;
+    constexpr int DT = D / 16;
     constexpr int NB = 4 / KS;                          // 32-query blocks per workgroup
     constexpr int NBUF = KS == 2 ? 2 : 1;
     constexpr int TILE2 = 2 * L::TILE;                  // elements of a K tile and its V tile
     __shared__ __attribute__((aligned(1024))) uint16_t buf[NBUF * KS * TILE2];
-    __shared__ float sm_m[KS][NB][64], sm_l[KS][NB][64];
+    __shared__ float sm_m[KS][NB][2][64], sm_l[KS][NB][2][64];
 
     int strip, qt;
     place_workgroup(a, strip, qt);
     const int h = strip % a.H, b = strip / a.H;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int g = lane >> 5, c = lane & 31;
+    const int g = lane >> 4, c = lane & 15;
     const int blk = wave % NB, kg = wave / NB;
     const int n = a.n;
     const int q0 = qt * (32 * NB) + blk * 32 - a.q_shift;
-    const int myq = q0 + c;
     const int64_t bh = (int64_t)b * a.H + h;
     const uint16_t* Qp = reinterpret_cast<const uint16_t*>(a.q) + b * a.q_sb + h * a.q_sh;
     const uint16_t* Kp = reinterpret_cast<const uint16_t*>(a.k) + b * a.k_sb + h * a.k_sh;
@@ -554,25 +607,13 @@ __global__ __launch_bounds__(256, 1) void prefill_mfma_split_kernel(PrefillArgs 
                               (s * KS + i) * kBN, n, lane, wave, wave_s);
     };
     load_step(0);
-    Frag qf[KSTEPS];
-    {
-        const uint16_t* qrow = Qp + (int64_t)max(0, min(myq, n - 1)) * a.q_st;
-#pragma unroll
-        for (int s = 0; s < KSTEPS; ++s) qf[s].u4 = *reinterpret_cast<const u32x4*>(qrow + 16 * s + 8 * g);
-    }
+    Frag qf[2][D / 32];
+    load_queries<D>(Qp, a.q_st, q0, n, c, g, qf);
     LaneMap<D> lm;
     lm.init(c, g);
-    f32x16 oacc[DT];
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
-    float m_i = -INFINITY, l_i = 0.f;
-    const bool wave_has_window = a.pre_logits != nullptr && q0 + 31 >= n - a.window && q0 < n && q0 >= 0;
-    const int w_idx = myq - (n - a.window);
-    const bool lane_in_window = wave_has_window && w_idx >= 0 && myq < n;
-    float* lg_row = lane_in_window ? a.pre_logits + (bh * a.window + w_idx) * a.vis_len : nullptr;
-    const int vis_lo = a.sys_len, vis_hi = a.sys_len + a.vis_len;
+    WaveRows<D> rows;
+    rows.init();
+    const Window win = window_of(a, bh, q0);
     const bool wave_live = q0 >= 0 && q0 < n;
 
     const int steps = (nt + KS - 1) / KS;
@@ -582,8 +623,7 @@ __global__ __launch_bounds__(256, 1) void prefill_mfma_split_kernel(PrefillArgs 
         if (NBUF == 2 && s + 1 < steps) load_step(s + 1);
         const int t = s * KS + kg;
         if (wave_live && t < nt && t * kBN <= q0)       // else the tile lies entirely above this wave's diagonal
-            consume_tile<D>(buf + ((s % NBUF) * KS + kg) * TILE2, t * kBN, q0, qf, oacc, m_i, l_i, a.scale_l2, lm, c, g, myq,
-                            lg_row, vis_lo, vis_hi);
+            consume_tile<D>(lds0 + ((s % NBUF) * KS + kg) * TILE2 * 2, t * kBN, q0, qf, rows, a.scale_l2, lm, c, g, win);
         if (NBUF == 1 && s + 1 < steps) {
             __syncthreads();                            // every wave is done with the buffer
             load_step(s + 1);
@@ -592,75 +632,91 @@ __global__ __launch_bounds__(256, 1) void prefill_mfma_split_kernel(PrefillArgs 
     // ---- merge the key groups ----------------------------------------------------------------
     // (a lane of every group holds the same query and the same columns; a group without tiles has sum 0 at maximum -inf)
     __syncthreads();
-    float* merge = reinterpret_cast<float*>(buf);       // [KS - 1][NB][16 * DT][64]
-    sm_m[kg][blk][lane] = m_i;
-    sm_l[kg][blk][lane] = l_i;
+    f32x4* merge = reinterpret_cast<f32x4*>(buf);       // [KS - 1][NB][2 * DT][64]
+#pragma unroll
+    for (int qc = 0; qc < 2; ++qc) { sm_m[kg][blk][qc][lane] = rows.m[qc]; sm_l[kg][blk][qc][lane] = rows.l[qc]; }
     if (kg > 0) {
-        float* dst = merge + ((kg - 1) * NB + blk) * (16 * DT * 64) + lane;
+        f32x4* dst = merge + ((kg - 1) * NB + blk) * (2 * DT * 64) + lane;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) dst[(dt * 16 + r) * 64] = oacc[dt][r];
+            for (int qc = 0; qc < 2; ++qc) dst[(2 * dt + qc) * 64] = rows.o[dt][qc];
     }
     __syncthreads();
     if (kg > 0 || !wave_live) return;                   // (no barrier below)
-    float m = m_i;                                      // -inf where every key of its tiles has logit -inf (of all groups': NaN)
+    float l_tot[2];
 #pragma unroll
-    for (int k = 1; k < KS; ++k) m = fmaxf(m, sm_m[k][blk][lane]);
-    const float f0 = exp2_fast(m_i - m);
-    float l = l_i * f0;
+    for (int qc = 0; qc < 2; ++qc) {
+        float m = rows.m[qc];                           // -inf where every key of its tiles has logit -inf (of all groups': NaN)
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+        for (int k = 1; k < KS; ++k) m = fmaxf(m, sm_m[k][blk][qc][lane]);
+        const float f0 = exp2_fast(rows.m[qc] - m);
+        float l = rows.l[qc] * f0;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[dt][r] *= f0;
+        for (int dt = 0; dt < DT; ++dt) rows.o[dt][qc] *= f0;
 #pragma unroll
-    for (int k = 1; k < KS; ++k) {
-        const float f = exp2_fast(sm_m[k][blk][lane] - m);
-        l = fmaf(sm_l[k][blk][lane], f, l);
-        const float* src = merge + ((k - 1) * NB + blk) * (16 * DT * 64) + lane;
+        for (int k = 1; k < KS; ++k) {
+            const float f = exp2_fast(sm_m[k][blk][qc][lane] - m);
+            l = fmaf(sm_l[k][blk][qc][lane], f, l);
+            const f32x4* src = merge + ((k - 1) * NB + blk) * (2 * DT * 64) + lane;
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[dt][r] = fmaf(src[(dt * 16 + r) * 64], f, oacc[dt][r]);
+            for (int dt = 0; dt < DT; ++dt) rows.o[dt][qc] += src[(2 * dt + qc) * 64] * f;
+        }
+        rows.m[qc] = m;
+        l_tot[qc] = wave_sum_from<16>(l);
     }
-    float l_lo, l_hi;
-    both_halves(l, l_lo, l_hi);
-    const float l_tot = l_lo + l_hi;
-    constexpr int kMergeElems = (KS - 1) * NB * 16 * DT * 64 * 2;       // of the merge area, in 16-bit elements
+    constexpr int kMergeElems = (KS - 1) * NB * 2 * DT * 64 * 8;       // of the merge area, in 16-bit elements
     static_assert(kMergeElems + NB * 32 * (D + 8) <= NBUF * KS * TILE2, "merge area and output blocks fit the tile buffers");
-    store_block<D>(a, b, h, buf + kMergeElems + blk * (32 * (D + 8)), oacc, 1.0f / l_tot, q0, n, true, lane, g, c);
-    if (lane_in_window && g == 0) {
-        a.pre_ml[(bh * a.window + w_idx) * 2] = m;
-        a.pre_ml[(bh * a.window + w_idx) * 2 + 1] = l_tot;
-    }
+    store_block<D>(a, b, h, buf + kMergeElems + blk * (32 * (D + 8)), rows, l_tot, q0, n, true, lane, g, c);
+    keep_row_sums(a, win, bh, c, g, rows.m, l_tot);
 }
 
 // Key groups for a launch (1: the kernel without groups): as many as leave every workgroup a place of its own at once.  The
 // device holds 256 workgroups of the split kernel at D = 128 (LDS), 512 at D = 64.  With one or two strips per dispatch lane
 // the lanes stay balanced a little beyond that.  Measured, us a call, 1 / 2 / 4 groups, D = 128 (strips x tokens): 8 x 739
-// 29.4 / 23.0 / 18.7, 16 x 420 22.1 / 20.0 / 15.9, 32 x 310 18.1 / 16.8 / 17.3, 32 x 739 30.6 / 24.2 / 32.6, 64 x 420 23.6 /
-// 20.8 / 33.3, but 24 x 739 30.5 / 32.6, 40 x 420 22.7 / 25.3, 64 x 560 26.9 / 29.9, 96 x 224 17.3 / 19.8; D = 64: 32 x 420
-// 18.5 / 16.7 / 14.3, 64 x 739 26.3 / 21.7 / 26.7, 96 x 560 22.9 / 23.5 / 27.1.  Prompts of one key tile leave a second group
-// nothing: 32 x 64, D = 128, 10.7 us with one group, 12.9 with four.
+// 30 / 22.1 / 17.5, 16 x 420 20 / 17.2 / 13.6, 32 x 310 17 / 15.3 / 16.2, 32 x 739 31 / 23.9 / 31.4, 64 x 420 21.3 /
+// 19.6 / 32.1, but 24 x 739 31.1 / 32.0 / 35.2, 40 x 420 21.0 / 22.9 / 26.9, 64 x 560 26.4 / 29.9 / 44, 96 x 224 15.0 / 17.4; D = 64: 32 x 420
+// 16 / 13.5 / 10.8, 64 x 739 25.5 / 21.9 / 26.0, 96 x 560 23.8 / 23.5 / 26.5.  Prompts of one key tile leave a second group
+// nothing: 32 x 64, D = 128, 10.7 us with one group, 12.9 with four.  Few strips of D = 64 gain from four groups up to one and a
+// half times the places (2 / 4 groups: 8 x 3000 55.2 / 45.8, 12 x 2000 40.5 / 35.5, 16 x 1500 33.1 / 30.4, but 40 x 739 20.7 / 21.8).
 int key_groups(int D, int n, int64_t strips) {
     if (n <= kBN) return 1;
     const int64_t places = D == 128 ? 256 : 512;
-    if ((n + 31) / 32 * strips <= places) return 4;
+    const int64_t four = (n + 31) / 32 * strips;
+    if (four <= places || (D == 64 && strips <= 16 && 2 * four <= 3 * places)) return 4;
     const int64_t two = (n + 63) / 64 * strips;
     if (two <= places || (strips % 32 == 0 && strips <= 64 && 4 * two <= 7 * places)) return 2;
     return 1;
 }
 
+// Whether a launch without key groups takes tiles of 64 keys (two workgroups per compute unit, shorter per workgroup) or of 32 (three,
+// four at D = 64: more work at a time).  The 64 win while the launch lasts not much longer than its heaviest workgroup: strips * (query
+// tiles + 1) / 2 is the number of those that its work amounts to.  us a call, 32 / 64 (strips x tokens), D = 128: 128 x 310 19.9 / 18.7,
+// 128 x 675 38.2 / 35.1, 80 x 1500 79.1 / 74.5, 40 x 3000 150 / 130, 320 x 200 20.4 / 19.5, 256 x 300 24.8 / 22.7, 224 x 500 37.0 / 37.3,
+// 200 x 600 40.9 / 42.2, 192 x 675 46.6 / 49.9, 320 x 300 29.5 / 31.9, 128 x 1200 76.5 / 78.6, 1280 x 200 52.2 / 59.0, but 256 x 500 40.8 / 39.8, 160 x
+// 800 52.0 / 50.2, 120 x 1200 76.0 / 74.4; D = 64: 320 x 739 55.8 / 53.2, 512 x 400 38.1 / 36.2, 256 x 1000 67.3 / 66.7, 384 x 739 61.3 / 62.4, 1280 x
+// 200 34.2 / 35.7.
+bool long_tiles(int D, int n_qt, int64_t strips) { return strips * (n_qt + 1) < (D == 128 ? 1200 : 2600); }
+
 // Strips of a dispatch lane whose tiles are dealt together at the end of a launch: as many as keep the K and V of an XCD's four
-// lanes within about twice its L2 (4 MB), but two to four, or one where one strip of each is more than that.  us a call at 1 / 2 / 4 / 8 strips, D = 128: 256 x 675 74.2 / 68.7 / 62.7 /
-// 70.2, 320 x 739 97.8 / 94.6 / 88.6 / 88.5, 1280 x 739 371.5 / 371.8 / 368.3 / 367.6, but 140 x 1500 (the first with its left-over
-// strips last) 151.6 / 127.4 / 131.3 / 134.3, 256 x 3136 907 / 907 / 917 / 1049.  One / two strips, long prompts: 64 x 4096 410 / 378, 128 x
-// 4096 771 / 767, 96 x 5120 853 / 892, 128 x 5120 1160 / 1179, 64 x 6144 834 / 839, 96 x 8192 2162 / 2217, 64 x 12288 3209 / 3393, 64 x 16384
-// 5719 / 6134 (left-over strips come first either way: 40 x 8192 1103 -> 927).
+// lanes within about twice its L2 (4 MB), but two to four, or one where one strip of each is more than that.  us a call at 1 / 2 / 4 / 8 strips, D = 128: 256 x 675 66.8 / 62.9 / 56.9 /
+// 60.0, 320 x 739 89.5 / 85.2 / 83.1 / 81.0, 1280 x 739 330.5 / 326.6 / 326.5 / 324.9, 140 x 1500 128.6 / 115.2 / 114.1 / 115.6, but 256 x 3136
+// 821 / 809 / 822 / 895.  One / two strips, long prompts: 64 x 4096 337 / 330, 128 x
+// 4096 677 / 673, 96 x 5120 775 / 780, 128 x 5120 1023 / 1034, 64 x 6144 732 / 738, 96 x 8192 1921 / 1943, 64 x 12288 2862 / 2919.  (Left-over
+// strips come first either way, with 32x32x16 MFMAs: 40 x 8192 1103 -> 927.)
 int spread_strips(int D, int n, int64_t strips) {
     const int64_t bytes = (int64_t)n * D * 16;          // of one strip of each of the four lanes
     const int64_t fit = ((int64_t)8 << 20) / bytes;
     return (int)std::min<int64_t>(strips / kLanes, fit < 1 ? 1 : std::max<int64_t>(2, std::min<int64_t>(4, fit)));
+}
+
+template <int D>
+void launch_whole(const PrefillArgs& a, dim3 grid, bool long_t, hipStream_t st) {
+    // (prompts of one query tile have no order to choose, and the choice costs them 0.2 of 11 us)
+    if (a.n_qt > 1 && long_t) prefill_mfma_kernel<D, true, 64><<<grid, 256, 0, st>>>(a);
+    else if (a.n_qt > 1) prefill_mfma_kernel<D, true, 32><<<grid, 256, 0, st>>>(a);
+    else if (long_t) prefill_mfma_kernel<D, false, 64><<<grid, 256, 0, st>>>(a);
+    else prefill_mfma_kernel<D, false, 32><<<grid, 256, 0, st>>>(a);
 }
 
 }  // namespace
@@ -681,11 +737,8 @@ st3_status launch_prefill_mfma(const PrefillArgs& a, int B, int D, hipStream_t s
     dim3 grid((unsigned)wgs);
     if (D != 128 && D != 64) return ST3_ERR_UNSUPPORTED;
     if (ks == 1) {
-        // (prompts of one query tile have no order to choose, and the choice costs them 0.2 of 11 us)
-        if (D == 128 && pa.n_qt > 1) prefill_mfma_kernel<128, true><<<grid, 256, 0, st>>>(pa);
-        else if (D == 128) prefill_mfma_kernel<128, false><<<grid, 256, 0, st>>>(pa);
-        else if (pa.n_qt > 1) prefill_mfma_kernel<64, true><<<grid, 256, 0, st>>>(pa);
-        else prefill_mfma_kernel<64, false><<<grid, 256, 0, st>>>(pa);
+        if (D == 128) launch_whole<128>(pa, grid, long_tiles(D, pa.n_qt, strips), st);
+        else launch_whole<64>(pa, grid, long_tiles(D, pa.n_qt, strips), st);
     } else if (ks == 2) {
         if (D == 128) prefill_mfma_split_kernel<128, 2><<<grid, 256, 0, st>>>(pa);
         else prefill_mfma_split_kernel<64, 2><<<grid, 256, 0, st>>>(pa);
