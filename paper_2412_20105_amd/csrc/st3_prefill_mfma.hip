@@ -198,7 +198,7 @@ struct WaveRows {
 // NSUB 32-key sub-tiles for one wave: S^T, one online-softmax update over all NSUB * 32 keys, O^T += V^T P^T.  Kt, Vt: LDS byte
 // addresses of the tile's K and V, this lane's part (LaneMap) included.  DIAG: the last sub-tile lies on the wave's diagonal (its keys
 // start at the wave's first query), the only place where some keys are invisible to some rows.
-template <int D, int NSUB, bool DIAG>
+template <int D, int NSUB, bool DIAG, bool LONE = false>
 __device__ __forceinline__ void tile_step(uint32_t Kt, uint32_t Vt, const Frag (&qf)[2][D / 32], WaveRows<D>& st, float scale_l2, int c,
                                           int g, int k0, const Window& win) {
     constexpr int KS = D / 32, DT = D / 16, NG = 2 * NSUB;
@@ -221,10 +221,10 @@ __device__ __forceinline__ void tile_step(uint32_t Kt, uint32_t Vt, const Frag (
 #pragma unroll
             for (int s = 0; s < KS; ++s) x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[grp & 1][s].v, qf[qc][s].v, x, 0, 0, 0);
             sacc[grp / 2][grp % 2][qc] = x;
-            __builtin_amdgcn_sched_barrier(0);
+            if (!LONE) __builtin_amdgcn_sched_barrier(0);
         }
     }
-    constexpr int VB = DT < 4 ? DT : 4;     // V^T fragments in flight
+    constexpr int VB = LONE ? DT : DT < 4 ? DT : 4;     // V^T fragments in flight
     Frag va[VB];
     auto load_v = [&](int i) {              // i-th of NSUB * DT: sub-tile i / DT, columns 16 (i % DT)
         const uint32_t at = (Vt ^ (32 * (i % DT))) + 64 * (i / DT) * D;
@@ -329,27 +329,32 @@ __device__ __forceinline__ void tile_step(uint32_t Kt, uint32_t Vt, const Frag (
     for (int i = 0; i < NSUB * DT; ++i) {
         const int sub = i / DT, dt = i % DT;
         if (i + VB - 1 < NSUB * DT && i > 0) load_v(i + VB - 1);
-        __builtin_amdgcn_sched_barrier(0);
+        if (!LONE) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int qc = 0; qc < 2; ++qc) {
             st.o[dt][qc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[i % VB].v, pb[sub][qc].v, st.o[dt][qc], 0, 0, 0);
             st.o[dt][qc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[i % VB].v, pl[sub][qc].v, st.o[dt][qc], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+            if (!LONE) __builtin_amdgcn_sched_barrier(0);
         }
     }
 }
 
-// The part of the tile at k0 (at LDS byte address `tile`) that the wave with first query q0 can see (k0 <= q0).
-template <int D>
+// The part of the tile of BN keys at k0 (at LDS byte address `tile`) that the wave with first query q0 can see (k0 <= q0).
+template <int D, int BN, bool LONE = false>
 __device__ __forceinline__ void consume_tile(uint32_t tile, int k0, int q0, const Frag (&qf)[2][D / 32], WaveRows<D>& st, float scale_l2,
                                              const LaneMap<D>& lm, int c, int g, const Window& win) {
-    const uint32_t Kt = tile + lm.k, Vt = tile + 2 * TileLayout<D>::TILE + lm.v;
-    if (k0 + kBN <= q0)         // below the diagonal: all 64 keys visible to all 32 rows
-        tile_step<D, 2, false>(Kt, Vt, qf, st, scale_l2, c, g, k0, win);
-    else if (k0 + 32 == q0)     // first half visible, second half on the diagonal
-        tile_step<D, 2, true>(Kt, Vt, qf, st, scale_l2, c, g, k0, win);
-    else                        // k0 == q0: first half on the diagonal, second half above it
-        tile_step<D, 1, true>(Kt, Vt, qf, st, scale_l2, c, g, k0, win);
+    const uint32_t Kt = tile + lm.k, Vt = tile + 2 * BN * D + lm.v;
+    if constexpr (BN == 32) {
+        if (k0 < q0) tile_step<D, 1, false, LONE>(Kt, Vt, qf, st, scale_l2, c, g, k0, win);
+        else tile_step<D, 1, true, LONE>(Kt, Vt, qf, st, scale_l2, c, g, k0, win);
+    } else {
+        if (k0 + BN <= q0)          // below the diagonal: all 64 keys visible to all 32 rows
+            tile_step<D, 2, false, LONE>(Kt, Vt, qf, st, scale_l2, c, g, k0, win);
+        else if (k0 + 32 == q0)     // first half visible, second half on the diagonal
+            tile_step<D, 2, true, LONE>(Kt, Vt, qf, st, scale_l2, c, g, k0, win);
+        else                        // k0 == q0: first half on the diagonal, second half above it
+            tile_step<D, 1, true, LONE>(Kt, Vt, qf, st, scale_l2, c, g, k0, win);
+    }
 }
 
 // Normalises and stores a wave's 32 x D block of outputs.
@@ -534,14 +539,7 @@ __global__ __launch_bounds__(256, BN == 32 ? 3 : 2) void prefill_mfma_kernel(Pre
     for (int t = 0; t < nt; ++t) {
         if (kRing == 2 && t + 1 < nt) issue(t + 1, next);
         const int k0 = t * BN;
-        const uint32_t tile = lds0 + slot * kBufBytes;
-        if (BN == 64) {
-            if (wave_live && k0 <= q0) consume_tile<D>(tile, k0, q0, qf, rows, a.scale_l2, lm, c, g, win);
-        } else {
-            const uint32_t Kt = tile + lm.k, Vt = tile + 2 * L::TILE + lm.v;
-            if (wave_live && k0 < q0) tile_step<D, 1, false>(Kt, Vt, qf, rows, a.scale_l2, c, g, k0, win);
-            else if (wave_live && k0 == q0) tile_step<D, 1, true>(Kt, Vt, qf, rows, a.scale_l2, c, g, k0, win);
-        }
+        if (wave_live && k0 <= q0) consume_tile<D, BN>(lds0 + slot * kBufBytes, k0, q0, qf, rows, a.scale_l2, lm, c, g, win);
         if (kRing == 3 && t + 2 < nt) {
             issue(t + 2, next);
             wait_direct_loads_but<2 * L::NI>();
@@ -560,17 +558,20 @@ __global__ __launch_bounds__(256, BN == 32 ? 3 : 2) void prefill_mfma_kernel(Pre
     keep_row_sums(a, win, bh, c, g, rows.m, l_tot);
 }
 
-// The same attention for launches that leave compute units idle (a short prompt, a single sequence).  128 / KS queries per
+// The same attention for launches that leave compute units idle (a short prompt, a few sequences).  128 / KS queries per
 // workgroup: its four waves are KS groups that own the same query blocks and take the key tiles in turn, tile i to group
 // i % KS, KS tiles at a time in LDS.  There are KS times the workgroups and each walks its tiles in a KS-th of the steps; at
-// the end group 0 merges the groups' (maximum, sum, accumulator) through LDS.  One workgroup per compute unit (128 KB of LDS:
-// KS = 2 keeps the next two tiles in flight, KS = 4 has room for the current four only).
+// the end group 0 merges the groups' (maximum, sum, accumulator) through LDS.  Bound by the latencies of a step: two workgroups per
+// compute unit (64 KB of LDS: tiles of 32 keys, KS = 2 keeps the next two in flight, KS = 4 has room for the current four only) hide
+// them from each other, and a wave, at two per SIMD, orders its reads and products as the compiler likes.  us a call, 32x32x16 MFMAs on
+// tiles of 64 keys and 128 KB, or without groups where those gained nothing -> so: 32 strips x 310 tokens 16.8 -> 13.5, 16 x 420 14.8 -> 13.4, 64 x 739
+// 35.6 -> 27.8, 40 x 739 33.9 -> 25.8, 20 x 1200 49.1 -> 35.5, 8 x 3000 106.7 -> 69.4; D = 64: 32 x 420 12.3 -> 10.8, 16 x 1500 36.8 -> 26.2.
 template <int D, int KS>
-__global__ __launch_bounds__(256, 1) void prefill_mfma_split_kernel(PrefillArgs a) {
-    using L = TileLayout<D>;
+__global__ __launch_bounds__(256, 2) void prefill_mfma_split_kernel(PrefillArgs a) {
+    constexpr int BN = 32, NBUF = KS == 2 ? 2 : 1;
+    using L = TileLayout<D, BN>;
     constexpr int DT = D / 16;
     constexpr int NB = 4 / KS;                          // 32-query blocks per workgroup
-    constexpr int NBUF = KS == 2 ? 2 : 1;
     constexpr int TILE2 = 2 * L::TILE;                  // elements of a K tile and its V tile
     __shared__ __attribute__((aligned(1024))) uint16_t buf[NBUF * KS * TILE2];
     __shared__ float sm_m[KS][NB][2][64], sm_l[KS][NB][2][64];
@@ -597,14 +598,14 @@ __global__ __launch_bounds__(256, 1) void prefill_mfma_split_kernel(PrefillArgs 
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     const uint32_t lds0 = lds_addr(buf);
     const int k_end = min(n, qt * (32 * NB) + 32 * NB - a.q_shift);     // keys this workgroup can see
-    const int nt = (k_end + kBN - 1) / kBN;
+    const int nt = (k_end + BN - 1) / BN;
     // the tiles of step s into buffer half s % NBUF (a tile past the last one is not loaded and not consumed)
     auto load_step = [&](int s) {
 #pragma unroll
         for (int i = 0; i < KS; ++i)
             if (s * KS + i < nt)
-                issue_tile<D>(lds0 + (uint32_t)(((s % NBUF) * KS + i) * TILE2 * 2), Kp, Vp, k_lane, v_lane, a.k_st, a.v_st,
-                              (s * KS + i) * kBN, n, lane, wave, wave_s);
+                issue_tile<D, BN>(lds0 + (uint32_t)(((s % NBUF) * KS + i) * TILE2 * 2), Kp, Vp, k_lane, v_lane, a.k_st, a.v_st,
+                              (s * KS + i) * BN, n, lane, wave, wave_s);
     };
     load_step(0);
     Frag qf[2][D / 32];
@@ -622,8 +623,8 @@ __global__ __launch_bounds__(256, 1) void prefill_mfma_split_kernel(PrefillArgs 
         __syncthreads();
         if (NBUF == 2 && s + 1 < steps) load_step(s + 1);
         const int t = s * KS + kg;
-        if (wave_live && t < nt && t * kBN <= q0)       // else the tile lies entirely above this wave's diagonal
-            consume_tile<D>(lds0 + ((s % NBUF) * KS + kg) * TILE2 * 2, t * kBN, q0, qf, rows, a.scale_l2, lm, c, g, win);
+        if (wave_live && t < nt && t * BN <= q0)       // else the tile lies entirely above this wave's diagonal
+            consume_tile<D, BN, true>(lds0 + ((s % NBUF) * KS + kg) * TILE2 * 2, t * BN, q0, qf, rows, a.scale_l2, lm, c, g, win);
         if (NBUF == 1 && s + 1 < steps) {
             __syncthreads();                            // every wave is done with the buffer
             load_step(s + 1);
@@ -671,22 +672,25 @@ __global__ __launch_bounds__(256, 1) void prefill_mfma_split_kernel(PrefillArgs 
     keep_row_sums(a, win, bh, c, g, rows.m, l_tot);
 }
 
-// Key groups for a launch (1: the kernel without groups): as many as leave every workgroup a place of its own at once.  The
-// device holds 256 workgroups of the split kernel at D = 128 (LDS), 512 at D = 64.  With one or two strips per dispatch lane
-// the lanes stay balanced a little beyond that.  Measured, us a call, 1 / 2 / 4 groups, D = 128 (strips x tokens): 8 x 739
-// 30 / 22.1 / 17.5, 16 x 420 20 / 17.2 / 13.6, 32 x 310 17 / 15.3 / 16.2, 32 x 739 31 / 23.9 / 31.4, 64 x 420 21.3 /
-// 19.6 / 32.1, but 24 x 739 31.1 / 32.0 / 35.2, 40 x 420 21.0 / 22.9 / 26.9, 64 x 560 26.4 / 29.9 / 44, 96 x 224 15.0 / 17.4; D = 64: 32 x 420
-// 16 / 13.5 / 10.8, 64 x 739 25.5 / 21.9 / 26.0, 96 x 560 23.8 / 23.5 / 26.5.  Prompts of one key tile leave a second group
-// nothing: 32 x 64, D = 128, 10.7 us with one group, 12.9 with four.  Few strips of D = 64 gain from four groups up to one and a
-// half times the places (2 / 4 groups: 8 x 3000 55.2 / 45.8, 12 x 2000 40.5 / 35.5, 16 x 1500 33.1 / 30.4, but 40 x 739 20.7 / 21.8).
+// Key groups for a launch (1: the kernel without groups).  The device holds 512 workgroups of the split kernel at D = 128, twice as many at
+// D = 64; groups pay while all workgroups find a place at once, and a little beyond where few strips are long.  us a call, 1 / 2 / 4 groups
+// (strips x tokens), D = 128:
+//   four while (n / 32) strips <= 256, or <= 768 with up to 12 strips: 8 x 739 30.4 / 21.4 / 17.2, 32 x 250 14.8 / 11.9 / 10.9, 8 x 2000 70.1 / 45.9 /
+//   39.1, 12 x 1500 54.1 / 42.2 / 37.3, 8 x 3000 100 / 71.4 / 69.4, 32 x 310 17.1 / 13.5 / 13.2, but 40 x 250 15.4 / 12.4 / 13.2, 20 x 500 22.9 / 17.2 / 18.1, 16 x 1500
+//   54.1 / 43.0 / 47.6, 8 x 5000 168 / 124 / 144
+//   two while (n / 64) strips <= 512, or <= 768 with up to 64 strips: 128 x 250 16.1 / 15.6, 80 x 300 18.2 / 16.5, 96 x 224 15.1 / 14.9, 64 x 739 33.4 / 27.8, 40 x
+//   1000 41.6 / 40.2, 32 x 1500 57.1 / 40.7, 16 x 3000 104 / 95.9, but 80 x 420 21.7 / 22.7, 160 x 200 16.0 / 17.7, 120 x 300 20.1 / 22.0; prompts of one
+//   query tile up to 128 strips: 128 x 100 10.9 / 10.6, 200 x 100 11.3 / 11.8
+// D = 64 (four up to 1024 or 1536, two up to 768 or 1536): 20 x 1000 30.8 / 24.6 / 21.5, 32 x 1000 31.3 / 21.7 / 17.7, 128 x 200 12.3 / 11.1 / 10.9, 16 x 3000 79.4 / 65.0 /
+// 59.4; 128 x 300 14.9 / 12.8 / 13.5, 256 x 150 11.7 / 10.8 / 13.5, 64 x 1500 47.7 / 45.7, but 256 x 200 14.5 / 15.8, 128 x 500 21.1 / 24.5, 160 x 380 17.6 / 18.9.
+// Prompts of one key tile leave a second group nothing: 32 x 64, D = 128, 10.7 us with one group, 12.9 with four.
 int key_groups(int D, int n, int64_t strips) {
     if (n <= kBN) return 1;
-    const int64_t places = D == 128 ? 256 : 512;
-    const int64_t four = (n + 31) / 32 * strips;
-    if (four <= places || (D == 64 && strips <= 16 && 2 * four <= 3 * places)) return 4;
-    const int64_t two = (n + 63) / 64 * strips;
-    if (two <= places || (strips % 32 == 0 && strips <= 64 && 4 * two <= 7 * places)) return 2;
-    return 1;
+    const bool d128 = D == 128;
+    const int64_t four = (n + 31) / 32 * strips, two = (n + 63) / 64 * strips;
+    if (four <= (d128 ? 256 : 1024) || (strips <= (d128 ? 12 : 16) && four <= (d128 ? 768 : 1536))) return 4;
+    if (n <= 128 && strips > (d128 ? 128 : 256)) return 1;
+    return two <= (d128 ? 512 : 768) || (strips <= 64 && two <= (d128 ? 768 : 1536)) ? 2 : 1;
 }
 
 // Whether a launch without key groups takes tiles of 64 keys (two workgroups per compute unit, shorter per workgroup) or of 32 (three,

@@ -1,4 +1,4 @@
-"""bf16 prefill attention on either side of the rule that picks 32- or 64-key tiles for launches without key groups, at the edges
+"""bf16 prefill attention on either side of the rules that pick key groups and, without those, 32- or 64-key tiles, at the edges
 of those tiles, against the same attention in 64 bits (bounds in _run)."""
 import pytest
 
@@ -27,6 +27,14 @@ def test_either_tile_at_the_rules_line(n, d, short_tiles):
 @pytest.mark.parametrize("window,sys_len,short", [(16, 33, 3), (5, 64, 30), (16, 0, 0)])
 def test_window_rows_and_visual_edges(d, short_tiles, window, sys_len, short):
     _run(*_strips(d, 200, short_tiles), d, 200, sys_len, 200 - sys_len - short, window)
+
+
+@pytest.mark.parametrize("B,H,d,n", [
+    (1, 8, 128, 1000), (4, 3, 128, 2047), (4, 3, 128, 2050), (1, 13, 128, 600), (8, 16, 128, 255), (8, 16, 128, 257), (3, 43, 128, 128),
+    (2, 32, 128, 767), (2, 32, 128, 770), (1, 16, 64, 3071), (1, 16, 64, 3073), (1, 17, 64, 1900), (16, 16, 64, 190), (16, 16, 64, 194),
+    (1, 257, 64, 128), (2, 32, 64, 1535)])
+def test_key_groups_at_the_rules_lines(B, H, d, n):
+    _run(B, H, d, n, 5, n - 20, 2)
 
 
 @pytest.mark.parametrize("d", [64, 128])
