@@ -275,6 +275,125 @@ __device__ __forceinline__ void attend_chunk(const DecodeArgs& a, const int spli
     }
 }
 
+// One workgroup: the whole strips of heads [h0, h1) of sequence b, one after the other (nsplit is 1).  What attend_chunk does for each, with
+// the next head's first tile on its way while the waves of the current one merge; and with `sums`, the mass's share of these heads is
+// added up here, since a whole strip's normaliser is known: instead of a logit for every head and visual row, one sum of probabilities for every
+// visual row leaves, in the place of head h0's logits.  Why: a write costs a streaming launch as much as reading ten times its bytes
+// (a plain kernel reads strips of 380 KB at 7.07 TB/s, with one KB written for each at 6.87, with two at 6.61, wherever the KB goes, whatever the store's policy
+// and moment).  Whole steps, us, with a logit for each head, with none (no mass wanted), with sums over up to 8 heads: 13B batch 32 2431, 2304, 2363, high
+// resolution batch 8 E4M3 638, 547, 594, 13B batch 8 with lazy layers 496, 470, 484.
+template <typename T, typename KT, int D, int U, bool NTS>
+__device__ __forceinline__ void attend_heads(const DecodeArgs& a, const int h0, const int h1, const int b, const bool sums, const int n_sums) {
+    using M = RowMap<KT, D>;
+    constexpr int EPL = M::EPL, LPR = M::LPR, TILE = U * M::RPL;
+    const int tid = threadIdx.x, lane0 = tid % kWave, wave = tid / kWave;
+    const int64_t bh0 = (int64_t)b * a.H + h0;
+    const KT* kb = reinterpret_cast<const KT*>(a.k) + b * a.stride_b;
+    const KT* vb = reinterpret_cast<const KT*>(a.v) + b * a.stride_b;
+    uint4 kr[U], vr[U];
+    const RowShift guess{a.hint_base, a.hint_gap};
+    issue_tile_within<KT, D, U, true>(kb + h0 * a.stride_h, vb + h0 * a.stride_h, a.stride_t, wave * TILE, a.chunk,
+                                     a.max_kv - (a.k_new != nullptr ? 1 : 0), 0, lane0, kr, vr, guess);
+    const int len_phys = min(a.kv_len[b] + (a.k_new != nullptr ? 1 : 0), a.max_kv);
+    const SeqLayout lay = seq_layout(a.sys_len, a.vis_len[b], a.max_vis, len_phys, a.tail_start, b);
+    const int len = lay.vlen;
+    const RowShift sh = lay.shift();
+    if (h0 == 0 && tid == 0 && a.pending != nullptr) {
+        a.pending[b * 4 + 0] = ((a.logits != nullptr && len > 0 && a.defer) ? 1 : 0) | (max(len, 0) << 1);
+        a.pending[b * 4 + 1] = a.nsplit;
+        a.pending[b * 4 + 2] = a.chunk;
+        a.pending[b * 4 + 3] = ((a.logits != nullptr && len > 0 && a.keep_all_logits) ? 1 : 0) | (lay.nv << 1);
+    }
+    if (len <= 0) {                                     // empty sequence: out = 0, no mass
+        for (int i = tid; i < (h1 - h0) * D; i += kDecodeThreads) store_out<T>(a.out, bh0 * D + i, 0.f);
+        return;
+    }
+    const int vis_lo = a.keep_all_logits ? 0 : a.sys_len;
+    const int vis_hi = a.keep_all_logits ? len : a.sys_len + lay.nv;
+    const bool has_new = a.k_new != nullptr && len_phys - 1 >= lay.base + lay.gap;
+    const int c1_cached = has_new ? len - 1 : len;
+    extern __shared__ float sm_lg[];
+    const int lg_lo = max(0, vis_lo), n_lg = min(len, vis_hi) - lg_lo;
+    float* lg_stage = a.logits != nullptr ? sm_lg : nullptr;
+    float* acc = sm_lg + n_sums;                        // a thread's own entries: i = tid, tid + 256, ...
+    __shared__ float sm_acc[kDecodeWaves][D];
+    __shared__ float sm_m[kDecodeWaves], sm_l[kDecodeWaves];
+    {
+        const int tile_end = min(wave * TILE + TILE, c1_cached);
+        const bool same = lay.gap == guess.gap && (lay.gap == 0 || lay.base == guess.split_row);
+        const bool in_front = tile_end <= lay.base && (guess.gap == 0 || tile_end <= guess.split_row);
+        if (!same && !in_front)
+            issue_tile<KT, D, U, true>(kb + h0 * a.stride_h, vb + h0 * a.stride_h, a.stride_t, wave * TILE, c1_cached, 0, lane0, kr, vr, sh);
+    }
+    for (int h = h0; h < h1; ++h) {
+        // (opaque: else what a lane works out for its first tile waits in registers from head to head)
+        int lane = lane0;
+        asm volatile("" : "+v"(lane));
+        const int64_t bh = (int64_t)b * a.H + h;
+        const KT* kbase = kb + h * a.stride_h;
+        const KT* vbase = vb + h * a.stride_h;
+        float qf[EPL];
+        load_row_slice<T, KT, D>(reinterpret_cast<const T*>(a.q) + bh * D, lane, qf);
+        const float k_unit = a.k_scale ? a.k_scale[bh] : 1.0f, v_unit = a.v_scale ? a.v_scale[bh] : 1.0f;
+        const float scale_l2 = a.scale_l2 * k_unit;
+        u32x4_t kn_raw = {0, 0, 0, 0}, vn_raw = {0, 0, 0, 0};
+        if (has_new && wave == 0)
+            NewRow<T, KT, D>::load_by_wave(reinterpret_cast<const T*>(a.k_new) + bh * D, reinterpret_cast<const T*>(a.v_new) + bh * D,
+                                           lane, k_unit, v_unit, kn_raw, vn_raw);
+#pragma unroll
+        for (int u = 0; u < U; ++u)                     // (rows past the end may hold anything)
+            if (wave * TILE + u * M::RPL + lane / LPR >= c1_cached) vr[u] = make_uint4(0, 0, 0, 0);
+        WaveState<EPL> st;
+        wave_attend_primed<KT, D, U, true>(qf, kbase, vbase, a.stride_t, wave * TILE, c1_cached, kDecodeWaves * TILE, 0, scale_l2, lane, st,
+                                           lg_stage, lg_lo, vis_hi, kr, vr, sh);
+        if (has_new && wave == 0) {
+            wave_attend_row<KT, D>(qf, make_uint4(kn_raw.x, kn_raw.y, kn_raw.z, kn_raw.w), make_uint4(vn_raw.x, vn_raw.y, vn_raw.z, vn_raw.w),
+                                   len - 1, scale_l2, lane, st, lg_stage, lg_lo, vis_hi);
+            if (lane < 2 * LPR) {
+                KT* dst = const_cast<KT*>(lane < LPR ? kbase : vbase) + (int64_t)(len_phys - 1) * a.stride_t + (lane % LPR) * EPL;
+                store_hint<NTS>(reinterpret_cast<u32x4_t*>(dst), lane < LPR ? kn_raw : vn_raw);
+            }
+        }
+        finish_wave<KT, D>(st);
+        if (lane < LPR) {
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) sm_acc[wave][lane * EPL + e] = st.acc[e];
+        }
+        if (lane == 0) { sm_m[wave] = st.m; sm_l[wave] = st.l; }
+        asm volatile("" : "+v"(lane));
+        if (h + 1 < h1)
+            issue_tile<KT, D, U, true>(kbase + a.stride_h, vbase + a.stride_h, a.stride_t, wave * TILE, c1_cached, 0, lane, kr, vr, sh);
+        __syncthreads();
+        float m = sm_m[0], l = 0.f, f[kDecodeWaves];
+#pragma unroll
+        for (int w = 1; w < kDecodeWaves; ++w) m = fmaxf(m, sm_m[w]);   // finite (WaveState)
+#pragma unroll
+        for (int w = 0; w < kDecodeWaves; ++w) {
+            f[w] = exp2_fast(sm_m[w] - m);              // wave without rows: its sums are 0
+            l = fmaf(sm_l[w], f[w], l);
+        }
+        if (tid < D) {
+            float o = 0.f;
+#pragma unroll
+            for (int w = 0; w < kDecodeWaves; ++w) o = fmaf(sm_acc[w][tid], f[w], o);
+            store_out<T, NTS>(a.out, bh * D + tid, o / l * v_unit);
+        }
+        if (sums) {
+            const float rl = 1.0f / l;
+            for (int i = tid; i < n_lg; i += kDecodeThreads) {
+                const float p = exp2_fast(sm_lg[i] - m) * rl, s = h == h0 ? p : acc[i] + p;
+                if (h + 1 < h1) acc[i] = s;
+                else store_hint<NTS>(a.logits + bh0 * a.capacity + lg_lo + i, s);
+            }
+        } else if (lg_stage != nullptr) {
+            float* lg = a.logits + bh * a.capacity + lg_lo;
+            for (int i = tid; i < n_lg; i += kDecodeThreads) store_hint<NTS>(lg + i, sm_lg[i]);
+            if (tid == 0) { a.part_ml[bh * a.nsplit_cap * 2] = m; a.part_ml[bh * a.nsplit_cap * 2 + 1] = l; }
+        }
+        __syncthreads();                                // (the next head's waves write the logits' and the sums' places)
+    }
+}
+
 // grid (nsplit, H, B)
 template <typename T, typename KT, int D, int U>
 __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS)
@@ -304,6 +423,32 @@ __device__ __forceinline__ StepWork step_work(const StepCommon& c) {
     w.b = z - w.li * c.B;
     return w;
 }
+// The same of a launch of groups of heads, whose grid is a line: rank_z workgroups that rank, then the layers' groups, of 8, 4, 2 and 1 heads
+// (w.h is the first one, `heads` how many).
+__device__ __forceinline__ StepWork step_work_grouped(const StepCommon& c, int& heads) {
+    StepWork w;
+    w.split = 0;
+    int x = (int)blockIdx.x, first = 0, per = 1;        // per: workgroups of a (layer, sequence)
+    w.ranks = x < c.rank_z;
+    heads = 1;
+    if (!w.ranks) {
+        x -= c.rank_z;
+        per = c.H;
+#pragma unroll
+        for (int i = 0, g = 8; i < 3; ++i, g /= 2) {
+            const int p = (c.H + g - 1) / g, all = c.groups[i] * c.B * p;
+            if (heads == 1) {
+                if (x < all) { heads = g; per = p; }
+                else { x -= all; first += c.groups[i]; }
+            }
+        }
+    }
+    const int y = __builtin_amdgcn_readfirstlane(x / per), z = __builtin_amdgcn_readfirstlane(y / c.B);
+    w.h = (x - y * per) * heads;
+    w.li = first + z;
+    w.b = y - z * c.B;
+    return w;
+}
 __device__ __forceinline__ void rank_workgroup(const StepCommon& c, const StepLayer& e, int b) {
     if (!(e.flags & kStepApart) || e.keep_count < 0) return;
     __shared__ SelectShared sm;
@@ -322,14 +467,17 @@ __device__ __forceinline__ void leave_entry(const StepTable& t, const StepLayer&
 // its bytes).  Whole step, us, one launch per layer -> up to 35 layers per launch: 7B batch 1 191 -> 42 (209 MB), 13B batch 8
 // with lazy layers 707 -> 496 (2.9 GB), high resolution batch 8 E4M3 830 -> 618 (3.6 GB), 13B batch 32 2514 -> 2407 (15.4 GB,
 // 6.4 TB/s; a kernel that only reads the same rows takes 2155).
-// ANY: the table may be wide, and the entries may be left for the plans (a build of its own: these cost 0.1 to 0.4 us a step at the
-// start of every workgroup).
-template <typename T, typename KT, int D, int U, bool NTS, bool ANY>
+// FORM: kStepPlain; kStepAny: the table may be wide, and the entries may be left for the plans (a build of its own: these cost 0.1 to 0.4 us a step at the
+// start of every workgroup); kStepGroups: workgroups of whole strips of several heads (c.groups), in a grid that is a line.
+enum StepForm { kStepPlain, kStepAny, kStepGroups };
+template <typename T, typename KT, int D, int U, bool NTS, StepForm FORM>
 __global__ __launch_bounds__(kDecodeThreads, ST3_DECODE_MIN_BLOCKS)
 __attribute__((amdgpu_waves_per_eu(ST3_DECODE_MIN_BLOCKS, ST3_DECODE_MIN_BLOCKS)))
 void decode_attend_layers_kernel(StepTable t) {
+    constexpr bool ANY = FORM == kStepAny;
     const StepCommon& c = t.c;
-    const StepWork w = step_work(c);
+    int heads = 1;
+    const StepWork w = FORM == kStepGroups ? step_work_grouped(c, heads) : step_work(c);
     if (w.li >= c.layers) return;
     constexpr bool coded = sizeof(KT) == 1;
     constexpr int words = coded ? kAttendWordsE4M3 : kAttendWords;
@@ -354,7 +502,12 @@ void decode_attend_layers_kernel(StepTable t) {
     a.stage_rows = 0;           // (the launcher's)
     a.pending = reinterpret_cast<int32_t*>(e.ws + wl.pending);
     a.k_new = e.k_new; a.v_new = e.v_new; a.out = e.out;
-    attend_chunk<T, KT, D, U, NTS>(a, w.split, w.h, w.b);
+    if constexpr (FORM == kStepGroups) {
+        const bool sums = (e.flags & kStepSums) != 0;
+        attend_heads<T, KT, D, U, NTS>(a, w.h, min(c.H, w.h + heads), w.b, sums, sums ? e.max_vis : 0);
+    } else {
+        attend_chunk<T, KT, D, U, NTS>(a, w.split, w.h, w.b);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -769,15 +922,23 @@ template <typename T, typename KT, int D>
 void launch_attend_layers(const StepTable& t, int lds_words, bool stream, hipStream_t st) {
     const dim3 grid(t.c.H, t.c.chunks, t.c.rank_z + t.c.B * t.c.layers);
     const size_t lds = (size_t)lds_words * sizeof(float);
+    constexpr int U0 = first_tile(AttendTiles<KT>{});
     if (t.c.wide || t.c.leave) {
-        constexpr int U = first_tile(AttendTiles<KT>{});
-        if (stream) launch_timed(decode_attend_layers_kernel<T, KT, D, U, true, true>, grid, lds, st, t.c.layers, t);
-        else launch_timed(decode_attend_layers_kernel<T, KT, D, U, false, true>, grid, lds, st, t.c.layers, t);
+        if (stream) launch_timed(decode_attend_layers_kernel<T, KT, D, U0, true, kStepAny>, grid, lds, st, t.c.layers, t);
+        else launch_timed(decode_attend_layers_kernel<T, KT, D, U0, false, kStepAny>, grid, lds, st, t.c.layers, t);
+        return;
+    }
+    if (t.c.groups[3]) {
+        int per_sequence = 0, left = t.c.layers;
+        for (int i = 0, g = 8; i < 3; ++i, g /= 2) { per_sequence += t.c.groups[i] * ((t.c.H + g - 1) / g); left -= t.c.groups[i]; }
+        const dim3 line(t.c.rank_z + t.c.B * (per_sequence + left * t.c.H));
+        if (stream) launch_timed(decode_attend_layers_kernel<T, KT, D, U0, true, kStepGroups>, line, lds, st, t.c.layers, t);
+        else launch_timed(decode_attend_layers_kernel<T, KT, D, U0, false, kStepGroups>, line, lds, st, t.c.layers, t);
         return;
     }
     with_tile(AttendTiles<KT>{}, 0, [&](auto u) {
-        if (stream) launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, true, false>, grid, lds, st, t.c.layers, t);
-        else launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, false, false>, grid, lds, st, t.c.layers, t);
+        if (stream) launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, true, kStepPlain>, grid, lds, st, t.c.layers, t);
+        else launch_timed(decode_attend_layers_kernel<T, KT, D, decltype(u)::value, false, kStepPlain>, grid, lds, st, t.c.layers, t);
     });
 }
 
@@ -1026,6 +1187,21 @@ static bool rank_beside(int rows, int heads, int64_t strips, int many_moves) {
     return rows <= 1024 || (187 - 10 * heads - strips - 20 * (int64_t)many_moves) * rows <= 270000;
 }
 
+// Heads that a workgroup takes one after the other, where no strip is cut and the rows are ranked beside the attention: the more, the fewer
+// sums of the mass are written (attend_heads), as long as there are workgroups enough.  GROUP_FIGURES
+// Heads that the workgroups of a layer of so many rows take one after the other (attend_heads), where rows are ranked beside the attention
+// and no strip is cut: the more, the fewer sums of the mass are written; but the launch must not end waiting for a long workgroup, so one takes no more
+// rows than a 384th of what the launch has behind the layer (`behind`), and the last layers go head by head.  Layers are visited in order: the number falls from layer
+// to layer.  us a step, head by head / a share of 768 / 384 / 256 / 128 (or 8 heads always): 13B batch 32 2431 / 2367 / 2363 / 2369 / 2363 (2391), high
+// resolution batch 8 E4M3 638 / 607 / 594 / 588 / 598 (595), bf16 1183 / 1143 / 1124 / 1121 / 1153 (1143), 13B batch 8 642 / 630 / 626 / 627 / 629 (700), with lazy
+// layers 496 / 489 / 484 / 498 / 492 (489), 7B batch 4 146 / 144 / 143 / 158 / 157, 8 layers of 12 heads, batch 32 53.3 / 53.2 / 52.1 / 58.5 / 62.6, D = 64, batch 16 276 / 269 / 264 / 262 /
+// 264.  Float32 rows are twice as long for the same logit and lose: 8 layers of 16 heads, batch 8 59.4 / 59.6 / 60.2.
+static int heads_together(int H, int64_t rows, int64_t behind) {
+    int g = 8;
+    while (g > 1 && (g > H || g * rows * 384 > behind)) g /= 2;
+    return g;
+}
+
 // Attention of every layer of a checked step: the ordinary layers, as many per launch as its table holds, then the lazy ones, caches of
 // either format in launches of their own (32 layers of the 7B shape, every other cache E4M3, us a step, layer by layer -> so:
 // batch 1 377 -> 60, batch 8 482 -> 290).
@@ -1036,7 +1212,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
                                const char* has_heirs, const EvictArgs* plan, char* needs_apply, StepCommon& common, StepLayer* e,
                                PlanNeeds& needs, hipStream_t st) {
     const int B = shape->batch, H = shape->heads, D = shape->head_dim;
-    common = StepCommon{B, H, D, (int16_t)mode, (int16_t)elem_bytes(shape->dtype), scale_log2(shape), 0, 0, 0, 0, 0};
+    common = StepCommon{B, H, D, (int16_t)mode, (int16_t)elem_bytes(shape->dtype), scale_log2(shape), 0, 0, 0, 0, 0, {0, 0, 0, 0}};
     int64_t rows[2] = {0, 0};           // of the ordinary and of the lazy layers
     int as_long = 0, shorter = 0;       // layers in which most sequences hold as many rows as the bound says, by the hint, or may not
     for (int i = 0; i < n_layers; ++i) {
@@ -1052,6 +1228,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
     std::vector<char> moves_here((size_t)n_layers, 0);
     std::vector<int> stage((size_t)n_layers, 0), groups[4];     // layers that may share launches, in launch order
     // (grid z is rank_z + B * layers, at most 65535)
+    bool cut = false;                   // some ordinary layer's strips are
     needs = PlanNeeds{0, false, max_layers_ranked(B, H) > 0, 0};
     int most_ranked = 0, many_moves = 0;        // rows of a layer that evicts; layers that evict more rows than a plan moves by itself
     for (int i = 0; i < n_layers; ++i) {
@@ -1082,6 +1259,7 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
         nsplit = (len + s.chunk - 1) / s.chunk;
         s.nsplit = (uint8_t)nsplit; s.nsplit_cap = (uint8_t)wl.nsplit_cap;
         needs.merge = needs.merge || nsplit > 1;
+        cut = cut || (!lazy && nsplit > 1);
         // Rows are moved by as many workgroups as they need, so however many an eviction moves, unless the order of the moves
         // matters (STABLE) or a strip's moves must stay together (a tail that closes up) and are many.  A launch of its own per
         // layer for more than 48 rows, as the other forms have it, before -> after, us a step: 7B shape evicting 50 rows a layer, batch 1
@@ -1121,6 +1299,8 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
     }
     for (int i = 0; i < n_layers; ++i)                  // (from here on nothing is refused)
         if (moves_here[(size_t)i]) needs_apply[i] = 0;
+    // (the builds that the diagnostic switch asks for have no groups)
+    const bool whole = needs.apart && !common.wide && !cut && debug_state().attend_tile == 0;
     for (const std::vector<int>& members : groups) {
         const int n = (int)members.size();
         if (n == 0) continue;
@@ -1135,6 +1315,23 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
             const st3_kv_layer* kv = &layers[first].kv;
             StepTable t;
             t.c = common; t.c.layers = cnt;
+            if (whole && !lazy && kv_elem_bytes(shape, kv) <= 2) {
+                int64_t behind = 0;                     // rows of the launch behind a layer
+                for (int j = 0; j < cnt; ++j) behind += (int64_t)B * H * (e[members[(size_t)(i0 + j)]].max_kv + 1);
+                int g = 8;
+                for (int j = 0; j < cnt; ++j) {
+                    StepLayer& s = e[members[(size_t)(i0 + j)]];
+                    behind -= (int64_t)B * H * (s.max_kv + 1);
+                    g = std::min(g, heads_together(H, s.max_kv + 1, behind));
+                    if (g == 1) break;
+                    t.c.groups[g == 8 ? 0 : g == 4 ? 1 : 2] += 1;
+                    t.c.groups[3] = 1;
+                    if ((s.flags & (kStepWantMass | kStepKeepAll)) != kStepWantMass || s.max_vis > kLogitStageMaxRows) continue;
+                    s.flags |= kStepSums;
+                    s.src_nsplit_cap = (uint8_t)g;
+                    stage[(size_t)members[(size_t)(i0 + j)]] = 2 * s.max_vis;   // a head's logits and the sums
+                }
+            }
             int64_t written = (int64_t)cnt * B * H * D * (2 * kv_elem_bytes(shape, kv) + elem_bytes(shape->dtype));
             int most = 1, lds_words = 0, ranked = 0;    // dynamic LDS: the logits a workgroup collects, or the keys it ranks
             for (int j = 0; j < cnt; ++j) {
@@ -1143,11 +1340,11 @@ st3_status enqueue_step_attend(const st3_attn_shape* shape, int n_layers, const 
                 most = std::max(most, (int)e[i].nsplit);
                 lds_words = std::max(lds_words, stage[(size_t)i]);
                 if (e[i].flags & kStepKeepAll) written += (int64_t)B * H * e[i].max_kv * sizeof(float);
-                else if (e[i].flags & kStepWantMass) written += (int64_t)B * H * e[i].max_vis * sizeof(float);
+                else if (e[i].flags & kStepWantMass) written += (int64_t)B * ((e[i].flags & kStepSums) ? (H + e[i].src_nsplit_cap - 1) / e[i].src_nsplit_cap : H) * e[i].max_vis * sizeof(float);
                 if ((e[i].flags & kStepApart) && e[i].keep_count >= 0) { lds_words = std::max(lds_words, e[i].max_vis); ranked += 1; }
             }
             t.c.chunks = (int16_t)most;
-            t.c.rank_z = ranked > 0 ? rank_rows_z(B, H, most, cnt) : 0;
+            t.c.rank_z = ranked == 0 ? 0 : t.c.groups[3] ? B * cnt : rank_rows_z(B, H, most, cnt);
             if (lazy) ST3_DISPATCH_KV(launch_inherit_layers, shape, kv, t, lds_words, st);
             else ST3_DISPATCH_KV(launch_attend_layers, shape, kv, t, lds_words, written > kStreamStoreBytes, st);
             i0 += cnt;

@@ -577,6 +577,35 @@ __device__ __forceinline__ void mass_block(const EvictArgs& a, int b, int j0, Ma
     }
 }
 
+// The same where the attention has left sums of probabilities over its groups of heads (kStepSums): `groups` rows, `step` heads apart.
+template <int NT>
+__device__ __forceinline__ void mass_sums_block(const EvictArgs& a, int b, int j0, int groups, int step, MassShared<NT>& sm) {
+    constexpr int kWaves = NT / kWave, kUR = 8;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), lane = threadIdx.x % kWave, j = j0 + 4 * lane;
+    const int per = (groups + kWaves - 1) / kWaves, g0 = min(groups, wave * per), g1 = min(groups, g0 + per);
+    const float* at = a.logits + a.sys_len + (int64_t)b * a.H * a.capacity + j;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    for (int g = g0; g < g1; g += kUR) {
+        f32x4_t v[kUR];
+#pragma unroll
+        for (int u = 0; u < kUR; ++u)
+            if (j < a.max_vis && g + u < g1) v[u] = *reinterpret_cast<const f32x4_a4_t*>(at + (int64_t)(g + u) * step * a.capacity);
+#pragma unroll
+        for (int u = 0; u < kUR; ++u)
+            if (g + u < g1) acc += v[u];
+    }
+    const int n = (a.pending[b * 4] & 1) ? min(a.own_pending[b * 4 + 3] >> 1, a.max_vis) : 0;      // (0: no mass is pending)
+    if (j0 >= n) return;                                // (uniform)
+    sm.part[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0 && j < n) {
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) acc += sm.part[w][lane];
+        float* out = a.mass_dst + b * a.mass_stride + j;
+        for (int i = 0; i < min(4, n - j); ++i) out[i] = acc[i] * (1.0f / (float)a.H);
+    }
+}
+
 // ---- host side (defined in st3_select.hip) --------------------------------------------------
 // Fills the plan arguments for one layer; needs_apply tells whether evict_apply_kernel must run
 // after the plan (evictions too large for the plan workgroup to move, or STABLE mode).

@@ -484,7 +484,10 @@ __global__ __launch_bounds__(256) void step_finish_kernel(StepTable t, int move_
     if (z < move_wgs + mass_wgs) {
         const EvictArgs a = plan_from_entry(t.c, e);
         if (z >= move_wgs) {
-            if (a.mass_dst != nullptr) mass_block<256>(a, b, (z - move_wgs) * kMassKeys, sm);
+            const int j0 = (z - move_wgs) * kMassKeys;
+            if (a.mass_dst == nullptr) return;
+            if (e.flags & kStepSums) mass_sums_block<256>(a, b, j0, (t.c.H + e.src_nsplit_cap - 1) / e.src_nsplit_cap, e.src_nsplit_cap, sm);
+            else mass_block<256>(a, b, j0, sm);
             return;
         }
         if (z == 0 && threadIdx.x == 0) evict_publish(a, b, evict_counts(a, b));

@@ -32,6 +32,8 @@ struct StepCommon {
     int8_t leave;               // 1: the attention leaves its entries in the layers' workspaces (kLeftWords)
     int16_t chunks;             // most chunks of any layer: the attention's grid is (H, chunks, rank_z + B * layers)
     int32_t rank_z;             // the grid's first z: its workgroups rank rows, one for each (layer, sequence); 0: no row is ranked
+    int8_t groups[4];           // layers of an attention's table whose workgroups take 8, 4, 2 heads (in this order) one after the other, and 1: the
+                                // others; groups[3]: 1 where the grid is for that (no strip is cut then), else 0
 };
 
 struct StepLayer {
@@ -58,11 +60,12 @@ struct StepLayer {
     int32_t hint_base, hint_gap;            // layout_hint; lazy layer: hint_base is the source cache's capacity
     int32_t capacity;
     uint8_t nsplit, nsplit_cap; // chunks per strip of this launch / that the workspace has room for (at most 64)
-    uint8_t src_nsplit_cap;     // lazy layer: of the source's workspace
+    uint8_t src_nsplit_cap;     // lazy layer: of the source's workspace; kStepSums: heads of a sum
     uint8_t flags;
 };
 constexpr uint8_t kStepInlineApply = 1, kStepKeepAll = 2, kStepLazy = 4, kStepWantMass = 8, kStepE4M3 = 16;
 constexpr uint8_t kStepApart = 32;      // the next eviction does not rank by this step's mass
+constexpr uint8_t kStepSums = 64;       // the attention leaves sums of probabilities over its groups of heads, in the logits' place, instead of logits
 
 // Words of an entry: pointers (low words, then high halves in pairs), then ten or eleven words of numbers.
 constexpr int kAttendPtrs = 12, kAttendPtrsE4M3 = 14, kFinishPtrs = 9, kPlanPtrs = 11;
@@ -86,7 +89,7 @@ struct StepTable {
     StepCommon c;
     uint32_t w[kStepTableWords];
 };
-static_assert(sizeof(StepTable) <= 4000, "the table travels by value");
+static_assert(sizeof(StepTable) <= 4016, "the table travels by value, two words beside it in some launches");
 
 // Slices (z) of the attention's grid that ranking takes: a workgroup for each (layer, sequence) of the launch.
 inline int rank_rows_z(int B, int H, int chunks, int layers) {
