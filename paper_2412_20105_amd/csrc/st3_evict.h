@@ -580,11 +580,12 @@ __device__ __forceinline__ void mass_block(const EvictArgs& a, int b, int j0, Ma
 // The same where the attention has left sums of probabilities over its groups of heads (kStepSums): `groups` rows, `step` heads apart.
 template <int NT>
 __device__ __forceinline__ void mass_sums_block(const EvictArgs& a, int b, int j0, int groups, int step, MassShared<NT>& sm) {
-    constexpr int kWaves = NT / kWave, kUR = 8;
+    constexpr int kWaves = NT / kWave, kUR = 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), lane = threadIdx.x % kWave, j = j0 + 4 * lane;
     const int per = (groups + kWaves - 1) / kWaves, g0 = min(groups, wave * per), g1 = min(groups, g0 + per);
     const float* at = a.logits + a.sys_len + (int64_t)b * a.H * a.capacity + j;
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1                                        // (unrolled, the launch takes 241 registers instead of 125, and its rows move a quarter slower)
     for (int g = g0; g < g1; g += kUR) {
         f32x4_t v[kUR];
 #pragma unroll
