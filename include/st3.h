@@ -162,6 +162,16 @@ ST3_EXPORT st3_status st3_prefill_attention(const st3_attn_shape* shape, const s
                                  int32_t score_window, const st3_tensor4* out, float* vis_mass,
                                  int64_t mass_stride, void* workspace, size_t workspace_bytes, void* stream);
 
+/* The same with queries that still lie where the unpruned prompt has them (Alg. 1 / Alg. 3, X = [S, V[T], I] without a copy of Q): row i of
+ * the prompt attended is row i of q for i < sys_len, row sys_len + q_ids[b*q_ids_stride + i - sys_len] for the vis_len visual ones
+ * (DEVICE int32, each in [0, q_vis); what lies outside reads the nearest row), and row i - vis_len + q_vis behind them:
+ * the rows that st3_gather_rows would have brought together.  q has n - vis_len + q_vis rows, q_vis >= vis_len.  k, v, out and the mass
+ * are as above. */
+ST3_EXPORT st3_status st3_prefill_attention_kept(const st3_attn_shape* shape, const st3_tensor4* q, const int32_t* q_ids,
+                                 int64_t q_ids_stride, int32_t q_vis, const st3_tensor4* k, const st3_tensor4* v, int32_t n,
+                                 int32_t sys_len, int32_t vis_len, int32_t score_window, const st3_tensor4* out,
+                                 float* vis_mass, int64_t mass_stride, void* workspace, size_t workspace_bytes, void* stream);
+
 /* ---------------------------------------------------------------------------------------------
  * Writes rows [0, n) of a [B,H,n,d] tensor of shape->dtype into rows [0, n) of a cache's K
  * (which = 0) or V (which = 1) in the cache's own format: a copy for ST3_KV_PLAIN, the E4M3

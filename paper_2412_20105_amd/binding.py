@@ -27,7 +27,7 @@ ST3_ANNEAL_COS, ST3_ANNEAL_LINEAR, ST3_ANNEAL_EXP, ST3_ANNEAL_DROP, ST3_ANNEAL_N
 
 EXPORTED = [
     "st3_status_string", "st3_last_hip_error", "st3_version", "st3_workspace_bytes", "st3_workspace_init",
-    "st3_prefill_attention", "st3_quantize_rows", "st3_kv_append", "st3_decode_attention", "st3_decode_attention_inherit",
+    "st3_prefill_attention", "st3_prefill_attention_kept", "st3_quantize_rows", "st3_kv_append", "st3_decode_attention", "st3_decode_attention_inherit",
     "st3_decode_attention_noalloc", "st3_select_topk",
     "st3_compact_rows", "st3_gather_rows", "st3_select_compact_layer", "st3_decode_layer_step", "st3_decode_step",
     "st3_decode_layer_attend", "st3_decode_plans", "st3_select_columns", "st3_select_compact_layers",
@@ -109,6 +109,10 @@ def lib() -> C.CDLL:
         L.st3_prefill_attention.argtypes = [P(AttnShape), P(Tensor4), P(Tensor4), P(Tensor4), C.c_int32, C.c_int32,
                                             C.c_int32, C.c_int32, P(Tensor4), C.c_void_p, C.c_int64, C.c_void_p,
                                             C.c_size_t, C.c_void_p]
+        L.st3_prefill_attention_kept.argtypes = [P(AttnShape), P(Tensor4), C.c_void_p, C.c_int64, C.c_int32, P(Tensor4), P(Tensor4),
+                                                 C.c_int32, C.c_int32, C.c_int32, C.c_int32, P(Tensor4), C.c_void_p, C.c_int64,
+                                                 C.c_void_p, C.c_size_t, C.c_void_p]
+        L.st3_prefill_attention_kept.restype = C.c_int
         L.st3_quantize_rows.argtypes = [P(AttnShape), P(Tensor4), P(KvLayer), C.c_int32, C.c_int32, C.c_void_p]
         L.st3_quantize_rows.restype = C.c_int
         L.st3_kv_append.argtypes = [P(AttnShape), P(KvLayer), P(Segments), C.c_void_p, C.c_void_p, C.c_void_p]
@@ -271,6 +275,15 @@ def st3_prefill_attention(shape, q, k, v, n, sys_len, vis_len, score_window, out
                                        score_window, C.byref(to), _ptr(vis_mass), ms, _ptr(workspace),
                                        0 if workspace is None else workspace.numel() * workspace.element_size(),
                                        _stream(stream)), "st3_prefill_attention")
+
+
+def st3_prefill_attention_kept(shape, q, q_ids, q_vis, k, v, n, sys_len, vis_len, score_window, out, vis_mass, workspace, stream=None):
+    tq, tk, tv, to = tensor4(q), tensor4(k), tensor4(v), tensor4(out)
+    ms = 0 if vis_mass is None else vis_mass.stride(0)
+    _check(lib().st3_prefill_attention_kept(C.byref(shape), C.byref(tq), q_ids.data_ptr(), q_ids.stride(0), q_vis, C.byref(tk),
+                                            C.byref(tv), n, sys_len, vis_len, score_window, C.byref(to), _ptr(vis_mass), ms,
+                                            _ptr(workspace), 0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                            _stream(stream)), "st3_prefill_attention_kept")
 
 
 def st3_quantize_rows(shape, src, kv: KvLayer, which: int, n: int, stream=None):

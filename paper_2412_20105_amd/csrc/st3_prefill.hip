@@ -25,7 +25,7 @@ __global__ __launch_bounds__(256) void prefill_rows_kernel(PrefillArgs a) {
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const int i = a.n - 1 - ((int)blockIdx.x * kRowsPerBlock + wave);
     if (i < 0) return;
-    const T* qrow = reinterpret_cast<const T*>(a.q) + b * a.q_sb + h * a.q_sh + (int64_t)i * a.q_st;
+    const T* qrow = reinterpret_cast<const T*>(a.q) + b * a.q_sb + h * a.q_sh + (int64_t)query_row(a, b, i) * a.q_st;
     const T* kbase = reinterpret_cast<const T*>(a.k) + b * a.k_sb + h * a.k_sh;
     const T* vbase = reinterpret_cast<const T*>(a.v) + b * a.v_sb + h * a.v_sh;
     float qf[EPL];
@@ -114,12 +114,11 @@ bool tensor_ok(const st3_tensor4* t, int eb, int d) {
 }  // namespace
 }  // namespace st3
 
-extern "C" st3_status st3_prefill_attention(const st3_attn_shape* shape, const st3_tensor4* q, const st3_tensor4* k,
-                                            const st3_tensor4* v, int32_t n, int32_t sys_len, int32_t vis_len,
-                                            int32_t score_window, const st3_tensor4* out, float* vis_mass,
-                                            int64_t mass_stride, void* workspace, size_t workspace_bytes,
-                                            void* stream) {
-    using namespace st3;
+namespace st3 {
+static st3_status prefill_attention(const st3_attn_shape* shape, const st3_tensor4* q, const int32_t* q_ids, int64_t q_ids_stride, int32_t q_vis,
+                                    const st3_tensor4* k, const st3_tensor4* v, int32_t n, int32_t sys_len, int32_t vis_len,
+                                    int32_t score_window, const st3_tensor4* out, float* vis_mass, int64_t mass_stride, void* workspace,
+                                    size_t workspace_bytes, void* stream) {
     st3_status s = check_shape(shape);
     if (s != ST3_OK) return s;
     const int B = shape->batch, H = shape->heads, D = shape->head_dim, eb = elem_bytes(shape->dtype);
@@ -147,6 +146,7 @@ extern "C" st3_status st3_prefill_attention(const st3_attn_shape* shape, const s
     a.o_sb = out->stride_b; a.o_sh = out->stride_h; a.o_st = out->stride_t;
     a.n = n; a.sys_len = sys_len; a.vis_len = vis_len; a.window = score_window; a.H = H;
     a.scale_l2 = scale_log2(shape);
+    a.q_ids = q_ids; a.q_ids_sb = q_ids_stride; a.q_vis = q_vis;
     if (want_mass) {
         char* ws = reinterpret_cast<char*>(workspace) + ws_base;
         a.pre_logits = reinterpret_cast<float*>(ws + wl.pre_logits);
@@ -180,4 +180,24 @@ extern "C" st3_status st3_prefill_attention(const st3_attn_shape* shape, const s
         else prefill_mass_kernel<8><<<grid, kMassWaves * kWave, 0, st>>>(m);
     }
     return check_launch();
+}
+}  // namespace st3
+
+extern "C" st3_status st3_prefill_attention(const st3_attn_shape* shape, const st3_tensor4* q, const st3_tensor4* k,
+                                            const st3_tensor4* v, int32_t n, int32_t sys_len, int32_t vis_len,
+                                            int32_t score_window, const st3_tensor4* out, float* vis_mass,
+                                            int64_t mass_stride, void* workspace, size_t workspace_bytes,
+                                            void* stream) {
+    return st3::prefill_attention(shape, q, nullptr, 0, 0, k, v, n, sys_len, vis_len, score_window, out, vis_mass, mass_stride, workspace,
+                                  workspace_bytes, stream);
+}
+
+extern "C" st3_status st3_prefill_attention_kept(const st3_attn_shape* shape, const st3_tensor4* q, const int32_t* q_ids,
+                                                 int64_t q_ids_stride, int32_t q_vis, const st3_tensor4* k, const st3_tensor4* v, int32_t n,
+                                                 int32_t sys_len, int32_t vis_len, int32_t score_window, const st3_tensor4* out,
+                                                 float* vis_mass, int64_t mass_stride, void* workspace, size_t workspace_bytes,
+                                                 void* stream) {
+    if (!q_ids || vis_len < 0 || q_vis < vis_len || q_ids_stride < vis_len) return ST3_ERR_INVALID_ARG;
+    return st3::prefill_attention(shape, q, q_ids, q_ids_stride, q_vis, k, v, n, sys_len, vis_len, score_window, out, vis_mass, mass_stride,
+                                  workspace, workspace_bytes, stream);
 }

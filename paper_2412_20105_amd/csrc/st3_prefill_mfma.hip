@@ -411,12 +411,12 @@ __device__ __forceinline__ void keep_row_sums(const PrefillArgs& a, const Window
     }
 }
 
-// A wave's query fragments: 32 rows from q0 on (rows that do not exist: the nearest that does).
+// A wave's query fragments: 32 rows from q0 on (rows that do not exist: the nearest that does).  Qp: the strip's row 0.
 template <int D>
-__device__ __forceinline__ void load_queries(const uint16_t* Qp, int64_t q_st, int q0, int n, int c, int g, Frag (&qf)[2][D / 32]) {
+__device__ __forceinline__ void load_queries(const PrefillArgs& a, const uint16_t* Qp, int b, int q0, int c, int g, Frag (&qf)[2][D / 32]) {
 #pragma unroll
     for (int qc = 0; qc < 2; ++qc) {
-        const uint16_t* qrow = Qp + (int64_t)max(0, min(q0 + 16 * qc + c, n - 1)) * q_st;
+        const uint16_t* qrow = Qp + (int64_t)query_row(a, b, max(0, min(q0 + 16 * qc + c, a.n - 1))) * a.q_st;
 #pragma unroll
         for (int s = 0; s < D / 32; ++s) qf[qc][s].u4 = *reinterpret_cast<const u32x4*>(qrow + 32 * s + 8 * g);
     }
@@ -522,7 +522,7 @@ __global__ __launch_bounds__(256, BN == 32 ? 3 : 2) void prefill_mfma_kernel(Pre
     };
     issue(0, 0);
     Frag qf[2][D / 32];
-    load_queries<D>(Qp, a.q_st, q0, n, c, g, qf);
+    load_queries<D>(a, Qp, b, q0, c, g, qf);
     LaneMap<D> lm;
     lm.init(c, g);
     WaveRows<D> rows;
@@ -609,7 +609,7 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_split_kernel(PrefillArgs 
     };
     load_step(0);
     Frag qf[2][D / 32];
-    load_queries<D>(Qp, a.q_st, q0, n, c, g, qf);
+    load_queries<D>(a, Qp, b, q0, c, g, qf);
     LaneMap<D> lm;
     lm.init(c, g);
     WaveRows<D> rows;

@@ -1,0 +1,75 @@
+"""Prefill attention that reads its queries through the ids of the kept visual tokens: bit for bit what gathering them first gives."""
+import pytest
+import torch
+
+from paper_2412_20105_amd import binding as st3
+from paper_2412_20105_amd import pipeline
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+BF, F32 = torch.bfloat16, torch.float32
+
+
+@pytest.mark.parametrize("B,H,d,dtype", [(2, 3, 128, BF), (1, 4, 64, BF), (7, 33, 128, BF), (24, 25, 128, BF), (2, 3, 64, F32), (1, 2, 128, F32)])
+@pytest.mark.parametrize("sys_len,vis,keep,txt,window", [(0, 40, 40, 0, 1), (5, 90, 33, 20, 1), (35, 300, 151, 64, 4), (3, 64, 0, 30, 1), (0, 70, 1, 0, 1)])
+def test_kept_queries(B, H, d, dtype, sys_len, vis, keep, txt, window):
+    g = torch.Generator(device=DEV).manual_seed(vis + keep + H)
+    q, k, v = (torch.randn((B, H, sys_len + (keep if i else vis) + txt, d), generator=g, device=DEV).to(dtype) for i in range(3))
+    n = sys_len + keep + txt
+    ids = torch.rand((B, vis + 3), generator=g, device=DEV)[:, :vis].argsort(dim=1).to(torch.int32)
+    ids = torch.cat([ids[:, :keep].sort(dim=1)[0].to(torch.int32), torch.full((B, 5), -7, dtype=torch.int32, device=DEV)], dim=1)
+    shape = st3.make_shape(B, H, d, st3.ST3_F32 if dtype == F32 else st3.ST3_BF16)
+    rows = torch.zeros((B, H, n, d), dtype=dtype, device=DEV)
+    st3.st3_gather_rows([(q, rows)], sys_len, ids, keep, vis, txt)
+    res = []
+    for kept in (False, True):
+        out, mass = torch.zeros_like(rows), torch.zeros((B, max(keep, 1)), device=DEV)
+        ws = torch.zeros((st3.st3_workspace_bytes(shape, n, keep, window),), dtype=torch.uint8, device=DEV)
+        if kept:
+            st3.st3_prefill_attention_kept(shape, q, ids, vis, k, v, n, sys_len, keep, window, out, mass, ws)
+        else:
+            st3.st3_prefill_attention(shape, rows, k, v, n, sys_len, keep, window, out, mass, ws)
+        res.append((out, mass))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+
+
+def test_ids_out_of_range_read_the_nearest_row():
+    q, k, v = (torch.randn((1, 2, 40, 128), device=DEV).to(BF) for _ in range(3))
+    shape = st3.make_shape(1, 2, 128, st3.ST3_BF16)
+    bad = torch.arange(30, dtype=torch.int32, device=DEV)[None].clone()
+    good = bad.clone()
+    bad[0, 0], bad[0, 29], good[0, 29] = -5, 1 << 30, 29
+    outs = []
+    for ids in (bad, good):
+        outs.append(torch.zeros_like(q))
+        st3.st3_prefill_attention_kept(shape, q, ids, 30, k, v, 40, 4, 30, 1, outs[-1], None, None)
+    assert torch.equal(*outs)
+
+
+@pytest.mark.parametrize("lazy", [None, {3: 2}])
+def test_generation_takes_queries_of_any_layout(lazy):
+    """Queries read in place, whatever their strides, or copied first where a lazy layer needs them too: the same results."""
+    L, B, H, d = 4, 2, 3, 128
+    keep = [[40], [40], [25], [25]]
+    g = torch.Generator(device=DEV).manual_seed(3)
+    n0 = 5 + 40 + 9
+    x = [[torch.randn((B, H, n0, d), generator=g, device=DEV).to(BF) for _ in range(3)] for _ in range(L)]
+    res = []
+    for odd in (False, True):
+        gen = pipeline.Generation(L, H, d, BF, B, 5, 40, 9, 0, keep, device=DEV, lazy=lazy)
+        got = []
+        for l, (q, k, v) in enumerate(x):
+            if odd:                     # strips apart, or heads first
+                wide = q.new_zeros((B, H, n0 + 2, d))
+                wide[:, :, :n0] = q
+                q = wide[:, :, :n0] if l % 2 else q.transpose(0, 1).contiguous().transpose(0, 1)
+            out, mass = gen.prefill_layer(l, q, k, v)
+            got += [out.clone(), mass.clone()]
+        res.append(got)
+    assert all(torch.equal(a, b) for a, b in zip(*res))
+    gen = pipeline.Generation(L, H, d, BF, B, 5, 40, 9, 0, keep, device=DEV, lazy=lazy)
+    rep = torch.randn((B, H, 1, d), generator=g, device=DEV).to(BF)
+    same = rep.expand(B, H, n0, d)      # a row stride of 0
+    assert not gen._attends_in_place(same)
+    with pytest.raises(st3.St3Error):   # (nor can the copy: refused as ever)
+        gen.prefill_layer(0, same, x[0][1], x[0][2])
