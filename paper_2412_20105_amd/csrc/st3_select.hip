@@ -219,17 +219,23 @@ struct GatherArgs {
 
 // grid (ceil(rows*vecs_per_row / (256*UR)), inner, batch*n_pairs); a thread moves UR 16-byte vectors.
 #ifndef ST3_GATHER_UR
-#define ST3_GATHER_UR 4         // 8 was measured 2x slower, 1-4 alike
+// Bound by HBM.  Two vectors a thread: workgroups in flight at the same time then touch addresses close to each other.
+// us at 1 / 2 / 3 / 4 / 8, three tensors of bf16 d = 128: 32 heads x batch 4, 527 of 671 rows 21.4 / 21.1 / 21.7 / 22.9 / 37.2;
+// 40 x 8, 395 rows 37.5 / 37.1 / 37.9 / 39.7 / 74.7 (194 MB read and written at 5.2 TB/s, the launch itself included); 40 x 32,
+// 527 rows 174 / 167 / 167 / 176 / 302 (1.04 GB, 6.2 TB/s).
+// The index lookups of a thread's vectors taken together before its loads change nothing.
+#define ST3_GATHER_UR 2
 #endif
 #ifndef ST3_GATHER_NT
 #define ST3_GATHER_NT 1
 #endif
 constexpr int kGatherUR = ST3_GATHER_UR;
-// Written bytes above which the rows go past the caches.  The launch itself is 10 % faster so from 128 MB on, but what reads the
-// rows next (the layer's attention) finds most of them in the last-level cache (256 MB) after ordinary stores, up to well
+// Written bytes above which the rows go past the caches.  The launch itself is 8 % faster so from 128 MB on, but what reads the
+// rows next (the layer's attention) finds most of them in the last-level cache (256 MB) after ordinary stores, up to somewhat
 // beyond its size.  us, ordinary -> non-temporal stores, gather alone and gather + one read of its output, buffers in rotation:
-// 128 MB written 54 -> 49, 141 -> 157; 187 MB 84 -> 73, 222 -> 246; 250 MB 110 -> 96, 284 -> 305; 375 MB 162 -> 141, 449 -> 455;
-// 437 MB 171 -> 154, 514 -> 505.
+// 123 MB written 47.6 -> 43.7, 94 -> 99; 185 MB 70 -> 64, 126 -> 128; 247 MB 92 -> 85, 152 -> 158; 370 MB 138 -> 126, 232 -> 219;
+// 432 MB 158 -> 146, 270 -> 248.  In a whole prefill the exact line matters little: 13B with the line at 300 MB instead, batch 28
+// 10.32 -> 10.23 ms, batch 32 11.79 -> 11.75, batch 36 13.2 -> 13.0.
 constexpr int64_t kGatherStreamBytes = (int64_t)400 << 20;
 template <bool NTS>        // NTS: non-temporal stores
 __global__ __launch_bounds__(256) void gather_rows_kernel(GatherArgs a) {
