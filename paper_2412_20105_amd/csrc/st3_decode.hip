@@ -281,7 +281,8 @@ __device__ __forceinline__ void attend_chunk(const DecodeArgs& a, const int spli
 // visual row leaves, in the place of head h0's logits.  Why: a write costs a streaming launch as much as reading ten times its bytes
 // (a plain kernel reads strips of 380 KB at 7.07 TB/s, with one KB written for each at 6.87, with two at 6.61, wherever the KB goes, whatever the store's policy
 // and moment).  Whole steps, us, with a logit for each head, with none (no mass wanted), with sums over up to 8 heads: 13B batch 32 2431, 2304, 2363, high
-// resolution batch 8 E4M3 638, 547, 594, 13B batch 8 with lazy layers 496, 470, 484.
+// resolution batch 8 E4M3 638, 547, 594, 13B batch 8 with lazy layers 496, 470, 484 (of the last, 2326, 585
+// and 476 with mass_sums_block's loop not unrolled).
 template <typename T, typename KT, int D, int U, bool NTS>
 __device__ __forceinline__ void attend_heads(const DecodeArgs& a, const int h0, const int h1, const int b, const bool sums, const int n_sums) {
     using M = RowMap<KT, D>;
