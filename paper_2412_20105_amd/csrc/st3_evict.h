@@ -235,11 +235,17 @@ __device__ __forceinline__ TopSet top_set(Key key_at, IdKey idkey_at, int n, int
     return t;
 }
 
-// Copies rows dst(i) <- src(i), i < count, on all strips of sequence b.  Callers guarantee that no destination of the batch is a
+// Copies rows move(i) = {destination, source}, i < count, on all strips of sequence b.  Callers guarantee that no destination of the batch is a
 // source of it.  A wave moves one row of as many strips as 64 lanes of 16 bytes cover, kUR such pieces in flight.  The pieces are
 // dealt to `parts` workgroups; by_strip: so that all pieces of a strip go to the same one.
-template <int NT, class Dst, class Src>
-__device__ __forceinline__ void copy_rows(const EvictArgs& a, int b, int part, int parts, bool by_strip, int count, Dst dst, Src src) {
+// Bound by the trips to memory: the list's entries, then rows of 256 bytes here and there.  The entries of a round are fetched
+// before the first of its rows (loads come back in order, so that an entry behind a row waits for it).  Rows are
+// stored past the caches (ordinary stores: the launch 28 -> 23 us, but the next step's attention, which evicts them, 406 -> 464) and
+// loaded through them.  us, entries one by one and non-temporal loads / entries together / and ordinary loads: launch behind the
+// attention of 13B batch 8 with fast annealing (285 moves a sequence, 94 MB) 31.4 / 28.3 / 28.6, the attention behind it 404 / 406 / 402;
+// whole steps of it 475 / 473 / 469, high resolution batch 2 E4M3 161.6 / 160.8 / 160.0, 8 layers of 12 heads, batch 32 52.0 / 50.0 / 49.2.
+template <int NT, class Move>
+__device__ __forceinline__ void copy_rows(const EvictArgs& a, int b, int part, int parts, bool by_strip, int count, Move move) {
     constexpr int kUR = 8, kWaves = NT / kWave;
     const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int strips = (a.k ? 2 : 1) * a.H;             // K may be absent (layers that keep V only)
@@ -249,21 +255,21 @@ __device__ __forceinline__ void copy_rows(const EvictArgs& a, int b, int part, i
     const int total = g0 < all ? count * groups : 0;
     const int qstep = by_strip ? kWaves : parts * kWaves;
     for (int q0 = by_strip ? wave : part * kWaves + wave; q0 < total; q0 += kUR * qstep) {
+        int2 m[kUR];
+#pragma unroll
+        for (int u = 0; u < kUR; ++u) m[u] = move(min(q0 + u * qstep, total - 1) / groups);
         u32x4_v tmp[kUR];
         char* to[kUR];
 #pragma unroll
         for (int u = 0; u < kUR; ++u) {
-            const int q = q0 + u * qstep;
+            const int q = min(q0 + u * qstep, total - 1), strip = ((q % groups) * gstep + g0) * spw + lane / vpr;
             to[u] = nullptr;
-            if (q >= total) continue;
-            const int i = q / groups;
-            const int strip = ((q - i * groups) * gstep + g0) * spw + lane / vpr;
-            if (strip >= strips) continue;
+            if (q0 + u * qstep >= total || strip >= strips) continue;
             const bool in_k = a.k && strip < a.H;
             char* base = (in_k ? a.k : a.v) + b * a.stride_b + (int64_t)(strip >= a.H ? strip - a.H : strip) * a.stride_h +
                          (lane % vpr) * 16;
-            tmp[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_v*>(base + src(i) * a.stride_t));
-            to[u] = base + dst(i) * a.stride_t;
+            tmp[u] = *reinterpret_cast<const u32x4_v*>(base + m[u].y * a.stride_t);
+            to[u] = base + m[u].x * a.stride_t;
         }
 #pragma unroll
         for (int u = 0; u < kUR; ++u)
@@ -473,11 +479,10 @@ __device__ __forceinline__ void evict_plan_body(const EvictArgs& a, int b, PlanS
         if (inl) {
             const int g = c.n - c.k, r = c.len - (a.sys_len + c.n);
             const int src0 = (r >= g) ? c.len - g : a.sys_len + c.n;
-            copy_rows<NT>(a, b, 0, 1, true, m.inner, [&](int i) { return (int64_t)sm.mv[i][0]; }, [&](int i) { return (int64_t)sm.mv[i][1]; });
+            copy_rows<NT>(a, b, 0, 1, true, m.inner, [&](int i) { return make_int2(sm.mv[i][0], sm.mv[i][1]); });
             if (m.tail > 0) {
                 __syncthreads();                        // those reads are done before [k, n) is overwritten
-                copy_rows<NT>(a, b, 0, 1, true, m.tail, [&](int i) { return (int64_t)(a.sys_len + c.k + i); },
-                                         [&](int i) { return (int64_t)(src0 + i); });
+                copy_rows<NT>(a, b, 0, 1, true, m.tail, [&](int i) { return make_int2(a.sys_len + c.k + i, src0 + i); });
             }
         } else {
             moves_left = m.inner + m.tail;
@@ -519,7 +524,7 @@ __device__ __forceinline__ void move_rows_block(const EvictArgs& a, int b, int p
     const int packed = a.move_cnt[b], inner = packed & ((1 << kMoveTailShift) - 1), tail = packed >> kMoveTailShift;
     const int32_t* mv = a.moves + (int64_t)b * a.max_moves * 2;
     auto apply = [&](int count) {
-        copy_rows<NT>(a, b, part, parts, tail > 0, count, [&](int i) { return (int64_t)mv[2 * i]; }, [&](int i) { return (int64_t)mv[2 * i + 1]; });
+        copy_rows<NT>(a, b, part, parts, tail > 0, count, [&](int i) { return reinterpret_cast<const int2*>(mv)[i]; });
     };
     apply(inner);
     if (tail > 0) {                                     // (uniform)
