@@ -62,6 +62,18 @@ class LayerCache:
         self.h_kv = 0
 
 
+def _apart(x: torch.Tensor, buffers: Sequence[torch.Tensor]) -> bool:
+    """Whether x [B,H,n,d], from its first element to its last, shares no memory with any of the (contiguous) buffers."""
+    (n0, n1, n2, n3), (s0, s1, s2, s3) = x.shape, x.stride()
+    lo = x.data_ptr()
+    hi = lo + ((n0 - 1) * s0 + (n1 - 1) * s1 + (n2 - 1) * s2 + (n3 - 1) * s3 + 1) * x.element_size()
+    for t in buffers:
+        p = t.data_ptr()
+        if p < hi and lo < p + t.nbytes:
+            return False
+    return True
+
+
 class Generation:
     """One batch of sequences going through prefill and decode steps.
 
@@ -186,14 +198,16 @@ class Generation:
         n_l = ns + alive + nx
         # stage the layer's inputs, K and V straight into the cache, in ONE gather
         # launch (Alg. 1/3: X = [S, V[T], I]; ids are the ascending original positions of the survivors).  The attention
-        # reads the surviving queries where they lie, except where later (lazy) layers need them too: those are staged.
+        # reads the surviving queries where they lie, except where later (lazy) layers need them too or this layer writes
+        # over them (a caller's Q may be what an earlier layer returned): those are staged.
         # (One layer of the 7B shape, batch 4, 675 tokens: the gather takes 13 us instead of 20.)
         fp8 = self.kv_scale is not None
         k_dst, v_dst = (self.k_stage, self.v_stage) if fp8 else (lc.k, lc.v)
         q_rows, in_place = self.q_stage, False
         if src is None:
             pairs = [(K, k_dst), (V, v_dst)]
-            in_place = l not in self._heirs and self._attends_in_place(Q)
+            in_place = (l not in self._heirs and self._attends_in_place(Q) and
+                        _apart(Q, (self.out_stage, self.q_stage, k_dst, v_dst, lc.ws, lc.mass)))
             if in_place:
                 q_rows = Q
             else:

@@ -73,3 +73,21 @@ def test_generation_takes_queries_of_any_layout(lazy):
     assert not gen._attends_in_place(same)
     with pytest.raises(st3.St3Error):   # (nor can the copy: refused as ever)
         gen.prefill_layer(0, same, x[0][1], x[0][2])
+
+
+@pytest.mark.parametrize("H,dtype", [(3, BF), (33, BF), (3, F32)])
+def test_a_layers_output_as_the_next_layers_queries(H, dtype):
+    """The tensor that prefill_layer returns is a buffer that the next layer writes: its rows are copied first, whether the layer prunes or not."""
+    L, B, d, n0 = 4, 4, 64, 5 + 300 + 9
+    keep = [[300], [300], [151], [151]]
+    g = torch.Generator(device=DEV).manual_seed(H)
+    q, k, v = (torch.randn((B, H, n0, d), generator=g, device=DEV).to(dtype) for _ in range(3))
+    res = []
+    for own in (False, True):
+        gen, got = pipeline.Generation(L, H, d, dtype, B, 5, 300, 9, 0, keep, device=DEV), []
+        for l in range(L):
+            src = q if l == 0 else gen.out_stage
+            out, mass = gen.prefill_layer(l, src.clone() if own else src, k, v)
+            got += [out.clone(), mass.clone()]
+        res.append(got)
+    assert all(torch.equal(a, b) for a, b in zip(*res))

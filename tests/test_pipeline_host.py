@@ -46,3 +46,66 @@ def test_current_stream_without_the_raw_handle(monkeypatch):
         with monkeypatch.context() as m:
             m.setattr(st3, missing, None)
             assert st3._stream(None) == 0x1234
+
+
+class RecordingLibrary:
+    """The library's calls, noted instead of made; pointers to structures as the structures' fields."""
+
+    def __init__(self):
+        self.calls = []
+
+    def __getattr__(self, name):
+        def call(*args):
+            self.calls.append((name, args))
+            return 1 << 12 if name == "st3_workspace_bytes" else 0
+        return call
+
+    def gathered(self):
+        """Sources of the last gather, and the queries and the name of the attention call behind it."""
+        (_, g), (name, a) = [c for c in self.calls if c[0] in ("st3_gather_rows", "st3_prefill_attention", "st3_prefill_attention_kept")][-2:]
+        return [g[0][i].src for i in range(g[1])], a[1]._obj.data, name
+
+
+@pytest.fixture
+def host(monkeypatch):
+    """make(...) -> (a Generation on host memory, its recorded calls)."""
+    rec = RecordingLibrary()
+    monkeypatch.setattr(st3, "lib", lambda: rec)
+    monkeypatch.setattr(st3, "_stream", lambda s: 0)
+    monkeypatch.setattr(st3, "tensor4", lambda t: st3.Tensor4(t.data_ptr(), t.stride(0), t.stride(1), t.stride(2)))
+    monkeypatch.setattr(st3, "kv_layer", lambda *a: st3.KvLayer())                  # (they take device tensors only)
+    monkeypatch.setattr(st3, "segments", lambda *a: st3.Segments(*a[:3]))
+
+    def make(keep, dtype=torch.bfloat16, B=2, **more):
+        gen = pipeline.Generation(len(keep), 3, 64, dtype, B, 4, keep[0][0], 6, len(keep[0]) - 1, keep, device="cpu", **more)
+        return gen, rec, [torch.zeros((B, 3, gen.N0, 64), dtype=dtype) for _ in range(3)]
+    return make
+
+
+def _overlapping_queries(gen, where):
+    lc = gen.layers[1]
+    if where == "returned":             # what layer 0's prefill has returned
+        return gen.out_stage[:, :, :gen.N0]
+    if where == "workspace":
+        lc.ws = torch.zeros(2 * gen.B * gen.H * gen.N0 * gen.d, dtype=torch.uint8)
+        return lc.ws.view(torch.bfloat16).view(gen.B, gen.H, gen.N0, gen.d)
+    base = {"last_rows": gen.out_stage, "cache": lc.v if gen.kv_scale is None else gen.v_stage, "stage": gen.q_stage}[where]
+    if where != "last_rows":
+        return base[:, :, :gen.N0]
+    wide = torch.zeros(2 * base.numel(), dtype=base.dtype)      # rows whose end reaches into the output's first row
+    gen.out_stage = wide[base.numel() - 8:][:base.numel()].view(base.shape)
+    return wide[:base.numel()].view(base.shape)
+
+
+@pytest.mark.parametrize("kv_scale", [None, 0.01])
+@pytest.mark.parametrize("where", ["returned", "last_rows", "cache", "stage", "workspace"])
+@pytest.mark.parametrize("kept", [20, 12])
+def test_queries_that_a_layers_prefill_writes_over_are_copied_first(host, where, kept, kv_scale):
+    gen, rec, (Q, K, V) = host([[20], [kept]], kv_scale=kv_scale)
+    gen.prefill_layer(0, Q, K, V)
+    assert rec.gathered() == ([K.data_ptr(), V.data_ptr()], Q.data_ptr(), "st3_prefill_attention")
+    q = _overlapping_queries(gen, where)
+    gen.prefill_layer(1, q, K, V)
+    assert rec.gathered() == ([q.data_ptr(), K.data_ptr(), V.data_ptr()], gen.q_stage.data_ptr(), "st3_prefill_attention")
+    gen.prefill_layer(1, Q, K, V)
+    assert rec.gathered() == ([K.data_ptr(), V.data_ptr()], Q.data_ptr(), "st3_prefill_attention_kept" if kept < 20 else "st3_prefill_attention")
