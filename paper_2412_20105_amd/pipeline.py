@@ -210,6 +210,7 @@ class Generation:
                         _apart(Q, (self.out_stage, self.q_stage, k_dst, v_dst, lc.ws, lc.mass)))
             if in_place:
                 q_rows = Q
+                assert K.element_size() == V.element_size() == Q.element_size()     # (as the gather asks of what it copies)
             else:
                 pairs.insert(0, (Q, self.q_stage))
             k_rows = k_dst

@@ -109,3 +109,13 @@ def test_queries_that_a_layers_prefill_writes_over_are_copied_first(host, where,
     assert rec.gathered() == ([q.data_ptr(), K.data_ptr(), V.data_ptr()], gen.q_stage.data_ptr(), "st3_prefill_attention")
     gen.prefill_layer(1, Q, K, V)
     assert rec.gathered() == ([K.data_ptr(), V.data_ptr()], Q.data_ptr(), "st3_prefill_attention_kept" if kept < 20 else "st3_prefill_attention")
+
+
+@pytest.mark.parametrize("which", [(1,), (2,), (1, 2)])
+def test_keys_and_values_of_another_element_size_are_refused(host, which):
+    """A row's bytes are those of the first tensor that is copied: elements of twice the size would be written past the caches' rows."""
+    gen, rec, x = host([[20], [12]])
+    x = [t.float() if i in which else t for i, t in enumerate(x)]
+    with pytest.raises(AssertionError):
+        gen.prefill_layer(0, *x)
+    assert not any(name.startswith(("st3_gather", "st3_prefill")) for name, _ in rec.calls)
