@@ -245,7 +245,8 @@ class Generation:
     def _attends_in_place(self, Q: torch.Tensor) -> bool:
         """Whether the attention can read the unpruned prompt's queries as the caller holds them (else they are copied)."""
         eb = Q.element_size()
-        return (tuple(Q.shape) == (self.B, self.H, self.N0, self.d) and Q.dtype == self.dtype and Q.stride(3) == 1
+        return (tuple(Q.shape) == (self.B, self.H, self.N0, self.d) and Q.dtype == self.dtype
+                and Q.device == self.out_stage.device and Q.stride(3) == 1
                 and Q.stride(2) >= self.d and Q.data_ptr() % 16 == 0 and all(s * eb % 16 == 0 for s in Q.stride()[:3]))
 
     # ------------------------------------------------------------------------------------

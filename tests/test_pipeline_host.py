@@ -119,3 +119,15 @@ def test_keys_and_values_of_another_element_size_are_refused(host, which):
     with pytest.raises(AssertionError):
         gen.prefill_layer(0, *x)
     assert not any(name.startswith(("st3_gather", "st3_prefill")) for name, _ in rec.calls)
+
+
+def test_queries_in_another_memory_are_copied(host):
+    """Queries that the device can read but does not hold (pinned host memory, a peer's): the gather reads them, not every tile."""
+    class Elsewhere(torch.Tensor):
+        device = torch.device("meta")
+
+    gen, rec, (Q, K, V) = host([[20], [12]])
+    away = Q.as_subclass(Elsewhere)
+    for l in range(2):
+        gen.prefill_layer(l, away, K, V)
+        assert rec.gathered() == ([Q.data_ptr(), K.data_ptr(), V.data_ptr()], gen.q_stage.data_ptr(), "st3_prefill_attention")
