@@ -165,7 +165,8 @@ ST3_EXPORT st3_status st3_prefill_attention(const st3_attn_shape* shape, const s
 /* The same with queries that still lie where the unpruned prompt has them (Alg. 1 / Alg. 3, X = [S, V[T], I] without a copy of Q): row i of
  * the prompt attended is row i of q for i < sys_len, row sys_len + q_ids[b*q_ids_stride + i - sys_len] for the vis_len visual ones
  * (DEVICE int32, each in [0, q_vis); what lies outside reads the nearest row), and row i - vis_len + q_vis behind them:
- * the rows that st3_gather_rows would have brought together.  q has n - vis_len + q_vis rows, q_vis >= vis_len.  k, v, out and the mass
+ * the rows that st3_gather_rows would have brought together.  q has n - vis_len + q_vis rows, q_vis >= vis_len, and shares
+ * no memory with out (ST3_ERR_INVALID_ARG; rows of one buffer may alternate where the strides of both are equal).  k, v, out and the mass
  * are as above. */
 ST3_EXPORT st3_status st3_prefill_attention_kept(const st3_attn_shape* shape, const st3_tensor4* q, const int32_t* q_ids,
                                  int64_t q_ids_stride, int32_t q_vis, const st3_tensor4* k, const st3_tensor4* v, int32_t n,

@@ -111,6 +111,24 @@ bool tensor_ok(const st3_tensor4* t, int eb, int d) {
     return (t->stride_t * eb) % 16 == 0 && (t->stride_h * eb) % 16 == 0 && (t->stride_b * eb) % 16 == 0;
 }
 
+// Whether one of the nx rows of a strip of x shares memory with one of the ny rows of a strip of y.  Tensors of equal strides may be parts of one
+// buffer, whose rows alternate; of others, all that lies between the first byte and the last counts.
+bool rows_meet(const st3_tensor4* x, int64_t nx, const st3_tensor4* y, int64_t ny, int B, int H, int D, int eb) {
+    const int64_t row = (int64_t)D * eb, d = (int64_t)(reinterpret_cast<intptr_t>(y->data) - reinterpret_cast<intptr_t>(x->data));
+    auto extent = [&](const st3_tensor4* t, int64_t n) { return ((B - 1) * t->stride_b + (H - 1) * t->stride_h + (n - 1) * t->stride_t) * eb + row; };
+    if (d >= extent(x, nx) || -d >= extent(y, ny)) return false;
+    if (x->stride_b != y->stride_b || x->stride_h != y->stride_h || x->stride_t != y->stride_t) return true;
+    const int64_t sb = x->stride_b * eb, sh = x->stride_h * eb, st = x->stride_t * eb;
+    for (int64_t b = 1 - B; b < B; ++b)
+        for (int64_t h = 1 - H; h < H; ++h) {
+            // rows i of x and j of y begin gap + (j - i) * st apart; the two nearest values of j - i on either side of -gap / st
+            const int64_t gap = d + b * sb + h * sh, near = -gap / st;
+            for (int64_t k = near - 1; k <= near + 1; ++k)
+                if (k > -nx && k < ny && gap + k * st < row && -(gap + k * st) < row) return true;
+        }
+    return false;
+}
+
 }  // namespace
 }  // namespace st3
 
@@ -128,6 +146,8 @@ static st3_status prefill_attention(const st3_attn_shape* shape, const st3_tenso
     if (n > 32768) return ST3_ERR_UNSUPPORTED;
     if (score_window < 1 || score_window > n || score_window > kMaxWindow) return ST3_ERR_INVALID_ARG;
     if (k->stride_t != v->stride_t) return ST3_ERR_UNSUPPORTED;
+    // queries by id: a workgroup reads rows in whose places of the output others write
+    if (q_ids && rows_meet(q, (int64_t)n - vis_len + q_vis, out, n, B, H, D, eb)) return ST3_ERR_INVALID_ARG;
     const bool want_mass = vis_mass != nullptr && vis_len > 0;
     if (want_mass && mass_stride < vis_len) return ST3_ERR_INVALID_ARG;
     const PrefillWs wl = prefill_ws(B, H, vis_len, score_window);

@@ -91,3 +91,20 @@ def test_a_layers_output_as_the_next_layers_queries(H, dtype):
             got += [out.clone(), mass.clone()]
         res.append(got)
     assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
+def test_queries_and_output_in_one_buffer():
+    """Token-major [B, n, 4, H, d]: rows of one buffer that alternate."""
+    B, H, d, n, sys_len, keep, vis = 2, 5, 128, 90, 4, 40, 77
+    g = torch.Generator(device=DEV).manual_seed(1)
+    rows = n - keep + vis
+    x = torch.randn((B, rows, 4, H, d), generator=g, device=DEV).to(BF)
+    q, k, v, out = (x[:, :, i].transpose(1, 2) for i in range(4))
+    ids = torch.stack([torch.randperm(vis, generator=g, device=DEV)[:keep].sort()[0] for _ in range(B)]).to(torch.int32)
+    shape = st3.make_shape(B, H, d, st3.ST3_BF16)
+    apart = torch.zeros((B, H, n, d), dtype=BF, device=DEV)
+    st3.st3_prefill_attention_kept(shape, q.contiguous(), ids, vis, k, v, n, sys_len, keep, 1, apart, None, None)
+    st3.st3_prefill_attention_kept(shape, q, ids, vis, k, v, n, sys_len, keep, 1, out, None, None)
+    assert torch.equal(out[:, :, :n], apart)
+    with pytest.raises(st3.St3Error):
+        st3.st3_prefill_attention_kept(shape, q, ids, vis, k, v, n, sys_len, keep, 1, q, None, None)

@@ -238,3 +238,39 @@ def test_ctypes_structures_have_the_layout_the_c_header_declares(tmp_path):
     got2 = dict(l.split() for l in subprocess.run([str(exe2)], check=True, capture_output=True, text=True).stdout.splitlines())
     for k, v in enums.items():
         assert int(got2[k]) == v, k
+
+
+def test_queries_read_by_id_are_apart_from_the_output():
+    """A workgroup's output would overwrite rows that others have still to read: refused; rows of one buffer may alternate."""
+    lib = st3.lib()
+    B, H, d, n, vis, q_vis = 2, 4, 64, 100, 64, 90
+    sh = st3.make_shape(B, H, d, st3.ST3_BF16)
+    base, far = 0x100000, 0x40000000
+
+    def call(q, out, n=n):
+        k = st3.Tensor4(far, H * 128 * d, 128 * d, d)
+        return lib.st3_prefill_attention_kept(C.byref(sh), C.byref(st3.Tensor4(*q)), far, vis, q_vis, C.byref(k), C.byref(k), n, 8, vis, 1,
+                                              C.byref(st3.Tensor4(*out)), far, vis, far, 16, None)
+
+    met, apart = st3.ST3_ERR_INVALID_ARG, st3.ST3_ERR_WORKSPACE_TOO_SMALL       # (what comes next is found wrong)
+    rows = n - vis + q_vis                      # 126 rows a strip
+    plain = (H * rows * d, rows * d, d)
+    q, end = (base, *plain), base + B * H * rows * d * 2
+    assert call(q, q) == met
+    assert call(q, (end - 16, *plain)) == met and call(q, (end, *plain)) == apart
+    # the output's last row ends n rows behind its last strip's start
+    last = ((B - 1) * H * rows + (H - 1) * rows + n) * d * 2
+    assert call(q, (base - last + 16, *plain)) == met and call(q, (base - last, *plain)) == apart
+    # other strides: from the first byte to the last
+    size, dense = B * H * n * d * 2, (H * n * d, n * d, d)
+    assert call(q, (base - size + 16, *dense)) == call(q, (end - 16, *dense)) == met
+    assert call(q, (base - size, *dense)) == call(q, (end, *dense)) == apart
+    # strips of one buffer: output rows in the room behind each strip's queries, and reaching into the next strip
+    wide = (H * 256 * d, 256 * d, d)
+    for gap, want in ((rows, apart), (rows - 1, met), (256 - n, apart), (256 - n + 1, met)):
+        assert call((base, *wide), (base + gap * d * 2, *wide)) == want, gap
+    # token-major [B, rows, 3, H, d]: the third of a token that follows the queries, and columns that meet them
+    token = (rows * 3 * H * d, d, 3 * H * d)
+    for cols, want in ((H * d, apart), (2 * H * d, apart), (0, met), ((H - 1) * d, met), (3 * H * d, met), ((3 * H - 1) * d, met),
+                       (-H * d, apart), (rows * 3 * H * d + H * d, apart), (rows * 3 * H * d, met)):
+        assert call((base + (1 << 20), *token), (base + (1 << 20) + cols * 2, *token)) == want, cols
