@@ -37,7 +37,7 @@ def keep_table_for(workload) -> List[List[int]]:
 
 
 class LayerCache:
-    def __init__(self, B, H, d, cap, cap_v, dtype, device, ws_bytes, value_only=False, kv_scale=None, lens=None):
+    def __init__(self, B, H, d, cap, cap_v, dtype, device, ws_bytes, value_only=False, kv_scale=None):
         # a lazy layer (QK heredity) never forms K, so it caches V alone.
         # kv_scale: None = rows of `dtype`; a float = E4M3 codes worth that much per unit, every strip
         cdt = dtype if kv_scale is None else torch.uint8
@@ -50,7 +50,7 @@ class LayerCache:
         self.score = torch.zeros((B, max(cap_v, 1)), dtype=torch.float32, device=device)
         self.ids = torch.zeros((B, max(cap_v, 1)), dtype=torch.int32, device=device)
         self.mass = torch.zeros((B, max(cap_v, 1)), dtype=torch.float32, device=device)
-        self.lens = torch.zeros((3, B), dtype=torch.int32, device=device) if lens is None else lens
+        self.lens = torch.zeros((3, B), dtype=torch.int32, device=device)
         self.vis_len, self.kv_len = self.lens[0], self.lens[1]
         self.tail_start = None      # lens[2] from the prefill on when the tail keeps its place (Generation(fixed_tail=True))
         self.h_tail = 0             # host copy of it
@@ -111,13 +111,12 @@ class Generation:
                 raise ValueError("a lazy layer keeps what its source keeps")
         self._heirs = frozenset(self.lazy.values())
         self.layers: List[LayerCache] = []
-        self._lens = torch.zeros((layers, 3, batch), dtype=torch.int32, device=device)     # of all layers
         for l in range(layers):
             cap = n_sys + self.keep[l][0] + n_txt + steps
             cap = max(cap, self.N0)                 # the unpruned prompt is staged in the cache first
             ws_bytes = st3.st3_workspace_bytes(self.shape, cap, n_vis, window)
             self.layers.append(LayerCache(batch, heads, head_dim, cap, n_vis, dtype, device, ws_bytes,
-                                          value_only=l in self.lazy, kv_scale=kv_scale, lens=self._lens[l]))
+                                          value_only=l in self.lazy, kv_scale=kv_scale))
             st3.st3_workspace_init(self.shape, cap, self.layers[-1].ws)
         self.kv_scale = kv_scale
         self.fixed_tail = fixed_tail
@@ -139,28 +138,18 @@ class Generation:
         for l in range(layers):
             alive = min(alive, self.keep[l][0]) if l else alive
             counts.append(alive)
-        self._lens0 = self._length_images(counts)
-        self._lens0_counts = counts
-        self._lens_ready: set = set()       # layers whose lengths layer 0's prefill has set and nothing has advanced since
+        images = self._length_images(counts)
+        self._lens0: List[tuple] = [(counts[l], images[l]) for l in range(layers)]
         self.t = 0
         eb = 2 if dtype == torch.bfloat16 else 4
         self._eb = eb
 
     # ------------------------------------------------------------------------------------
-    def _set_prefill_lens(self, l: int, alive: int):
-        """Layer l's lengths as its prefill leaves them, with `alive` visual rows.  They follow from the keep table, so layer 0
-        sets those of all layers in one copy (one launch instead of one a layer: a 7B job, batch 4: 3827 -> 3779 us)."""
-        if self._lens0_counts[l] != alive:
-            self._lens0_counts[l] = alive
-            self._lens0[l].copy_(self._length_images([alive])[0])
-            self._lens_ready.discard(l)
-        if l == 0:
-            self._lens.copy_(self._lens0)
-            self._lens_ready = set(range(1, self.L))
-        elif l in self._lens_ready:
-            self._lens_ready.remove(l)
-        else:
-            self.layers[l].lens.copy_(self._lens0[l])
+    def _lens_after_prefill(self, l: int, alive: int) -> torch.Tensor:
+        """Device image [3, B] of layer l's lengths behind its prefill, with `alive` visual rows."""
+        if self._lens0[l][0] != alive:
+            self._lens0[l] = (alive, self._length_images([alive])[0])
+        return self._lens0[l][1]
 
     def _length_images(self, counts: Sequence[int]) -> torch.Tensor:
         ns, nx = self.n_sys, self.n_txt
@@ -234,7 +223,7 @@ class Generation:
         # ranking column: scores of the most recent prune event, else the layer's own mass
         if self._inherit is not lc.score:
             lc.score.copy_(lc.mass if self._inherit is None else self._inherit)
-        self._set_prefill_lens(l, alive)
+        lc.lens.copy_(self._lens_after_prefill(l, alive))
         lc.h_vis, lc.h_kv = alive, n_l
         if self.fixed_tail:         # [system | kept visual | instruction] is contiguous now: the tail starts here for good
             lc.tail_start = lc.lens[2]
@@ -253,7 +242,6 @@ class Generation:
     def begin_decode(self):
         """The eviction that precedes the FIRST decode step (Alg. 3 truncates a layer's cache before
         its attention at every step; later steps do it right after the previous step's attention)."""
-        self._lens_ready.clear()            # the calls below advance them
         arr = self._step_array()
         targets = [min(self.keep[l][1], lc.h_vis) if self.T >= 1 else lc.h_vis for l, lc in enumerate(self.layers)]
         for s, lc, target in zip(arr, self.layers, targets):

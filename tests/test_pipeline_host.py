@@ -131,3 +131,26 @@ def test_queries_in_another_memory_are_copied(host):
     for l in range(2):
         gen.prefill_layer(l, away, K, V)
         assert rec.gathered() == ([Q.data_ptr(), K.data_ptr(), V.data_ptr()], gen.q_stage.data_ptr(), "st3_prefill_attention")
+
+
+@pytest.mark.parametrize("fixed_tail", [True, False])
+def test_layer_0_prefilled_again_leaves_the_other_layers_lengths(host, fixed_tail):
+    """Behind decode steps every layer's lengths on the device are the host's, whichever layers are prefilled again."""
+    gen, rec, x = host([[20, 15, 12], [20, 20, 18], [10, 7, 7]], fixed_tail=fixed_tail)
+
+    def lengths():
+        return [lc.lens[:2].tolist() for lc in gen.layers]
+
+    for l in range(3):
+        gen.prefill_layer(l, *x)
+        assert lengths()[l] == [[gen.layers[l].h_vis] * 2, [gen.layers[l].h_kv] * 2]
+    gen.decode_step(1, torch.zeros((3, 3, 2, 3, 64), dtype=torch.bfloat16))
+    for lc in gen.layers:                   # what the step's launches do
+        lc.vis_len.fill_(lc.h_vis)
+        lc.kv_len.fill_(lc.h_kv)
+    for again in (0, 2, 0):
+        before = lengths()
+        gen.prefill_layer(again, *x)
+        for l, (lc, was) in enumerate(zip(gen.layers, before)):
+            assert lengths()[l] == [[lc.h_vis] * 2, [lc.h_kv] * 2], (again, l)
+            assert l == again or lengths()[l] == was
