@@ -80,7 +80,8 @@ constexpr int kDecodeTargetWgsMerged = ST3_DECODE_TARGET_WGS_MERGED;
 constexpr int kDecodeTargetWgsMax = kDecodeTargetWgs > kDecodeTargetWgsMerged ? kDecodeTargetWgs : kDecodeTargetWgsMerged;
 constexpr int kDecodeMaxSplit = 64;
 // Largest chunk of a strip (rows): a decode_attend_kernel workgroup collects the logits it keeps in LDS, 4 bytes per row
-// of its chunk at most: 16 KB, so that the seven workgroups a compute unit can hold still fit its 160 KB.
+// of its chunk at most: 16 KB, so that the seven workgroups a compute unit can hold still fit its 160 KB.  (A workgroup of several
+// heads keeps the sums of its visual rows' probabilities beside one head's logits: up to 32 KB, where a layer has that many visual rows.)
 constexpr int kLogitStageMaxRows = 4096;
 #ifndef ST3_DECODE_MIN_CHUNK
 #define ST3_DECODE_MIN_CHUNK 64

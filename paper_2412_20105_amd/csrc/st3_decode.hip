@@ -280,9 +280,9 @@ __device__ __forceinline__ void attend_chunk(const DecodeArgs& a, const int spli
 // added up here, since a whole strip's normaliser is known: instead of a logit for every head and visual row, one sum of probabilities for every
 // visual row leaves, in the place of head h0's logits.  Why: a write costs a streaming launch as much as reading ten times its bytes
 // (a plain kernel reads strips of 380 KB at 7.07 TB/s, with one KB written for each at 6.87, with two at 6.61, wherever the KB goes, whatever the store's policy
-// and moment).  Whole steps, us, with a logit for each head, with none (no mass wanted), with sums over up to 8 heads: 13B batch 32 2431, 2304, 2363, high
-// resolution batch 8 E4M3 638, 547, 594, 13B batch 8 with lazy layers 496, 470, 484 (of the last, 2326, 585
-// and 476 with mass_sums_block's loop not unrolled).
+// and moment).  Whole steps, us, with a logit for each head, with none (no mass wanted), with sums over up to 8 heads, and the same with mass_sums_block's
+// loop not unrolled, as it is now: 13B batch 32 2431, 2304, 2363, 2326, high resolution batch 8 E4M3 638, 547, 594, 585, 13B batch 8 with lazy
+// layers 496, 470, 484, 476.
 template <typename T, typename KT, int D, int U, bool NTS>
 __device__ __forceinline__ void attend_heads(const DecodeArgs& a, const int h0, const int h1, const int b, const bool sums, const int n_sums) {
     using M = RowMap<KT, D>;
@@ -1188,15 +1188,14 @@ static bool rank_beside(int rows, int heads, int64_t strips, int many_moves) {
     return rows <= 1024 || (187 - 10 * heads - strips - 20 * (int64_t)many_moves) * rows <= 270000;
 }
 
-// Heads that a workgroup takes one after the other, where no strip is cut and the rows are ranked beside the attention: the more, the fewer
-// sums of the mass are written (attend_heads), as long as there are workgroups enough.  GROUP_FIGURES
 // Heads that the workgroups of a layer of so many rows take one after the other (attend_heads), where rows are ranked beside the attention
 // and no strip is cut: the more, the fewer sums of the mass are written; but the launch must not end waiting for a long workgroup, so one takes no more
 // rows than a 384th of what the launch has behind the layer (`behind`), and the last layers go head by head.  Layers are visited in order: the number falls from layer
-// to layer.  us a step, head by head / a share of 768 / 384 / 256 / 128 (or 8 heads always): 13B batch 32 2431 / 2367 / 2363 / 2369 / 2363 (2391), high
-// resolution batch 8 E4M3 638 / 607 / 594 / 588 / 598 (595), bf16 1183 / 1143 / 1124 / 1121 / 1153 (1143), 13B batch 8 642 / 630 / 626 / 627 / 629 (700), with lazy
-// layers 496 / 489 / 484 / 498 / 492 (489), 7B batch 4 146 / 144 / 143 / 158 / 157, 8 layers of 12 heads, batch 32 53.3 / 53.2 / 52.1 / 58.5 / 62.6, D = 64, batch 16 276 / 269 / 264 / 262 /
-// 264.  Float32 rows are twice as long for the same logit and lose: 8 layers of 16 heads, batch 8 59.4 / 59.6 / 60.2.
+// to layer.  us a step, head by head / a share of 768 / 384 / 256 / 128 (or 8 heads always): 13B batch 32 2399 / 2314 / 2314 / 2316 / 2315 (2342), high
+// resolution batch 8 E4M3 634 / 595 / 582 / 578 / 588 (584), bf16 1144 / 1084 / 1069 / 1063 / 1095 (1086), 13B batch 8 with fast annealing 522 / 505 / 504 / 502 / 508
+// (570), with lazy layers 489 / 471 / 468 / 483 / 478 (474), 7B batch 4 146 / 143 / 142 / 157 / 155 (150), 8 layers of 12 heads, batch 32 133 / 133 / 131 / 132 /
+// 151 (149), 32 layers of D = 64, batch 16 330 / 313 / 310 / 313 / 314 (314).  Float32 rows are twice as long for the same logit and go head by head; a share of
+// 768 / 384 would gain them little: batch 8 of 16 heads, 8 layers 87.1 / 87.2 / 87.2, 32 layers 307 / 305 / 304, of D = 64, batch 16 318 / 309 / 308.
 static int heads_together(int H, int64_t rows, int64_t behind) {
     int g = 8;
     while (g > 1 && (g > H || g * rows * 384 > behind)) g /= 2;

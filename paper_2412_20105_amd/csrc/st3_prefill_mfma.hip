@@ -155,9 +155,10 @@ __device__ __forceinline__ i16x4 lds_read_tr(uint32_t at) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<__attribute__((address_space(3))) i16x4*>(at));
 }
 
-// Where a lane finds its operands in a tile (byte offsets, fixed for the whole kernel).  K fragment s of row c: unit (2s + g) ^ k_swz,
-// which is the first one's address ^ 32 s; transpose read of d-tile dt: row (4g + (c%16)/4), unit (4dt + 2(c/16) + (c%4)/2) ^ v_swz,
-// half c%2: the first one's ^ 64 dt.  (Tiles start at multiples of a row's bytes, so the ^ may come last: two registers, not twelve.)
+// Where a lane finds its operands in a tile (byte offsets, fixed for the whole kernel).  K fragment s of row c: unit (4s + g) ^ k_swz(c),
+// which is the first one's address ^ 64 s; transpose read of the 16 columns dt: row 4g + c/4, unit (2dt + (c%4)/2) ^ v_swz(row),
+// half c%2: the first one's ^ 32 dt.  (g < 4 and (c%4)/2 < 2, so the + is an ^ too; tiles start at multiples of a row's bytes, so the ^ may
+// come last: two registers, not twelve.)
 template <int D>
 struct LaneMap {
     uint32_t k, v;
@@ -296,7 +297,7 @@ __device__ __forceinline__ void tile_step(uint32_t Kt, uint32_t Vt, const Frag (
             for (int r = 0; r < 4; ++r) mx[qc] = fmaxf(mx[qc], sacc[x / 2][x % 2][qc][r]);
         mx[qc] *= scale_l2;
     }
-    if (__any(mx[0] - st.m[0] > kLazy || mx[1] - st.m[1] > kLazy)) {   // m = -inf before the first key: it moves
+    if (__any(mx[0] - st.m[0] > kLazy || mx[1] - st.m[1] > kLazy)) {   // m is the lowest float before the first key of a finite logit: it moves
 #pragma unroll
         for (int qc = 0; qc < 2; ++qc) {
             const float m_cand = fmaxf(st.m[qc], wave_max_from<16>(mx[qc]));
@@ -631,7 +632,7 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_split_kernel(PrefillArgs 
         }
     }
     // ---- merge the key groups ----------------------------------------------------------------
-    // (a lane of every group holds the same query and the same columns; a group without tiles has sum 0 at maximum -inf)
+    // (a lane of every group holds the same query and the same columns)
     __syncthreads();
     f32x4* merge = reinterpret_cast<f32x4*>(buf);       // [KS - 1][NB][2 * DT][64]
 #pragma unroll
@@ -648,7 +649,7 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_split_kernel(PrefillArgs 
     float l_tot[2];
 #pragma unroll
     for (int qc = 0; qc < 2; ++qc) {
-        float m = rows.m[qc];                           // -inf where every key of its tiles has logit -inf (of all groups': NaN)
+        float m = rows.m[qc];                           // (a group without tiles, or with keys of logit -inf only, has sum 0 at the lowest float)
 #pragma unroll
         for (int k = 1; k < KS; ++k) m = fmaxf(m, sm_m[k][blk][qc][lane]);
         const float f0 = exp2_fast(rows.m[qc] - m);
@@ -683,9 +684,11 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_split_kernel(PrefillArgs 
 //   query tile up to 128 strips: 128 x 100 10.9 / 10.6, 200 x 100 11.3 / 11.8
 // D = 64 (four up to 1024 or 1536, two up to 768 or 1536): 20 x 1000 30.8 / 24.6 / 21.5, 32 x 1000 31.3 / 21.7 / 17.7, 128 x 200 12.3 / 11.1 / 10.9, 16 x 3000 79.4 / 65.0 /
 // 59.4; 128 x 300 14.9 / 12.8 / 13.5, 256 x 150 11.7 / 10.8 / 13.5, 64 x 1500 47.7 / 45.7, but 256 x 200 14.5 / 15.8, 128 x 500 21.1 / 24.5, 160 x 380 17.6 / 18.9.
-// Prompts of one key tile leave a second group nothing: 32 x 64, D = 128, 10.7 us with one group, 12.9 with four.
+// Prompts of up to 64 tokens are one key tile or two: a second group saves a step and the merge takes it back, or more.  us a launch without the mass, 1 / 2 / 4
+// groups, D = 128: 32 x 33 5.0 / 5.2 / 6.0, 32 x 64 5.2 / 5.5 / 6.0, 128 x 48 5.3 / 5.5 / 6.2, 320 x 64 8.4 / 9.4 / 13.4, 1280 x 33 15.2 / 16.9 / 30.3; D = 64: 32 x 33
+// 3.9 / 3.9 / 4.3, 128 x 64 4.1 / 4.1 / 4.4, 640 x 48 6.5 / 7.0 / 9.0, 1280 x 48 10.1 / 9.6 / 13.7.
 int key_groups(int D, int n, int64_t strips) {
-    if (n <= kBN) return 1;
+    if (n <= 64) return 1;
     const bool d128 = D == 128;
     const int64_t four = (n + 31) / 32 * strips, two = (n + 63) / 64 * strips;
     if (four <= (d128 ? 256 : 1024) || (strips <= (d128 ? 12 : 16) && four <= (d128 ? 768 : 1536))) return 4;

@@ -234,8 +234,9 @@ constexpr int kGatherUR = ST3_GATHER_UR;
 // rows next (the layer's attention) finds most of them in the last-level cache (256 MB) after ordinary stores, up to somewhat
 // beyond its size.  us, ordinary -> non-temporal stores, gather alone and gather + one read of its output, buffers in rotation:
 // 123 MB written 47.6 -> 43.7, 94 -> 99; 185 MB 70 -> 64, 126 -> 128; 247 MB 92 -> 85, 152 -> 158; 370 MB 138 -> 126, 232 -> 219;
-// 432 MB 158 -> 146, 270 -> 248.  In a whole prefill the exact line matters little: 13B with the line at 300 MB instead, batch 28
-// 10.32 -> 10.23 ms, batch 32 11.79 -> 11.75, batch 36 13.2 -> 13.0.
+// 432 MB 158 -> 146, 270 -> 248.  So for this reader the sides cross between 250 and 370 MB; the line lies beyond that, where the launch alone
+// gains most and no reader was seen to lose.  At 300 MB whole prefills would gain little: 13B batch 28 10.32 -> 10.23 ms, batch 32 11.79 ->
+// 11.75, batch 36 13.2 -> 13.0.
 constexpr int64_t kGatherStreamBytes = (int64_t)400 << 20;
 template <bool NTS>        // NTS: non-temporal stores
 __global__ __launch_bounds__(256) void gather_rows_kernel(GatherArgs a) {

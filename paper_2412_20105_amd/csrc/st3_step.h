@@ -30,8 +30,9 @@ struct StepCommon {
     int32_t layers;             // entries of the table
     int8_t wide;                // 1: the table's entries are wide
     int8_t leave;               // 1: the attention leaves its entries in the layers' workspaces (kLeftWords)
-    int16_t chunks;             // most chunks of any layer: the attention's grid is (H, chunks, rank_z + B * layers)
-    int32_t rank_z;             // the grid's first z: its workgroups rank rows, one for each (layer, sequence); 0: no row is ranked
+    int16_t chunks;             // most chunks of any layer: the attention's grid is (H, chunks, rank_z + B * layers), without groups
+    int32_t rank_z;             // the grid's first z, or with groups, in a grid that is a line, its first workgroups: they rank rows, one for each
+                                // (layer, sequence); 0: no row is ranked
     int8_t groups[4];           // layers of an attention's table whose workgroups take 8, 4, 2 heads (in this order) one after the other, and 1: the
                                 // others; groups[3]: 1 where the grid is for that (no strip is cut then), else 0
 };
